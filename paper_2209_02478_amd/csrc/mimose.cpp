@@ -749,16 +749,21 @@ void Step::embed_sort(const int32_t* tokens) {
   int32_t* s = c_->stage;
   std::vector<int32_t>& count = c_->sort_count;
   count.assign((size_t)f_.vocab + 1, 0);
-  for (int t = 0; t < T_; ++t) ++count[(size_t)tokens[t] + 1];
+  // positions that are padding carry a zero gradient: they are left out
+  auto each_position = [&](auto&& f) {
+    for (int b = 0; b < B_; ++b)
+      for (int t = b * L_, e = t + (lens_host ? lens_host[b] : L_); t < e; ++t) f(t);
+  };
+  each_position([&](int t) { ++count[(size_t)tokens[t] + 1]; });
   n_seg_ = 0;
   int32_t* seg = s + 3 * (size_t)T_;
   for (int v = 0; v < f_.vocab; ++v) {
     if (count[v + 1]) seg[n_seg_++] = count[v];
     count[v + 1] += count[v];
   }
-  seg[n_seg_] = T_;
+  seg[n_seg_] = count[f_.vocab];
   int32_t* order = s + 2 * (size_t)T_;
-  for (int t = 0; t < T_; ++t) order[count[tokens[t]]++] = t;
+  each_position([&](int t) { order[count[tokens[t]]++] = t; });
   HIPCHK(c_, hipMemcpyAsync(order_, order, (2 * (size_t)T_ + 1) * 4, hipMemcpyHostToDevice, st_));
   HIPCHK(c_, hipEventRecord(c_->ev_stage[stage_turn_], st_));     // the last copy out of this staging buffer
   c_->stage_busy[stage_turn_] = true;

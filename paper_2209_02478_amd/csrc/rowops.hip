@@ -565,6 +565,20 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
   }
 }
 
+// VEC (1 or 4) consecutive elements as floats, in one access
+template <typename T, int VEC>
+__device__ __forceinline__ void load_few(const T* p, float (&v)[VEC]) {
+  if (VEC == 1) { v[0] = ld<T>(p); return; }
+  if (sizeof(T) == 2) {
+    const uint2 u = *(const uint2*)p;
+    v[0] = __uint_as_float(u.x << 16); v[1 % VEC] = __uint_as_float(u.x & 0xFFFF0000u);
+    v[2 % VEC] = __uint_as_float(u.y << 16); v[3 % VEC] = __uint_as_float(u.y & 0xFFFF0000u);
+  } else {
+    const float4 u = *(const float4*)p;
+    v[0] = u.x; v[1 % VEC] = u.y; v[2 % VEC] = u.z; v[3 % VEC] = u.w;
+  }
+}
+
 // dpos[p][c] = sum over samples b (in order) of d[b*L+p][c]; rows p >= L are cleared.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_bwd_pos_kernel(const T* __restrict__ d, float* __restrict__ dpos,
@@ -578,22 +592,76 @@ __global__ __launch_bounds__(256) void embed_bwd_pos_kernel(const T* __restrict_
   dpos[idx] = s;
 }
 
-// One wave per distinct token id: rows of d at that id's positions (ascending) are summed
-// and added onto the id's gradient row.
-template <typename T>
-__global__ __launch_bounds__(256) void embed_bwd_tok_kernel(const T* __restrict__ d, const int32_t* __restrict__ ids,
-                                                            const int32_t* __restrict__ order,
-                                                            const int32_t* __restrict__ seg, int n_seg,
-                                                            float* __restrict__ dtok, int H) {
-  const int lane = threadIdx.x & 63, sidx = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (sidx >= n_seg) return;
-  const int beg = seg[sidx], end = seg[sidx + 1];
-  const int id = ids[order[beg]];
-  float* out = dtok + (int64_t)id * H;
-  for (int c = lane; c < H; c += 64) {
-    float s = 0.f;
-    for (int k = beg; k < end; ++k) s += ld<T>(d + (int64_t)order[k] * H + c);
-    out[c] += s;
+// Rows of d at each distinct token id's positions (ascending) are summed and added onto the id's
+// gradient row.  A wave owns one id and a group of 64 * VEC columns, with eight rows in flight.
+// Frequent ids (separators, articles) would leave one wave with a serial chain over thousands of
+// rows: an id with more than kLongRun positions is shared out over its block's 16 waves, whose
+// parts are added in order.  (One wave with one row in flight took 16.7 ms for an id at 4800
+// positions, H = 768; a memory latency per row.)
+constexpr int kLongRun = 64;
+template <typename T, int VEC>
+__global__ __launch_bounds__(1024) void embed_bwd_tok_kernel(const T* __restrict__ d, const int32_t* __restrict__ ids,
+                                                             const int32_t* __restrict__ order,
+                                                             const int32_t* __restrict__ seg, int n_seg,
+                                                             float* __restrict__ dtok, int H) {
+  __shared__ float red[16][64 * VEC];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = (blockIdx.y * 64 + lane) * VEC;
+  const bool in = c < H;
+  auto sum_rows = [&](int beg, int end, float (&acc)[VEC]) {
+    for (int k0 = beg; k0 < end; k0 += 64) {
+      const int n = min(64, end - k0);
+      const int mine = lane < n ? order[k0 + lane] : 0;
+      for (int j = 0; j < n; j += 8) {
+        float v[8][VEC];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int64_t row = __builtin_amdgcn_readlane(mine, (j + u) & 63);
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) v[u][e] = 0.f;
+          if (j + u < n && in) load_few<T, VEC>(d + row * H + c, v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[e] += v[u][e];
+      }
+    }
+  };
+  auto add_to = [&](int id, const float (&acc)[VEC]) {
+    float* out = dtok + (int64_t)id * H + c;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) out[e] += acc[e];
+  };
+  const int s0 = blockIdx.x * 16;
+  bool any_long = false;                              // the same in every wave
+  for (int q = 0; q < 16 && s0 + q < n_seg; ++q) any_long |= seg[s0 + q + 1] - seg[s0 + q] > kLongRun;
+  if (s0 + wave < n_seg) {
+    const int beg = seg[s0 + wave], end = seg[s0 + wave + 1];
+    if (end - beg <= kLongRun) {
+      float acc[VEC] = {};
+      sum_rows(beg, end, acc);
+      if (in) add_to(ids[order[beg]], acc);
+    }
+  }
+  if (!any_long) return;
+  for (int q = 0; q < 16 && s0 + q < n_seg; ++q) {
+    const int beg = seg[s0 + q], end = seg[s0 + q + 1];
+    if (end - beg <= kLongRun) continue;
+    const int part = (end - beg + 15) / 16;
+    float acc[VEC] = {};
+    sum_rows(beg + wave * part, min(end, beg + (wave + 1) * part), acc);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) red[wave][lane * VEC + e] = acc[e];
+    __syncthreads();
+    if (wave == q && in) {
+      float tot[VEC] = {};
+      for (int w = 0; w < 16; ++w)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) tot[e] += red[w][lane * VEC + e];
+      add_to(ids[order[beg]], tot);
+    }
+    __syncthreads();
   }
 }
 
@@ -839,17 +907,25 @@ void embed_fwd(int dtype, const int32_t* ids, const void* tok, const void* pos, 
   else embed_fwd_t<float>(ids, tok, pos, gamma, beta, sum_out, y, B, L, H, eps, has_ln, st);
 }
 
+template <typename T>
+static void embed_bwd_t(const void* d, const int32_t* ids, const int32_t* order, const int32_t* seg, int n_seg,
+                        float* dtok, float* dpos, int B, int L, int H, int max_seq, hipStream_t st) {
+  hipLaunchKernelGGL(embed_bwd_pos_kernel<T>, dim3((unsigned)(((int64_t)max_seq * H + 255) / 256)), dim3(256), 0, st,
+                     (const T*)d, dpos, B, L, H, max_seq);
+  if (n_seg <= 0) return;
+  const unsigned gx = (unsigned)((n_seg + 15) / 16);
+  if (H % 4 == 0 && (((uintptr_t)d) & 15) == 0)
+    hipLaunchKernelGGL((embed_bwd_tok_kernel<T, 4>), dim3(gx, (H + 255) / 256), dim3(1024), 0, st, (const T*)d, ids, order,
+                       seg, n_seg, dtok, H);
+  else
+    hipLaunchKernelGGL((embed_bwd_tok_kernel<T, 1>), dim3(gx, (H + 63) / 64), dim3(1024), 0, st, (const T*)d, ids, order,
+                       seg, n_seg, dtok, H);
+}
 void embed_bwd(int dtype, const void* d, const int32_t* ids, const int32_t* order, const int32_t* seg,
                int n_seg, float* dtok, float* dpos, int B, int L, int H, int max_seq, hipStream_t st) {
   if (B * L <= 0) return;
-  dim3 gp((unsigned)(((int64_t)max_seq * H + 255) / 256)), gt((n_seg + 3) / 4);
-  if (dtype == BF16) {
-    hipLaunchKernelGGL(embed_bwd_pos_kernel<bf16_t>, gp, dim3(256), 0, st, (const bf16_t*)d, dpos, B, L, H, max_seq);
-    hipLaunchKernelGGL(embed_bwd_tok_kernel<bf16_t>, gt, dim3(256), 0, st, (const bf16_t*)d, ids, order, seg, n_seg, dtok, H);
-  } else {
-    hipLaunchKernelGGL(embed_bwd_pos_kernel<float>, gp, dim3(256), 0, st, (const float*)d, dpos, B, L, H, max_seq);
-    hipLaunchKernelGGL(embed_bwd_tok_kernel<float>, gt, dim3(256), 0, st, (const float*)d, ids, order, seg, n_seg, dtok, H);
-  }
+  if (dtype == BF16) embed_bwd_t<bf16_t>(d, ids, order, seg, n_seg, dtok, dpos, B, L, H, max_seq, st);
+  else embed_bwd_t<float>(d, ids, order, seg, n_seg, dtok, dpos, B, L, H, max_seq, st);
 }
 
 void convert_from_f32(int dtype, const float* src, void* dst, int64_t n, hipStream_t st) {

@@ -460,6 +460,30 @@ def test_embedding_fwd_bwd(dtype, has_ln):
     close(host(gpos), ref_pos, 0, k=20.0)
 
 
+# runs of one id around the length a single wave still sums, and far beyond it; widths whose last
+# column group is partial, and one that takes the scalar accesses
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("H", [64, 264, 1024, 70])
+def test_embedding_bwd_frequent_ids(dtype, H):
+    rng = np.random.default_rng(4)
+    runs = [1, 63, 64, 65, 7, 128, 129, 700, 1, 9, 8, 1, 2, 3, 5, 6, 7, 11, 1023]
+    ids = rng.permutation(np.repeat(np.arange(3, 3 + len(runs)), runs)).astype(np.int32)
+    B, L, V, max_seq = 2, len(ids) // 2, 40, len(ids)
+    ids = ids[:B * L]
+    d = rng.standard_normal((B * L, H)).astype(np.float32)
+    order = np.argsort(ids, kind="stable").astype(np.int32)
+    si = ids[order]
+    starts = np.flatnonzero(np.r_[True, si[1:] != si[:-1]]).astype(np.int32)
+    gtok = torch.ones((V, H), dtype=torch.float32, device=DEV)
+    gpos = torch.zeros((max_seq, H), dtype=torch.float32, device=DEV)
+    mi.mimose_op_embed_bwd(dtype, dev(d, dtype), torch.tensor(ids, device=DEV), torch.tensor(order, device=DEV),
+                           torch.tensor(np.r_[starts, B * L].astype(np.int32), device=DEV), len(starts), gtok, gpos, B, L, H,
+                           max_seq)
+    sync()
+    ref = np.ones((V, H)); np.add.at(ref, ids, quant(d, dtype))
+    close(host(gtok), ref, 0, k=200.0)
+
+
 # ---------------------------------------------------------------- dropout (counter-based masks)
 @pytest.mark.parametrize("dtype,io_f32", [(0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("n", [4096 + 3, 5, 1 << 18])
