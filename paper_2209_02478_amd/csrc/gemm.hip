@@ -13,7 +13,7 @@
 // gfx950, so no operand is ever transposed in memory or in registers.  The
 // reduction order over k is fixed by the shape alone: results are reproducible
 // bit for bit.
-// fp32: a plain 64x64x16 LDS-tiled kernel (small-model configuration only).
+// fp32: gemm_f32.hip.
 #include "device_common.h"
 #include "gemm_device.h"
 
@@ -24,57 +24,6 @@
 #include "kernels.h"
 
 namespace mk {
-
-// ------------------------------------------------------------------ fp32
-__global__ __launch_bounds__(256) void sgemm_kernel(GemmDev p) {
-  __shared__ float As[16][68];
-  __shared__ float Bs[16][68];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const float* A = (const float*)p.A;
-  const float* B = (const float*)p.B;
-  float acc[4][4] = {};
-  const bool do_rowsum = p.a_rowsum && blockIdx.x == 0 && tid < 64;
-  float rs = 0.f;
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int idx = tid + i * 256;
-      int r, k;
-      if (p.a_k) { r = idx >> 4; k = idx & 15; } else { r = idx & 63; k = idx >> 6; }
-      int gm = m0 + r, gk = k0 + k;
-      float v = 0.f;
-      if (gm < p.M && gk < p.K) v = p.a_k ? A[(int64_t)gm * p.lda + gk] : A[(int64_t)gk * p.lda + gm];
-      As[k][r] = v;
-      if (p.b_k) { r = idx >> 4; k = idx & 15; } else { r = idx & 63; k = idx >> 6; }
-      int gn = n0 + r;
-      gk = k0 + k;
-      v = 0.f;
-      if (gn < p.N && gk < p.K) v = p.b_k ? B[(int64_t)gn * p.ldb + gk] : B[(int64_t)gk * p.ldb + gn];
-      Bs[k][r] = v;
-    }
-    __syncthreads();
-    if (do_rowsum)
-#pragma unroll
-      for (int k = 0; k < 16; ++k) rs += As[k][tid];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[k][ty * 4 + i]; b[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) epilogue<float>(p, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j]);
-  if (do_rowsum && m0 + tid < p.M) p.a_rowsum[m0 + tid] = rs;
-}
 
 // ------------------------------------------------------------------ bf16 MFMA
 constexpr int BM = 128, BN = 128, BK = 64;
@@ -449,6 +398,9 @@ static void launch_bgemm(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEve
 // direct-to-LDS pipeline (gemm_dma.hip); false when the operands do not meet its alignment rules
 bool launch_bgemm_dma(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
 
+// fp32 on the matrix cores (gemm_f32.hip)
+void launch_sgemm(const GemmDev& p, int rows, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
 bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
@@ -462,8 +414,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   p.a_tail_zero = g.a_tail_zero ? 1 : 0;
   if (p.gelu && (p.c_f32 || !p.gelu_out)) return false;
   if (dtype == F32) {
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-    hipExtLaunchKernelGGL(sgemm_kernel, grid, dim3(256), 0, st, g.time_start, g.time_stop, 0, p);
+    launch_sgemm(p, g.rule_rows > 0 ? g.rule_rows : g.M, st, g.time_start, g.time_stop);
     return true;
   }
   if ((g.lda & 7) || (g.ldb & 7) || !aligned16(g.A) || !aligned16(g.B)) return false;

@@ -36,6 +36,9 @@ struct GemmArgs {
   // A k-major with K not a multiple of 8: its columns [K, K rounded up to 8) exist (lda covers
   // them) and hold zeros, so a kernel that moves whole 16-byte chunks may read them
   bool a_tail_zero = false;
+  // rows the choice of kernel is made from (0: M): a product issued in row ranges names the whole
+  // here, so that every range sums in the order the whole would
+  int rule_rows = 0;
   void* workspace = nullptr;       // optional scratch of gemm_workspace_bytes(M, N) for split reductions
   size_t workspace_bytes = 0;
   // optional, both or neither: recorded by the product kernel's own start and end (not by markers
