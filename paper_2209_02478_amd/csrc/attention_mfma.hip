@@ -125,7 +125,7 @@ __device__ __forceinline__ void store_rows(bf16_t* dst, const f32x16 (&acc)[2], 
 // ------------------------------------------------------------------ forward
 template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
-                                                     float* __restrict__ lse, const int32_t* __restrict__ lens,
+                                                     float* __restrict__ lse, Rows rows,
                                                      int L, int nh, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
   __shared__ __attribute__((aligned(16))) bf16_t Vt[D][LDTT];   // [d][key]
@@ -133,9 +133,11 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
-  const bf16_t* base = qkv + (int64_t)b * L * ld3 + hh * D;
+  const Sample sm = sample_rows(rows, b, L);
+  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  const bf16_t* base = qkv + sm.first * ld3 + hh * D;
   const int qi = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + ql;
-  const int qc = min(qi, L - 1);
+  const int qc = min(qi, sm.n - 1);
   const float scale = 0.125f, c2 = scale * LOG2E;    // exp(scale * s - x) == exp2(c2 * s - LOG2E * x)
 
   bf16x8 qf[4];
@@ -144,20 +146,20 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
   f32x16 o[2];
   zero(o[0]); zero(o[1]);
   float m = -INFINITY, l = 0.f;                       // running maximum of the raw (unscaled) scores, sum of exps
-  const int Lk = lens ? lens[b] : L;                  // keys from Lk on are padding (1 <= Lk <= L)
+  const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
   const int kend = CAUSAL ? min(Lk, (int)(blockIdx.x + 1) * ROWS_PER_BLOCK) : Lk;
 
   // threads 0..127 stage K, the others V; the next tile's loads are in flight during the MFMAs
   const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;
   const int t128 = tid & 127;
   uint4 pre[4];
-  fetch_tile(mine, ld3, 0, L - 1, t128, pre);
+  fetch_tile(mine, ld3, 0, sm.n - 1, t128, pre);
   for (int k0 = 0; k0 < kend; k0 += TK) {
     __syncthreads();
     if (tid < 128) stash_tile<true, false>(pre, t128, Ks, nullptr);
     else stash_tile<false, true>(pre, t128, nullptr, Vt);
     __syncthreads();
-    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, L - 1, t128, pre);
+    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
     f32x16 s[2];
     float mx = -INFINITY;
 #pragma unroll
@@ -219,8 +221,8 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
           o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_t(Vt, 32 * db + ql, 32 * kb + 16 * c, h), pf, o[db], 0, 0, 0);
       }
   }
-  if (qi < L) {
-    store_rows(ctx + ((int64_t)b * L + qi) * H + hh * D, o, h, (DROP ? drop.scale : 1.f) / l);
+  if (qi < sm.n) {
+    store_rows(ctx + (sm.first + qi) * H + hh * D, o, h, (DROP ? drop.scale : 1.f) / l);
     if (h == 0) lse[(int64_t)bh * L + qi] = m * scale + __logf(l);
   }
 }
@@ -230,7 +232,7 @@ template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx,
                                                         const bf16_t* __restrict__ dctx,
                                                         const float* __restrict__ lse, float* __restrict__ delta,
-                                                        bf16_t* __restrict__ dqkv, const int32_t* __restrict__ lens, int L,
+                                                        bf16_t* __restrict__ dqkv, Rows rows, int L,
                                                         int nh, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
   __shared__ __attribute__((aligned(16))) bf16_t Kt[D][LDTT];   // [d][key]
@@ -239,9 +241,11 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
-  const bf16_t* base = qkv + (int64_t)b * L * ld3 + hh * D;
+  const Sample sm = sample_rows(rows, b, L);
+  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  const bf16_t* base = qkv + sm.first * ld3 + hh * D;
   const int qi = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + ql;
-  const int qc = min(qi, L - 1);
+  const int qc = min(qi, sm.n - 1);
   const float scale = 0.125f;
 
   // delta = sum over the head's columns of dO * O for this query: each half of the wave holds 32
@@ -251,30 +255,30 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     qf[kk] = ld_frag(base + (int64_t)qc * ld3 + 16 * kk + 8 * h);
-    gf[kk] = ld_frag(dctx + ((int64_t)b * L + qc) * H + hh * D + 16 * kk + 8 * h);
-    const bf16x8 of = ld_frag(ctx + ((int64_t)b * L + qc) * H + hh * D + 16 * kk + 8 * h);
+    gf[kk] = ld_frag(dctx + (sm.first + qc) * H + hh * D + 16 * kk + 8 * h);
+    const bf16x8 of = ld_frag(ctx + (sm.first + qc) * H + hh * D + 16 * kk + 8 * h);
 #pragma unroll
     for (int e = 0; e < 8; ++e) delta_q = fmaf((float)of[e], (float)gf[kk][e], delta_q);
   }
   delta_q += __shfl_xor(delta_q, 32, 64);
-  if (h == 0 && qi < L) delta[(int64_t)bh * L + qi] = delta_q;
+  if (h == 0 && qi < sm.n) delta[(int64_t)bh * L + qi] = delta_q;
   const float c2 = scale * LOG2E;
   const float nlse_q = -LOG2E * lse[(int64_t)bh * L + qc];
   f32x16 dq[2];
   zero(dq[0]); zero(dq[1]);
-  const int Lk = lens ? lens[b] : L;                  // keys from Lk on are padding (1 <= Lk <= L)
+  const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
   const int kend = CAUSAL ? min(Lk, (int)(blockIdx.x + 1) * ROWS_PER_BLOCK) : Lk;
 
   const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;     // threads 0..127 stage K, the others V
   const int t128 = tid & 127;
   uint4 pre[4];
-  fetch_tile(mine, ld3, 0, L - 1, t128, pre);
+  fetch_tile(mine, ld3, 0, sm.n - 1, t128, pre);
   for (int k0 = 0; k0 < kend; k0 += TK) {
     __syncthreads();
     if (tid < 128) stash_tile<true, true>(pre, t128, Ks, Kt);
     else stash_tile<true, false>(pre, t128, Vs, nullptr);
     __syncthreads();
-    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, L - 1, t128, pre);
+    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       f32x16 s, dp;
@@ -313,14 +317,14 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
       }
     }
   }
-  if (qi < L) store_rows(dqkv + ((int64_t)b * L + qi) * ld3 + hh * D, dq, h, scale);
+  if (qi < sm.n) store_rows(dqkv + (sm.first + qi) * ld3 + hh * D, dq, h, scale);
 }
 
 // ------------------------------------------------------------------ dK, dV
 template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                                         bf16_t* __restrict__ dqkv, const int32_t* __restrict__ lens, int L,
+                                                         bf16_t* __restrict__ dqkv, Rows rows, int L,
                                                         int nh, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Qs[TK][LDT];   // [query][d]
   __shared__ __attribute__((aligned(16))) bf16_t Qt[D][LDTT];   // [d][query]
@@ -331,10 +335,12 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
-  const bf16_t* base = qkv + (int64_t)b * L * ld3 + hh * D;
-  const bf16_t* gbase = dctx + (int64_t)b * L * H + hh * D;
+  const Sample sm = sample_rows(rows, b, L);
+  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  const bf16_t* base = qkv + sm.first * ld3 + hh * D;
+  const bf16_t* gbase = dctx + sm.first * H + hh * D;
   const int ki = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + kl;
-  const int kc = min(ki, L - 1);
+  const int kc = min(ki, sm.n - 1);
   const float scale = 0.125f, c2 = scale * LOG2E;
 
   bf16x8 kf[4], vf[4];
@@ -346,8 +352,8 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
   f32x16 dk[2], dv[2];
   zero(dk[0]); zero(dk[1]); zero(dv[0]); zero(dv[1]);
   const int qstart = CAUSAL ? blockIdx.x * ROWS_PER_BLOCK : 0;     // earlier queries never see these keys
-  const int Lk = lens ? lens[b] : L;                               // keys from Lk on are padding: their dK, dV are zero
-  const int qend = (int)blockIdx.x * ROWS_PER_BLOCK >= Lk ? 0 : L; // a block of padded keys only writes zeros
+  const int Lk = sm.keys;                                          // keys from Lk on are padding: their dK, dV are zero
+  const int qend = (int)blockIdx.x * ROWS_PER_BLOCK >= Lk ? 0 : sm.n; // a block of padded keys only writes zeros
 
   const bf16_t* mine = tid < 128 ? base : gbase;                 // threads 0..127 stage Q, the others dO
   const int64_t mine_ld = tid < 128 ? ld3 : (int64_t)H;
@@ -355,9 +361,9 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
   uint4 pre[4];
   float pre_lse = 0.f, pre_delta = 0.f;
   auto fetch = [&](int q0) {
-    fetch_tile(mine, mine_ld, q0, L - 1, t128, pre);
+    fetch_tile(mine, mine_ld, q0, sm.n - 1, t128, pre);
     if (tid < TK) {
-      const int q = min(q0 + tid, L - 1);
+      const int q = min(q0 + tid, sm.n - 1);
       pre_lse = lse[(int64_t)bh * L + q];
       pre_delta = delta[(int64_t)bh * L + q];
     }
@@ -391,7 +397,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
         bool keep[4] = {true, true, true, true};
         if (DROP) {
           const int c = lane & 3;
-          const int qmine = min(q0 + qq + c, L - 1);
+          const int qmine = min(q0 + qq + c, sm.n - 1);
           const uint4 w = attn_drop_words(drop, (int64_t)bh * L + qmine, (L + 3) >> 2, ki & ~3);
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
@@ -415,11 +421,11 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
           }
         }
       }
-      if (CAUSAL || q0 + TK > L) {
+      if (CAUSAL || q0 + TK > sm.n) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int q = q0 + 32 * qb + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (q >= L || (CAUSAL && ki > q)) { s[r] = 0.f; dp[r] = 0.f; }
+          if (q >= sm.n || (CAUSAL && ki > q)) { s[r] = 0.f; dp[r] = 0.f; }
         }
       }
 #pragma unroll
@@ -433,31 +439,31 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
       }
     }
   }
-  if (ki < L) {
+  if (ki < sm.n) {
     if (ki >= Lk) { zero(dk[0]); zero(dk[1]); zero(dv[0]); zero(dv[1]); }   // whatever the lane's column held
-    bf16_t* out = dqkv + ((int64_t)b * L + ki) * ld3 + hh * D;
+    bf16_t* out = dqkv + (sm.first + ki) * ld3 + hh * D;
     store_rows(out + H, dk, h, scale);
     store_rows(out + 2 * H, dv, h, 1.f);
   }
 }
 
-void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const int32_t* lens, int B, int L, int nh, int causal,
+void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                         const DropDesc& drop, hipStream_t st) {
   dim3 grid((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, B * nh);
-#define FWD_(C, D) hipLaunchKernelGGL((fa_fwd_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (bf16_t*)ctx, lse, lens, L, nh, drop)
+#define FWD_(C, D) hipLaunchKernelGGL((fa_fwd_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (bf16_t*)ctx, lse, rows, L, nh, drop)
   if (drop.thr) { if (causal) FWD_(true, true); else FWD_(false, true); }
   else { if (causal) FWD_(true, false); else FWD_(false, false); }
 #undef FWD_
 }
 
 void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
-                        const int32_t* lens, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
+                        const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
   dim3 grid((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, B * nh);
 #define BWD_(C, D)                                                                                               \
   hipLaunchKernelGGL((fa_bwd_dq_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)ctx,  \
-                     (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, lens, L, nh, drop);                          \
+                     (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, rows, L, nh, drop);                          \
   hipLaunchKernelGGL((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
-                     delta, (bf16_t*)dqkv, lens, L, nh, drop)
+                     delta, (bf16_t*)dqkv, rows, L, nh, drop)
   if (drop.thr) { if (causal) { BWD_(true, true); } else { BWD_(false, true); } }
   else { if (causal) { BWD_(true, false); } else { BWD_(false, false); } }
 #undef BWD_

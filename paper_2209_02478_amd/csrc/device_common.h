@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.h"
+
 namespace mk {
 
 typedef uint16_t bf16_t;   // raw bfloat16 bits
@@ -20,6 +22,27 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
   const f32x2_t v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// rows of sample b: the first, how many there are, how many of them may be attended to
+struct Sample { int64_t first; int n, keys; };
+__device__ __forceinline__ Sample sample_rows(const Rows& r, int b, int L) {
+  if (r.ends) {
+    const int first = b ? r.ends[b - 1] : r.first, n = r.ends[b] - first;
+    return {first - r.first, n, n};
+  }
+  return {(int64_t)b * L, L, r.lens ? r.lens[b] : L};
+}
+
+// row of the padded batch that row `row` of the real rows alone stands for
+__device__ __forceinline__ int padded_row(const Rows& r, int row, int B, int L) {
+  if (!r.ends) return row;
+  int lo = 0, hi = B - 1;                             // the first sample that ends behind the row
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (r.ends[mid] > row) hi = mid; else lo = mid + 1;
+  }
+  return lo * L + row - (lo ? r.ends[lo - 1] : 0);
 }
 
 template <typename T> __device__ __forceinline__ float ld(const T* p);

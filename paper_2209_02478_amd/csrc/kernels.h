@@ -22,6 +22,19 @@ struct DropDesc {
   uint32_t step = 0;     // iteration number
 };
 
+// Where the samples of a batch of B x L tokens are.  Neither array: sample b fills rows b*L ..
+// b*L + L - 1.  lens (device, [B]): the same rows, of which the first lens[b] are real; keys from
+// lens[b] on get no weight.  ends (device, [B]): the real rows alone, one sample after the other,
+// sample b in rows ends[b-1] .. ends[b] - 1.  Indices inside a sample stay those of the padded
+// batch everywhere (lse, delta, dropout masks).
+// ends may point at the entry of a later sample, with first the row that sample begins at: then
+// row pointers are those of that row.
+struct Rows {
+  const int32_t* lens = nullptr;
+  const int32_t* ends = nullptr;
+  int32_t first = 0;
+};
+
 struct GemmArgs {
   const void* A; int64_t lda; bool a_kmajor;
   const void* B; int64_t ldb; bool b_kmajor;
@@ -80,21 +93,21 @@ int layernorm_bwd_static(int dtype, const void* dy, bool dy_f32, const void* x, 
                          void* dx, const void* add, float* dgamma, float* dbeta, int T, int H, float eps,
                          hipStream_t st);
 void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st);
-// lens (optional, device, [B]): real tokens per sample of a padded batch; keys from lens[b] on get
-// no weight.  nullptr: every sample fills its row.  drop: dropout of the probabilities (the
+// drop: dropout of the probabilities (the
 // softmax normaliser counts all of them; ctx = (mask * scale * P) V).
-void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const int32_t* lens, int B, int L, int nh, int d,
+void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,
                    int causal, const DropDesc& drop, hipStream_t st);
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse,
-                   float* delta, void* dqkv, const int32_t* lens, int B, int L, int nh, int d, int causal,
+                   float* delta, void* dqkv, const Rows& rows, int B, int L, int nh, int d, int causal,
                    const DropDesc& drop, hipStream_t st);
 void softmax_xent(int dtype, void* logits, int64_t ld, const int32_t* labels, float* row_loss,
                   float* loss, int T, int V, int n_valid, hipStream_t st);
+// T: rows (B * L, or the real ones when rows.ends is given)
 void embed_fwd(int dtype, const int32_t* ids, const void* tok, const void* pos, const void* gamma,
-               const void* beta, void* sum_out, void* y, int B, int L, int H, float eps, int has_ln,
+               const void* beta, void* sum_out, void* y, const Rows& rows, int T, int B, int L, int H, float eps, int has_ln,
                hipStream_t st);
 void embed_bwd(int dtype, const void* d, const int32_t* ids, const int32_t* order,
-               const int32_t* seg, int n_seg, float* dtok, float* dpos, int B, int L, int H,
+               const int32_t* seg, int n_seg, float* dtok, float* dpos, const Rows& rows, int B, int L, int H,
                int max_seq, hipStream_t st);
 // dst (storage dtype) = round(src fp32)
 void convert_from_f32(int dtype, const float* src, void* dst, int64_t n, hipStream_t st);
@@ -113,9 +126,10 @@ void adamw_update(int lowp_dtype, const AdamTensor* tensors, const AdamChunk* ch
                   hipStream_t st);
 // dst[n] = (resid ? resid[n] : 0) + mask * d.scale * src[n] with the mask of d (element i: word i % 4
 // of block i / 4).  dst and src have the storage type, or fp32 when io_f32; resid has the storage
-// type; dst may be src.
+// type; dst may be src.  With rows.ends: element e of row r is the mask's element of that token in
+// the padded batch of B x L rows of H (a multiple of 4); else B, L and H are not looked at.
 void dropout_apply(int dtype, void* dst, const void* src, bool io_f32, const void* resid, int64_t n, const DropDesc& d,
-                   hipStream_t st);
+                   const Rows& rows, int B, int L, int H, hipStream_t st);
 // dst fp32 = src (storage dtype)
 void convert_to_f32(int dtype, const void* src, float* dst, int64_t n, hipStream_t st);
 

@@ -219,11 +219,18 @@ void build_params(mimose_ctx* c) {
 class Step {
  public:
   Step(mimose_ctx* c, int B, int L, uint64_t plan, bool collect)
-      : c_(c), f_(c->cfg), B_(B), L_(L), T_(B * L), plan_(plan), collect_(collect), dry_(c->dry),
+      : c_(c), f_(c->cfg), B_(B), L_(L), T_(B * L), Tpad_(B * L), plan_(plan), collect_(collect), dry_(c->dry),
         st_(c->stream), dt_(c->cfg.dtype), es_(c->elt()) {}
 
   void run(const int32_t* tokens, const int32_t* labels, float* loss_out, bool wait);
-  const int32_t* lens_host = nullptr;   // padded batch: real tokens per sample ([B], host), else null
+  // Padded batch: real tokens per sample ([B], host).  Its real rows alone go through the model, one
+  // sample after the other (padding gets no attention, scores nothing and passes no gradient on),
+  // while every tensor keeps the size of the padded batch, which is what the planner knows.
+  void set_lengths(const int32_t* lens) {
+    lens_host = lens;
+    T_ = 0;
+    for (int b = 0; b < B_; ++b) T_ += lens[b];
+  }
 
   // collected bytes (valid after run)
   uint64_t e_bytes = 0, g_bytes = 0;
@@ -232,13 +239,16 @@ class Step {
  private:
   mimose_ctx* c_;
   const mimose_model_cfg& f_;
-  int B_, L_, T_;
+  const int32_t* lens_host = nullptr;
+  int B_, L_;
+  int T_, Tpad_;        // rows of the step; rows its tensors are allocated for (B * L)
   uint64_t plan_;
   bool collect_, dry_;
   hipStream_t st_;
   int dt_, es_;
   // embedding-stage tensors
-  int32_t *ids_ = nullptr, *labels_ = nullptr, *order_ = nullptr, *seg_ = nullptr, *lens_ = nullptr;
+  int32_t *ids_ = nullptr, *labels_ = nullptr, *order_ = nullptr, *seg_ = nullptr, *ends_ = nullptr;
+  mk::Rows rows() const { return mk::Rows{nullptr, ends_, 0}; }
   // Gradient of the residual stream.  Post-LN blocks in bf16 carry it in fp32 (gA_, gB_) and
   // keep the bf16 copies the products consume in oA_, oB_; otherwise the carriers have the
   // storage type and oA_/oB_ alias them (LayerNorm backward then works in place).
@@ -304,7 +314,7 @@ class Step {
   }
   // io (storage type, or fp32 when io_f32) = resid + dropout(src); src may be io
   void dropout(void* dst, const void* src, bool io_f32, const void* resid, uint32_t site) {
-    if (!dry_) mk::dropout_apply(dt_, dst, src, io_f32, resid, (int64_t)T_ * f_.hidden, drop_desc(site), st_);
+    if (!dry_) mk::dropout_apply(dt_, dst, src, io_f32, resid, (int64_t)T_ * f_.hidden, drop_desc(site), rows(), B_, L_, f_.hidden, st_);
   }
   // dX[T,in] = dY[T,out] W[out,in] (+ resid)
   void dgrad(const void* dY, int64_t ldy, int out, int wi, void* dX, int in, const void* resid = nullptr,
@@ -387,7 +397,7 @@ class Step {
   void ln_bwd(const void* dy, const void* x, int gi, int bi, void* dx, const void* add, bool dy_f32 = false,
               bool x_f32 = false) {
     const uint64_t m = c_->arena.top();
-    float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(T_) * 2 * f_.hidden * 4);
+    float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(Tpad_) * 2 * f_.hidden * 4);
     const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * (add ? 2.0 : 1.0);
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
     if (!dry_)
@@ -400,7 +410,7 @@ class Step {
   // the weight-gradient stream after the next fork, off the chain of data gradients.
   float* ln_bwd_rows(const void* dy, const void* x, int gi, void* dx, const void* add, bool dy_f32 = false,
                      bool x_f32 = false) {
-    float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(T_) * 2 * f_.hidden * 4);
+    float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(Tpad_) * 2 * f_.hidden * 4);
     const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * (add ? 2.0 : 1.0);
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
     if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, st_);
@@ -423,9 +433,16 @@ class Step {
   }
 
   void embed_stage(const int32_t* tokens, const int32_t* labels);
-  void embed_sort(const int32_t* tokens);
+  void embed_sort();
   void alloc_layer(int l, LayerActs& A);
   void layer_forward(int l, LayerActs& A, bool rebuild = false);
+  // first row of sample b (b == B: one past the last row)
+  int64_t first_row(int b) const {
+    if (!lens_host) return (int64_t)b * L_;
+    int64_t r = 0;
+    for (int i = 0; i < b; ++i) r += lens_host[i];
+    return r;
+  }
   void layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s);
   bool split_forward() const;
   void cross_sync();
@@ -436,27 +453,28 @@ class Step {
 
 void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   const int H = f_.hidden;
-  // ids, labels, sort order, run boundaries, per-sample lengths (the last B only read for padded batches)
-  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)(4 * (int64_t)T_ + 1 + B_) * 4);
-  ids_ = ints; labels_ = ints ? ints + T_ : nullptr; order_ = ints ? ints + 2 * (int64_t)T_ : nullptr;
-  seg_ = ints ? ints + 3 * (int64_t)T_ : nullptr;
-  lens_ = ints && lens_host ? ints + 4 * (int64_t)T_ + 1 : nullptr;
+  // ids, labels, sort order, run boundaries, where each sample's rows end (the last B only read for padded batches)
+  const int64_t TP = Tpad_;
+  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)(4 * TP + 1 + B_) * 4);
+  ids_ = ints; labels_ = ints ? ints + TP : nullptr; order_ = ints ? ints + 2 * TP : nullptr;
+  seg_ = ints ? ints + 3 * TP : nullptr;
+  ends_ = ints && lens_host ? ints + 4 * TP + 1 : nullptr;
   wide_ = !f_.pre_ln && dt_ == mk::BF16;
-  gA_ = walloc((int64_t)T_ * H);
-  gB_ = walloc((int64_t)T_ * H);
-  oA_ = wide_ ? talloc((int64_t)T_ * H) : gA_;
-  oB_ = wide_ ? talloc((int64_t)T_ * H) : gB_;
-  if (!f_.pre_ln) emb_sum_ = talloc((int64_t)T_ * H);
-  h0_ = talloc((int64_t)T_ * H);
+  gA_ = walloc(TP * H);
+  gB_ = walloc(TP * H);
+  oA_ = wide_ ? talloc(TP * H) : gA_;
+  oB_ = wide_ ? talloc(TP * H) : gB_;
+  if (!f_.pre_ln) emb_sum_ = talloc(TP * H);
+  h0_ = talloc(TP * H);
   if (late_ok()) {
-    late_dqkv_ = talloc(3 * (int64_t)T_ * H);
+    late_dqkv_ = talloc(3 * TP * H);
     late_ws_bytes_ = dt_ == mk::BF16 ? mk::gemm_workspace_bytes(3 * H, H) : 0;
     late_ws_ = late_ws_bytes_ ? c_->arena.alloc(late_ws_bytes_) : nullptr;
   }
   if (dry_) return;
 
   // host side: stable sort of positions by token id, run boundaries of equal ids
-  const size_t need = 4 * (size_t)T_ + 1 + (size_t)B_;
+  const size_t need = 4 * (size_t)TP + 1 + (size_t)B_;
   const int turn = c_->stage_turn;
   c_->stage_turn ^= 1;
   if (c_->stage_busy[turn]) {               // copies of the step before last out of this buffer: long done
@@ -472,23 +490,27 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   c_->stage = c_->stage_buf[turn];
   stage_turn_ = turn;
   int32_t* s = c_->stage;
-  std::memcpy(s, tokens, (size_t)T_ * 4);
-  std::memcpy(s + T_, labels, (size_t)T_ * 4);
-  if (lens_host) {                        // padded positions are never scored
-    for (int b = 0; b < B_; ++b)
-      for (int p = lens_host[b]; p < L_; ++p) s[T_ + (size_t)b * L_ + p] = -1;
-    std::memcpy(s + 4 * (size_t)T_ + 1, lens_host, (size_t)B_ * 4);
-    HIPCHK(c_, hipMemcpyAsync(lens_, s + 4 * (size_t)T_ + 1, (size_t)B_ * 4, hipMemcpyHostToDevice, st_));
+  if (lens_host) {
+    int32_t* ends = s + 4 * TP + 1;
+    for (int b = 0, t = 0; b < B_; ++b) {
+      std::memcpy(s + t, tokens + (size_t)b * L_, (size_t)lens_host[b] * 4);
+      std::memcpy(s + TP + t, labels + (size_t)b * L_, (size_t)lens_host[b] * 4);
+      ends[b] = t += lens_host[b];
+    }
+    HIPCHK(c_, hipMemcpyAsync(ends_, ends, (size_t)B_ * 4, hipMemcpyHostToDevice, st_));
+  } else {
+    std::memcpy(s, tokens, (size_t)T_ * 4);
+    std::memcpy(s + TP, labels, (size_t)T_ * 4);
   }
-  HIPCHK(c_, hipMemcpyAsync(ints, s, 2 * (size_t)T_ * 4, hipMemcpyHostToDevice, st_));
+  HIPCHK(c_, hipMemcpyAsync(ints, s, 2 * (size_t)TP * 4, hipMemcpyHostToDevice, st_));
   Timed t(this, MIMOSE_K_EMBED_FWD, (f_.pre_ln ? 3.0 : 4.0) * T_ * H * es_d());
   mk::embed_fwd(dt_, ids_, w(c_->i_tok), w(c_->i_pos), f_.pre_ln ? nullptr : w(c_->i_eg),
-                f_.pre_ln ? nullptr : w(c_->i_eb), emb_sum_, h0_, B_, L_, H, f_.ln_eps, !f_.pre_ln, st_);
+                f_.pre_ln ? nullptr : w(c_->i_eb), emb_sum_, h0_, rows(), T_, B_, L_, H, f_.ln_eps, !f_.pre_ln, st_);
   if (drop_on()) dropout(h0_, h0_, false, nullptr, 0);
 }
 
 void Step::alloc_layer(int l, LayerActs& A) {
-  const int64_t TH = (int64_t)T_ * f_.hidden, TF = (int64_t)T_ * ffn_of(f_, l);
+  const int64_t TH = (int64_t)Tpad_ * f_.hidden, TF = (int64_t)Tpad_ * ffn_of(f_, l);
   if (!A.has_out) {                   // first pass: the boundary tensor goes first
     A.mark = c_->arena.top();
     A.out = talloc(TH);
@@ -515,8 +537,8 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   const LayerIdx& p = c_->lidx[l];
   const int H = f_.hidden, F = ffn_of(f_, l), nh = f_.n_heads, d = H / nh;
   const int gelu = f_.gelu_tanh ? mk::GELU_TANH : mk::GELU_ERF;
-  const int64_t r0 = (int64_t)b0 * L_;
-  const int rows = nb * L_;
+  const int64_t r0 = first_row(b0);
+  const int rows = (int)(first_row(b0 + nb) - r0);
   auto at = [&](const void* base, int64_t width, bool f32 = false) -> void* {
     return (char*)const_cast<void*>(base) + r0 * width * (f32 ? 4 : (int64_t)es_);
   };
@@ -536,8 +558,8 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   const void* a = x;
   if (f_.pre_ln) { ln(x, p.ln1g, p.ln1b, at(A.n1, H), false); a = at(A.n1, H); }
   lin(a, H, p.wqkv, p.bqkv, at(A.qkv, 3 * H), 3 * H, nullptr, nullptr, 0, false);
-  mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_, lens_ ? lens_ + b0 : nullptr, nb, L_,
-                    nh, d, f_.causal, mk::DropDesc(), s);
+  mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_,
+                    mk::Rows{nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s);
   lin(at(A.ctx, H), H, p.wo, p.bo, at(A.s1, H, wide_), H, x, nullptr, 0, wide_);
   if (f_.pre_ln) {
     ln(at(A.s1, H), p.ln2g, p.ln2b, at(A.u, H), false);
@@ -577,7 +599,7 @@ void Step::layer_forward(int l, LayerActs& A, bool rebuild) {
   {
     Timed t(this, MIMOSE_K_ATTN_FWD, 4.0 * T_ * L_ * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
-      mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, lens_, B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_);
+      mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, rows(), B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_);
   }
   // with dropout the product lands in the sum's buffer and an element-wise pass makes
   // sum = residual + dropout(product) in place; without it the residual rides in the epilogue
@@ -603,7 +625,7 @@ void Step::layer_forward(int l, LayerActs& A, bool rebuild) {
 void Step::layer_backward(int l, LayerActs& A) {
   const LayerIdx& p = c_->lidx[l];
   const int H = f_.hidden, F = ffn_of(f_, l), nh = f_.n_heads, d = H / nh;
-  const int64_t TH = (int64_t)T_ * H, TF = (int64_t)T_ * F;
+  const int64_t TH = (int64_t)Tpad_ * H, TF = (int64_t)Tpad_ * F;
   Arena& ar = c_->arena;
   if (late_ok()) reserve_workspace({{H, F}, {F, H}, {H, H}});
   else reserve_workspace({{H, F}, {F, H}, {H, H}, {3 * H, H}});
@@ -627,8 +649,9 @@ void Step::layer_backward(int l, LayerActs& A) {
   void* dact = talloc(TF);
   dgrad(dffn, H, H, p.w2, dact, F);
   {
-    Timed t(this, MIMOSE_K_GELU_BWD, 3.0 * TF * es_d());
-    if (!dry_) mk::gelu_bwd(dt_, dact, A.pre, TF, f_.gelu_tanh, st_);        // dact = d pre
+    const int64_t n = (int64_t)T_ * F;
+    Timed t(this, MIMOSE_K_GELU_BWD, 3.0 * n * es_d());
+    if (!dry_) mk::gelu_bwd(dt_, dact, A.pre, n, f_.gelu_tanh, st_);        // dact = d pre
   }
   wgrad(dact, F, F, A.u, H, p.w1, p.b1);
   // dact stays allocated until the end of the layer: the weight-gradient stream may still read
@@ -660,7 +683,7 @@ void Step::layer_backward(int l, LayerActs& A) {
   {
     Timed t(this, MIMOSE_K_ATTN_BWD, 8.0 * T_ * L_ * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
-      mk::attention_bwd(dt_, A.qkv, A.ctx, dctx, A.lse, delta, dqkv, lens_, B_, L_, nh, d, f_.causal,
+      mk::attention_bwd(dt_, A.qkv, A.ctx, dctx, A.lse, delta, dqkv, rows(), B_, L_, nh, d, f_.causal,
                         drop_desc(4 * (uint32_t)(l + 1), true), st_);
   }
   const void* a = f_.pre_ln ? A.n1 : A.x;
@@ -682,7 +705,7 @@ void Step::layer_backward(int l, LayerActs& A) {
 // Head forward, loss, head backward.  Leaves the gradient of the last layer's output in gA_.
 void Step::head(float* loss_dev) {
   const int H = f_.hidden, V = f_.vocab;
-  const int64_t TH = (int64_t)T_ * H, ldv = c_->ldv();
+  const int64_t TH = (int64_t)Tpad_ * H, ldv = c_->ldv();
   const int gelu = f_.gelu_tanh ? mk::GELU_TANH : mk::GELU_ERF;
   const void* hlast = f_.n_layers ? c_->acts[f_.n_layers - 1].out : h0_;
   reserve_workspace({{V, H}, {H, H}});
@@ -697,8 +720,8 @@ void Step::head(float* loss_dev) {
     ln_fwd(gz, c_->i_hg, c_->i_hb, t);
     dec_in = t;
   }
-  void* logits = talloc((int64_t)T_ * ldv);
-  float* row_loss = (float*)c_->arena.alloc((uint64_t)T_ * 4);
+  void* logits = talloc((int64_t)Tpad_ * ldv);
+  float* row_loss = (float*)c_->arena.alloc((uint64_t)Tpad_ * 4);
   {
     mk::GemmArgs a{dec_in, H, true, w(c_->i_tok), H, true, logits, ldv, false, T_, V, H};
     a.bias = f_.head ? w(c_->i_bdec) : nullptr;
@@ -731,7 +754,7 @@ void Step::head(float* loss_dev) {
     void* dt = talloc(TH);
     vocab_dgrad(dt, false);
     ln_bwd(dt, gz, c_->i_hg, c_->i_hb, dt, nullptr);                          // dt = d gz
-    if (!dry_) mk::gelu_bwd(dt_, dt, z, TH, f_.gelu_tanh, st_);               // dt = d z
+    if (!dry_) mk::gelu_bwd(dt_, dt, z, (int64_t)T_ * H, f_.gelu_tanh, st_);               // dt = d z
     wgrad(dt, H, H, hs, H, c_->i_wt, c_->i_bt);
     dgrad(dt, H, H, c_->i_wt, dhs, H, nullptr, wide_);
   } else {
@@ -745,27 +768,23 @@ void Step::head(float* loss_dev) {
 // boundaries of equal ids.  Only the last kernels of the step read them, so this runs after the
 // forward launches are queued, while the device is busy (second half of the pinned staging
 // buffer; the first half is still being read by the copy of the ids).
-void Step::embed_sort(const int32_t* tokens) {
+void Step::embed_sort() {
   if (dry_) return;
   int32_t* s = c_->stage;
   std::vector<int32_t>& count = c_->sort_count;
   count.assign((size_t)f_.vocab + 1, 0);
-  // positions that are padding carry a zero gradient: they are left out
-  auto each_position = [&](auto&& f) {
-    for (int b = 0; b < B_; ++b)
-      for (int t = b * L_, e = t + (lens_host ? lens_host[b] : L_); t < e; ++t) f(t);
-  };
-  each_position([&](int t) { ++count[(size_t)tokens[t] + 1]; });
+  const int32_t* ids = s;                 // the staged ids: real rows alone
+  for (int t = 0; t < T_; ++t) ++count[(size_t)ids[t] + 1];
   n_seg_ = 0;
-  int32_t* seg = s + 3 * (size_t)T_;
+  int32_t* seg = s + 3 * (size_t)Tpad_;
   for (int v = 0; v < f_.vocab; ++v) {
     if (count[v + 1]) seg[n_seg_++] = count[v];
     count[v + 1] += count[v];
   }
   seg[n_seg_] = count[f_.vocab];
-  int32_t* order = s + 2 * (size_t)T_;
-  each_position([&](int t) { order[count[tokens[t]]++] = t; });
-  HIPCHK(c_, hipMemcpyAsync(order_, order, (2 * (size_t)T_ + 1) * 4, hipMemcpyHostToDevice, st_));
+  int32_t* order = s + 2 * (size_t)Tpad_;
+  for (int t = 0; t < T_; ++t) order[count[ids[t]]++] = t;
+  HIPCHK(c_, hipMemcpyAsync(order_, order, (2 * (size_t)Tpad_ + 1) * 4, hipMemcpyHostToDevice, st_));
   HIPCHK(c_, hipEventRecord(c_->ev_stage[stage_turn_], st_));     // the last copy out of this staging buffer
   c_->stage_busy[stage_turn_] = true;
 }
@@ -775,7 +794,7 @@ void Step::embed_backward() {
   if (drop_on()) dropout(gA_, gA_, wide_, nullptr, 0);
   if (!f_.pre_ln) ln_bwd(gA_, emb_sum_, c_->i_eg, c_->i_eb, oA_, nullptr, wide_, false);
   if (!dry_)
-    mk::embed_bwd(dt_, oA_, ids_, order_, seg_, n_seg_, g(c_->i_tok), g(c_->i_pos), B_, L_, H, f_.max_seq, st_);
+    mk::embed_bwd(dt_, oA_, ids_, order_, seg_, n_seg_, g(c_->i_tok), g(c_->i_pos), rows(), B_, L_, H, f_.max_seq, st_);
 }
 
 void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bool wait) {
@@ -801,7 +820,11 @@ void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bo
   // the two halves of the batch run through the layers on two streams, meeting only where a
   // dropped layer's memory is handed to the next layer and at the end
   const bool split = split_forward() && N > 0;
-  const int nb0 = B_ / 2;
+  int nb0 = 1;                            // about half of the rows
+  for (int64_t at = first_row(1); nb0 + 1 < B_; ++nb0) {
+    at += lens_host ? lens_host[nb0] : L_;
+    if (2 * at > T_) break;
+  }
   if (split) {
     if (hipEventRecord(c_->ev_fork, st_) != hipSuccess || hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "fork of the forward streams failed"};
@@ -843,7 +866,7 @@ void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bo
       throw StepError{MIMOSE_ERR_HIP, "join of the forward streams failed"};
   }
 
-  embed_sort(tokens);                     // host work hidden behind the queued forward
+  embed_sort();                           // host work hidden behind the queued forward
   const uint64_t m_head = ar.top();
   ar.begin_section();
   head(loss_dev);
@@ -955,7 +978,7 @@ int do_step(mimose_ctx* c, const int32_t* tokens, const int32_t* labels, const i
   // ---- run
   c->dry = dry;
   Step s(c, B, L, plan, collect);
-  s.lens_host = dry ? nullptr : lengths;
+  if (!dry && lengths) s.set_lengths(lengths);
   float lv = 0.f;
   try {
     s.run(tokens, labels, &lv, dry || loss != nullptr);

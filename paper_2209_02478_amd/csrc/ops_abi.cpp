@@ -105,7 +105,7 @@ int mimose_op_attention_fwd(int32_t dtype, const void* qkv, void* ctx, float* ls
                             uint32_t site, uint32_t step, void* stream) {
   if (bad_dtype(dtype) || !qkv || !ctx || !lse || B < 0 || L < 0 || nh < 1 || bad_head(d) || bad_p(p_drop))
     return MIMOSE_ERR_INVALID_ARG;
-  mk::attention_fwd(dtype, qkv, ctx, lse, lengths, B, L, nh, d, causal, make_desc(p_drop, seed, site, step),
+  mk::attention_fwd(dtype, qkv, ctx, lse, mk::Rows{lengths, nullptr, 0}, B, L, nh, d, causal, make_desc(p_drop, seed, site, step),
                     (hipStream_t)stream);
   return done();
 }
@@ -117,7 +117,7 @@ int mimose_op_attention_bwd(int32_t dtype, const void* qkv, const void* ctx, con
   if (bad_dtype(dtype) || !qkv || !ctx || !dctx || !lse || !delta || !dqkv || B < 0 || L < 0 || nh < 1 || bad_head(d) ||
       bad_p(p_drop))
     return MIMOSE_ERR_INVALID_ARG;
-  mk::attention_bwd(dtype, qkv, ctx, dctx, lse, delta, dqkv, lengths, B, L, nh, d, causal,
+  mk::attention_bwd(dtype, qkv, ctx, dctx, lse, delta, dqkv, mk::Rows{lengths, nullptr, 0}, B, L, nh, d, causal,
                     make_desc(p_drop, seed, site, step), (hipStream_t)stream);
   return done();
 }
@@ -125,7 +125,7 @@ int mimose_op_attention_bwd(int32_t dtype, const void* qkv, const void* ctx, con
 int mimose_op_dropout(int32_t dtype, void* dst, const void* src, int32_t io_f32, const void* resid, int64_t n, float p,
                       uint64_t seed, uint32_t site, uint32_t step, void* stream) {
   if (bad_dtype(dtype) || !dst || !src || n < 0 || bad_p(p)) return MIMOSE_ERR_INVALID_ARG;
-  mk::dropout_apply(dtype, dst, src, io_f32 != 0, resid, n, make_desc(p, seed, site, step), (hipStream_t)stream);
+  mk::dropout_apply(dtype, dst, src, io_f32 != 0, resid, n, make_desc(p, seed, site, step), mk::Rows(), 0, 0, 0, (hipStream_t)stream);
   return done();
 }
 
@@ -141,7 +141,7 @@ int mimose_op_embed_fwd(int32_t dtype, const int32_t* ids, const void* tok, cons
                         int32_t has_ln, void* stream) {
   if (bad_dtype(dtype) || !ids || !tok || !pos || !y || B < 0 || L < 0 || H < 1 || H > mk::kMaxRowWidth) return MIMOSE_ERR_INVALID_ARG;
   if (has_ln && (!gamma || !beta)) return MIMOSE_ERR_INVALID_ARG;
-  mk::embed_fwd(dtype, ids, tok, pos, gamma, beta, sum_out, y, B, L, H, eps, has_ln, (hipStream_t)stream);
+  mk::embed_fwd(dtype, ids, tok, pos, gamma, beta, sum_out, y, mk::Rows(), B * L, B, L, H, eps, has_ln, (hipStream_t)stream);
   return done();
 }
 
@@ -150,7 +150,7 @@ int mimose_op_embed_bwd(int32_t dtype, const void* d, const int32_t* ids, const 
                         void* stream) {
   if (bad_dtype(dtype) || !d || !ids || !order || !seg || !dtok || !dpos || B < 0 || L < 0 || H < 1 || n_seg < 0 || max_seq < L)
     return MIMOSE_ERR_INVALID_ARG;
-  mk::embed_bwd(dtype, d, ids, order, seg, n_seg, dtok, dpos, B, L, H, max_seq, (hipStream_t)stream);
+  mk::embed_bwd(dtype, d, ids, order, seg, n_seg, dtok, dpos, mk::Rows(), B, L, H, max_seq, (hipStream_t)stream);
   return done();
 }
 

@@ -532,12 +532,12 @@ template <typename T, int NPL>
 __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restrict__ ids, const T* __restrict__ tok,
                                                         const T* __restrict__ pos, const T* __restrict__ gamma,
                                                         const T* __restrict__ beta, T* __restrict__ sum_out,
-                                                        T* __restrict__ y, int Trows, int L, int H, float eps,
-                                                        int has_ln) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                        T* __restrict__ y, Rows rows, int Trows, int B, int L, int H,
+                                                        float eps, int has_ln) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= Trows) return;
   const T* tr = tok + (int64_t)ids[row] * H;
-  const T* pr = pos + (int64_t)(row % L) * H;
+  const T* pr = pos + (int64_t)(padded_row(rows, row, B, L) % L) * H;
   float v[NPL];
 #pragma unroll
   for (int i = 0; i < NPL; ++i) {
@@ -579,16 +579,19 @@ __device__ __forceinline__ void load_few(const T* p, float (&v)[VEC]) {
   }
 }
 
-// dpos[p][c] = sum over samples b (in order) of d[b*L+p][c]; rows p >= L are cleared.
+// dpos[p][c] = sum over samples b (in order) of d[row of b's token p][c]; rows p >= L are cleared.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_bwd_pos_kernel(const T* __restrict__ d, float* __restrict__ dpos,
-                                                            int B, int L, int H, int max_seq) {
+                                                            Rows rows, int B, int L, int H, int max_seq) {
   int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (int64_t)max_seq * H) return;
   int p = (int)(idx / H), c = (int)(idx - (int64_t)p * H);
   float s = 0.f;
   if (p < L)
-    for (int b = 0; b < B; ++b) s += ld<T>(d + ((int64_t)b * L + p) * H + c);
+    for (int b = 0; b < B; ++b) {
+      const Sample sm = sample_rows(rows, b, L);
+      if (p < sm.n) s += ld<T>(d + (sm.first + p) * H + c);
+    }
   dpos[idx] = s;
 }
 
@@ -681,11 +684,16 @@ __global__ __launch_bounds__(256) void widen_kernel(const T* __restrict__ src, f
 // i / 4.  Four elements per thread; dst may be src.
 template <typename TIO, typename TR>
 __global__ __launch_bounds__(256) void dropout_kernel(TIO* __restrict__ dst, const TIO* src, const TR* __restrict__ resid,
-                                                      int64_t n, DropDesc d) {
+                                                      int64_t n, DropDesc d, Rows rows, int B, int L, int H) {
   const int64_t blk = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t i0 = 4 * blk;
   if (i0 >= n) return;
-  const uint4 w4 = drop_words(d, (uint64_t)blk);
+  uint64_t mask_blk = (uint64_t)blk;
+  if (rows.ends) {
+    const int row = (int)(i0 / H);
+    mask_blk = ((uint64_t)padded_row(rows, row, B, L) * H + (uint64_t)(i0 - (int64_t)row * H)) >> 2;
+  }
+  const uint4 w4 = drop_words(d, mask_blk);
   const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
   const int cnt = (int)min((int64_t)4, n - i0);
   for (int e = 0; e < cnt; ++e) {
@@ -890,28 +898,28 @@ void softmax_xent(int dtype, void* logits, int64_t ldl, const int32_t* labels, f
 
 template <typename T>
 static void embed_fwd_t(const int32_t* ids, const void* tok, const void* pos, const void* g, const void* b,
-                        void* sum_out, void* y, int B, int L, int H, float eps, int has_ln, hipStream_t st) {
-  int T_ = B * L;
+                        void* sum_out, void* y, const Rows& rows, int T_, int B, int L, int H, float eps, int has_ln,
+                        hipStream_t st) {
   dim3 grid((T_ + 3) / 4);
 #define M_(NPL) hipLaunchKernelGGL((embed_fwd_kernel<T, NPL>), grid, dim3(256), 0, st, ids, (const T*)tok,     \
-                                   (const T*)pos, (const T*)g, (const T*)b, (T*)sum_out, (T*)y, T_, L, H, eps, \
-                                   has_ln)
+                                   (const T*)pos, (const T*)g, (const T*)b, (T*)sum_out, (T*)y, rows, T_, B, L, \
+                                   H, eps, has_ln)
   DISPATCH_NPL(H, M_);
 #undef M_
 }
 void embed_fwd(int dtype, const int32_t* ids, const void* tok, const void* pos, const void* gamma,
-               const void* beta, void* sum_out, void* y, int B, int L, int H, float eps, int has_ln,
-               hipStream_t st) {
-  if (B * L <= 0) return;
-  if (dtype == BF16) embed_fwd_t<bf16_t>(ids, tok, pos, gamma, beta, sum_out, y, B, L, H, eps, has_ln, st);
-  else embed_fwd_t<float>(ids, tok, pos, gamma, beta, sum_out, y, B, L, H, eps, has_ln, st);
+               const void* beta, void* sum_out, void* y, const Rows& rows, int T, int B, int L, int H, float eps,
+               int has_ln, hipStream_t st) {
+  if (T <= 0) return;
+  if (dtype == BF16) embed_fwd_t<bf16_t>(ids, tok, pos, gamma, beta, sum_out, y, rows, T, B, L, H, eps, has_ln, st);
+  else embed_fwd_t<float>(ids, tok, pos, gamma, beta, sum_out, y, rows, T, B, L, H, eps, has_ln, st);
 }
 
 template <typename T>
 static void embed_bwd_t(const void* d, const int32_t* ids, const int32_t* order, const int32_t* seg, int n_seg,
-                        float* dtok, float* dpos, int B, int L, int H, int max_seq, hipStream_t st) {
+                        float* dtok, float* dpos, const Rows& rows, int B, int L, int H, int max_seq, hipStream_t st) {
   hipLaunchKernelGGL(embed_bwd_pos_kernel<T>, dim3((unsigned)(((int64_t)max_seq * H + 255) / 256)), dim3(256), 0, st,
-                     (const T*)d, dpos, B, L, H, max_seq);
+                     (const T*)d, dpos, rows, B, L, H, max_seq);
   if (n_seg <= 0) return;
   const unsigned gx = (unsigned)((n_seg + 15) / 16);
   if (H % 4 == 0 && (((uintptr_t)d) & 15) == 0)
@@ -922,10 +930,10 @@ static void embed_bwd_t(const void* d, const int32_t* ids, const int32_t* order,
                        seg, n_seg, dtok, H);
 }
 void embed_bwd(int dtype, const void* d, const int32_t* ids, const int32_t* order, const int32_t* seg,
-               int n_seg, float* dtok, float* dpos, int B, int L, int H, int max_seq, hipStream_t st) {
+               int n_seg, float* dtok, float* dpos, const Rows& rows, int B, int L, int H, int max_seq, hipStream_t st) {
   if (B * L <= 0) return;
-  if (dtype == BF16) embed_bwd_t<bf16_t>(d, ids, order, seg, n_seg, dtok, dpos, B, L, H, max_seq, st);
-  else embed_bwd_t<float>(d, ids, order, seg, n_seg, dtok, dpos, B, L, H, max_seq, st);
+  if (dtype == BF16) embed_bwd_t<bf16_t>(d, ids, order, seg, n_seg, dtok, dpos, rows, B, L, H, max_seq, st);
+  else embed_bwd_t<float>(d, ids, order, seg, n_seg, dtok, dpos, rows, B, L, H, max_seq, st);
 }
 
 void convert_from_f32(int dtype, const float* src, void* dst, int64_t n, hipStream_t st) {
@@ -943,18 +951,18 @@ void convert_to_f32(int dtype, const void* src, float* dst, int64_t n, hipStream
 }
 
 void dropout_apply(int dtype, void* dst, const void* src, bool io_f32, const void* resid, int64_t n, const DropDesc& d,
-                   hipStream_t st) {
+                   const Rows& rows, int B, int L, int H, hipStream_t st) {
   if (n <= 0) return;
   dim3 grid((unsigned)(((n + 3) / 4 + 255) / 256));
   if (dtype == BF16 && !io_f32)
     hipLaunchKernelGGL((dropout_kernel<bf16_t, bf16_t>), grid, dim3(256), 0, st, (bf16_t*)dst, (const bf16_t*)src,
-                       (const bf16_t*)resid, n, d);
+                       (const bf16_t*)resid, n, d, rows, B, L, H);
   else if (dtype == BF16)
     hipLaunchKernelGGL((dropout_kernel<float, bf16_t>), grid, dim3(256), 0, st, (float*)dst, (const float*)src,
-                       (const bf16_t*)resid, n, d);
+                       (const bf16_t*)resid, n, d, rows, B, L, H);
   else
     hipLaunchKernelGGL((dropout_kernel<float, float>), grid, dim3(256), 0, st, (float*)dst, (const float*)src,
-                       (const float*)resid, n, d);
+                       (const float*)resid, n, d, rows, B, L, H);
 }
 
 void adamw_update(int lowp_dtype, const AdamTensor* tensors, const AdamChunk* chunks, int n_chunks, AdamHyper h,
