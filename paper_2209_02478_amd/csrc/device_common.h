@@ -27,14 +27,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // rows of sample b: the first, how many there are, how many of them may be attended to
 struct Sample { int64_t first; int n, keys; };
 __device__ __forceinline__ Sample sample_rows(const Rows& r, int b, int L) {
-  if (r.ends) {
-    const int first = b ? r.ends[b - 1] : r.first, n = r.ends[b] - first;
-    return {first - r.first, n, n};
-  }
-  return {(int64_t)b * L, L, r.lens ? r.lens[b] : L};
+  const int keys = r.lens ? r.lens[b] : L;
+  if (!r.ends) return {(int64_t)b * L, L, keys};
+  const int first = b ? r.ends[b - 1] : r.first;
+  return {first - r.first, r.ends[b] - first, keys};
 }
 
-// row of the padded batch that row `row` of the real rows alone stands for
+// row of the padded batch that row `row` stands for
 __device__ __forceinline__ int padded_row(const Rows& r, int row, int B, int L) {
   if (!r.ends) return row;
   int lo = 0, hi = B - 1;                             // the first sample that ends behind the row

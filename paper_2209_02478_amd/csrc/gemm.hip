@@ -125,7 +125,7 @@ struct Tile {
 // k loop of one block.  Global loads run two k tiles ahead of the MFMAs (two register sets), LDS
 // holds two tiles, one barrier per k tile.  EDGE: tile crosses a matrix edge or K has a tail.
 template <bool AK, bool BKM, bool EDGE>
-__device__ __forceinline__ void mainloop(const GemmDev& p, bf16_t* As, bf16_t* Bs, int m0, int n0, int kt_begin, int nk,
+__device__ __forceinline__ void mainloop(const GemmDev& p, bf16_t* As, bf16_t* Bs, int m0, int n0, int k_begin, int k_end,
                                          int tid, int lane, int wm, int wn, bool do_rowsum, f32x16 (&acc)[2][2],
                                          float& rs) {
   typedef Tile<AK> TA;
@@ -135,13 +135,13 @@ __device__ __forceinline__ void mainloop(const GemmDev& p, bf16_t* As, bf16_t* B
   // two register sets (named, never indexed at run time, so they stay in registers)
   u32x4 ra0[NCH], rb0[NCH], ra1[NCH], rb1[NCH];
   auto fetch = [&](u32x4 (&xa)[NCH], u32x4 (&xb)[NCH], int kt) {      // k tile kt (relative) -> register set
-    const int k0 = (kt_begin + kt) * BK;
+    const int k0 = k_begin + kt * BK;
     if (!EDGE) {
       TA::load(xa, A, p.lda, m0, k0, tid);
       TB::load(xb, B, p.ldb, n0, k0, tid);
     } else {
-      const typename TA::Regs ea = TA::load_edge(A, p.lda, p.M, p.K, m0, k0, tid);
-      const typename TB::Regs eb = TB::load_edge(B, p.ldb, p.N, p.K, n0, k0, tid);
+      const typename TA::Regs ea = TA::load_edge(A, p.lda, p.M, k_end, m0, k0, tid);
+      const typename TB::Regs eb = TB::load_edge(B, p.ldb, p.N, k_end, n0, k0, tid);
 #pragma unroll
       for (int i = 0; i < NCH; ++i) { xa[i] = ea.v[i]; xb[i] = eb.v[i]; }
     }
@@ -172,6 +172,7 @@ __device__ __forceinline__ void mainloop(const GemmDev& p, bf16_t* As, bf16_t* B
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
     }
   };
+  const int nk = (k_end - k_begin + BK - 1) / BK;
   if (nk <= 0) return;
   fetch(ra0, rb0, 0);
   stash(ra0, rb0, 0);
@@ -244,18 +245,14 @@ __global__ __launch_bounds__(256, 2) void bgemm_kernel(GemmDev p, int tiles_n, i
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // this block's k tiles: [kt_begin, kt_begin + nk)
-  const int nk_all = (p.K + BK - 1) / BK;
-  const int per_split = (nk_all + p.splits - 1) / p.splits;
-  const int kt_begin = split * per_split;
-  const int nk = max(0, min(nk_all, kt_begin + per_split) - kt_begin);
+  const int k_begin = p.kb[split], k_end = p.kb[split + 1];
   const bool do_rowsum = p.a_rowsum && tile_n == 0;
   float rs = 0.f;
   // tiles fully inside the matrices take the loop without any bounds logic
-  if (m0 + BM <= p.M && n0 + BN <= p.N && p.K % BK == 0)
-    mainloop<AK, BKM, false>(p, As, Bs, m0, n0, kt_begin, nk, tid, lane, wm, wn, do_rowsum, acc, rs);
+  if (m0 + BM <= p.M && n0 + BN <= p.N && (k_end - k_begin) % BK == 0)
+    mainloop<AK, BKM, false>(p, As, Bs, m0, n0, k_begin, k_end, tid, lane, wm, wn, do_rowsum, acc, rs);
   else
-    mainloop<AK, BKM, true>(p, As, Bs, m0, n0, kt_begin, nk, tid, lane, wm, wn, do_rowsum, acc, rs);
+    mainloop<AK, BKM, true>(p, As, Bs, m0, n0, k_begin, k_end, tid, lane, wm, wn, do_rowsum, acc, rs);
 
   GemmDev q = p;
   float* rowsum = p.a_rowsum;
@@ -413,14 +410,27 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   p.splits = 1; p.partial = nullptr;
   p.a_tail_zero = g.a_tail_zero ? 1 : 0;
   if (p.gelu && (p.c_f32 || !p.gelu_out)) return false;
+  const int rule_rows = g.rule_rows > 0 ? g.rule_rows : g.M;
   if (dtype == F32) {
-    launch_sgemm(p, g.rule_rows > 0 ? g.rule_rows : g.M, st, g.time_start, g.time_stop);
+    launch_sgemm(p, rule_rows, st, g.time_start, g.time_stop);
     return true;
   }
   if ((g.lda & 7) || (g.ldb & 7) || !aligned16(g.A) || !aligned16(g.B)) return false;
   const bool may_split = g.workspace && g.c_f32 && !g.bias && !g.resid && !g.gelu && aligned16(g.workspace);
+  const int rule_k = g.k_blocks ? g.k_padded : g.K;
+  // the parts of the reduction, in whole steps of `unit` indices (of the padded batch)
+  auto cut = [&](int splits, int unit) {
+    const int steps = (rule_k + unit - 1) / unit, per = (steps + splits - 1) / splits;
+    p.splits = splits;
+    for (int i = 0; i <= splits; ++i) {
+      int64_t at = std::min<int64_t>((int64_t)i * per * unit, rule_k);
+      if (g.k_blocks && at < rule_k) at = (int64_t)g.k_blocks[at / kRowBlock] * kRowBlock;
+      p.kb[i] = (int)std::min<int64_t>(at, g.K);
+    }
+  };
+  cut(1, 64);
   auto splits_for = [&](int want) {
-    const int by_k = (g.K + 255) / 256;                                   // >= 256 reduction indices per part
+    const int by_k = (rule_k + 255) / 256;                                   // >= 256 reduction indices per part
     const int sp = want < by_k ? want : by_k;
     return may_split && sp > 1 && g.workspace_bytes >= ((size_t)sp * g.M * g.N + (size_t)sp * g.M) * 4 ? sp : 1;
   };
@@ -430,22 +440,22 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
                    (!g.gelu_out || aligned16(g.gelu_out));
   p.vec = vec ? 1 : 0;
   // a very long reduction behind a k-major A and an m-major B (the head's data gradient)
-  if (g.a_kmajor && !g.b_kmajor && g.K >= kLongK && g.M >= 256 && g.N >= 256 && !g.bias && !g.resid && !g.gelu &&
-      !g.a_rowsum && g.M <= kLongKRows) {
-    int sp = long_k_splits(g.M, g.N);
+  if (g.a_kmajor && !g.b_kmajor && g.K >= kLongK && rule_rows >= 256 && g.N >= 256 && !g.bias && !g.resid && !g.gelu &&
+      !g.a_rowsum && rule_rows <= kLongKRows) {
+    int sp = long_k_splits(rule_rows, g.N);
     if (sp > 1 && !(g.workspace && aligned16(g.workspace) && g.workspace_bytes >= (size_t)sp * g.M * g.N * 4)) sp = 1;
-    p.splits = sp;
+    cut(sp, 64);
     p.partial = sp > 1 ? (float*)g.workspace : nullptr;
     if (launch_bgemm_pp(p, st, g.time_start, sp > 1 ? nullptr : g.time_stop)) {
       if (sp > 1) launch_splitk_reduce(p, st, g.time_stop);
       return true;
     }
-    p.splits = 1; p.partial = nullptr;
+    cut(1, 64); p.partial = nullptr;
   }
   // few output tiles and a long reduction (weight gradients): cut k so the whole chip works
   {
     const int sp = splits_for(gemm_splits(g.M, g.N));
-    if (sp > 1) { p.splits = sp; p.partial = (float*)g.workspace; }
+    if (sp > 1) { cut(sp, 32); p.partial = (float*)g.workspace; }
   }
   // large tiles where their rounds are well filled (a choice made from the shape alone)
   if (p.splits == 1 && use_pp(g.M, g.N, g.K) && launch_bgemm_pp(p, st, g.time_start, g.time_stop)) return true;

@@ -19,6 +19,7 @@ struct GemmDev {
   int a_k, b_k, c_f32, gelu;
   int vec;               // C, bias, residual and GELU output allow 16-byte accesses at columns n % 8 == 0
   int a_tail_zero;       // A k-major, K % 8 != 0: the columns up to the next multiple of 8 exist and are zero
+  int kb[9];             // part s of the reduction: indices kb[s] .. kb[s + 1] - 1
   int splits;            // > 1: k range cut in `splits` parts, raw fp32 tiles go to `partial`
   float* partial;        // [splits][M][N] followed by [splits][M] row sums
 };
@@ -97,6 +98,8 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
       continue;
     }
     const int n = nh + (lane % LPR) * 8, c0 = 2 * (lane % LPR);
+    float cb[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};    // the columns' bias: the same for every row
+    if (p.bias && n + 8 <= p.N) unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.bias + n), cb);
     for (int it = 0; it < 64 / RPI; ++it) {
       const int row = it * RPI + lane / LPR, m = m0w + row;
       if (m >= p.M || n >= p.N) continue;
@@ -109,9 +112,8 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
       }
       float f[8];
       if (p.bias) {
-        unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.bias + n), f);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += f[e];
+        for (int e = 0; e < 8; ++e) v[e] += cb[e];
       }
       if (p.resid) {
         unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.resid + (int64_t)m * p.ldr + n), f);

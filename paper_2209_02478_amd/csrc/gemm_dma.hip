@@ -162,10 +162,8 @@ __global__ __launch_bounds__(256, 3) void bgemm_dma_kernel(GemmDev p, int tiles_
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int nk_all = (p.K + BK - 1) / BK;
-  const int per_split = (nk_all + p.splits - 1) / p.splits;
-  const int kt_begin = split * per_split;
-  const int nk = max(0, min(nk_all, kt_begin + per_split) - kt_begin);
+  const int k_begin = p.kb[split], k_end = p.kb[split + 1];
+  const int nk = (k_end - k_begin + BK - 1) / BK;
   const bool do_rowsum = p.a_rowsum && tile_n == 0;
   float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -174,8 +172,8 @@ __global__ __launch_bounds__(256, 3) void bgemm_dma_kernel(GemmDev p, int tiles_
 #pragma unroll
   for (int j = 0; j < DMA_PER_WAVE; ++j) {
     const int slot = (wave * DMA_PER_WAVE + j) * 64 + lane;
-    srcA[j] = make_src<AK>((const bf16_t*)p.A, p.lda, p.M, m0, kt_begin * BK, slot);
-    srcB[j] = make_src<BKM>((const bf16_t*)p.B, p.ldb, p.N, n0, kt_begin * BK, slot);
+    srcA[j] = make_src<AK>((const bf16_t*)p.A, p.lda, p.M, m0, k_begin, slot);
+    srcB[j] = make_src<BKM>((const bf16_t*)p.B, p.ldb, p.N, n0, k_begin, slot);
   }
   // LDS side of a load: byte address of the ring + stage + this wave's share, all scalar, so that
   // issuing a load is an M0 write, the load itself and a pointer increment
@@ -189,9 +187,9 @@ __global__ __launch_bounds__(256, 3) void bgemm_dma_kernel(GemmDev p, int tiles_
     for (int j = 0; j < DMA_PER_WAVE; ++j) {
       const bf16_t* ga = srcA[j].p;
       const bf16_t* gb = srcB[j].p;
-      if (KTAIL) {                                                    // chunks past K read zeros
-        if (srcA[j].k_first + k_issue >= p.K) ga = (const bf16_t*)g_zero_chunk;
-        if (srcB[j].k_first + k_issue >= p.K) gb = (const bf16_t*)g_zero_chunk;
+      if (KTAIL) {                                                    // chunks past the part's end read zeros
+        if (srcA[j].k_first + k_issue >= k_end) ga = (const bf16_t*)g_zero_chunk;
+        if (srcB[j].k_first + k_issue >= k_end) gb = (const bf16_t*)g_zero_chunk;
       }
       direct_load(ga, a_lds + (uint32_t)j * 1024u);
       direct_load(gb, b_lds + (uint32_t)j * 1024u);
@@ -299,7 +297,8 @@ template <bool AK, bool BKM>
 static void launch_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
-  const bool ktail = p.K % BK != 0;
+  bool ktail = false;
+  for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % BK != 0;
   dim3 grid(per * 8), block(256);
   // t0, t1 (optional): events bound to this kernel's own start and end
   if (ktail) hipExtLaunchKernelGGL((bgemm_dma_kernel<AK, BKM, true>), grid, block, 0, st, t0, t1, 0, p, tiles_n, total, per);

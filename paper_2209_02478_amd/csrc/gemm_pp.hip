@@ -174,10 +174,8 @@ __global__ __launch_bounds__(512) void bgemm_pp_kernel(GemmDev p, int tiles_n, i
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[a][b][i][j][r] = 0.f;
 
-  const int nk_all = (p.K + PBK - 1) / PBK;
-  const int per_split = (nk_all + p.splits - 1) / p.splits;
-  const int kt_begin = split * per_split;
-  const int nk = max(0, min(nk_all, kt_begin + per_split) - kt_begin);
+  const int k_begin = p.kb[split], k_end = p.kb[split + 1];
+  const int nk = (k_end - k_begin + PBK - 1) / PBK;
   const bool do_rowsum = p.a_rowsum && tile_n == 0;   // A m-major only (the launcher sees to it)
   float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -187,21 +185,21 @@ __global__ __launch_bounds__(512) void bgemm_pp_kernel(GemmDev p, int tiles_n, i
   int ka[G::A_LOADS], kb[G::B_LOADS];
 #pragma unroll
   for (int jj = 0; jj < G::A_LOADS; ++jj)
-    pa[jj] = pp_src<AK, BM>((const bf16_t*)p.A, p.lda, p.M, m0, kt_begin * PBK, wave * G::A_LOADS + jj, lane, ka[jj]);
+    pa[jj] = pp_src<AK, BM>((const bf16_t*)p.A, p.lda, p.M, m0, k_begin, wave * G::A_LOADS + jj, lane, ka[jj]);
 #pragma unroll
   for (int jj = 0; jj < G::B_LOADS; ++jj)
-    pb[jj] = pp_src<BKM, BN>((const bf16_t*)p.B, p.ldb, p.N, n0, kt_begin * PBK, wave * G::B_LOADS + jj, lane, kb[jj]);
+    pb[jj] = pp_src<BKM, BN>((const bf16_t*)p.B, p.ldb, p.N, n0, k_begin, wave * G::B_LOADS + jj, lane, kb[jj]);
   const int64_t step_a = AK ? PBK : (int64_t)PBK * p.lda, step_b = BKM ? PBK : (int64_t)PBK * p.ldb;
   bf16_t* const ring_b = ring + NA * G::A_ELEMS;
   // the next tile to request of each operand: its first reduction index and its slot
-  int ka_next = kt_begin * PBK, kb_next = kt_begin * PBK, slot_a_next = 0, slot_b_next = 0;
+  int ka_next = k_begin, kb_next = k_begin, slot_a_next = 0, slot_b_next = 0;
   // one direct load of the next A (B) tile, and the bookkeeping once all of a tile's are out
   // (the LDS side is scalar arithmetic on byte addresses: slot base + this wave's share)
   const uint32_t lds_a0 = pp_lds_address(ring) + (uint32_t)wave * G::A_LOADS * 1024u;
   const uint32_t lds_b0 = pp_lds_address(ring_b) + (uint32_t)wave * G::B_LOADS * 1024u;
   auto load_a = [&](int jj) {
     const bf16_t* ga = pa[jj];
-    if (KTAIL && ka_next + ka[jj] >= p.K) ga = (const bf16_t*)g_zero16;        // chunks past K read zeros
+    if (KTAIL && ka_next + ka[jj] >= k_end) ga = (const bf16_t*)g_zero16;        // chunks past the part's end read zeros
     pp_direct_load(ga, lds_a0 + (uint32_t)slot_a_next * (G::A_ELEMS * 2u) + (uint32_t)jj * 1024u);
     pa[jj] += step_a;
   };
@@ -211,7 +209,7 @@ __global__ __launch_bounds__(512) void bgemm_pp_kernel(GemmDev p, int tiles_n, i
   };
   auto load_b = [&](int jj) {
     const bf16_t* gb = pb[jj];
-    if (KTAIL && kb_next + kb[jj] >= p.K) gb = (const bf16_t*)g_zero16;
+    if (KTAIL && kb_next + kb[jj] >= k_end) gb = (const bf16_t*)g_zero16;
     pp_direct_load(gb, lds_b0 + (uint32_t)slot_b_next * (G::B_ELEMS * 2u) + (uint32_t)jj * 1024u);
     pb[jj] += step_b;
   };
@@ -398,7 +396,9 @@ static void launch_pp(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_
   const int tiles_m = (p.M + G::BM - 1) / G::BM, tiles_n = (p.N + G::BN - 1) / G::BN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
   dim3 grid(per * 8), block(512);
-  if (p.K % PBK)
+  bool ktail = false;
+  for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % PBK != 0;
+  if (ktail)
     hipExtLaunchKernelGGL((bgemm_pp_kernel<AK, BKM, true, WM, WN, TM, TN, NA, NB>), grid, block, G::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
   else
     hipExtLaunchKernelGGL((bgemm_pp_kernel<AK, BKM, false, WM, WN, TM, TN, NA, NB>), grid, block, G::SMEM, st, t0, t1, 0, p, tiles_n, total, per);

@@ -23,17 +23,23 @@ struct DropDesc {
 };
 
 // Where the samples of a batch of B x L tokens are.  Neither array: sample b fills rows b*L ..
-// b*L + L - 1.  lens (device, [B]): the same rows, of which the first lens[b] are real; keys from
-// lens[b] on get no weight.  ends (device, [B]): the real rows alone, one sample after the other,
-// sample b in rows ends[b-1] .. ends[b] - 1.  Indices inside a sample stay those of the padded
-// batch everywhere (lse, delta, dropout masks).
-// ends may point at the entry of a later sample, with first the row that sample begins at: then
-// row pointers are those of that row.
+// b*L + L - 1.  lens (device, [B]): of a sample's rows the first lens[b] are real, no query gives the
+// others' keys weight.  ends (device, [B]): padding was left out of the rows and sample b has rows
+// ends[b-1] .. ends[b] - 1, at least its real ones (lens is given too).  Indices inside a sample
+// stay those of the padded batch everywhere (lse, delta, dropout masks).
+// ends and lens may point at the entries of a later sample, with first the row that sample begins
+// at: then row pointers are those of that row.
 struct Rows {
   const int32_t* lens = nullptr;
   const int32_t* ends = nullptr;
   int32_t first = 0;
 };
+
+// Rows of a padded batch that are left out: whole blocks of kRowBlock rows of padding, whose
+// gradients are zeros.  A kernel that sums over rows in groups (MFMA steps of 16 reduction indices,
+// LayerNorm's chunks) then meets the groups of the whole batch, minus groups of zeros, so the sums
+// are the same bit for bit.
+constexpr int kRowBlock = 16;
 
 struct GemmArgs {
   const void* A; int64_t lda; bool a_kmajor;
@@ -49,9 +55,13 @@ struct GemmArgs {
   // A k-major with K not a multiple of 8: its columns [K, K rounded up to 8) exist (lda covers
   // them) and hold zeros, so a kernel that moves whole 16-byte chunks may read them
   bool a_tail_zero = false;
-  // rows the choice of kernel is made from (0: M): a product issued in row ranges names the whole
-  // here, so that every range sums in the order the whole would
+  // rows the choice of kernel is made from (0: M): a product issued in row ranges, or with padding
+  // left out of its rows, names the whole here, so that every row sums in the order it would there
   int rule_rows = 0;
+  // reduction over the rows of a batch with padding left out: the padded row count, and for each of
+  // its blocks of kRowBlock rows (and one past the last) how many kept blocks lie before it (host)
+  int k_padded = 0;
+  const int32_t* k_blocks = nullptr;
   void* workspace = nullptr;       // optional scratch of gemm_workspace_bytes(M, N) for split reductions
   size_t workspace_bytes = 0;
   // optional, both or neither: recorded by the product kernel's own start and end (not by markers
@@ -73,6 +83,12 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st);
 // x_f32: in a bf16 configuration the input rows are fp32 (an unrounded residual sum)
 void layernorm_fwd(int dtype, const void* x, bool x_f32, const void* gamma, const void* beta,
                    void* y, int T, int H, float eps, hipStream_t st);
+// x = resid + dropout(x) in place, then y = LayerNorm(x) (left out when y is null): one pass.
+// resid: storage type.  H must be a multiple of 8 (bf16) or 4 (fp32), every pointer 16-byte aligned;
+// masks and rows as in dropout_apply.
+void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, const void* gamma, const void* beta,
+                           void* y, int T, int H, float eps, const DropDesc& d, const Rows& rows, int B, int L,
+                           hipStream_t st);
 // partial: fp32 scratch of partial_rows(T) * 2 * H elements
 // dx = LayerNorm backward (+ add when given); dx may alias dy when they have the same type;
 // dy_f32 / x_f32: in a bf16 configuration those inputs are fp32
@@ -80,9 +96,20 @@ void layernorm_bwd(int dtype, const void* dy, bool dy_f32, const void* x, bool x
                    const void* gamma, void* dx, const void* add, float* dgamma, float* dbeta,
                    float* partial, int T, int H, float eps, hipStream_t st);
 // the two halves of layernorm_bwd: dx and the per-chunk partial sums; then dgamma, dbeta from them
+// masked (optional): dx as stored with the dropout mask of d applied, for the branch behind a
+// dropped product; H and pointers then as in dropout_layernorm_fwd.
+struct LnBwdMasked {
+  void* masked = nullptr;
+  DropDesc d;
+  Rows rows;
+  int B = 0, L = 0;
+};
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
-                        const void* add, float* partial, int T, int H, float eps, hipStream_t st);
-void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, int T, int H, hipStream_t st);
+                        const void* add, float* partial, int T, int H, float eps, const LnBwdMasked& extra, hipStream_t st);
+// chunk_at (optional, device): T is the padded row count, and chunk_at[c] says which of the partial
+// rows belongs to its rows c * kRowBlock .. (-1: left out, they would add zeros)
+void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T, int H,
+                          hipStream_t st);
 int partial_rows(int T);
 // layernorm_bwd with the partial sums in a fixed device array of the library (no allocation, no
 // workspace argument).  Returns 0, -1 when partial_rows(T) * 2 * H exceeds

@@ -223,15 +223,23 @@ class Step {
         st_(c->stream), dt_(c->cfg.dtype), es_(c->elt()) {}
 
   void run(const int32_t* tokens, const int32_t* labels, float* loss_out, bool wait);
-  // Padded batch: real tokens per sample ([B], host).  Its real rows alone go through the model, one
-  // sample after the other (padding gets no attention, scores nothing and passes no gradient on),
-  // while every tensor keeps the size of the padded batch, which is what the planner knows.
+  // Padded batch: real tokens per sample ([B], host).  Padding gets no attention, scores nothing and
+  // passes no gradient on, so blocks of kRowBlock rows that hold nothing else are left out of every
+  // kernel, while every tensor keeps the size of the padded batch, which is what the planner knows.
+  // (Single rows of padding stay: the sums over rows are then those of the padded batch bit for bit.)
+  // fp32 sums are not held to that: there every row of padding is left out.
   void set_lengths(const int32_t* lens) {
     lens_host = lens;
-    T_ = 0;
-    for (int b = 0; b < B_; ++b) T_ += lens[b];
+    row_block_ = dt_ == mk::BF16 ? mk::kRowBlock : 1;
+    const int nb = (Tpad_ + row_block_ - 1) / row_block_;
+    blocks_.assign((size_t)nb + 1, 0);
+    for (int b = 0; b < B_; ++b)
+      for (int j = b * L_ / row_block_; j <= (b * L_ + lens[b] - 1) / row_block_; ++j) blocks_[j + 1] = 1;
+    for (int j = 0; j < nb; ++j) blocks_[j + 1] += blocks_[j];
+    // the batch's last block may be a part of one
+    const int last = blocks_[nb] > blocks_[nb - 1] ? Tpad_ - (nb - 1) * row_block_ : row_block_;
+    T_ = (blocks_[nb] - 1) * row_block_ + last;
   }
-
   // collected bytes (valid after run)
   uint64_t e_bytes = 0, g_bytes = 0;
   std::vector<uint64_t> a_bytes, b_bytes, w_bytes;
@@ -242,13 +250,16 @@ class Step {
   const int32_t* lens_host = nullptr;
   int B_, L_;
   int T_, Tpad_;        // rows of the step; rows its tensors are allocated for (B * L)
+  int row_block_ = 1;             // padded batch: rows per block, kept blocks before each block
+  std::vector<int32_t> blocks_;
   uint64_t plan_;
   bool collect_, dry_;
   hipStream_t st_;
   int dt_, es_;
   // embedding-stage tensors
-  int32_t *ids_ = nullptr, *labels_ = nullptr, *order_ = nullptr, *seg_ = nullptr, *ends_ = nullptr;
-  mk::Rows rows() const { return mk::Rows{nullptr, ends_, 0}; }
+  int32_t *ids_ = nullptr, *labels_ = nullptr, *order_ = nullptr, *seg_ = nullptr, *ends_ = nullptr,
+          *lens_ = nullptr, *chunk_at_ = nullptr;
+  mk::Rows rows() const { return mk::Rows{lens_, ends_, 0}; }
   // Gradient of the residual stream.  Post-LN blocks in bf16 carry it in fp32 (gA_, gB_) and
   // keep the bf16 copies the products consume in oA_, oB_; otherwise the carriers have the
   // storage type and oA_/oB_ alias them (LayerNorm backward then works in place).
@@ -277,10 +288,13 @@ class Step {
   void* talloc(int64_t elems) { return c_->arena.alloc((uint64_t)elems * es_); }
   void* walloc(int64_t elems) { return c_->arena.alloc((uint64_t)elems * (wide_ ? 4 : es_)); }
 
+  // rows a product's kernel is chosen by: bf16 sums the way the padded batch would
+  int rule_rows() const { return dt_ == mk::BF16 ? Tpad_ : T_; }
   void gemm(const mk::GemmArgs& a) {
     if (dry_) return;
     forked_ = false;                      // the main stream moves on: later side work needs a new fork
     mk::GemmArgs b = a;
+    if (b.rule_rows == 0) b.rule_rows = rule_rows();
     if (c_->prof_on) {                    // timed by the kernel's own start and end, not by markers around the launch
       b.time_start = c_->prof_event();
       b.time_stop = c_->prof_event();
@@ -323,10 +337,16 @@ class Step {
     a.resid = resid; a.ldr = in;
     gemm(a);
   }
+  // a product whose reduction runs over the step's rows
+  void over_rows(mk::GemmArgs& a) const {
+    a.rule_rows = a.M;
+    if (lens_host && dt_ == mk::BF16) { a.k_padded = Tpad_; a.k_blocks = blocks_.data(); }
+  }
   // dW[out,in] = dY^T X, db[out] = column sums of dY
   void wgrad(const void* dY, int64_t ldy, int out, const void* X, int in, int wi, int bi, bool late = false) {
     mk::GemmArgs a{dY, ldy, false, X, in, false, g(wi), in, true, out, in, T_};
     a.a_rowsum = bi >= 0 ? g(bi) : nullptr;
+    over_rows(a);
     with_workspace(a, late);
   }
   // Weight-gradient products may cut their reduction in parts; the scratch for that is taken
@@ -394,32 +414,44 @@ class Step {
     Timed t(this, MIMOSE_K_LN_FWD, (x_f32 ? 6.0 : 2.0 * es_d()) * T_ * f_.hidden);
     if (!dry_) mk::layernorm_fwd(dt_, x, x_f32, w(gi), w(bi), y, T_, f_.hidden, f_.ln_eps, st_);
   }
+  // x = resid + dropout(x), y = LayerNorm(x)
+  void drop_ln_fwd(void* x, const void* resid, uint32_t site, int gi, int bi, void* y, bool x_f32 = false) {
+    Timed t(this, MIMOSE_K_LN_FWD, ((x_f32 ? 8.0 : 2.0 * es_d()) + 2.0 * es_d()) * T_ * f_.hidden);
+    if (!dry_)
+      mk::dropout_layernorm_fwd(dt_, x, x_f32, resid, w(gi), w(bi), y, T_, f_.hidden, f_.ln_eps, drop_desc(site), rows(), B_,
+                                L_, st_);
+  }
   void ln_bwd(const void* dy, const void* x, int gi, int bi, void* dx, const void* add, bool dy_f32 = false,
               bool x_f32 = false) {
     const uint64_t m = c_->arena.top();
     float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(Tpad_) * 2 * f_.hidden * 4);
     const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * (add ? 2.0 : 1.0);
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
-    if (!dry_)
-      mk::layernorm_bwd(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, g(gi), g(bi), partial, T_, f_.hidden, f_.ln_eps, st_);
+    if (!dry_) {
+      mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, mk::LnBwdMasked(), st_);
+      mk::layernorm_bwd_reduce(partial, g(gi), g(bi), chunk_at_, chunk_at_ ? Tpad_ : T_, f_.hidden, st_);
+    }
     c_->arena.pop_to(m);
   }
 
   // The same in two halves, for the layers' backward: the row pass on the main stream (its
   // partial sums stay allocated until the layer's end), the small reduction to dgamma, dbeta on
   // the weight-gradient stream after the next fork, off the chain of data gradients.
-  float* ln_bwd_rows(const void* dy, const void* x, int gi, void* dx, const void* add, bool dy_f32 = false,
-                     bool x_f32 = false) {
+  // masked (optional): dx behind the dropout mask of `site`.
+  float* ln_bwd_rows(const void* dy, const void* x, int gi, void* dx, const void* add, void* masked, uint32_t site) {
+    const bool dy_f32 = wide_, x_f32 = wide_;
     float* partial = (float*)c_->arena.alloc((uint64_t)mk::partial_rows(Tpad_) * 2 * f_.hidden * 4);
-    const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * (add ? 2.0 : 1.0);
+    const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * ((add ? 2.0 : 1.0) + (masked ? 1.0 : 0.0));
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
-    if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, st_);
+    mk::LnBwdMasked ex;
+    if (masked) { ex.masked = masked; ex.d = drop_desc(site); ex.rows = rows(); ex.B = B_; ex.L = L_; }
+    if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, ex, st_);
     return partial;
   }
   void ln_bwd_reduce(const float* partial, int gi, int bi) {
     if (dry_) return;
     const bool aside = c_->side && !c_->prof_on;
-    mk::layernorm_bwd_reduce(partial, g(gi), g(bi), T_, f_.hidden, aside ? c_->side : st_);
+    mk::layernorm_bwd_reduce(partial, g(gi), g(bi), chunk_at_, chunk_at_ ? Tpad_ : T_, f_.hidden, aside ? c_->side : st_);
     if (aside) side_busy_ = true;
   }
   // One fork serves everything issued on the weight-gradient stream until the main stream
@@ -438,10 +470,10 @@ class Step {
   void layer_forward(int l, LayerActs& A, bool rebuild = false);
   // first row of sample b (b == B: one past the last row)
   int64_t first_row(int b) const {
-    if (!lens_host) return (int64_t)b * L_;
-    int64_t r = 0;
-    for (int i = 0; i < b; ++i) r += lens_host[i];
-    return r;
+    const int64_t at = (int64_t)b * L_;
+    if (!lens_host) return at;
+    if (b == B_) return T_;
+    return (int64_t)blocks_[at / row_block_] * row_block_ + at % row_block_;
   }
   void layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s);
   bool split_forward() const;
@@ -453,12 +485,17 @@ class Step {
 
 void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   const int H = f_.hidden;
-  // ids, labels, sort order, run boundaries, where each sample's rows end (the last B only read for padded batches)
-  const int64_t TP = Tpad_;
-  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)(4 * TP + 1 + B_) * 4);
+  // ids, labels, sort order, run boundaries; for padded batches where each sample's rows end, its
+  // real tokens, and which chunk of kept rows each chunk of the padded batch is
+  const int64_t TP = Tpad_, nb = (TP + mk::kRowBlock - 1) / mk::kRowBlock, n_ints = 4 * TP + 1 + 2 * (int64_t)B_ + nb;
+  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)n_ints * 4);
   ids_ = ints; labels_ = ints ? ints + TP : nullptr; order_ = ints ? ints + 2 * TP : nullptr;
   seg_ = ints ? ints + 3 * TP : nullptr;
-  ends_ = ints && lens_host ? ints + 4 * TP + 1 : nullptr;
+  if (ints && lens_host) {
+    ends_ = ints + 4 * TP + 1;
+    lens_ = ends_ + B_;
+    if (dt_ == mk::BF16) chunk_at_ = lens_ + B_;
+  }
   wide_ = !f_.pre_ln && dt_ == mk::BF16;
   gA_ = walloc(TP * H);
   gB_ = walloc(TP * H);
@@ -474,7 +511,7 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   if (dry_) return;
 
   // host side: stable sort of positions by token id, run boundaries of equal ids
-  const size_t need = 4 * (size_t)TP + 1 + (size_t)B_;
+  const size_t need = (size_t)n_ints;
   const int turn = c_->stage_turn;
   c_->stage_turn ^= 1;
   if (c_->stage_busy[turn]) {               // copies of the step before last out of this buffer: long done
@@ -491,13 +528,17 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   stage_turn_ = turn;
   int32_t* s = c_->stage;
   if (lens_host) {
-    int32_t* ends = s + 4 * TP + 1;
-    for (int b = 0, t = 0; b < B_; ++b) {
-      std::memcpy(s + t, tokens + (size_t)b * L_, (size_t)lens_host[b] * 4);
-      std::memcpy(s + TP + t, labels + (size_t)b * L_, (size_t)lens_host[b] * 4);
-      ends[b] = t += lens_host[b];
+    int32_t *ends = s + 4 * TP + 1, *lens = ends + B_, *chunk_at = lens + B_;
+    for (int b = 0; b < B_; ++b) {
+      const int64_t t = first_row(b), n = first_row(b + 1) - t;
+      std::memcpy(s + t, tokens + (size_t)b * L_, (size_t)n * 4);
+      for (int64_t i = 0; i < n; ++i) s[TP + t + i] = i < lens_host[b] ? labels[(size_t)b * L_ + i] : -1;
+      ends[b] = (int32_t)(t + n);
+      lens[b] = lens_host[b];
     }
-    HIPCHK(c_, hipMemcpyAsync(ends_, ends, (size_t)B_ * 4, hipMemcpyHostToDevice, st_));
+    if (chunk_at_)
+      for (int64_t j = 0; j < nb; ++j) chunk_at[j] = blocks_[j + 1] > blocks_[j] ? blocks_[j] : -1;
+    HIPCHK(c_, hipMemcpyAsync(ends_, ends, (2 * (size_t)B_ + (size_t)nb) * 4, hipMemcpyHostToDevice, st_));
   } else {
     std::memcpy(s, tokens, (size_t)T_ * 4);
     std::memcpy(s + TP, labels, (size_t)T_ * 4);
@@ -548,7 +589,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
     a.bias = w(bi);
     a.resid = resid; a.ldr = out;
     a.gelu_out = act; a.gelu = ge;
-    a.rule_rows = T_;
+    a.rule_rows = rule_rows();
     if (!mk::gemm(dt_, a, s)) throw StepError{MIMOSE_ERR_INVALID_ARG, "gemm: unsupported alignment"};
   };
   auto ln = [&](const void* x, int gi, int bi, void* y, bool x_f32) {
@@ -559,7 +600,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   if (f_.pre_ln) { ln(x, p.ln1g, p.ln1b, at(A.n1, H), false); a = at(A.n1, H); }
   lin(a, H, p.wqkv, p.bqkv, at(A.qkv, 3 * H), 3 * H, nullptr, nullptr, 0, false);
   mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_,
-                    mk::Rows{nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s);
+                    mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s);
   lin(at(A.ctx, H), H, p.wo, p.bo, at(A.s1, H, wide_), H, x, nullptr, 0, wide_);
   if (f_.pre_ln) {
     ln(at(A.s1, H), p.ln2g, p.ln2b, at(A.u, H), false);
@@ -601,23 +642,24 @@ void Step::layer_forward(int l, LayerActs& A, bool rebuild) {
     if (!dry_)
       mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, rows(), B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_);
   }
-  // with dropout the product lands in the sum's buffer and an element-wise pass makes
+  // with dropout the product lands in the sum's buffer and the LayerNorm behind it first makes
   // sum = residual + dropout(product) in place; without it the residual rides in the epilogue
   const bool drop = drop_on();
   const uint32_t site_o = 4 * (uint32_t)(l + 1) + 1, site_f = site_o + 1;
   linear(A.ctx, H, p.wo, p.bo, A.s1, H, H, drop ? nullptr : A.x, nullptr, 0, wide_);
-  if (drop) dropout(A.s1, A.s1, wide_, A.x, site_o);
   if (f_.pre_ln) {
-    ln_fwd(A.s1, p.ln2g, p.ln2b, A.u);
+    if (drop) drop_ln_fwd(A.s1, A.x, site_o, p.ln2g, p.ln2b, A.u);
+    else ln_fwd(A.s1, p.ln2g, p.ln2b, A.u);
     linear(A.u, H, p.w1, p.b1, A.pre, F, F, nullptr, A.act, gelu);
     linear(A.act, F, p.w2, p.b2, A.out, H, H, drop ? nullptr : A.s1);
     if (drop) dropout(A.out, A.out, false, A.s1, site_f);
   } else {
-    ln_fwd(A.s1, p.ln1g, p.ln1b, A.u, wide_);
+    if (drop) drop_ln_fwd(A.s1, A.x, site_o, p.ln1g, p.ln1b, A.u, wide_);
+    else ln_fwd(A.s1, p.ln1g, p.ln1b, A.u, wide_);
     linear(A.u, H, p.w1, p.b1, A.pre, F, F, nullptr, A.act, gelu);
     linear(A.act, F, p.w2, p.b2, A.s2, H, H, drop ? nullptr : A.u, nullptr, 0, wide_);
-    if (drop) dropout(A.s2, A.s2, wide_, A.u, site_f);
-    if (!rebuild) ln_fwd(A.s2, p.ln2g, p.ln2b, A.out, wide_);
+    if (drop) drop_ln_fwd(A.s2, A.u, site_f, p.ln2g, p.ln2b, rebuild ? nullptr : A.out, wide_);
+    else if (!rebuild) ln_fwd(A.s2, p.ln2g, p.ln2b, A.out, wide_);
   }
 }
 
@@ -632,12 +674,13 @@ void Step::layer_backward(int l, LayerActs& A) {
   const uint64_t m0 = ar.top();
   // post-LN: oA = d s2 (LayerNorm 2 backward of the incoming gradient); pre-LN: the incoming
   // gradient is d s2 itself (oA aliases gA)
-  float* part2 = f_.pre_ln ? nullptr : ln_bwd_rows(gA_, A.s2, p.ln2g, oA_, nullptr, wide_, wide_);
   // with dropout the branch sees the masked gradient (a copy: the residual path keeps the whole one)
   const bool drop = drop_on();
   const uint32_t site_o = 4 * (uint32_t)(l + 1) + 1, site_f = site_o + 1;
-  const void* dffn = oA_;
-  if (drop) { void* m = talloc(TH); dropout(m, oA_, false, nullptr, site_f); dffn = m; }
+  void* masked2 = drop ? talloc(TH) : nullptr;
+  float* part2 = f_.pre_ln ? nullptr : ln_bwd_rows(gA_, A.s2, p.ln2g, oA_, nullptr, masked2, site_f);
+  if (drop && f_.pre_ln) dropout(masked2, oA_, false, nullptr, site_f);
+  const void* dffn = drop ? masked2 : oA_;
   fork();
   if (part2) ln_bwd_reduce(part2, p.ln2g, p.ln2b);
   wgrad(dffn, H, H, A.act, F, p.w2, p.b2);
@@ -657,15 +700,15 @@ void Step::layer_backward(int l, LayerActs& A) {
   // dact stays allocated until the end of the layer: the weight-gradient stream may still read
   // it, and waiting for that stream here would idle the chip for the length of the hand-over
   float* part1;
+  void* masked1 = drop ? talloc(TH) : nullptr;
   if (f_.pre_ln) {
     dgrad(dact, F, F, p.w1, gB_, H);                                          // gB = d LN2(u)
-    part1 = ln_bwd_rows(gB_, A.s1, p.ln2g, gB_, gA_);                         // gB = d u
+    part1 = ln_bwd_rows(gB_, A.s1, p.ln2g, gB_, gA_, masked1, site_o);        // gB = d u
   } else {
     dgrad(dact, F, F, p.w1, gB_, H, oA_, wide_);                              // gB = d u = d s2 + FFN path
-    part1 = ln_bwd_rows(gB_, A.s1, p.ln1g, oB_, nullptr, wide_, wide_);       // oB = d s1
+    part1 = ln_bwd_rows(gB_, A.s1, p.ln1g, oB_, nullptr, masked1, site_o);    // oB = d s1
   }
-  const void* dproj = oB_;
-  if (drop) { void* m = talloc(TH); dropout(m, oB_, false, nullptr, site_o); dproj = m; }
+  const void* dproj = drop ? masked1 : oB_;
   fork();
   if (f_.pre_ln) ln_bwd_reduce(part1, p.ln2g, p.ln2b);
   else ln_bwd_reduce(part1, p.ln1g, p.ln1b);
@@ -736,6 +779,7 @@ void Step::head(float* loss_dev) {
   {
     mk::GemmArgs a{logits, ldv, false, dec_in, H, false, g(c_->i_tok), H, true, V, H, T_};
     a.a_rowsum = f_.head ? g(c_->i_bdec) : nullptr;
+    over_rows(a);
     with_workspace(a);
   }
   void* dhs = f_.pre_ln ? talloc(TH) : gA_;            // post-LN: straight into the (possibly fp32) carrier
@@ -773,8 +817,13 @@ void Step::embed_sort() {
   int32_t* s = c_->stage;
   std::vector<int32_t>& count = c_->sort_count;
   count.assign((size_t)f_.vocab + 1, 0);
-  const int32_t* ids = s;                 // the staged ids: real rows alone
-  for (int t = 0; t < T_; ++t) ++count[(size_t)ids[t] + 1];
+  const int32_t* ids = s;                 // the staged ids
+  auto each_position = [&](auto&& f) {    // padding carries a zero gradient: left out
+    if (!lens_host) { for (int t = 0; t < T_; ++t) f(t); return; }
+    for (int b = 0; b < B_; ++b)
+      for (int64_t t = first_row(b), e = t + lens_host[b]; t < e; ++t) f((int)t);
+  };
+  each_position([&](int t) { ++count[(size_t)ids[t] + 1]; });
   n_seg_ = 0;
   int32_t* seg = s + 3 * (size_t)Tpad_;
   for (int v = 0; v < f_.vocab; ++v) {
@@ -783,7 +832,7 @@ void Step::embed_sort() {
   }
   seg[n_seg_] = count[f_.vocab];
   int32_t* order = s + 2 * (size_t)Tpad_;
-  for (int t = 0; t < T_; ++t) order[count[ids[t]]++] = t;
+  each_position([&](int t) { order[count[ids[t]]++] = t; });
   HIPCHK(c_, hipMemcpyAsync(order_, order, (2 * (size_t)Tpad_ + 1) * 4, hipMemcpyHostToDevice, st_));
   HIPCHK(c_, hipEventRecord(c_->ev_stage[stage_turn_], st_));     // the last copy out of this staging buffer
   c_->stage_busy[stage_turn_] = true;
@@ -821,10 +870,7 @@ void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bo
   // dropped layer's memory is handed to the next layer and at the end
   const bool split = split_forward() && N > 0;
   int nb0 = 1;                            // about half of the rows
-  for (int64_t at = first_row(1); nb0 + 1 < B_; ++nb0) {
-    at += lens_host ? lens_host[nb0] : L_;
-    if (2 * at > T_) break;
-  }
+  while (nb0 + 1 < B_ && 2 * first_row(nb0 + 1) <= T_) ++nb0;
   if (split) {
     if (hipEventRecord(c_->ev_fork, st_) != hipSuccess || hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "fork of the forward streams failed"};

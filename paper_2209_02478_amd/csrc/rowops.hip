@@ -122,7 +122,8 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const TD* __restrict__ dy, 
 // out[c] = sum over partial rows, c in [0, ncols): 16 row groups x 16 columns per block,
 // each group adds its rows in order, groups are combined in order.  (Fallback for column counts
 // or pointers that do not allow 16-byte accesses.)
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial, int P,
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial,
+                                                              const int32_t* __restrict__ chunk_at, int P,
                                                               int ncols, float* __restrict__ out0,
                                                               float* __restrict__ out1, int split) {
   __shared__ float red[16][17];
@@ -130,7 +131,10 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
   const int c = blockIdx.x * 16 + cg;
   float s = 0.f;
   if (c < ncols)
-    for (int r = rg; r < P; r += 16) s += partial[(int64_t)r * ncols + c];
+    for (int r = rg; r < P; r += 16) {
+      const int at = chunk_at ? chunk_at[r] : r;
+      if (at >= 0) s += partial[(int64_t)at * ncols + c];
+    }
   red[rg][cg] = s;
   __syncthreads();
   if (rg == 0 && c < ncols) {
@@ -144,7 +148,8 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // The same sums with whole 128-byte lines: a block owns 32 columns, 32 row groups x 8 lanes of four
 // columns; a group adds rows g, g + 32, ... in order, eight loads in flight at a time (a chain of
 // dependent loads costs a memory latency per row), groups are combined in order.
-__global__ __launch_bounds__(256) void reduce_partials_vec_kernel(const float* __restrict__ partial, int P,
+__global__ __launch_bounds__(256) void reduce_partials_vec_kernel(const float* __restrict__ partial,
+                                                                  const int32_t* __restrict__ chunk_at, int P,
                                                                   int ncols, float* __restrict__ out0,
                                                                   float* __restrict__ out1, int split) {
   __shared__ float4 red[32][8];
@@ -157,7 +162,8 @@ __global__ __launch_bounds__(256) void reduce_partials_vec_kernel(const float* _
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int r = r0 + 32 * u;
-        v[u] = r < P ? *(const float4*)(partial + (int64_t)r * ncols + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int at = r < P ? (chunk_at ? chunk_at[r] : r) : -1;
+        v[u] = at >= 0 ? *(const float4*)(partial + (int64_t)at * ncols + c) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
@@ -239,15 +245,33 @@ __device__ __forceinline__ void chunk_stats(const float (&v)[NC][E], int nchunks
   rstd = rsqrtf(wave_sum(q) / (float)H + eps);
 }
 
-template <typename TX, typename T, int NC>
-__global__ __launch_bounds__(256) void ln_fwd_vec_kernel(const TX* __restrict__ x, const T* __restrict__ gamma,
-                                                         const T* __restrict__ beta, T* __restrict__ y, int Trows,
-                                                         int H, float eps) {
+// the masked and scaled elements of chunk c of a row: v = keep ? v * scale : 0
+template <int E>
+__device__ __forceinline__ void drop_chunk(const DropDesc& d, int64_t mask_row, int H, int c, float (&v)[E]) {
+  const uint64_t blk = ((uint64_t)mask_row * H + (uint64_t)c * E) >> 2;
+#pragma unroll
+  for (int q = 0; q < E / 4; ++q) {
+    const uint4 w = drop_words(d, blk + q);
+    v[4 * q] = w.x >= d.thr ? v[4 * q] * d.scale : 0.f;
+    v[4 * q + 1] = w.y >= d.thr ? v[4 * q + 1] * d.scale : 0.f;
+    v[4 * q + 2] = w.z >= d.thr ? v[4 * q + 2] * d.scale : 0.f;
+    v[4 * q + 3] = w.w >= d.thr ? v[4 * q + 3] * d.scale : 0.f;
+  }
+}
+struct DropRows { DropDesc d; Rows rows; int B, L; };
+
+// DROP: x = resid + dropout(x) first, written back (what LayerNorm's backward reads); the pass is
+// bound by memory, so making the masks here instead of in a pass of their own saves that pass.
+template <typename TX, typename T, int NC, bool DROP>
+__global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, const T* __restrict__ gamma,
+                                                         const T* __restrict__ beta, T* __restrict__ y,
+                                                         int Trows, int H, float eps, const T* __restrict__ resid,
+                                                         DropRows dr) {
   constexpr int E = Chunk<T>::N;
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= Trows) return;
   const int nchunks = H / E;
-  const TX* xr = x + (int64_t)row * H;
+  TX* xr = x + (int64_t)row * H;
   float v[NC][E];
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
@@ -257,6 +281,28 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(const TX* __restrict__ 
 #pragma unroll
       for (int e = 0; e < E; ++e) v[i][e] = 0.f;
   }
+  if (DROP) {
+    const int64_t mask_row = padded_row(dr.rows, row, dr.B, dr.L);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int c = lane + 64 * i;
+      if (c >= nchunks) continue;
+      float r[E];
+      Chunk<T>::load(resid + (int64_t)row * H + c * E, r);
+      drop_chunk<E>(dr.d, mask_row, H, c, v[i]);
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[i][e] = rnd<TX>(v[i][e] + r[e]);
+      constexpr int N = Chunk<TX>::N;
+#pragma unroll
+      for (int k = 0; k < E / N; ++k) {
+        float t[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) t[e] = v[i][k * N + e];
+        Chunk<TX>::store(xr + c * E + k * N, t);
+      }
+    }
+  }
+  if (DROP && !y) return;
   float mean, rstd;
   chunk_stats<NC, E>(v, nchunks, lane, H, eps, mean, rstd);
   T* yr = y + (int64_t)row * H;
@@ -280,7 +326,7 @@ template <typename TD, typename TX, typename T, int NC>
 __global__ __launch_bounds__(256) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
                                                          const T* __restrict__ gamma, T* __restrict__ dx,
                                                          const T* __restrict__ add, float* __restrict__ partial,
-                                                         int Trows, int H, float eps) {
+                                                         T* __restrict__ masked, DropRows dr, int Trows, int H, float eps) {
   constexpr int E = Chunk<T>::N;
   constexpr int R = kRowsPerChunk / 4;
   __shared__ float red[4][2][64 * NC * E];
@@ -347,6 +393,12 @@ __global__ __launch_bounds__(256) void ln_bwd_vec_kernel(const TD* __restrict__ 
           for (int e = 0; e < E; ++e) o[e] += a[e];
         }
         Chunk<T>::store(dx + (int64_t)row * H + c * E, o);
+        if (masked) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) o[e] = rnd<T>(o[e]);
+          drop_chunk<E>(dr.d, padded_row(dr.rows, row, dr.B, dr.L), H, c, o);
+          Chunk<T>::store(masked + (int64_t)row * H + c * E, o);
+        }
       }
     }
   }
@@ -781,8 +833,8 @@ static void ln_fwd_t(const void* x, const void* g, const void* b, void* y, int T
   dim3 grid((T_ + 3) / 4);
   if (vec_ok<T>(H, {x, g, b, y})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-#define V_(NC) hipLaunchKernelGGL((ln_fwd_vec_kernel<TX, T, NC>), grid, dim3(256), 0, st, (const TX*)x, (const T*)g, \
-                                   (const T*)b, (T*)y, T_, H, eps)
+#define V_(NC) hipLaunchKernelGGL((ln_fwd_vec_kernel<TX, T, NC, false>), grid, dim3(256), 0, st, (TX*)const_cast<void*>(x), \
+                                   (const T*)g, (const T*)b, (T*)y, T_, H, eps, (const T*)nullptr, DropRows())
     if (nc <= 1) { V_(1); return; }
     if (nc <= 2) { V_(2); return; }
     if (nc <= 4) { V_(4); return; }
@@ -801,16 +853,38 @@ void layernorm_fwd(int dtype, const void* x, bool x_f32, const void* gamma, cons
   else ln_fwd_t<bf16_t, bf16_t>(x, gamma, beta, y, T_, H, eps, st);
 }
 
+template <typename TX, typename T>
+static void drop_ln_fwd_t(void* x, const void* resid, const void* g, const void* b, void* y, int T_, int H, float eps,
+                          const DropRows& dr, hipStream_t st) {
+  dim3 grid((T_ + 3) / 4);
+  const int nc = (H / Chunk<T>::N + 63) / 64;
+#define V_(NC) hipLaunchKernelGGL((ln_fwd_vec_kernel<TX, T, NC, true>), grid, dim3(256), 0, st, (TX*)x, (const T*)g, \
+                                   (const T*)b, (T*)y, T_, H, eps, (const T*)resid, dr)
+  if (nc <= 1) V_(1); else if (nc <= 2) V_(2); else V_(4);
+#undef V_
+}
+void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, const void* gamma, const void* beta,
+                           void* y, int T_, int H, float eps, const DropDesc& d, const Rows& rows, int B, int L,
+                           hipStream_t st) {
+  if (T_ <= 0) return;
+  const DropRows dr{d, rows, B, L};
+  if (dtype != BF16) drop_ln_fwd_t<float, float>(x, resid, gamma, beta, y, T_, H, eps, dr, st);
+  else if (x_f32) drop_ln_fwd_t<float, bf16_t>(x, resid, gamma, beta, y, T_, H, eps, dr, st);
+  else drop_ln_fwd_t<bf16_t, bf16_t>(x, resid, gamma, beta, y, T_, H, eps, dr, st);
+}
+
 template <typename TD, typename TX, typename T>
 static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, const void* add, float* partial,
-                     int T_, int H, float eps, hipStream_t st) {
+                     int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
 #define V_(NC) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC>), grid, dim3(256), 0, st, (const TD*)dy, \
-                                   (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, T_, H, eps)
+                                   (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
+                                   DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
     if (nc <= 1) { V_(1); return; }
     if (nc <= 2) { V_(2); return; }
+    if (ex.masked) { V_(4); return; }
 #undef V_
   }
 #define M_(NPL) hipLaunchKernelGGL((ln_bwd_kernel<TD, TX, T, NPL>), grid, dim3(256), 0, st, (const TD*)dy,    \
@@ -819,29 +893,31 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
 #undef M_
 }
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
-                        const void* add, float* partial, int T_, int H, float eps, hipStream_t st) {
+                        const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {
   if (T_ <= 0) return;
-  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, st);
-  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, st);
-  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, st);
-  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, st);
-  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, st);
+  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
+  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
+  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
+  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
+  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
 }
-void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, int T_, int H, hipStream_t st) {
+static_assert(kRowsPerChunk == kRowBlock, "padding is left out in whole chunks");
+void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T_, int H,
+                          hipStream_t st) {
   if (T_ <= 0) return;
   int P = (T_ + kRowsPerChunk - 1) / kRowsPerChunk;
   if ((H & 1) == 0 && (((uintptr_t)partial) & 15) == 0)      // rows of 2H floats: every float4 inside a row, lines aligned
-    hipLaunchKernelGGL(reduce_partials_vec_kernel, dim3((2 * H + 31) / 32), dim3(256), 0, st, partial, P, 2 * H, dgamma,
+    hipLaunchKernelGGL(reduce_partials_vec_kernel, dim3((2 * H + 31) / 32), dim3(256), 0, st, partial, chunk_at, P, 2 * H, dgamma,
                        dbeta, H);
   else
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((2 * H + 15) / 16), dim3(256), 0, st, partial, P, 2 * H, dgamma,
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((2 * H + 15) / 16), dim3(256), 0, st, partial, chunk_at, P, 2 * H, dgamma,
                        dbeta, H);
 }
 void layernorm_bwd(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
                    const void* add, float* dgamma, float* dbeta, float* partial, int T_, int H, float eps,
                    hipStream_t st) {
-  layernorm_bwd_rows(dtype, dy, dy_f32, x, x_f32, gamma, dx, add, partial, T_, H, eps, st);
-  layernorm_bwd_reduce(partial, dgamma, dbeta, T_, H, st);
+  layernorm_bwd_rows(dtype, dy, dy_f32, x, x_f32, gamma, dx, add, partial, T_, H, eps, LnBwdMasked(), st);
+  layernorm_bwd_reduce(partial, dgamma, dbeta, nullptr, T_, H, st);
 }
 int partial_rows(int T_) { return (T_ + kRowsPerChunk - 1) / kRowsPerChunk; }
 
