@@ -398,6 +398,30 @@ bool launch_bgemm_dma(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_
 // fp32 on the matrix cores (gemm_f32.hip)
 void launch_sgemm(const GemmDev& p, int rows, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
 
+// small tiles, deep ring (gemm_ring.hip); false when the operands do not meet its alignment rules
+bool launch_bgemm_ring(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+// Its block tiles are 64 x 32, 64 x 64, 128 x 64 and 128 x 128 (variants 0..3), one block per compute
+// unit; a product gets the smallest that covers it in one round of the 256 units: more blocks than
+// that queue, fewer leave units idle and each with a longer tile.  Measured against the kernels below
+// at 768 columns and K = 3072: 74 rows 46 -> 11 us, 600 rows 46 -> 11, 1600 rows 45 -> 18, 2816 rows
+// 33 -> 26, 4400 rows 46 -> 33; level at 6400 rows (300 tiles of 128 x 128, two rounds: not taken).
+static int ring_variant(int M, int N) {
+  auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
+  if (tiles(64, 32) <= 256) return 0;
+  if (tiles(64, 64) <= 256) return 1;
+  if (tiles(128, 64) <= 256) return 2;
+  return tiles(128, 128) <= 256 ? 3 : -1;
+}
+// Weight gradients keep the parts of their reduction (gemm_splits) and with them the number of units.
+// The 128 x 128 ring is ahead where the units fill one round nearly (256 at 1024 and 4096 x 1024:
+// 249 -> 222 us at K = 20480, 37 -> 31 at K = 2000) and behind where they start a second one (288 at
+// 768 x 3072: 57 -> 66 us at K = 6400), which blocks that share a compute unit absorb, or where the
+// reduction is short.
+static bool ring_wgrad(int M, int N, int K, int splits) {
+  const int units = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * splits;
+  return K >= 1024 && units <= 256 && units >= 192;
+}
+
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
 bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
@@ -456,6 +480,17 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   {
     const int sp = splits_for(gemm_splits(g.M, g.N));
     if (sp > 1) { cut(sp, 32); p.partial = (float*)g.workspace; }
+  }
+  // forward and data-gradient products that one round of smaller tiles covers
+  if (p.splits == 1 && !g.a_rowsum) {
+    const int which = ring_variant(rule_rows, g.N);
+    if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
+  }
+  // weight gradients of exactly one round
+  if (!g.a_kmajor && !g.b_kmajor && ring_wgrad(g.M, g.N, rule_k, p.splits) &&
+      launch_bgemm_ring(p, 3, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
+    if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
+    return true;
   }
   // large tiles where their rounds are well filled (a choice made from the shape alone)
   if (p.splits == 1 && use_pp(g.M, g.N, g.K) && launch_bgemm_pp(p, st, g.time_start, g.time_stop)) return true;

@@ -65,6 +65,40 @@ __device__ __forceinline__ u32x4 pack_bf16x8(const float (&f)[8]) {
   return w;
 }
 
+// eight consecutive columns of row m, from column n on, through the epilogue (cb: their bias)
+__device__ __forceinline__ void finish8(const GemmDev& p, int m, int n, float (&v)[8], const float (&cb)[8]) {
+  if (n + 8 > p.N) {                                          // ragged end of the row
+    for (int e = 0; e < 8; ++e) epilogue<bf16_t>(p, m, n + e, v[e]);
+    return;
+  }
+  float f[8];
+  if (p.bias) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += cb[e];
+  }
+  if (p.resid) {
+    unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.resid + (int64_t)m * p.ldr + n), f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += f[e];
+  }
+  const int64_t o = (int64_t)m * p.ldc + n;
+  if (p.c_f32) {
+    *(float4*)((float*)p.C + o) = make_float4(v[0], v[1], v[2], v[3]);
+    *(float4*)((float*)p.C + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    return;
+  }
+  *(u32x4*)((bf16_t*)p.C + o) = pack_bf16x8(v);
+  if (p.gelu == GELU_ERF) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = gelu_erf_bf16(v[e]);
+    *(u32x4*)((bf16_t*)p.gelu_out + o) = pack_bf16x8(f);
+  } else if (p.gelu == GELU_TANH) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = gelu_tanh_bf16(v[e]);
+    *(u32x4*)((bf16_t*)p.gelu_out + o) = pack_bf16x8(f);
+  }
+}
+
 // m0w, n0w: first row / column of this wave's 64 x 64 part; wstage: 16 KB / HALVES of LDS owned
 // by this wave (HALVES == 2: the two 32-column halves take turns in 8 KB).  Every thread of the
 // block must call it.
@@ -106,36 +140,7 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
       const float4 lo = *(const float4*)&wstage[row * COLS + ((c0 ^ (row & (CHUNKS - 1))) << 2)];
       const float4 hi = *(const float4*)&wstage[row * COLS + (((c0 + 1) ^ (row & (CHUNKS - 1))) << 2)];
       float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      if (n + 8 > p.N) {                                        // ragged end of the row
-        for (int e = 0; e < 8; ++e) epilogue<bf16_t>(p, m, n + e, v[e]);
-        continue;
-      }
-      float f[8];
-      if (p.bias) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += cb[e];
-      }
-      if (p.resid) {
-        unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.resid + (int64_t)m * p.ldr + n), f);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += f[e];
-      }
-      const int64_t o = (int64_t)m * p.ldc + n;
-      if (p.c_f32) {
-        *(float4*)((float*)p.C + o) = make_float4(v[0], v[1], v[2], v[3]);
-        *(float4*)((float*)p.C + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
-        continue;
-      }
-      *(u32x4*)((bf16_t*)p.C + o) = pack_bf16x8(v);
-      if (p.gelu == GELU_ERF) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = gelu_erf_bf16(v[e]);
-        *(u32x4*)((bf16_t*)p.gelu_out + o) = pack_bf16x8(f);
-      } else if (p.gelu == GELU_TANH) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = gelu_tanh_bf16(v[e]);
-        *(u32x4*)((bf16_t*)p.gelu_out + o) = pack_bf16x8(f);
-      }
+      finish8(p, m, n, v, cb);
     }
   }
 }

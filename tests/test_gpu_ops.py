@@ -248,6 +248,56 @@ def test_gemm_long_reduction_in_parts(c_f32):
     close(host(C), ref, 0 if c_f32 else dtype, k=40.0 if c_f32 else 2.0)
 
 
+# products that one round of small tiles covers: each tile size of the ring kernel, whole and ragged
+# rows, columns and reduction lengths (one, an odd and an even count of 64-deep stages)
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K", [(70, 96, 64), (33, 8, 200), (130, 4104, 136), (640, 776, 192), (1700, 768, 72),
+                                   (1536, 1600, 320), (2500, 776, 264)])
+def test_gemm_ring_tiles(a_k, b_k, M, N, K):
+    dtype = 1
+    rng = np.random.default_rng(M + N + K)
+    up = lambda v: (v + 7) // 8 * 8
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    B = rng.standard_normal((N, K)).astype(np.float32)
+    bias, resid = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    def lay(X, kmajor):
+        if kmajor:
+            return np.ascontiguousarray(X), X.shape[1]
+        buf = np.zeros((X.shape[1], up(X.shape[0])), np.float32)
+        buf[:, :X.shape[0]] = X.T
+        return buf, up(X.shape[0])
+    (Ab, lda), (Bb, ldb) = lay(A, a_k), lay(B, b_k)
+    dA, dB, dbias, dres = dev(Ab, dtype), dev(Bb, dtype), dev(bias, dtype), dev(resid, dtype)
+    base = quant(A, dtype) @ quant(B, dtype).T
+    C = torch.full((M, N + 8), 7.0, dtype=dA.dtype, device=DEV)
+    mi.mimose_op_gemm(dtype, dA, lda, a_k, dB, ldb, b_k, C, N + 8, 0, M, N, K, bias=dbias, resid=dres, ldr=N)
+    sync()
+    assert np.all(host(C)[:, N:] == 7.0), "wrote outside the N columns"
+    close(host(C)[:, :N], base + quant(bias, dtype) + quant(resid, dtype), dtype, k=2.0)
+    G = torch.zeros((M, N + 8), dtype=dA.dtype, device=DEV)
+    mi.mimose_op_gemm(dtype, dA, lda, a_k, dB, ldb, b_k, C, N + 8, 0, M, N, K, bias=dbias, gelu_out=G, gelu=1)
+    sync()
+    pre = base + quant(bias, dtype)
+    close(host(G)[:, :N], om.gelu_fwd(pre, False), dtype, scale=np.abs(pre).max(), k=3.0)
+
+
+# weight gradients on the ring: parts with an odd and an even count of stages, a ragged last part
+@pytest.mark.parametrize("T", [1024, 1100, 2000, 2089])
+def test_gemm_ring_weight_gradient(T):
+    dtype, M, N = 1, 1024, 1024
+    rng = np.random.default_rng(T)
+    dY, X = rng.standard_normal((T, M)).astype(np.float32), rng.standard_normal((T, N)).astype(np.float32)
+    nws = mi.mimose_op_gemm_workspace_bytes(M, N)
+    ws = torch.zeros(nws, dtype=torch.uint8, device=DEV)
+    W = torch.full((M, N), 9.0, dtype=torch.float32, device=DEV)
+    rs = torch.full((M,), 9.0, dtype=torch.float32, device=DEV)
+    mi.mimose_op_gemm(dtype, dev(dY, dtype), M, 0, dev(X, dtype), N, 0, W, N, 1, M, N, T, a_rowsum=rs, workspace=ws,
+                      workspace_bytes=nws)
+    sync()
+    close(host(W), quant(dY, dtype).T @ quant(X, dtype), 0, k=40.0)
+    close(host(rs), quant(dY, dtype).sum(0), 0, k=40.0)
+
+
 def test_gemm_rejects_misaligned_bf16():
     a = torch.zeros(64 * 20, dtype=torch.bfloat16, device=DEV)
     with pytest.raises(mi.MimoseError):
