@@ -120,23 +120,39 @@ __device__ __forceinline__ void store_rows(bf16_t* dst, const f32x16 (&acc)[2], 
     }
 }
 
+// Which row block (of nb) of which sample and head a block works on; false: none.  Consecutive block
+// ids go to the 8 XCDs in turn, so an id's low three bits pick the pair of sample and head: all row
+// blocks of a pair run on one XCD, whose L2 then fetches the pair's rows once, and the heads of a
+// sample, all equally long, spread over the XCDs.  (With the row block as the fastest index a causal
+// batch of 8 row blocks gave one XCD every longest block and another every shortest.)
+// longest_last: the row block with most work is the last one; it starts first.  16 causal samples of
+// 1024 tokens, 16 heads: forward 111 -> 91 us, backward 337 -> 283; without a mask level or 4 % ahead.
+__device__ __forceinline__ bool row_block(int nb, int pairs, bool longest_last, int& rb, int& bh) {
+  const int slot = blockIdx.x >> 3, group = slot / nb, i = slot - group * nb;
+  rb = longest_last ? nb - 1 - i : i;
+  bh = group * 8 + (blockIdx.x & 7);
+  return bh < pairs;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ forward
 template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
                                                      float* __restrict__ lse, Rows rows,
-                                                     int L, int nh, DropDesc drop) {
+                                                     int L, int nh, int pairs, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
   __shared__ __attribute__((aligned(16))) bf16_t Vt[D][LDTT];   // [d][key]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ql = lane & 31, h = lane >> 5;
+  int rb, bh;
+  if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, true, rb, bh)) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  if (rb * ROWS_PER_BLOCK >= sm.n) return;
   const bf16_t* base = qkv + sm.first * ld3 + hh * D;
-  const int qi = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + ql;
+  const int w0 = rb * ROWS_PER_BLOCK + wave * 32, qi = w0 + ql;
   const int qc = min(qi, sm.n - 1);
   const float scale = 0.125f, c2 = scale * LOG2E;    // exp(scale * s - x) == exp2(c2 * s - LOG2E * x)
 
@@ -147,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
   zero(o[0]); zero(o[1]);
   float m = -INFINITY, l = 0.f;                       // running maximum of the raw (unscaled) scores, sum of exps
   const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
-  const int kend = CAUSAL ? min(Lk, (int)(blockIdx.x + 1) * ROWS_PER_BLOCK) : Lk;
+  const int kend = CAUSAL ? min(Lk, (rb + 1) * ROWS_PER_BLOCK) : Lk;
 
   // threads 0..127 stage K, the others V; the next tile's loads are in flight during the MFMAs
   const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;
@@ -160,6 +176,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
     else stash_tile<false, true>(pre, t128, nullptr, Vt);
     __syncthreads();
     if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
+    if (w0 >= sm.n || (CAUSAL && k0 > w0 + 31)) continue;   // none of this wave's queries sees the tile
     f32x16 s[2];
     float mx = -INFINITY;
 #pragma unroll
@@ -233,18 +250,20 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
                                                         const bf16_t* __restrict__ dctx,
                                                         const float* __restrict__ lse, float* __restrict__ delta,
                                                         bf16_t* __restrict__ dqkv, Rows rows, int L,
-                                                        int nh, DropDesc drop) {
+                                                        int nh, int pairs, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
   __shared__ __attribute__((aligned(16))) bf16_t Kt[D][LDTT];   // [d][key]
   __shared__ __attribute__((aligned(16))) bf16_t Vs[TK][LDT];   // [key][d]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ql = lane & 31, h = lane >> 5;
+  int rb, bh;
+  if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, true, rb, bh)) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  if (rb * ROWS_PER_BLOCK >= sm.n) return;
   const bf16_t* base = qkv + sm.first * ld3 + hh * D;
-  const int qi = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + ql;
+  const int w0 = rb * ROWS_PER_BLOCK + wave * 32, qi = w0 + ql;
   const int qc = min(qi, sm.n - 1);
   const float scale = 0.125f;
 
@@ -267,7 +286,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
   f32x16 dq[2];
   zero(dq[0]); zero(dq[1]);
   const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
-  const int kend = CAUSAL ? min(Lk, (int)(blockIdx.x + 1) * ROWS_PER_BLOCK) : Lk;
+  const int kend = CAUSAL ? min(Lk, (rb + 1) * ROWS_PER_BLOCK) : Lk;
 
   const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;     // threads 0..127 stage K, the others V
   const int t128 = tid & 127;
@@ -279,6 +298,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
     else stash_tile<true, false>(pre, t128, Vs, nullptr);
     __syncthreads();
     if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
+    if (w0 >= sm.n || (CAUSAL && k0 > w0 + 31)) continue;   // none of this wave's queries sees the tile
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       f32x16 s, dp;
@@ -325,21 +345,23 @@ template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16_t* __restrict__ dqkv, Rows rows, int L,
-                                                        int nh, DropDesc drop) {
+                                                        int nh, int pairs, DropDesc drop) {
   __shared__ __attribute__((aligned(16))) bf16_t Qs[TK][LDT];   // [query][d]
   __shared__ __attribute__((aligned(16))) bf16_t Qt[D][LDTT];   // [d][query]
   __shared__ __attribute__((aligned(16))) bf16_t Gs[TK][LDT];   // dO [query][d]
   __shared__ __attribute__((aligned(16))) bf16_t Gt[D][LDTT];   // dO [d][query]
   __shared__ __attribute__((aligned(16))) float lse_s[TK], delta_s[TK];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kl = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kl = lane & 31, h = lane >> 5;
+  int rb, bh;
+  if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, false, rb, bh)) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if ((int)blockIdx.x * ROWS_PER_BLOCK >= sm.n) return;
+  if (rb * ROWS_PER_BLOCK >= sm.n) return;
   const bf16_t* base = qkv + sm.first * ld3 + hh * D;
   const bf16_t* gbase = dctx + sm.first * H + hh * D;
-  const int ki = blockIdx.x * ROWS_PER_BLOCK + wave * 32 + kl;
+  const int w0 = rb * ROWS_PER_BLOCK + wave * 32, ki = w0 + kl;
   const int kc = min(ki, sm.n - 1);
   const float scale = 0.125f, c2 = scale * LOG2E;
 
@@ -351,9 +373,9 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
   }
   f32x16 dk[2], dv[2];
   zero(dk[0]); zero(dk[1]); zero(dv[0]); zero(dv[1]);
-  const int qstart = CAUSAL ? blockIdx.x * ROWS_PER_BLOCK : 0;     // earlier queries never see these keys
+  const int qstart = CAUSAL ? rb * ROWS_PER_BLOCK : 0;     // earlier queries never see these keys
   const int Lk = sm.keys;                                          // keys from Lk on are padding: their dK, dV are zero
-  const int qend = (int)blockIdx.x * ROWS_PER_BLOCK >= Lk ? 0 : sm.n; // a block of padded keys only writes zeros
+  const int qend = rb * ROWS_PER_BLOCK >= Lk ? 0 : sm.n; // a block of padded keys only writes zeros
 
   const bf16_t* mine = tid < 128 ? base : gbase;                 // threads 0..127 stage Q, the others dO
   const int64_t mine_ld = tid < 128 ? ld3 : (int64_t)H;
@@ -376,6 +398,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
     if (tid < TK) { lse_s[tid] = -LOG2E * pre_lse; delta_s[tid] = pre_delta; }   // lse_s: ready for exp2
     __syncthreads();
     if (q0 + TK < qend) fetch(q0 + TK);
+    if (w0 >= Lk || (CAUSAL && q0 + TK <= w0)) continue;   // no query of the tile sees this wave's keys
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
       f32x16 s, dp;
@@ -449,8 +472,9 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
 
 void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                         const DropDesc& drop, hipStream_t st) {
-  dim3 grid((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, B * nh);
-#define FWD_(C, D) hipLaunchKernelGGL((fa_fwd_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (bf16_t*)ctx, lse, rows, L, nh, drop)
+  const int pairs = B * nh;
+  const dim3 grid((unsigned)((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) * 8u * (unsigned)((pairs + 7) / 8));
+#define FWD_(C, D) hipLaunchKernelGGL((fa_fwd_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (bf16_t*)ctx, lse, rows, L, nh, pairs, drop)
   if (drop.thr) { if (causal) FWD_(true, true); else FWD_(false, true); }
   else { if (causal) FWD_(true, false); else FWD_(false, false); }
 #undef FWD_
@@ -458,12 +482,13 @@ void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const Rows& rows
 
 void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
                         const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
-  dim3 grid((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, B * nh);
+  const int pairs = B * nh;
+  const dim3 grid((unsigned)((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) * 8u * (unsigned)((pairs + 7) / 8));
 #define BWD_(C, D)                                                                                               \
   hipLaunchKernelGGL((fa_bwd_dq_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)ctx,  \
-                     (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, rows, L, nh, drop);                          \
+                     (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop);                          \
   hipLaunchKernelGGL((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
-                     delta, (bf16_t*)dqkv, rows, L, nh, drop)
+                     delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop)
   if (drop.thr) { if (causal) { BWD_(true, true); } else { BWD_(false, true); } }
   else { if (causal) { BWD_(true, false); } else { BWD_(false, false); } }
 #undef BWD_

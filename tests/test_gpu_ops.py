@@ -436,6 +436,15 @@ def test_attention_padded(dtype, causal, L, nh, d, lengths):
     attention_case(dtype, len(lengths), L, nh, d, causal, seed=L + 7, lengths=lengths)
 
 
+# pairs of sample and head that do not fill the 8 XCDs, tiles of 64 keys and blocks of 128 queries
+# whole, one row short and one row over, several row blocks of which a causal tile misses some waves
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("L,nh,lengths", [(63, 1, None), (64, 3, [64, 1, 31]), (65, 2, None), (127, 3, [33, 127, 95]),
+                                          (256, 1, [256] * 8 + [97]), (257, 5, [257, 64, 256])])
+def test_attention_tile_edges(causal, L, nh, lengths):
+    attention_case(1, len(lengths) if lengths else 3, L, nh, 64, causal, seed=L + 3, lengths=lengths)
+
+
 # dropout of the probabilities: the kept set is the oracle's (integer comparisons of generator
 # words), so the usual tolerances apply; lengths off the 4-key grid, several key tiles, padding
 @pytest.mark.parametrize("dtype", [0, 1])
