@@ -5,8 +5,11 @@
 // statistics of a row are then reductions over a lane's own registers plus one exchange with
 // lane^32, and a lane's probabilities, converted to bf16, are directly the B operand of the
 // next product (P V, dS K, P^T dO, dS^T Q) without passing through LDS.  The operand that
-// multiplies them must be contiguous along the reduction index, so K / V / Q / dO tiles are
-// also stored transposed in LDS (register transpose of 4x8 blocks on the way in).
+// multiplies them is needed contiguous along the reduction index, which is the tile's row: the
+// transposing LDS reads of gfx950 (ds_read_b64_tr_b16) hand it out from the tile as it lies, so a
+// tile is in LDS once and comes there straight from memory (global_load_lds), into one of two
+// buffers while the other is multiplied, with one barrier per tile (backward of 32 x 512 x 12 heads
+// 151 -> 135 us against tiles carried through registers and stored twice, as they lie and transposed).
 //
 // MFMA 32x32x16 register layout used below (A: 32 x 16, B: 16 x 32, D: 32 x 32):
 //   A, B: lane holds row/column lane%32 and reduction indices 8*(lane/32) .. +7
@@ -29,11 +32,7 @@ namespace {
 
 constexpr int D = 64;          // head size
 constexpr int TK = 64;         // rows of a streamed tile
-constexpr int LDT = 72;        // LDS row stride in elements of the tiles read 16 bytes at a time (144 bytes)
-// Row stride of the transposed tiles, which are written and read 8 bytes at a time: 34 dwords, an
-// odd multiple of two, so that the 8-byte reads of lanes 0..31 (one row each) fall in all different
-// banks; with 36 dwords rows r and r + 16 met in the same banks (half of those reads conflicted).
-constexpr int LDTT = 68;
+constexpr int TILE = TK * D;   // elements of a tile in LDS: rows of 128 bytes, no padding (a direct load fills 1 KB in lane order)
 constexpr int ROWS_PER_BLOCK = 128;
 
 constexpr float LOG2E = 1.44269504088896340736f;
@@ -55,52 +54,75 @@ __device__ __forceinline__ bf16x8 regs_to_frag(const f32x16& v, int c) {
   u.w = pack2(v[8 * c + 6], v[8 * c + 7]);
   return __builtin_bit_cast(bf16x8, u);
 }
-// A operand from a transposed tile: row `row`, reduction indices base+4h+{0..3}, base+8+4h+{0..3}
-__device__ __forceinline__ bf16x8 ld_frag_t(const bf16_t (*tile)[LDTT], int row, int base, int h) {
-  uint2 lo = *(const uint2*)&tile[row][base + 4 * h];
-  uint2 hi = *(const uint2*)&tile[row][base + 8 + 4 * h];
-  uint4 u = make_uint4(lo.x, lo.y, hi.x, hi.y);
-  return __builtin_bit_cast(bf16x8, u);
-}
 
-// 128 threads bring one 64 x 64 tile (rows r0.., row stride ld, rows clamped to last) into LDS,
-// as is ([row][d]) and / or transposed ([d][row]).  t in [0,128): 4 rows x 8 columns each.
-// Two steps, so that the loads of the next tile can fly while the current one is multiplied.
-__device__ __forceinline__ void fetch_tile(const bf16_t* src, int64_t ld, int r0, int last, int t, uint4 (&v)[4]) {
-  const int rq = t >> 3, cb = t & 7;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// 16-byte chunk c of a tile's row r lies at position c ^ swizzle(r).  A plain read (16 rows, one
+// chunk) and a transposing read (4 rows, 4 chunks in 32 lanes) then both meet all 64 banks once:
+// rows two apart differ in bit 2, rows four apart in the low bits.
+__device__ __forceinline__ int swizzle(int r) { return ((r & 2) << 1) | ((r >> 2) & 3); }
+
+// A wave's fragments of a tile, as element offsets computed once.
+struct FragAt {
+  int plain[4];      // row (lane % 32) of a 32-row block, head columns 16 kk + 8 h .. +7
+  int turned[2];     // head column (lane % 32) of 32-column block db, rows 4 h + {0..3}; rows + 8: chunk position ^ 2
+  __device__ __forceinline__ void init(int lane) {
+    const int h = lane >> 5, r = lane & 31, q = (lane & 15) >> 2;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    int r = min(r0 + 4 * rq + j, last);
-    v[j] = *(const uint4*)(src + (int64_t)r * ld + 8 * cb);
-  }
-}
-template <bool NORMAL, bool TRANSPOSED>
-__device__ __forceinline__ void stash_tile(const uint4 (&v)[4], int t, bf16_t (*normal)[LDT], bf16_t (*transposed)[LDTT]) {
-  const int rq = t >> 3, cb = t & 7;
-  if (NORMAL) {
+    for (int kk = 0; kk < 4; ++kk) plain[kk] = r * D + (((2 * kk + h) ^ swizzle(r)) << 3);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *(uint4*)&normal[4 * rq + j][8 * cb] = v[j];
-  }
-  if (TRANSPOSED) {
-    const uint32_t* w0 = (const uint32_t*)&v[0];
-    const uint32_t* w1 = (const uint32_t*)&v[1];
-    const uint32_t* w2 = (const uint32_t*)&v[2];
-    const uint32_t* w3 = (const uint32_t*)&v[3];
-#pragma unroll
-    for (int mm = 0; mm < 8; ++mm) {
-      const int d = mm >> 1;
-      uint2 o;
-      if (mm & 1) {
-        o.x = (w0[d] >> 16) | (w1[d] & 0xFFFF0000u);
-        o.y = (w2[d] >> 16) | (w3[d] & 0xFFFF0000u);
-      } else {
-        o.x = (w0[d] & 0xFFFFu) | (w1[d] << 16);
-        o.y = (w2[d] & 0xFFFFu) | (w3[d] << 16);
-      }
-      *(uint2*)&transposed[8 * cb + mm][4 * rq] = o;
+    for (int db = 0; db < 2; ++db) {
+      const int chunk = 4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+      turned[db] = (4 * h + q) * D + ((chunk ^ swizzle(4 * h + q)) << 3) + 4 * (lane & 1);
     }
   }
+  // row 32 * block + lane % 32 of the tile, columns 16 kk + 8 h .. +7
+  __device__ __forceinline__ bf16x8 row(const bf16_t* tile, int block, int kk) const {
+    return ld_frag(tile + block * 32 * D + plain[kk]);
+  }
+  // head column 32 db + lane % 32, tile rows base + 4h + {0..3}, base + 8 + 4h + {0..3} (base % 16 == 0).
+  // Within 16 lanes of a transposing read, lane i gets column i of the 4 x 16 block whose row k lies
+  // at the four lanes 4k ..; 8 rows on, bit 1 of swizzle() flips.
+  __device__ __forceinline__ bf16x8 column(const bf16_t* tile, int db, int base) const {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + base * D + turned[db]));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (base + 8) * D + (turned[db] ^ 16)));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
+
+// One wave-level direct load: lane i's 16 bytes at g land at lds + 16 * i.  Inline assembly, so the
+// compiler does not track it: landed() waits by hand.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
+__device__ __forceinline__ void direct_load(const bf16_t* g, uint32_t lds_byte_address) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
 }
+#pragma clang diagnostic pop
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)p);
+}
+// Every wave's direct loads so far are in LDS, and every wave is done reading what it read before.
+__device__ __forceinline__ void landed() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
+// The block's share of bringing rows r0 .. r0 + 63 (row stride ld, rows past `last` are read as
+// `last`) of one operand into a tile: each of the four waves loads 16 rows in two pieces.
+struct TileLoad {
+  int row, chunk;
+  __device__ __forceinline__ void init(int wave, int lane) {
+    row = 16 * wave + (lane >> 3);
+    chunk = ((lane & 7) ^ swizzle(row)) << 3;         // swizzle(row + 8) = swizzle(row) ^ 2
+  }
+  __device__ __forceinline__ void issue(const bf16_t* src, int64_t ld, int r0, int last, int wave, uint32_t tile) const {
+    direct_load(src + (int64_t)min(r0 + row, last) * ld + chunk, tile + (uint32_t)wave * 2048u);
+    direct_load(src + (int64_t)min(r0 + row + 8, last) * ld + (chunk ^ 16), tile + (uint32_t)wave * 2048u + 1024u);
+  }
+};
 
 __device__ __forceinline__ void zero(f32x16& v) {
 #pragma unroll
@@ -141,8 +163,7 @@ template <bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
                                                      float* __restrict__ lse, Rows rows,
                                                      int L, int nh, int pairs, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
-  __shared__ __attribute__((aligned(16))) bf16_t Vt[D][LDTT];   // [d][key]
+  __shared__ __attribute__((aligned(1024))) bf16_t tiles[2][2][TILE];   // [buffer][K, V][key][d]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ql = lane & 31, h = lane >> 5;
   int rb, bh;
   if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, true, rb, bh)) return;
@@ -165,17 +186,20 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
   const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
   const int kend = CAUSAL ? min(Lk, (rb + 1) * ROWS_PER_BLOCK) : Lk;
 
-  // threads 0..127 stage K, the others V; the next tile's loads are in flight during the MFMAs
-  const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;
-  const int t128 = tid & 127;
-  uint4 pre[4];
-  fetch_tile(mine, ld3, 0, sm.n - 1, t128, pre);
-  for (int k0 = 0; k0 < kend; k0 += TK) {
-    __syncthreads();
-    if (tid < 128) stash_tile<true, false>(pre, t128, Ks, nullptr);
-    else stash_tile<false, true>(pre, t128, nullptr, Vt);
-    __syncthreads();
-    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
+  FragAt at;
+  at.init(lane);
+  TileLoad load;
+  load.init(wave, lane);
+  const uint32_t lds = lds_address(&tiles[0][0][0]);
+  auto fetch = [&](int k0, int buf) {
+    load.issue(base + H, ld3, k0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE));
+    load.issue(base + 2 * H, ld3, k0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE) + 2u * TILE);
+  };
+  fetch(0, 0);
+  for (int k0 = 0, buf = 0; k0 < kend; k0 += TK, buf ^= 1) {
+    landed();
+    if (k0 + TK < kend) fetch(k0 + TK, buf ^ 1);
+    const bf16_t *Ks = tiles[buf][0], *Vs = tiles[buf][1];
     if (w0 >= sm.n || (CAUSAL && k0 > w0 + 31)) continue;   // none of this wave's queries sees the tile
     f32x16 s[2];
     float mx = -INFINITY;
@@ -184,7 +208,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
       zero(s[kb]);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(&Ks[32 * kb + ql][16 * kk + 8 * h]), qf[kk], s[kb], 0, 0, 0);
+        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.row(Ks, kb, kk), qf[kk], s[kb], 0, 0, 0);
       if (CAUSAL || k0 + TK > Lk) {                   // only tiles that touch the mask pay for it
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -235,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
         const bf16x8 pf = regs_to_frag(s[kb], c);
 #pragma unroll
         for (int db = 0; db < 2; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_t(Vt, 32 * db + ql, 32 * kb + 16 * c, h), pf, o[db], 0, 0, 0);
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.column(Vs, db, 32 * kb + 16 * c), pf, o[db], 0, 0, 0);
       }
   }
   if (qi < sm.n) {
@@ -251,9 +275,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
                                                         const float* __restrict__ lse, float* __restrict__ delta,
                                                         bf16_t* __restrict__ dqkv, Rows rows, int L,
                                                         int nh, int pairs, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[TK][LDT];   // [key][d]
-  __shared__ __attribute__((aligned(16))) bf16_t Kt[D][LDTT];   // [d][key]
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[TK][LDT];   // [key][d]
+  __shared__ __attribute__((aligned(1024))) bf16_t tiles[2][2][TILE];   // [buffer][K, V][key][d]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ql = lane & 31, h = lane >> 5;
   int rb, bh;
   if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, true, rb, bh)) return;
@@ -288,16 +310,20 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
   const int Lk = sm.keys;                             // keys from Lk on are padding (1 <= Lk)
   const int kend = CAUSAL ? min(Lk, (rb + 1) * ROWS_PER_BLOCK) : Lk;
 
-  const bf16_t* mine = tid < 128 ? base + H : base + 2 * H;     // threads 0..127 stage K, the others V
-  const int t128 = tid & 127;
-  uint4 pre[4];
-  fetch_tile(mine, ld3, 0, sm.n - 1, t128, pre);
-  for (int k0 = 0; k0 < kend; k0 += TK) {
-    __syncthreads();
-    if (tid < 128) stash_tile<true, true>(pre, t128, Ks, Kt);
-    else stash_tile<true, false>(pre, t128, Vs, nullptr);
-    __syncthreads();
-    if (k0 + TK < kend) fetch_tile(mine, ld3, k0 + TK, sm.n - 1, t128, pre);
+  FragAt at;
+  at.init(lane);
+  TileLoad load;
+  load.init(wave, lane);
+  const uint32_t lds = lds_address(&tiles[0][0][0]);
+  auto fetch = [&](int k0, int buf) {
+    load.issue(base + H, ld3, k0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE));
+    load.issue(base + 2 * H, ld3, k0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE) + 2u * TILE);
+  };
+  fetch(0, 0);
+  for (int k0 = 0, buf = 0; k0 < kend; k0 += TK, buf ^= 1) {
+    landed();
+    if (k0 + TK < kend) fetch(k0 + TK, buf ^ 1);
+    const bf16_t *Ks = tiles[buf][0], *Vs = tiles[buf][1];
     if (w0 >= sm.n || (CAUSAL && k0 > w0 + 31)) continue;   // none of this wave's queries sees the tile
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
@@ -305,8 +331,8 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
       zero(s); zero(dp);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(&Ks[32 * kb + ql][16 * kk + 8 * h]), qf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(&Vs[32 * kb + ql][16 * kk + 8 * h]), gf[kk], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.row(Ks, kb, kk), qf[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.row(Vs, kb, kk), gf[kk], dp, 0, 0, 0);
       }
       if (DROP) {                                     // d(P) of a dropped probability is zero, of a kept one scaled
         const int64_t row = (int64_t)bh * L + qc;
@@ -333,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(const bf16_t* __restr
         const bf16x8 dsf = regs_to_frag(s, c);
 #pragma unroll
         for (int db = 0; db < 2; ++db)
-          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_t(Kt, 32 * db + ql, 32 * kb + 16 * c, h), dsf, dq[db], 0, 0, 0);
+          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.column(Ks, db, 32 * kb + 16 * c), dsf, dq[db], 0, 0, 0);
       }
     }
   }
@@ -346,11 +372,8 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16_t* __restrict__ dqkv, Rows rows, int L,
                                                         int nh, int pairs, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[TK][LDT];   // [query][d]
-  __shared__ __attribute__((aligned(16))) bf16_t Qt[D][LDTT];   // [d][query]
-  __shared__ __attribute__((aligned(16))) bf16_t Gs[TK][LDT];   // dO [query][d]
-  __shared__ __attribute__((aligned(16))) bf16_t Gt[D][LDTT];   // dO [d][query]
-  __shared__ __attribute__((aligned(16))) float lse_s[TK], delta_s[TK];
+  __shared__ __attribute__((aligned(1024))) bf16_t tiles[2][2][TILE];   // [buffer][Q, dO][query][d]
+  __shared__ __attribute__((aligned(16))) float lse_s[2][TK], delta_s[2][TK];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kl = lane & 31, h = lane >> 5;
   int rb, bh;
   if (!row_block((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, pairs, false, rb, bh)) return;
@@ -377,41 +400,42 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
   const int Lk = sm.keys;                                          // keys from Lk on are padding: their dK, dV are zero
   const int qend = rb * ROWS_PER_BLOCK >= Lk ? 0 : sm.n; // a block of padded keys only writes zeros
 
-  const bf16_t* mine = tid < 128 ? base : gbase;                 // threads 0..127 stage Q, the others dO
-  const int64_t mine_ld = tid < 128 ? ld3 : (int64_t)H;
-  const int t128 = tid & 127;
-  uint4 pre[4];
+  FragAt at;
+  at.init(lane);
+  TileLoad load;
+  load.init(wave, lane);
+  const uint32_t lds = lds_address(&tiles[0][0][0]);
   float pre_lse = 0.f, pre_delta = 0.f;
-  auto fetch = [&](int q0) {
-    fetch_tile(mine, mine_ld, q0, sm.n - 1, t128, pre);
+  auto fetch = [&](int q0, int buf) {
+    load.issue(base, ld3, q0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE));
+    load.issue(gbase, H, q0, sm.n - 1, wave, lds + (uint32_t)buf * (4u * TILE) + 2u * TILE);
     if (tid < TK) {
       const int q = min(q0 + tid, sm.n - 1);
       pre_lse = lse[(int64_t)bh * L + q];
       pre_delta = delta[(int64_t)bh * L + q];
     }
   };
-  if (qstart < qend) fetch(qstart);
-  for (int q0 = qstart; q0 < qend; q0 += TK) {
-    __syncthreads();
-    if (tid < 128) stash_tile<true, true>(pre, t128, Qs, Qt);
-    else stash_tile<true, true>(pre, t128, Gs, Gt);
-    if (tid < TK) { lse_s[tid] = -LOG2E * pre_lse; delta_s[tid] = pre_delta; }   // lse_s: ready for exp2
-    __syncthreads();
-    if (q0 + TK < qend) fetch(q0 + TK);
+  if (qstart < qend) fetch(qstart, 0);
+  for (int q0 = qstart, buf = 0; q0 < qend; q0 += TK, buf ^= 1) {
+    // lse_s: ready for exp2.  This buffer was last read two tiles ago, before the last barrier.
+    if (tid < TK) { lse_s[buf][tid] = -LOG2E * pre_lse; delta_s[buf][tid] = pre_delta; }
+    landed();
+    if (q0 + TK < qend) fetch(q0 + TK, buf ^ 1);
     if (w0 >= Lk || (CAUSAL && q0 + TK <= w0)) continue;   // no query of the tile sees this wave's keys
+    const bf16_t *Qs = tiles[buf][0], *Gs = tiles[buf][1];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
       f32x16 s, dp;
       zero(s); zero(dp);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(&Qs[32 * qb + kl][16 * kk + 8 * h]), kf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(&Gs[32 * qb + kl][16 * kk + 8 * h]), vf[kk], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.row(Qs, qb, kk), kf[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.row(Gs, qb, kk), vf[kk], dp, 0, 0, 0);
       }
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int qq = 32 * qb + 8 * g + 4 * h;
-        const float4 nl = *(const float4*)&lse_s[qq], dl = *(const float4*)&delta_s[qq];
+        const float4 nl = *(const float4*)&lse_s[buf][qq], dl = *(const float4*)&delta_s[buf][qq];
         const float nls[4] = {nl.x, nl.y, nl.z, nl.w}, dls[4] = {dl.x, dl.y, dl.z, dl.w};
         // Dropout: this lane holds one key and four queries; a generator block covers four keys
         // of one query.  The four lanes of a quad (four neighbouring keys) each make the block of
@@ -456,8 +480,8 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
         const bf16x8 pf = regs_to_frag(s, c), dsf = regs_to_frag(dp, c);
 #pragma unroll
         for (int db = 0; db < 2; ++db) {
-          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_t(Gt, 32 * db + kl, 32 * qb + 16 * c, h), pf, dv[db], 0, 0, 0);
-          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_t(Qt, 32 * db + kl, 32 * qb + 16 * c, h), dsf, dk[db], 0, 0, 0);
+          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.column(Gs, db, 32 * qb + 16 * c), pf, dv[db], 0, 0, 0);
+          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.column(Qs, db, 32 * qb + 16 * c), dsf, dk[db], 0, 0, 0);
         }
       }
     }
