@@ -270,7 +270,10 @@ __global__ __launch_bounds__(256, 2) void bgemm_kernel(GemmDev p, int tiles_n, i
     if ((tid & 1) == 0 && m < p.M) rowsum[m] = tot;
   }
   static_assert(2 * (TA::ELEMS + TB::ELEMS) * sizeof(bf16_t) >= 4 * 64 * 64 * sizeof(float), "staging needs 16 KB per wave");
-  store_tile<1>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, (float*)smem_raw + wave * 4096);
+  u32x4 resid[8];
+  load_resid<1>(q, m0 + wm * 64, n0 + wn * 64, lane, resid);
+  __syncthreads();                                    // the operand tiles are dead
+  store_tile<1>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, (float*)smem_raw + wave * 4096, resid, [] {});
 }
 
 // C[m][n] = sum over splits (in order) of partial tiles; row sums likewise.  C is fp32, or bf16

@@ -65,6 +65,16 @@ __device__ __forceinline__ u32x4 pack_bf16x8(const float (&f)[8]) {
   return w;
 }
 
+// eight finished values of row m, from column n on
+__device__ __forceinline__ void put8(const GemmDev& p, int m, int n, const float (&v)[8]) {
+  const int64_t o = (int64_t)m * p.ldc + n;
+  if (p.c_f32) {
+    *(float4*)((float*)p.C + o) = make_float4(v[0], v[1], v[2], v[3]);
+    *(float4*)((float*)p.C + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+  } else {
+    *(u32x4*)((bf16_t*)p.C + o) = pack_bf16x8(v);
+  }
+}
 // eight consecutive columns of row m, from column n on, through the epilogue (cb: their bias)
 __device__ __forceinline__ void finish8(const GemmDev& p, int m, int n, float (&v)[8], const float (&cb)[8]) {
   if (n + 8 > p.N) {                                          // ragged end of the row
@@ -81,13 +91,8 @@ __device__ __forceinline__ void finish8(const GemmDev& p, int m, int n, float (&
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += f[e];
   }
+  put8(p, m, n, v);
   const int64_t o = (int64_t)m * p.ldc + n;
-  if (p.c_f32) {
-    *(float4*)((float*)p.C + o) = make_float4(v[0], v[1], v[2], v[3]);
-    *(float4*)((float*)p.C + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
-    return;
-  }
-  *(u32x4*)((bf16_t*)p.C + o) = pack_bf16x8(v);
   if (p.gelu == GELU_ERF) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = gelu_erf_bf16(v[e]);
@@ -99,17 +104,43 @@ __device__ __forceinline__ void finish8(const GemmDev& p, int m, int n, float (&
   }
 }
 
-// m0w, n0w: first row / column of this wave's 64 x 64 part; wstage: 16 KB / HALVES of LDS owned
-// by this wave (HALVES == 2: the two 32-column halves take turns in 8 KB).  Every thread of the
-// block must call it.
+// How a wave walks its 64 x 64 part, 32 (HALVES == 2) or 64 columns wide: every lane eight columns of
+// a row, in eight steps altogether.
 template <int HALVES>
+struct Walk {
+  static constexpr int COLS = 64 / HALVES, LPR = COLS / 8, RPI = 64 / LPR, STEPS = 64 / RPI;   // columns, lanes per row, rows per step, steps per half
+  static __device__ __forceinline__ int row(int step, int lane) { return step * RPI + lane / LPR; }
+  static __device__ __forceinline__ int col(int half, int lane) { return half * COLS + (lane % LPR) * 8; }
+};
+
+// The residuals of a wave's 64 x 64 part, all requested before the part is stored: requested one step
+// of the walk at a time they cost a memory latency per step.  Products with a residual and fp32 output,
+// 1024 columns: T = 16384, K = 1024 57 -> 48 us, K = 4096 (forward) 134 -> 124; T = 6352 92 -> 90; 768
+// columns: T = 6400, K = 768 27 -> 23, K = 3072 62 -> 58.
+__device__ __forceinline__ bool resid_ahead(const GemmDev& p) { return p.vec && p.resid && !p.gelu; }
+template <int HALVES>
+__device__ __forceinline__ void load_resid(const GemmDev& p, int m0w, int n0w, int lane, u32x4 (&r)[8]) {
+  typedef Walk<HALVES> W;
+  if (!resid_ahead(p)) return;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int m = m0w + W::row(q % W::STEPS, lane), n = n0w + W::col(q / W::STEPS, lane);
+    if (m < p.M && n + 8 <= p.N) r[q] = *(const u32x4*)((const bf16_t*)p.resid + (int64_t)m * p.ldr + n);
+  }
+}
+
+// m0w, n0w: first row / column of this wave's 64 x 64 part; wstage: 16 KB / HALVES of LDS that only
+// this wave uses from here on (HALVES == 2: the two 32-column halves take turns in 8 KB); r: load_resid's.
+// AHEAD: whether residuals were loaded ahead.  staged_all: called once the accumulators are in LDS and
+// their registers free.
+template <int HALVES, bool AHEAD = true, typename F>
 __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)[2][2], int m0w, int n0w, int lane,
-                                           float* wstage) {
-  constexpr int COLS = 64 / HALVES, CHUNKS = COLS / 4, LPR = COLS / 8;   // staged columns, float4 chunks, lanes per row
-  constexpr int RPI = 64 / LPR;                                          // rows per loop iteration
+                                           float* wstage, const u32x4 (&r)[8], F&& staged_all) {
+  typedef Walk<HALVES> W;
+  constexpr int COLS = W::COLS, CHUNKS = COLS / 4;              // staged columns, float4 chunks
 #pragma unroll
   for (int h = 0; h < HALVES; ++h) {
-    __syncthreads();                                            // operand tiles / the previous half are dead
+    __builtin_amdgcn_wave_barrier();                            // the previous half's reads stay before
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -121,26 +152,49 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
           *(float4*)&wstage[row * COLS + ((c ^ (row & (CHUNKS - 1))) << 2)] =
               make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
         }
-    __syncthreads();
-    const int nh = n0w + h * COLS;
+    __builtin_amdgcn_wave_barrier();
+    if (h == HALVES - 1) staged_all();
     if (!p.vec) {                                               // unaligned operands: one element at a time
       for (int idx = lane; idx < 64 * COLS; idx += 64) {
         const int row = idx / COLS, col = idx % COLS;
-        epilogue<bf16_t>(p, m0w + row, nh + col,
+        epilogue<bf16_t>(p, m0w + row, n0w + h * COLS + col,
                          wstage[row * COLS + ((((col >> 2) ^ (row & (CHUNKS - 1))) << 2) | (col & 3))]);
       }
       continue;
     }
-    const int n = nh + (lane % LPR) * 8, c0 = 2 * (lane % LPR);
+    const int n = n0w + W::col(h, lane), c0 = 2 * (lane % W::LPR);
     float cb[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};    // the columns' bias: the same for every row
     if (p.bias && n + 8 <= p.N) unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.bias + n), cb);
-    for (int it = 0; it < 64 / RPI; ++it) {
-      const int row = it * RPI + lane / LPR, m = m0w + row;
-      if (m >= p.M || n >= p.N) continue;
+    auto staged = [&](int row, float (&v)[8]) {
       const float4 lo = *(const float4*)&wstage[row * COLS + ((c0 ^ (row & (CHUNKS - 1))) << 2)];
       const float4 hi = *(const float4*)&wstage[row * COLS + (((c0 + 1) ^ (row & (CHUNKS - 1))) << 2)];
-      float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      finish8(p, m, n, v, cb);
+      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+    };
+    if (AHEAD && resid_ahead(p)) {
+#pragma unroll
+      for (int it = 0; it < W::STEPS; ++it) {
+        const int row = W::row(it, lane), m = m0w + row;
+        if (m >= p.M || n >= p.N) continue;
+        float v[8];
+        staged(row, v);
+        if (n + 8 > p.N) {
+          for (int e = 0; e < 8; ++e) epilogue<bf16_t>(p, m, n + e, v[e]);
+          continue;
+        }
+        float f[8];
+        unpack_bf16x8(r[h * W::STEPS + it], f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = v[e] + cb[e] + f[e];
+        put8(p, m, n, v);
+      }
+    } else {
+      for (int it = 0; it < W::STEPS; ++it) {
+        const int row = W::row(it, lane), m = m0w + row;
+        if (m >= p.M || n >= p.N) continue;
+        float v[8];
+        staged(row, v);
+        finish8(p, m, n, v, cb);
+      }
     }
   }
 }

@@ -370,16 +370,23 @@ __global__ __launch_bounds__(512) void bgemm_pp_kernel(GemmDev p, int tiles_n, i
       if (m0 + tid < p.M) rowsum[m0 + tid] = tot;
     }
   }
-  // 64 x 64 pieces through LDS: 16 KB per wave when the ring has 128 KB, else two 8 KB halves
-  __syncthreads();
+  // 64 x 64 pieces through LDS: 16 KB per wave when the ring has 128 KB, else two 8 KB halves.  A
+  // piece's residuals are requested while the piece before it is stored.
   constexpr int HALVES = G::SMEM >= 8 * 16384 ? 1 : 2;
   static_assert(G::SMEM >= 8 * 16384 / HALVES, "staging space");
+  constexpr int PIECES = (TM / 2) * (TN / 2);
   float* wstage = (float*)ring + wave * (4096 / HALVES);
+  auto piece_m = [&](int i) { return m0 + wm * TM * 32 + i / (TN / 2) * 64; };
+  auto piece_n = [&](int i) { return n0 + wn * TN * 32 + i % (TN / 2) * 64; };
+  constexpr bool AHEAD = !KTAIL;                      // the pointers of a ragged reduction leave too few registers
+  u32x4 resid[2][8];
+  if (AHEAD) load_resid<HALVES>(q, piece_m(0), piece_n(0), lane, resid[0]);
+  __syncthreads();
 #pragma unroll
-  for (int a = 0; a < TM / 2; ++a)
-#pragma unroll
-    for (int b = 0; b < TN / 2; ++b)
-      store_tile<HALVES>(q, acc[a][b], m0 + wm * TM * 32 + a * 64, n0 + wn * TN * 32 + b * 64, lane, wstage);
+  for (int i = 0; i < PIECES; ++i)
+    store_tile<HALVES, AHEAD>(q, acc[i / (TN / 2)][i % (TN / 2)], piece_m(i), piece_n(i), lane, wstage, resid[i & 1], [&] {
+      if (AHEAD && i + 1 < PIECES) load_resid<HALVES>(q, piece_m(i + 1), piece_n(i + 1), lane, resid[(i + 1) & 1]);
+    });
 }
 
 template <bool AK, bool BKM, int WM, int WN, int TM, int TN, int NA, int NB>

@@ -222,6 +222,18 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
   }
   if (nk & 1) mfmas(S0());
   __builtin_amdgcn_s_waitcnt(r_wait(0));
+  // all residuals of the wave's tiles at once (one tile's after another's store cost a memory latency each)
+  u32x4 resid[TM][TN][2];
+  if (!WG && resid_ahead(p))
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int m = m0 + (wm * TM + i) * 32 + it * 16 + (lane >> 2), n = n0 + (wn * TN + j) * 32 + (lane & 3) * 8;
+          if (m < p.M && n + 8 <= p.N) resid[i][j][it] = *(const u32x4*)((const bf16_t*)p.resid + (int64_t)m * p.ldr + n);
+        }
 
   // 32 x 32 tiles through LDS, so that the stores are rows: register r of a lane is row lane%32,
   // column 8*(r/4) + 4*(lane/32) + r%4; float4 chunk c of row r sits at c ^ (r & 7)
@@ -273,7 +285,13 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
         const float4 hi = *(const float4*)&ws[row * 32 + (((c0 + 1) ^ (row & 7)) << 2)];
         float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         if (m >= p.M || n >= p.N) continue;
-        if (q.vec) finish8(q, m, n, v, cb);
+        if (!WG && resid_ahead(p) && n + 8 <= p.N) {
+          float f[8];
+          unpack_bf16x8(resid[i][j][it], f);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = v[e] + cb[e] + f[e];
+          put8(p, m, n, v);
+        } else if (q.vec) finish8(q, m, n, v, cb);
         else
           for (int e = 0; e < 8; ++e) epilogue<bf16_t>(q, m, n + e, v[e]);
       }
