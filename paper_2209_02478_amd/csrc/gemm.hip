@@ -329,9 +329,8 @@ int gemm_splits(int M, int N) {
   return s < 1 ? 1 : (s > 8 ? 8 : s);
 }
 
-// the kernel with 256 x 256 tiles (gemm_pp.hip) and its tile count
+// the kernel with 256 x 256 tiles (gemm_pp.hip)
 bool launch_bgemm_pp(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
-int bgemm_pp_tiles(int M, int N);
 // Which products go to the large-tile kernel: it runs one block per compute unit, so its time is
 // a whole number of rounds of 256 tiles, and it pays where those rounds are well filled.  Measured
 // against the 128 x 128 kernels with K = 768 and 2304 or 3072 columns over row counts from 4608
@@ -341,7 +340,7 @@ int bgemm_pp_tiles(int M, int N);
 // parts, and the fp32 parts written and read again cost more than the large tile saves.
 static bool use_pp(int M, int N, int K) {
   if (M < 256 || N < 256 || K < 512) return false;
-  const int units = bgemm_pp_tiles(M, N), rounds = (units + 255) / 256;
+  const int units = gemm_large_tiles(M, N), rounds = (units + 255) / 256;
   const double fill = (double)units / (256.0 * rounds);
   return fill >= 0.62;
 }
@@ -356,7 +355,7 @@ constexpr int kLongK = 8192;
 constexpr int64_t kLongKRows = 24576;            // parts x M at most
 size_t gemm_long_k_workspace_bytes(int N) { return (size_t)kLongKRows * N * 4; }
 static int long_k_splits(int M, int N) {
-  const int tiles = bgemm_pp_tiles(M, N);
+  const int tiles = gemm_large_tiles(M, N);
   int s = (205 + tiles - 1) / tiles;
   const int cap = (int)(kLongKRows / M);
   if (s > cap) s = cap;

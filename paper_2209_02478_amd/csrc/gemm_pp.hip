@@ -433,6 +433,6 @@ bool launch_bgemm_pp(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t
 
 // Units of 256 x 256 tiles a product of this shape has, and how well they fill the 256 compute
 // units round by round (one block per compute unit).
-int bgemm_pp_tiles(int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); }
+int gemm_large_tiles(int M, int N) { return ((M + 255) / 256) * ((N + 255) / 256); }
 
 }  // namespace mk

@@ -77,6 +77,9 @@ size_t gemm_workspace_bytes(int M, int N);
 // a function of the column count alone, so that it is a constant of the model
 size_t gemm_long_k_workspace_bytes(int N);
 
+// 256 x 256 tiles of an M x N product: the large-tile kernel runs them one per compute unit, 256 at a time
+int gemm_large_tiles(int M, int N);
+
 // returns false when the arguments violate the kernel's alignment assumptions
 bool gemm(int dtype, const GemmArgs& g, hipStream_t st);
 

@@ -339,6 +339,29 @@ def test_stream_layout_does_not_change_the_bits(name):
     m.close()
 
 
+@pytest.mark.parametrize("name,B,L", [("fp32_postln", 11, 48), ("bf16_postln", 4, 90), ("bf16_preln_causal", 3, 80),
+                                      ("bf16_stages", 5, 96)])
+def test_halves_of_the_batch_change_no_bits(name, B, L):
+    """The same for batches large enough (2^15 elements per tensor) to run the forward in halves."""
+    shape = SMALL[name]
+    params = synthdata.make_params(shape, 95, perturb=True)
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=256 * MiB)
+    m.load_params(params)
+    whole = synthdata.make_batch(shape, B, L, 96) + (None,)
+    padded = synthdata.make_padded_batch(shape, [max(1, L - 7 * b) for b in range(B + 3)], 97)
+    for tokens, labels, lens in (whole, padded):
+        for plan in (0, 0b10):
+            m.force_plan(plan)
+            out = []
+            for timed in (1, 0):
+                mi.mimose_profile_enable(m.ctx, timed)
+                out.append((m.train_step(tokens, labels, lengths=lens)[0], m.grads()))
+            assert out[0][0] == out[1][0]
+            for k in out[0][1]:
+                assert np.array_equal(out[0][1][k], out[1][1][k]), (plan, k)
+    m.close()
+
+
 def test_static_plan_mode_same_gradients_more_recompute():
     """One plan for the longest input (the static planner of Section 3.2) against the input-aware
     planner on the small workload: bit-identical losses and gradients on every step, never fewer
