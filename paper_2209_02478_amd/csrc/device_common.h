@@ -87,38 +87,27 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ float gelu_erf(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f));
 }
-// GELU where the result is rounded to bf16.  The tile store of a feed-forward product evaluates it
-// once per output on a unit that does nothing else meanwhile, so its instructions are the product's
-// time: no divisions, constants folded, and the half of each function that tends to zero is the one
-// computed, so that nothing cancels (largest error against 64 bits over |x| < 9 before the rounding:
-// 3.3e-7 for the erf form, 4.7e-7 with a division and 1 + erf).
-// 16384 x 4096 outputs of K = 1024, erf form: 187 -> 176 us; 6352 x 4096 85 -> 80; 6400 x 3072 60 -> 58.
-//
-// half_erfc = erfc(|x| / sqrt 2) / 2 by the rational approximation of Abramowitz & Stegun 7.1.26
-// (absolute error < 0.75e-7); density = exp(-x^2 / 2), the approximation's own exponential
-__device__ __forceinline__ float half_erfc(float x, float& density) {
-  const float d = fmaf(0.3275911f * 0.70710678118654752440f, fabsf(x), 1.0f), r = __builtin_amdgcn_rcpf(d);
-  const float t = fmaf(fmaf(-d, r, 1.0f), r, r);      // one Newton step: as good as a division
-  density = __builtin_amdgcn_exp2f(x * x * (-0.5f * 1.44269504088896340736f));
-  float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
-  p = fmaf(t, p, 0.5f * 1.421413741f);
-  p = fmaf(t, p, 0.5f * -0.284496736f);
-  p = fmaf(t, p, 0.5f * 0.254829592f);
-  return p * t * density;
+// erf by the rational approximation of Abramowitz & Stegun 7.1.26 (absolute error < 1.5e-7),
+// one exponential and one reciprocal: used where the result is rounded to bf16 anyway
+__device__ __forceinline__ float erf_as(float x) {
+  const float ax = fabsf(x);
+  const float t = __frcp_rn(fmaf(0.3275911f, ax, 1.0f));
+  float p = fmaf(t, 1.061405429f, -1.453152027f);
+  p = fmaf(t, p, 1.421413741f);
+  p = fmaf(t, p, -0.284496736f);
+  p = fmaf(t, p, 0.254829592f);
+  const float r = 1.0f - p * t * __expf(-ax * ax);
+  return copysignf(r, x);
 }
 __device__ __forceinline__ float gelu_erf_bf16(float x) {
-  float density;
-  const float ax = fminf(fabsf(x), 64.0f);            // keeps infinities out of the product; both terms see NaN
-  return fmaf(-ax, half_erfc(ax, density), 0.5f * (x + fabsf(x)));
+  return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752440f));
 }
-// tanh form: 0.5 (1 - tanh |u|) = 1 / (1 + exp(2|u|)), exact limits at both ends
-__device__ __forceinline__ float half_tanhc(float x) {
-  const float c = 2.0f * 0.79788456080286535588f * 1.44269504088896340736f;
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fabsf(x) * fmaf(c * 0.044715f, x * x, c)));
-}
+// tanh form with tanh(u) = 1 - 2 / (1 + exp(2u)): exact limits at both ends, relative error ~1e-6
 __device__ __forceinline__ float gelu_tanh_bf16(float x) {
-  const float ax = fminf(fabsf(x), 64.0f);
-  return fmaf(-ax, half_tanhc(ax), 0.5f * (x + fabsf(x)));
+  const float c = 0.79788456080286535588f;
+  const float u = c * (x + 0.044715f * x * x * x);
+  const float t = 1.0f - 2.0f * __frcp_rn(1.0f + __expf(2.0f * u));
+  return 0.5f * x * (1.0f + t);
 }
 __device__ __forceinline__ float gelu_tanh(float x) {
   const float c = 0.79788456080286535588f;
@@ -129,15 +118,18 @@ __device__ __forceinline__ float gelu_erf_grad(float x) {
   float pdf = 0.39894228040143267794f * __expf(-0.5f * x * x);
   return cdf + x * pdf;
 }
-// the derivatives where the result is rounded to bf16
+// the same with the rational erf above: its exponential, exp(-x^2 / 2), is also the density's, so
+// the derivative costs one exponential and one reciprocal (used where the result is rounded to bf16)
 __device__ __forceinline__ float gelu_erf_grad_bf16(float x) {
-  float density;
-  const float q = half_erfc(x, density);
-  return fmaf(x * 0.39894228040143267794f, density, 0.5f + copysignf(0.5f - q, x));
-}
-__device__ __forceinline__ float gelu_tanh_grad_bf16(float x) {
-  const float c = 2.0f * 0.79788456080286535588f, h = half_tanhc(x);
-  return fmaf(fmaf(-h, h, h) * x, fmaf(3.0f * 0.044715f * c, x * x, c), 0.5f + copysignf(0.5f - h, x));
+  const float ax = fabsf(x) * 0.70710678118654752440f;
+  const float t = __frcp_rn(fmaf(0.3275911f, ax, 1.0f));
+  float p = fmaf(t, 1.061405429f, -1.453152027f);
+  p = fmaf(t, p, 1.421413741f);
+  p = fmaf(t, p, -0.284496736f);
+  p = fmaf(t, p, 0.254829592f);
+  const float e = __expf(-ax * ax);
+  const float erf_x = copysignf(1.0f - p * t * e, x);
+  return 0.5f * (1.0f + erf_x) + x * 0.39894228040143267794f * e;
 }
 __device__ __forceinline__ float gelu_tanh_grad(float x) {
   const float c = 0.79788456080286535588f;
