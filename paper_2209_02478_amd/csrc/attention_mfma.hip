@@ -234,9 +234,9 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
     }
     mx = fmaxf(mx, other_half(mx));
     const float mnew = fmaxf(m, mx);                  // finite: key 0 is visible to every query
+    float alpha = 1.f;
     if (__any(mx > m)) {                              // else alpha is 1 in every lane: nothing to scale
-      const float alpha = fast_exp2((m - mnew) * c2);
-      l *= alpha;
+      alpha = fast_exp2((m - mnew) * c2);
 #pragma unroll
       for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -253,7 +253,8 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
         s[kb][r] = p;
         rs += p;
       }
-    l += rs;                                          // this half's keys; the normaliser counts every probability
+    rs += other_half(rs);
+    l = fmaf(l, alpha, rs);                           // the normaliser counts every probability
     if (DROP) {                                       // dropped ones leave the P V product; the scale waits for the end
       const int64_t row = (int64_t)bh * L + qc;
 #pragma unroll
@@ -277,7 +278,6 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(const bf16_t* __restrict
           o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.column(Vs, db, 32 * kb + 16 * c), pf, o[db], 0, 0, 0);
       }
   }
-  l += other_half(l);
   if (qi < sm.n) {
     store_rows(ctx + (sm.first + qi) * H + hh * D, o, h, (DROP ? drop.scale : 1.f) / l);
     if (h == 0) lse[(int64_t)bh * L + qi] = m * scale + __logf(l);
