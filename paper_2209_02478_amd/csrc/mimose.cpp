@@ -228,6 +228,8 @@ class Step {
   // kernel, while every tensor keeps the size of the padded batch, which is what the planner knows.
   // (Single rows of padding stay: the sums over rows are then those of the padded batch bit for bit.)
   // fp32 sums are not held to that: there every row of padding is left out.
+  // The tables that say which rows are left go behind the rows that are left in h0's buffer; where
+  // what is left out is too little to hold them, nothing is.
   void set_lengths(const int32_t* lens) {
     lens_host = lens;
     row_block_ = dt_ == mk::BF16 ? mk::kRowBlock : 1;
@@ -239,6 +241,8 @@ class Step {
     // the batch's last block may be a part of one
     const int last = blocks_[nb] > blocks_[nb - 1] ? Tpad_ - (nb - 1) * row_block_ : row_block_;
     T_ = (blocks_[nb] - 1) * row_block_ + last;
+    packed_ = T_ < Tpad_ && (int64_t)(Tpad_ - T_) * f_.hidden * es_ >= n_table_ints() * 4;
+    if (!packed_) T_ = Tpad_;
   }
   // collected bytes (valid after run)
   uint64_t e_bytes = 0, g_bytes = 0;
@@ -250,8 +254,12 @@ class Step {
   const int32_t* lens_host = nullptr;
   int B_, L_;
   int T_, Tpad_;        // rows of the step; rows its tensors are allocated for (B * L)
-  int row_block_ = 1;             // padded batch: rows per block, kept blocks before each block
+  bool packed_ = false;           // padded batch with rows left out
+  int row_block_ = 1;             // rows per block, kept blocks before each block
   std::vector<int32_t> blocks_;
+  // tables of a packed batch: where each sample's rows end, its real tokens, and (bf16) which chunk
+  // of kept rows each chunk of the padded batch is
+  int64_t n_table_ints() const { return 2 * (int64_t)B_ + (dt_ == mk::BF16 ? (Tpad_ + mk::kRowBlock - 1) / mk::kRowBlock : 0); }
   uint64_t plan_;
   bool collect_, dry_;
   hipStream_t st_;
@@ -340,7 +348,7 @@ class Step {
   // a product whose reduction runs over the step's rows
   void over_rows(mk::GemmArgs& a) const {
     a.rule_rows = a.M;
-    if (lens_host && dt_ == mk::BF16) { a.k_padded = Tpad_; a.k_blocks = blocks_.data(); }
+    if (packed_ && dt_ == mk::BF16) { a.k_padded = Tpad_; a.k_blocks = blocks_.data(); }
   }
   // dW[out,in] = dY^T X, db[out] = column sums of dY
   void wgrad(const void* dY, int64_t ldy, int out, const void* X, int in, int wi, int bi, bool late = false) {
@@ -471,7 +479,7 @@ class Step {
   // first row of sample b (b == B: one past the last row)
   int64_t first_row(int b) const {
     const int64_t at = (int64_t)b * L_;
-    if (!lens_host) return at;
+    if (!packed_) return at;
     if (b == B_) return T_;
     return (int64_t)blocks_[at / row_block_] * row_block_ + at % row_block_;
   }
@@ -485,17 +493,12 @@ class Step {
 
 void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   const int H = f_.hidden;
-  // ids, labels, sort order, run boundaries; for padded batches where each sample's rows end, its
-  // real tokens, and which chunk of kept rows each chunk of the padded batch is
-  const int64_t TP = Tpad_, nb = (TP + mk::kRowBlock - 1) / mk::kRowBlock, n_ints = 4 * TP + 1 + 2 * (int64_t)B_ + nb;
-  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)n_ints * 4);
+  // ids, labels, sort order, run boundaries, real tokens of each sample (the last B read for padded batches alone)
+  const int64_t TP = Tpad_;
+  int32_t* ints = (int32_t*)c_->arena.alloc((uint64_t)(4 * TP + 1 + B_) * 4);
   ids_ = ints; labels_ = ints ? ints + TP : nullptr; order_ = ints ? ints + 2 * TP : nullptr;
   seg_ = ints ? ints + 3 * TP : nullptr;
-  if (ints && lens_host) {
-    ends_ = ints + 4 * TP + 1;
-    lens_ = ends_ + B_;
-    if (dt_ == mk::BF16) chunk_at_ = lens_ + B_;
-  }
+  if (ints && lens_host && !packed_) lens_ = ints + 4 * TP + 1;
   wide_ = !f_.pre_ln && dt_ == mk::BF16;
   gA_ = walloc(TP * H);
   gB_ = walloc(TP * H);
@@ -503,6 +506,11 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   oB_ = wide_ ? talloc(TP * H) : gB_;
   if (!f_.pre_ln) emb_sum_ = talloc(TP * H);
   h0_ = talloc(TP * H);
+  if (h0_ && packed_) {
+    ends_ = (int32_t*)((char*)h0_ + (int64_t)T_ * H * es_);
+    lens_ = ends_ + B_;
+    if (dt_ == mk::BF16) chunk_at_ = lens_ + B_;
+  }
   if (late_ok()) {
     late_dqkv_ = talloc(3 * TP * H);
     late_ws_bytes_ = dt_ == mk::BF16 ? mk::gemm_workspace_bytes(3 * H, H) : 0;
@@ -511,7 +519,8 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   if (dry_) return;
 
   // host side: stable sort of positions by token id, run boundaries of equal ids
-  const size_t need = (size_t)n_ints;
+  const int64_t n_tables = packed_ ? n_table_ints() : B_;
+  const size_t need = (size_t)(4 * TP + 1 + n_tables);
   const int turn = c_->stage_turn;
   c_->stage_turn ^= 1;
   if (c_->stage_busy[turn]) {               // copies of the step before last out of this buffer: long done
@@ -528,17 +537,19 @@ void Step::embed_stage(const int32_t* tokens, const int32_t* labels) {
   stage_turn_ = turn;
   int32_t* s = c_->stage;
   if (lens_host) {
-    int32_t *ends = s + 4 * TP + 1, *lens = ends + B_, *chunk_at = lens + B_;
+    int32_t *ends = s + 4 * TP + 1, *lens = packed_ ? ends + B_ : ends;
     for (int b = 0; b < B_; ++b) {
       const int64_t t = first_row(b), n = first_row(b + 1) - t;
       std::memcpy(s + t, tokens + (size_t)b * L_, (size_t)n * 4);
       for (int64_t i = 0; i < n; ++i) s[TP + t + i] = i < lens_host[b] ? labels[(size_t)b * L_ + i] : -1;
-      ends[b] = (int32_t)(t + n);
+      if (packed_) ends[b] = (int32_t)(t + n);
       lens[b] = lens_host[b];
     }
-    if (chunk_at_)
-      for (int64_t j = 0; j < nb; ++j) chunk_at[j] = blocks_[j + 1] > blocks_[j] ? blocks_[j] : -1;
-    HIPCHK(c_, hipMemcpyAsync(ends_, ends, (2 * (size_t)B_ + (size_t)nb) * 4, hipMemcpyHostToDevice, st_));
+    if (chunk_at_) {
+      int32_t* chunk_at = lens + B_;
+      for (size_t j = 0; j + 1 < blocks_.size(); ++j) chunk_at[j] = blocks_[j + 1] > blocks_[j] ? blocks_[j] : -1;
+    }
+    HIPCHK(c_, hipMemcpyAsync(packed_ ? ends_ : lens_, ends, (size_t)n_tables * 4, hipMemcpyHostToDevice, st_));
   } else {
     std::memcpy(s, tokens, (size_t)T_ * 4);
     std::memcpy(s + TP, labels, (size_t)T_ * 4);

@@ -239,6 +239,35 @@ def test_padded_batches(name):
     m.close()
 
 
+@pytest.mark.parametrize("dtype,H,B,L,cut", [("fp32", 32, 20, 9, [1]),        # one row left out, tables of 160 bytes: not in 128
+                                             ("fp32", 32, 14, 9, [1]),        # 112 bytes: in 128
+                                             ("bf16", 32, 3, 107, [1]),       # the last block of one row, 108 bytes: not in 64
+                                             ("bf16", 64, 3, 107, [1]),       # in 128
+                                             ("bf16", 64, 8, 96, [0, 80, 0, 33, 0, 95])])
+def test_padded_batch_at_the_budget_of_the_whole_one(dtype, H, B, L, cut):
+    """A padded batch needs not a byte more than the unpadded one of its B and L, also where the rows
+    it could leave out are too few to hold the tables that leaving them out takes.  `cut`: rows
+    missing from the last samples."""
+    shape = synthdata.ModelShape(2, H, H // 32, 4 * H, 300, L, dtype)
+    params = synthdata.make_params(shape, 55, perturb=True)
+    d = synthdata.shape_dict(shape)
+    cal = mi.Mimose(d, 0, device=None)
+    cal.force_plan(0)
+    peak0, _ = cal.dry_step(B, L)
+    cal.close()
+    lengths = np.full(B, L)
+    lengths[B - len(cut):] -= cut
+    tokens, labels, lens = synthdata.make_padded_batch(shape, lengths, 56)
+    m = mi.Mimose(d, peak0)
+    m.load_params(params)
+    m.force_plan(0)
+    fp32 = dtype == "fp32"
+    _, peak, _, _ = check_against_oracle(shape, m, params, tokens, labels, 1e-4 if fp32 else 1e-2, 1e-3 if fp32 else 2e-2,
+                                         lengths=lens)
+    assert peak == peak0
+    m.close()
+
+
 @pytest.mark.parametrize("name", list(SMALL))
 def test_dropout_parity_and_replay(name):
     """Dropout with counter-based masks: parity with the oracle given (p, seed, iteration), the

@@ -211,6 +211,28 @@ def test_components_are_polynomial_in_input_size():
     m.close()
 
 
+@pytest.mark.parametrize("name,B,L", [("bert_base", 32, 200), ("bert_base", 32, 512), ("tiny", 8, 64), ("gpt2_medium", 16, 333)])
+def test_embedding_stage_holds_nothing_for_padded_batches_alone(name, B, L):
+    """Bytes of the embedding stage: ids, labels, sort order, run boundaries and lengths (4 T + 1 + B
+    integers), the gradient carriers, embedding sum and output, and the post-LN stacks' step-long
+    slot; a step that leaves rows of padding out finds room for its tables inside these."""
+    wl, m = host_ctx(name)
+    s, T, H = wl.shape, B * L, wl.shape.hidden
+    up = lambda n: (n + 255) // 256 * 256
+    es = 2 if s.dtype == "bf16" else 4
+    want = up(4) + up((4 * T + 1 + B) * 4) + up(T * H * es)              # loss, integers, embedding output
+    if s.pre_ln:
+        want += 2 * up(T * H * es)                                       # gradient carriers
+    else:
+        want += 2 * up(T * H * 4) + (2 * up(T * H * 2) if es == 2 else 0) + up(T * H * es) + up(3 * T * H * es)
+        if es == 2:
+            want += up(mi.mimose_op_gemm_workspace_bytes(3 * H, H))
+    m.force_plan(0)
+    m.dry_step(B, L)
+    assert components_of(m).e == want
+    m.close()
+
+
 def budget_for(name):
     wl, m = host_ctx(name)
     m.force_plan(0)
