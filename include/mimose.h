@@ -71,6 +71,8 @@ typedef struct {
   uint64_t cache_hits, cache_misses, cache_entries;
   uint64_t planner_ns_last, planner_ns_total;
   uint64_t recomputed_layers_last, recomputed_layers_total;
+  /* products of forward and backward, and of the rebuilt layers' forward, over the real tokens (of
+   * a padded batch: those its lengths name, whatever rows of padding the kernels also run) */
   double useful_flops_last, recompute_flops_last;
   double useful_flops_total, recompute_flops_total;
   uint64_t peak_bytes_last, peak_bytes_max, predicted_peak_last;

@@ -215,6 +215,14 @@ void build_params(mimose_ctx* c) {
   }
 }
 
+// query-key pairs of a batch, causal masking aside (lengths: real tokens of each sample, or null: L each)
+double attention_pairs(int B, int L, const int32_t* lengths) {
+  if (!lengths) return (double)B * L * L;
+  double n = 0.0;
+  for (int b = 0; b < B; ++b) n += (double)lengths[b] * lengths[b];
+  return n;
+}
+
 // ------------------------------------------------------------------ step executor
 class Step {
  public:
@@ -658,7 +666,7 @@ void Step::layer_forward(int l, LayerActs& A, bool rebuild) {
   if (f_.pre_ln) { ln_fwd(A.x, p.ln1g, p.ln1b, A.n1); a = A.n1; }
   linear(a, H, p.wqkv, p.bqkv, A.qkv, 3 * H, 3 * H);
   {
-    Timed t(this, MIMOSE_K_ATTN_FWD, 4.0 * T_ * L_ * H * (f_.causal ? 0.5 : 1.0));
+    Timed t(this, MIMOSE_K_ATTN_FWD, 4.0 * attention_pairs(B_, L_, lens_host) * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
       mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, rows(), B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_);
   }
@@ -744,7 +752,7 @@ void Step::layer_backward(int l, LayerActs& A) {
   float* delta = (float*)ar.alloc((uint64_t)B_ * nh * L_ * 4);
   if (late_ok() && !dry_) wait_late();
   {
-    Timed t(this, MIMOSE_K_ATTN_BWD, 8.0 * T_ * L_ * H * (f_.causal ? 0.5 : 1.0));
+    Timed t(this, MIMOSE_K_ATTN_BWD, 8.0 * attention_pairs(B_, L_, lens_host) * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
       mk::attention_bwd(dt_, A.qkv, A.ctx, dctx, A.lse, delta, dqkv, rows(), B_, L_, nh, d, f_.causal,
                         drop_desc(4 * (uint32_t)(l + 1), true), st_);
@@ -975,18 +983,24 @@ void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bo
   }
 }
 
-void flops(const mimose_model_cfg& f, int B, int L, uint64_t plan, double* useful, double* re) {
-  const double T = (double)B * L, H = f.hidden, V = f.vocab;
-  const double attn = 4.0 * L * H * (f.causal ? 0.5 : 1.0);
+// operations of the batch's real tokens (lengths: real tokens of each sample, or null: L each)
+void flops(const mimose_model_cfg& f, int B, int L, const int32_t* lengths, uint64_t plan, double* useful, double* re) {
+  double T = (double)B * L;
+  const double H = f.hidden, V = f.vocab, pairs = attention_pairs(B, L, lengths);
+  if (lengths) {
+    T = 0.0;
+    for (int b = 0; b < B; ++b) T += lengths[b];
+  }
+  const double attn = 4.0 * pairs * H * (f.causal ? 0.5 : 1.0);
   const double head = 2.0 * H * V + (f.head ? 2.0 * H * H : 0.0);
   double layers = 0.0;
   *re = 0.0;
   for (int l = 0; l < f.n_layers; ++l) {
-    const double layer = 8.0 * H * H + 4.0 * H * ffn_of(f, l) + attn;
+    const double layer = T * (8.0 * H * H + 4.0 * H * ffn_of(f, l)) + attn;
     layers += layer;
-    if ((plan >> l) & 1) *re += T * layer;
+    if ((plan >> l) & 1) *re += layer;
   }
-  *useful = 3.0 * T * (layers + head);
+  *useful = 3.0 * (layers + T * head);
 }
 
 int do_step(mimose_ctx* c, const int32_t* tokens, const int32_t* labels, const int32_t* lengths, int32_t B, int32_t L,
@@ -1101,7 +1115,7 @@ int do_step(mimose_ctx* c, const int32_t* tokens, const int32_t* labels, const i
   auto& S = c->stats;
   const int n_re = __builtin_popcountll(plan);
   double uf, rf;
-  flops(f, B, L, plan, &uf, &rf);
+  flops(f, B, L, dry ? nullptr : lengths, plan, &uf, &rf);
   S.steps++;
   if (!dry) c->drop_step++;                 // the next iteration draws other masks
   S.sheltered_steps = c->planner->sheltered_steps_seen();

@@ -268,6 +268,32 @@ def test_padded_batch_at_the_budget_of_the_whole_one(dtype, H, B, L, cut):
     m.close()
 
 
+@pytest.mark.parametrize("name", ["fp32_postln", "bf16_preln_causal", "bf16_stages"])
+def test_padded_step_counts_the_operations_of_its_real_tokens(name):
+    """useful and recompute flops of a padded step are those of its samples at their own lengths, and
+    the attention kernels' work is that of the real pairs."""
+    shape = SMALL[name]
+    cfg = om.Cfg.from_shape(synthdata.shape_dict(shape))
+    lengths = [shape.max_seq, 3, 40, 17, 1]
+    tokens, labels, lens = synthdata.make_padded_batch(shape, lengths, 57)
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=256 * MiB)
+    m.load_params(synthdata.make_params(shape, 58))
+    m.force_plan(0b10)
+    for ls, want in ((lens, [om.flops_per_step(cfg, 1, n, plan=0b10) for n in lengths]),
+                     (None, [om.flops_per_step(cfg, len(lengths), shape.max_seq, plan=0b10)])):
+        mi.mimose_profile_enable(m.ctx, 1)
+        m.train_step(tokens, labels, lengths=ls)
+        st = m.stats()
+        assert st["useful_flops_last"] == sum(u for u, _ in want)
+        assert st["recompute_flops_last"] == sum(r for _, r in want)
+        pairs = sum(n * n for n in lengths) if ls is not None else len(lengths) * shape.max_seq ** 2
+        once = 4.0 * pairs * shape.hidden * (0.5 if shape.causal else 1.0)
+        assert mi.mimose_profile_read(m.ctx, mi.KERNEL_CLASSES.index("attention_fwd"))[2] == once * (shape.n_layers + 1)
+        assert mi.mimose_profile_read(m.ctx, mi.KERNEL_CLASSES.index("attention_bwd"))[2] == 2 * once * shape.n_layers
+        mi.mimose_profile_enable(m.ctx, 0)
+    m.close()
+
+
 @pytest.mark.parametrize("name", list(SMALL))
 def test_dropout_parity_and_replay(name):
     """Dropout with counter-based masks: parity with the oracle given (p, seed, iteration), the
