@@ -276,7 +276,9 @@ int mimose_get_step_memory(mimose_ctx* ctx, uint64_t* fixed, uint64_t* embed, ui
                            uint64_t* kept, uint64_t* boundary, uint64_t* bwd);
 
 /* Forward time of each layer in the last sheltered (collecting) step, in ns, as fed to the
- * estimator (Section 4.1).  ns: host array of n_layers.  NOT_READY before the first such step. */
+ * estimator (Section 4.1).  ns: host array of n_layers.  NOT_READY before the first such step.
+ * Of a padded batch: with cost_aware the whole batch's, padding included; else (nothing reads it
+ * then) that of the rows the step ran. */
 int mimose_get_layer_times(mimose_ctx* ctx, uint64_t* ns);
 
 int mimose_get_stats(mimose_ctx* ctx, mimose_stats* out);

@@ -238,8 +238,10 @@ class Step {
   // fp32 sums are not held to that: there every row of padding is left out.
   // The tables that say which rows are left go behind the rows that are left in h0's buffer; where
   // what is left out is too little to hold them, nothing is.
-  void set_lengths(const int32_t* lens) {
+  // whole: leave nothing out.
+  void set_lengths(const int32_t* lens, bool whole) {
     lens_host = lens;
+    if (whole) return;
     row_block_ = dt_ == mk::BF16 ? mk::kRowBlock : 1;
     const int nb = (Tpad_ + row_block_ - 1) / row_block_;
     blocks_.assign((size_t)nb + 1, 0);
@@ -1058,7 +1060,12 @@ int do_step(mimose_ctx* c, const int32_t* tokens, const int32_t* labels, const i
   // ---- run
   c->dry = dry;
   Step s(c, B, L, plan, collect);
-  if (!dry && lengths) s.set_lengths(lengths);
+  // A cost-aware planner keeps a layer's forward time at x = B * L (Section 4.1), so its collecting steps
+  // run the batch whole: the time of the rows that are left says nothing about that size (2 x 768-wide
+  // layers, 32 x 256 with a quarter of the rows real: 0.14 ms against the whole batch's 0.25).  In bf16
+  // the bits are those of the steps that leave padding out; fp32 sums are not, so there no step of such
+  // a context leaves any out.
+  if (!dry && lengths) s.set_lengths(lengths, f.cost_aware && (collect || f.dtype == mk::F32));
   float lv = 0.f;
   try {
     s.run(tokens, labels, &lv, dry || loss != nullptr);

@@ -294,6 +294,34 @@ def test_padded_step_counts_the_operations_of_its_real_tokens(name):
     m.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_cost_aware_layer_times_are_those_of_the_whole_size(dtype):
+    """A cost-aware planner keeps a layer's forward time at x = B L (Section 4.1), while a padded
+    batch's rows of padding are left out of the kernels: its collecting steps run the whole batch, or
+    padded and whole batches of one size contradict each other.  Whether padding was left out or
+    not, loss and gradients are the same bits."""
+    shape = synthdata.ModelShape(2, 768, 12, 3072, 1000, 256, dtype)
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=2048 * MiB, sheltered_steps=12, cost_aware=1)
+    m.load_params(synthdata.make_params(shape, 59, perturb=True))
+    lengths = [256] + [60] * 31
+    seen = {False: [], True: []}
+    for i in range(12):
+        tokens, labels, lens = synthdata.make_padded_batch(shape, lengths, 60 + i)
+        loss, _, plan = m.train_step(tokens, labels, lengths=lens if i % 2 else None)
+        assert plan == 0b11                                     # still collecting
+        seen[bool(i % 2)].append(m.layer_times())
+    G = m.grads()
+    m.force_plan(0b11)                                          # no longer collecting: padding left out (bf16)
+    again, _, _ = m.train_step(tokens, labels, lengths=lens)
+    assert again == loss
+    for k, g in m.grads().items():
+        assert np.array_equal(g, G[k]), k
+    whole, padded = (np.median(np.array(seen[k][1:]), axis=0) for k in (False, True))
+    print("layer times, whole batch", whole, "padded", padded)
+    assert np.all(padded < 1.3 * whole) and np.all(whole < 1.3 * padded)      # 0.57 of it with padding left out
+    m.close()
+
+
 @pytest.mark.parametrize("name", list(SMALL))
 def test_dropout_parity_and_replay(name):
     """Dropout with counter-based masks: parity with the oracle given (p, seed, iteration), the
