@@ -366,6 +366,20 @@ int mimose_op_attention_bwd(int32_t dtype, const void* qkv, const void* ctx, con
 int mimose_op_dropout(int32_t dtype, void* dst, const void* src, int32_t io_f32, const void* resid,
                       int64_t n, float p, uint64_t seed, uint32_t site, uint32_t step,
                       void* stream);
+/* x[T,H] = resid + dropout(x) in place with the mask of (seed, site, step) over its T*H elements,
+ * then y = LayerNorm(x); y NULL: the sum alone.  x, x_f32, resid, gamma, beta, y as in
+ * mimose_op_dropout and mimose_op_layernorm_fwd. */
+int mimose_op_dropout_layernorm_fwd(int32_t dtype, void* x, int32_t x_f32, const void* resid,
+                                    const void* gamma, const void* beta, void* y, int32_t T, int32_t H,
+                                    float eps, float p, uint64_t seed, uint32_t site, uint32_t step,
+                                    void* stream);
+/* mimose_op_layernorm_bwd, and masked[T,H] (storage type, no alias of dy or dx) = dropout(dx as
+ * stored) with the mask of (seed, site, step). */
+int mimose_op_layernorm_bwd_dropout(int32_t dtype, const void* dy, int32_t dy_f32, const void* x,
+                                    int32_t x_f32, const void* gamma, void* dx, const void* add,
+                                    void* masked, float* dgamma, float* dbeta, float* partial,
+                                    int32_t T, int32_t H, float eps, float p, uint64_t seed,
+                                    uint32_t site, uint32_t step, void* stream);
 /* logits [T, ld] (first V columns valid) -> in place d loss / d logits (columns >= V zeroed);
  * row_loss fp32[T]; loss: device fp32 scalar = sum(row_loss)/n_valid. */
 int mimose_op_softmax_xent(int32_t dtype, void* logits, int64_t ld, const int32_t* labels,

@@ -95,6 +95,10 @@ SIGNATURES = {
     "mimose_op_layernorm_fwd": (C.c_int, [_i32, _vp, _i32, _vp, _vp, _vp, _i32, _i32, _f32, _vp]),
     "mimose_op_layernorm_bwd": (C.c_int, [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _i32, _f32,
                                           _vp]),
+    "mimose_op_dropout_layernorm_fwd": (C.c_int, [_i32, _vp, _i32, _vp, _vp, _vp, _vp, _i32, _i32, _f32, _f32, _u64,
+                                                  C.c_uint32, C.c_uint32, _vp]),
+    "mimose_op_layernorm_bwd_dropout": (C.c_int, [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _i32,
+                                                  _f32, _f32, _u64, C.c_uint32, C.c_uint32, _vp]),
     "mimose_op_partial_rows": (_i32, [_i32]),
     "mimose_op_layernorm_bwd_noalloc": (C.c_int, [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _i32, _i32, _f32,
                                                   _vp]),
@@ -381,6 +385,18 @@ def mimose_op_attention_bwd(dtype, qkv, ctx_in, dctx, lse, delta, dqkv, B, L, n_
 def mimose_op_dropout(dtype, dst, src, io_f32, resid, n, p, seed, site, step, stream=None):
     _check(load_library().mimose_op_dropout(dtype, _ptr(dst), _ptr(src), int(io_f32), _ptr(resid), n, p, seed, site, step,
                                             _ptr(stream)))
+
+
+def mimose_op_dropout_layernorm_fwd(dtype, x, x_f32, resid, gamma, beta, y, T, H, eps, p, seed, site, step, stream=None):
+    _check(load_library().mimose_op_dropout_layernorm_fwd(dtype, _ptr(x), int(x_f32), _ptr(resid), _ptr(gamma), _ptr(beta),
+                                                          _ptr(y), T, H, eps, p, seed, site, step, _ptr(stream)))
+
+
+def mimose_op_layernorm_bwd_dropout(dtype, dy, dy_f32, x, x_f32, gamma, dx, add, masked, dgamma, dbeta, partial, T, H, eps,
+                                    p, seed, site, step, stream=None):
+    _check(load_library().mimose_op_layernorm_bwd_dropout(dtype, _ptr(dy), int(dy_f32), _ptr(x), int(x_f32), _ptr(gamma),
+                                                          _ptr(dx), _ptr(add), _ptr(masked), _ptr(dgamma), _ptr(dbeta),
+                                                          _ptr(partial), T, H, eps, p, seed, site, step, _ptr(stream)))
 
 
 def mimose_set_dropout(ctx, p_hidden: float, p_attn: float, seed: int, first_step: int = 0):

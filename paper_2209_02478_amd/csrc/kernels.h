@@ -86,9 +86,9 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st);
 // x_f32: in a bf16 configuration the input rows are fp32 (an unrounded residual sum)
 void layernorm_fwd(int dtype, const void* x, bool x_f32, const void* gamma, const void* beta,
                    void* y, int T, int H, float eps, hipStream_t st);
-// x = resid + dropout(x) in place, then y = LayerNorm(x) (left out when y is null): one pass.
-// resid: storage type.  H must be a multiple of 8 (bf16) or 4 (fp32), every pointer 16-byte aligned;
-// masks and rows as in dropout_apply.
+// x = resid + dropout(x) in place, then y = LayerNorm(x) (left out when y is null).  resid: storage
+// type; masks and rows as in dropout_apply.  One pass where H is a multiple of 8 (bf16) or 4 (fp32)
+// and every pointer 16-byte aligned, else two.
 void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, const void* gamma, const void* beta,
                            void* y, int T, int H, float eps, const DropDesc& d, const Rows& rows, int B, int L,
                            hipStream_t st);
@@ -100,7 +100,7 @@ void layernorm_bwd(int dtype, const void* dy, bool dy_f32, const void* x, bool x
                    float* partial, int T, int H, float eps, hipStream_t st);
 // the two halves of layernorm_bwd: dx and the per-chunk partial sums; then dgamma, dbeta from them
 // masked (optional): dx as stored with the dropout mask of d applied, for the branch behind a
-// dropped product; H and pointers then as in dropout_layernorm_fwd.
+// dropped product; in the same pass under the conditions of dropout_layernorm_fwd, else in its own.
 struct LnBwdMasked {
   void* masked = nullptr;
   DropDesc d;

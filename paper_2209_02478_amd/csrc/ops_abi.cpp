@@ -129,6 +129,30 @@ int mimose_op_dropout(int32_t dtype, void* dst, const void* src, int32_t io_f32,
   return done();
 }
 
+int mimose_op_dropout_layernorm_fwd(int32_t dtype, void* x, int32_t x_f32, const void* resid, const void* gamma,
+                                    const void* beta, void* y, int32_t T, int32_t H, float eps, float p, uint64_t seed,
+                                    uint32_t site, uint32_t step, void* stream) {
+  if (bad_dtype(dtype) || !x || !resid || !gamma || !beta || T < 0 || H < 1 || H > mk::kMaxRowWidth || bad_p(p))
+    return MIMOSE_ERR_INVALID_ARG;
+  mk::dropout_layernorm_fwd(dtype, x, x_f32 != 0, resid, gamma, beta, y, T, H, eps, make_desc(p, seed, site, step), mk::Rows(), 0, 0,
+                            (hipStream_t)stream);
+  return done();
+}
+
+int mimose_op_layernorm_bwd_dropout(int32_t dtype, const void* dy, int32_t dy_f32, const void* x, int32_t x_f32,
+                                    const void* gamma, void* dx, const void* add, void* masked, float* dgamma, float* dbeta,
+                                    float* partial, int32_t T, int32_t H, float eps, float p, uint64_t seed, uint32_t site,
+                                    uint32_t step, void* stream) {
+  if (bad_dtype(dtype) || !dy || !x || !gamma || !dx || !masked || !dgamma || !dbeta || !partial || T < 0 || H < 1 ||
+      H > mk::kMaxRowWidth || add == dx || masked == dx || masked == dy || (dx == dy && dtype == 1 && dy_f32) || bad_p(p))
+    return MIMOSE_ERR_INVALID_ARG;
+  mk::LnBwdMasked ex;
+  ex.masked = masked; ex.d = make_desc(p, seed, site, step);
+  mk::layernorm_bwd_rows(dtype, dy, dy_f32 != 0, x, x_f32 != 0, gamma, dx, add, partial, T, H, eps, ex, (hipStream_t)stream);
+  mk::layernorm_bwd_reduce(partial, dgamma, dbeta, nullptr, T, H, (hipStream_t)stream);
+  return done();
+}
+
 int mimose_op_softmax_xent(int32_t dtype, void* logits, int64_t ld, const int32_t* labels, float* row_loss,
                            float* loss, int32_t T, int32_t V, int32_t n_valid, void* stream) {
   if (bad_dtype(dtype) || !logits || !labels || !row_loss || !loss || T < 0 || V < 1 || ld < V) return MIMOSE_ERR_INVALID_ARG;

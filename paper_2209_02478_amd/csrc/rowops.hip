@@ -867,6 +867,12 @@ void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, co
                            void* y, int T_, int H, float eps, const DropDesc& d, const Rows& rows, int B, int L,
                            hipStream_t st) {
   if (T_ <= 0) return;
+  const bool vec = dtype == BF16 ? vec_ok<bf16_t>(H, {x, resid, gamma, beta, y}) : vec_ok<float>(H, {x, resid, gamma, beta, y});
+  if (!vec) {                                         // the same in two passes
+    dropout_apply(dtype, x, x, x_f32, resid, (int64_t)T_ * H, d, rows, B, L, H, st);
+    if (y) layernorm_fwd(dtype, x, x_f32, gamma, beta, y, T_, H, eps, st);
+    return;
+  }
   const DropRows dr{d, rows, B, L};
   if (dtype != BF16) drop_ln_fwd_t<float, float>(x, resid, gamma, beta, y, T_, H, eps, dr, st);
   else if (x_f32) drop_ln_fwd_t<float, bf16_t>(x, resid, gamma, beta, y, T_, H, eps, dr, st);
@@ -877,7 +883,7 @@ template <typename TD, typename TX, typename T>
 static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, const void* add, float* partial,
                      int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
-  if (vec_ok<T>(H, {dy, x, g, dx, add})) {
+  if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
 #define V_(NC) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC>), grid, dim3(256), 0, st, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
@@ -891,6 +897,8 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, T_, H, eps)
   DISPATCH_NPL(H, M_);
 #undef M_
+  if (ex.masked)                                      // dx is stored: the mask in a pass of its own
+    dropout_apply(sizeof(T) == 2 ? BF16 : F32, ex.masked, dx, false, nullptr, (int64_t)T_ * H, ex.d, ex.rows, ex.B, ex.L, H, st);
 }
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
                         const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {

@@ -573,3 +573,60 @@ def test_dropout_op(dtype, io_f32, n, with_resid):
     close(got, ref, io_dtype, k=1.5)
     assert np.array_equal(host(inplace), got)
     assert 0.25 < (keep == 0).mean() < 0.35 or n < 100
+
+
+# H % 8 and H % 4, and `shift`: elements by which every row operand starts off a 16-byte boundary,
+# decide between the one-pass kernels and separate passes
+@pytest.mark.parametrize("dtype,wide", [(0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("T,H,shift", [(37, 64, 0), (130, 768, 0), (5, 1024, 0), (18, 24, 0), (18, 20, 0), (18, 70, 0),
+                                       (18, 64, 1), (33, 768, 4)])
+def test_dropout_inside_layernorm(dtype, wide, T, H, shift):
+    """x = resid + dropout(x), y = LayerNorm(x), and LayerNorm's backward with a masked copy of dx: the
+    kept set and the sum are those of the element-wise pass bit for bit, the rest the oracle's."""
+    from oracle import philox as ph
+    rng = np.random.default_rng(T * H + shift)
+    p, seed, site, step = float(np.float32(0.2)), 0xA5A5A5A5DEADBEEF, 4 * 3 + 2, 77
+    io = 0 if wide else dtype
+
+    def at(a, dt):                                    # a copy that starts `shift` elements into its buffer
+        buf = torch.zeros(a.size + shift, dtype=dev(a, dt).dtype, device=DEV)
+        buf[shift:] = dev(a, dt).reshape(-1)
+        return buf[shift:].view(T, H)
+
+    x, resid, dy, add = (rng.standard_normal((T, H)).astype(np.float32) for _ in range(4))
+    g = (1 + 0.2 * rng.standard_normal(H)).astype(np.float32)
+    b = (0.1 * rng.standard_normal(H)).astype(np.float32)
+    dg_, db_, dres, dadd = dev(g, dtype), dev(b, dtype), at(resid, dtype), at(add, dtype)
+    keep = ph.keep_scale(np.arange(T * H, dtype=np.uint64), p, seed, site, step).reshape(T, H)
+
+    separate = at(x, io)
+    mi.mimose_op_dropout(dtype, separate, separate, wide, dres, T * H, p, seed, site, step)
+    xs, y = at(x, io), at(np.full((T, H), 9.0, np.float32), dtype)
+    mi.mimose_op_dropout_layernorm_fwd(dtype, xs, wide, dres, dg_, db_, y, T, H, 1e-5, p, seed, site, step)
+    alone = at(x, io)
+    mi.mimose_op_dropout_layernorm_fwd(dtype, alone, wide, dres, dg_, db_, None, T, H, 1e-5, p, seed, site, step)
+    sync()
+    assert torch.equal(xs, separate) and torch.equal(alone, separate)
+    close(host(xs), quant(resid, dtype) + keep * quant(x, io), io, k=1.5)
+    y_ref, saved = om.layernorm_fwd(host(xs), quant(g, dtype), quant(b, dtype), 1e-5)
+    close(host(y), y_ref, dtype, k=2.0)
+
+    ddy = at(dy, io)
+    out, masked = (at(np.full((T, H), 9.0, np.float32), dtype) for _ in range(2))
+    dgam, dbet = (torch.zeros(H, dtype=torch.float32, device=DEV) for _ in range(2))
+    partial = torch.zeros(mi.mimose_op_partial_rows(T) * 2 * H, dtype=torch.float32, device=DEV)
+    mi.mimose_op_layernorm_bwd_dropout(dtype, ddy, wide, xs, wide, dg_, out, dadd, masked, dgam, dbet, partial, T, H, 1e-5,
+                                       p, seed, site, step)
+    want = at(np.zeros((T, H), np.float32), dtype)
+    mi.mimose_op_dropout(dtype, want, out, 0, None, T * H, p, seed, site, step)
+    sync()
+    dx_ref, dg_ref, db_ref = om.layernorm_bwd(quant(dy, io), saved, quant(g, dtype))
+    close(host(out), dx_ref + quant(add, dtype), dtype, k=3.0)
+    close(host(dgam), dg_ref, 0, k=50.0)
+    close(host(dbet), db_ref, 0, k=50.0)
+    assert torch.equal(masked, want) and (host(masked) != 9.0).all()
+    assert np.array_equal(host(masked) != 0, (keep != 0) & (host(out) != 0))
+    for alias in (out, ddy):
+        with pytest.raises(mi.MimoseError):
+            mi.mimose_op_layernorm_bwd_dropout(dtype, ddy, wide, xs, wide, dg_, out, dadd, alias, dgam, dbet, partial, T, H,
+                                               1e-5, p, seed, site, step)
