@@ -431,7 +431,9 @@ def test_halves_of_the_batch_change_no_bits(name, B, L):
     m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=256 * MiB)
     m.load_params(params)
     whole = synthdata.make_batch(shape, B, L, 96) + (None,)
-    padded = synthdata.make_padded_batch(shape, [max(1, L - 7 * b) for b in range(B + 3)], 97)
+    # fp32 leaves every row of padding out, and halves want 2^15 elements of what is left
+    padded = synthdata.make_padded_batch(shape, [max(1, L - 7 * (b % 6)) for b in range(B + 7)], 97)
+    assert min(whole[0].size, int(padded[2].sum())) * shape.hidden >= 1 << 15
     for tokens, labels, lens in (whole, padded):
         for plan in (0, 0b10):
             m.force_plan(plan)
@@ -442,6 +444,32 @@ def test_halves_of_the_batch_change_no_bits(name, B, L):
             assert out[0][0] == out[1][0]
             for k in out[0][1]:
                 assert np.array_equal(out[0][1][k], out[1][1][k]), (plan, k)
+    m.close()
+
+
+@pytest.mark.parametrize("H,F,lengths", [(128, 512, [512, 3, 512, 17]),       # reductions in 8 parts of 256 rows
+                                         (1024, 1024, [1024, 100])])          # in 4 of 512, one round of units
+def test_parts_of_a_reduction_that_are_all_padding(H, F, lengths):
+    """A weight gradient cuts its reduction over the padded batch's rows; where the rows of a whole part
+    are padding the part is empty.  Parity with the oracle, and the bits of the step that leaves
+    nothing out (the collecting step of a cost-aware context)."""
+    shape = synthdata.ModelShape(2, H, H // 64, F, 300, max(lengths), "bf16")
+    params = synthdata.make_params(shape, 98, perturb=True)
+    tokens, labels, lens = synthdata.make_padded_batch(shape, lengths, 99)
+    tiles = (H // 128) ** 2                                      # of the square weights' gradients
+    rows = tokens.size // min(8, 256 // tiles)
+    real = np.arange(tokens.shape[1])[None, :] < lens[:, None]
+    assert rows >= 256 and not real.reshape(-1, rows).any(axis=1).all()
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=1024 * MiB, cost_aware=1)
+    m.load_params(params)
+    whole, _, plan = m.train_step(tokens, labels, lengths=lens)
+    assert plan == 0b11
+    G = m.grads()
+    m.force_plan(0)
+    loss, _, _, _ = check_against_oracle(shape, m, params, tokens, labels, 1e-2, 2e-2, np.float32, lengths=lens)
+    assert loss == whole
+    for k, g in m.grads().items():
+        assert np.array_equal(g, G[k]), k
     m.close()
 
 
