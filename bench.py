@@ -16,7 +16,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_HBM_GBS = 8000.0
-GEMM_SOURCES = ("gemm.hip", "gemm_dma.hip", "gemm_pp.hip", "gemm_device.h")
+GEMM_SOURCES = ("gemm.hip", "gemm_dma.hip", "gemm_pp.hip", "gemm_ring.hip", "gemm_device.h")
+GEMM_KERNELS = {"bf16": "bgemm_kernel / bgemm_dma_kernel / bgemm_pp_kernel / bgemm_ring_kernel", "fp32": "sgemm_mfma_kernel"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bert_base_gemm_hbm_traffic.txt")
 
 
@@ -246,7 +247,7 @@ def main():
         "kernels_timing": "gemm: events bound to each kernel's own start and end; other classes: markers around the launch, "
                           "which read a few microseconds more than the kernel itself (see profiles/ for the kernel trace)",
         "update": upd,
-        "roofline": {"bound": "mfma", "kernel": "bgemm_kernel / bgemm_dma_kernel / bgemm_pp_kernel (every product of the timed steps, the reduction kernel of a split product included)",
+        "roofline": {"bound": "mfma", "kernel": GEMM_KERNELS[shape.dtype] + " (every product of the timed steps, the reduction kernel of a split product included)",
                      "achieved": gemm_tflops, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(gemm_tflops / PEAK_BF16_TFLOPS, 4),
                      "avg_launch_us": kernels.get("gemm", {}).get("avg_us"),

@@ -47,7 +47,8 @@ __device__ __forceinline__ void epilogue(const GemmDev& p, int m, int n, float v
 // through LDS instead (the operand tiles are dead by then): every wave parks its 64 x 64 floats in
 // 16 KB of its own, then walks them 8 rows at a time, 8 lanes per row with 8 consecutive columns
 // each, so bias / residual loads and the C / GELU stores are whole 128-byte lines.  The walk is a
-// rolled loop, which also keeps the kernel's code small.  Float4 chunk c of row r sits at chunk
+// rolled loop, which keeps the kernel's code small, except where the residuals were loaded ahead:
+// they sit in registers that only an unrolled walk can name.  Float4 chunk c of row r sits at chunk
 // position c ^ (r & 15): conflict-free for the accumulator writes (16 rows, one chunk) and for
 // the row reads (two rows, all even or all odd chunks).
 

@@ -306,7 +306,8 @@ class Step {
   void* talloc(int64_t elems) { return c_->arena.alloc((uint64_t)elems * es_); }
   void* walloc(int64_t elems) { return c_->arena.alloc((uint64_t)elems * (wide_ ? 4 : es_)); }
 
-  // rows a product's kernel is chosen by: bf16 sums the way the padded batch would
+  // rows a product's kernel is chosen by: the padded batch's in bf16, so that a reduction in parts has
+  // the parts it would have there; fp32 sums are not held to the padded batch's
   int rule_rows() const { return dt_ == mk::BF16 ? Tpad_ : T_; }
   void gemm(const mk::GemmArgs& a) {
     if (dry_) return;
@@ -641,9 +642,14 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
 // - the bf16 products as wide as the model fill one round of large tiles to three quarters or more,
 //   and then the wider ones fill theirs: the halves' launches would only get in each other's way.
 //   The whole batch in one piece is ahead by 0.1-1.6 % at 192-200 tiles, 1.6-3.1 % at 224-256, behind
-//   by 0.7-3.4 % at 96-150 tiles and from 320 on (3.2 % there, 0.2 % at 1024).
-// - a forward of a few thousand elements per tensor is its launches: the smallest configuration
-//   (132 rows of 64) takes 0.59 ms in halves and 0.48 in one piece, 74 rows of 768 the same in both.
+//   by 0.7-3.4 % at 96-150 tiles and from 320 on (3.2 % there, 0.2 % at 1024).  At 160 tiles (one
+//   measurement, causal) it was ahead by 1.5 % too: the line at 192 is on the safe side.
+// - a forward of a few thousand elements per tensor is its launches: 2 layers of 64 columns in one
+//   piece are ahead by 18-20 % at 2048 to 16896 elements per tensor and by 13 % at 32768.  Above, the
+//   line is not a sharp one: 12 bf16 layers of 768 columns in one piece are behind by 3 % at 24576 and
+//   36864 elements, ahead by 10 % at 56832, by 4-6 % at 98304-196608, behind by 0.5-1.3 % at
+//   294912-393216 and level at 786432; in fp32 ahead by 1-2 % at 24576-122880 and behind by 4 % at
+//   393216; 24 causal layers of 1024 columns ahead by 1-3 % at 131072-262144.
 bool Step::split_forward() const {
   const int tiles = dt_ == mk::BF16 ? mk::gemm_large_tiles(T_, f_.hidden) : 0;
   if ((tiles >= 192 && tiles <= 256) || (int64_t)T_ * f_.hidden < (1 << 15)) return false;

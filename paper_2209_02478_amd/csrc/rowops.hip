@@ -321,7 +321,8 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
 }
 
 // Backward: block = 4 waves = kRowsPerChunk rows, every wave takes 4 rows and issues all their
-// loads before any arithmetic.  Same outputs and the same summation order as ln_bwd_kernel.
+// loads before any arithmetic.  Same outputs as ln_bwd_kernel, and the same order of the sums over
+// rows; the sums over a row's columns run over other columns per lane.
 template <typename TD, typename TX, typename T, int NC>
 __global__ __launch_bounds__(256) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
                                                          const T* __restrict__ gamma, T* __restrict__ dx,
