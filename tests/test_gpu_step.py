@@ -448,6 +448,7 @@ def test_halves_of_the_batch_change_no_bits(name, B, L):
 
 
 @pytest.mark.parametrize("H,F,lengths", [(128, 512, [512, 3, 512, 17]),       # reductions in 8 parts of 256 rows
+                                         (128, 256, [1536, 40, 1536, 700]),   # 384 chunks of partial LayerNorm sums
                                          (1024, 1024, [1024, 100])])          # in 4 of 512, one round of units
 def test_parts_of_a_reduction_that_are_all_padding(H, F, lengths):
     """A weight gradient cuts its reduction over the padded batch's rows; where the rows of a whole part
