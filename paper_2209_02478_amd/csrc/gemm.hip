@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256, 2) void bgemm_kernel(GemmDev p, int tiles_n, i
   u32x4 resid[8];
   load_resid<1>(q, m0 + wm * 64, n0 + wn * 64, lane, resid);
   __syncthreads();                                    // the operand tiles are dead
-  store_tile<1>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, (float*)smem_raw + wave * 4096, resid, [] {});
+  store_tile<1>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, (float*)smem_raw + wave * 4096, resid);
 }
 
 // C[m][n] = sum over splits (in order) of partial tiles; row sums likewise.  C is fp32, or bf16
@@ -329,20 +329,24 @@ int gemm_splits(int M, int N) {
   return s < 1 ? 1 : (s > 8 ? 8 : s);
 }
 
-// the kernel with 256 x 256 tiles (gemm_pp.hip)
-bool launch_bgemm_pp(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
-// Which products go to the large-tile kernel: it runs one block per compute unit, so its time is
-// a whole number of rounds of 256 tiles, and it pays where those rounds are well filled.  Measured
-// against the 128 x 128 kernels with K = 768 and 2304 or 3072 columns over row counts from 4608
-// to 9984 (same box, same run): ahead by 25-34 % when the last round is filled to 0.77 or more,
-// by 2-9 % between 0.63 and 0.70, behind by 2-15 % from 0.61 down.  Products that cut their
-// reduction in parts stay with the small tiles: with few large output tiles they need more
-// parts, and the fp32 parts written and read again cost more than the large tile saves.
-static bool use_pp(int M, int N, int K) {
-  if (M < 256 || N < 256 || K < 512) return false;
-  const int units = gemm_large_tiles(M, N), rounds = (units + 255) / 256;
-  const double fill = (double)units / (256.0 * rounds);
-  return fill >= 0.62;
+// persistent blocks on tiles of 256 x 256 and 128 x 256 (gemm_large.h); false when the operands do not meet
+// its requirements
+bool launch_bgemm_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+bool launch_bgemm_large128(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+static int tiles128(int M, int N) { return ((M + 127) / 128) * ((N + 255) / 256); }
+static int rounds(int tiles) { return (tiles + 255) / 256; }
+// Rows of the tiles (256 or 128) of a forward or data-gradient product, or 0: the kernels with 128 x 128.
+// One block per compute unit, so the time is a whole number of rounds of 256 tiles; a round of the
+// smaller tiles takes about two thirds of one of the larger (0.95 against 1.5 us per 64 reduction indices,
+// and 6-8 us of start and store).  One round against two thirds: ahead by 20-28 % at 88-128 large tiles
+// (8192 x 768 K = 3072: 74 -> 54 us; 6352 x 1024 K = 4096: 88 -> 64), three against two (320 large tiles)
+// by 0-6 %; from there on the larger are ahead by up to a fifth.  The 128 x 128 kernels are left where a
+// second round of large tiles has just begun (264 tiles of 768 reduction indices: 40 against 43 us).
+static int large_rows(int M, int N, int K) {
+  if (M < 256 || N < 256 || K < 512) return 0;
+  const int large = gemm_large_tiles(M, N), r = rounds(large), r128 = rounds(tiles128(M, N));
+  if (large < 66 || (large > 256 && large <= 280)) return 0;
+  return 2 * r128 <= 3 * r ? 128 : 256;
 }
 
 // Data-gradient products with a very long reduction and few output tiles (the head's, whose
@@ -414,15 +418,6 @@ static int ring_variant(int M, int N) {
   if (tiles(128, 64) <= 256) return 2;
   return tiles(128, 128) <= 256 ? 3 : -1;
 }
-// Weight gradients keep the parts of their reduction (gemm_splits) and with them the number of units.
-// The 128 x 128 ring is ahead where the units fill one round nearly (256 at 1024 and 4096 x 1024:
-// 249 -> 222 us at K = 20480, 37 -> 31 at K = 2000) and behind where they start a second one (288 at
-// 768 x 3072: 57 -> 66 us at K = 6400), which blocks that share a compute unit absorb, or where the
-// reduction is short.
-static bool ring_wgrad(int M, int N, int K, int splits) {
-  const int units = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * splits;
-  return K >= 1024 && units <= 256 && units >= 192;
-}
 
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
@@ -472,7 +467,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
     if (sp > 1 && !(g.workspace && aligned16(g.workspace) && g.workspace_bytes >= (size_t)sp * g.M * g.N * 4)) sp = 1;
     cut(sp, 64);
     p.partial = sp > 1 ? (float*)g.workspace : nullptr;
-    if (launch_bgemm_pp(p, st, g.time_start, sp > 1 ? nullptr : g.time_stop)) {
+    if (launch_bgemm_large(p, st, g.time_start, sp > 1 ? nullptr : g.time_stop)) {
       if (sp > 1) launch_splitk_reduce(p, st, g.time_stop);
       return true;
     }
@@ -482,6 +477,18 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   {
     const int sp = splits_for(gemm_splits(g.M, g.N));
     if (sp > 1) { cut(sp, 32); p.partial = (float*)g.workspace; }
+  }
+  // Weight gradients: 128 x 256 tiles, also where they leave compute units idle (128 units at 4096 x 1024,
+  // whose reduction is not cut; 144 at 3072 x 768 in two parts): alone that is slower (16384 x 4096 x 1024:
+  // 166 us on 256 units of 128 x 128, 250 on 128), but a unit's time is a quarter less and the other
+  // stream's kernels have the rest.  Iterations against the 128 x 128 kernels: bert_large_stress 256 x 512
+  // 1.06 of the speed, bert_large 64 x 320 1.03, 16 x 256 1.02, 16 x 100 1.06, bert_base 32 x 512 1.01, 32 x 200
+  // 1.01, 32 x 88 1.02, padded 12 x 397 1.02, gpt2_medium 16 x 1024 1.00, 4 x 400 1.05, 12 x 400 0.99.
+  // Same parts and order of every sum, so the same bits.
+  if (!g.a_kmajor && !g.b_kmajor && rule_k >= 1024 && g.M >= 256 && g.N >= 256 && tiles128(g.M, g.N) <= 256 &&
+      launch_bgemm_large128(p, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
+    if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
+    return true;
   }
   // Forward and data-gradient products that one round of smaller tiles covers.  Judged by the whole
   // batch's rows, as in the products above, not by those of a half or of a batch without its padding:
@@ -493,14 +500,12 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
     const int which = ring_variant(rule_rows, g.N);
     if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
   }
-  // weight gradients of exactly one round
-  if (!g.a_kmajor && !g.b_kmajor && ring_wgrad(g.M, g.N, rule_k, p.splits) &&
-      launch_bgemm_ring(p, 3, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
-    if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
-    return true;
+  // large tiles (a choice made from the shape alone)
+  if (p.splits == 1) {
+    const int rows = large_rows(g.M, g.N, g.K);
+    if (rows == 256 && launch_bgemm_large(p, st, g.time_start, g.time_stop)) return true;
+    if (rows == 128 && launch_bgemm_large128(p, st, g.time_start, g.time_stop)) return true;
   }
-  // large tiles where their rounds are well filled (a choice made from the shape alone)
-  if (p.splits == 1 && use_pp(g.M, g.N, g.K) && launch_bgemm_pp(p, st, g.time_start, g.time_stop)) return true;
   // B m-major (weight gradients, data gradients): the direct-to-LDS pipeline measures faster there;
   // the register-staged kernel below is ahead when both operands are k-major (forward)
   if (!g.b_kmajor && launch_bgemm_dma(p, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {

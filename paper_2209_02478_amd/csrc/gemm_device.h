@@ -132,11 +132,9 @@ __device__ __forceinline__ void load_resid(const GemmDev& p, int m0w, int n0w, i
 
 // m0w, n0w: first row / column of this wave's 64 x 64 part; wstage: 16 KB / HALVES of LDS that only
 // this wave uses from here on (HALVES == 2: the two 32-column halves take turns in 8 KB); r: load_resid's.
-// AHEAD: whether residuals were loaded ahead.  staged_all: called once the accumulators are in LDS and
-// their registers free.
-template <int HALVES, bool AHEAD = true, typename F>
+template <int HALVES>
 __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)[2][2], int m0w, int n0w, int lane,
-                                           float* wstage, const u32x4 (&r)[8], F&& staged_all) {
+                                           float* wstage, const u32x4 (&r)[8]) {
   typedef Walk<HALVES> W;
   constexpr int COLS = W::COLS, CHUNKS = COLS / 4;              // staged columns, float4 chunks
 #pragma unroll
@@ -154,7 +152,6 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
               make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
         }
     __builtin_amdgcn_wave_barrier();
-    if (h == HALVES - 1) staged_all();
     if (!p.vec) {                                               // unaligned operands: one element at a time
       for (int idx = lane; idx < 64 * COLS; idx += 64) {
         const int row = idx / COLS, col = idx % COLS;
@@ -171,7 +168,7 @@ __device__ __forceinline__ void store_tile(const GemmDev& p, const f32x16 (&acc)
       const float4 hi = *(const float4*)&wstage[row * COLS + (((c0 + 1) ^ (row & (CHUNKS - 1))) << 2)];
       v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
     };
-    if (AHEAD && resid_ahead(p)) {
+    if (resid_ahead(p)) {
 #pragma unroll
       for (int it = 0; it < W::STEPS; ++it) {
         const int row = W::row(it, lane), m = m0w + row;

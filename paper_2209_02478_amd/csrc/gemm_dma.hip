@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256, 3) void bgemm_dma_kernel(GemmDev p, int tiles_
   u32x4 resid[8];
   load_resid<2>(q, m0 + wm * 64, n0 + wn * 64, lane, resid);
   __syncthreads();                                    // the operand tiles are dead
-  store_tile<2>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, wstage, resid, [] {});
+  store_tile<2>(q, acc, m0 + wm * 64, n0 + wn * 64, lane, wstage, resid);
 }
 
 template <bool AK, bool BKM>

@@ -1,0 +1,580 @@
+// bf16 GEMM, large block tiles walked by persistent blocks.
+//
+// C[M,N] = sum_k A(m,k) B(n,k).  One block of 8 waves per compute unit takes tile after tile of 256 x 256
+// (FM = 8) or 128 x 256 (FM = 4); a wave owns 16 * FM x 64 of it as MFMA tiles of 16 x 16 x 32.  Why these
+// sizes on gfx950: a compute unit draws about 54 bytes per clock from the L2, a 128 x 128 tile needs
+// 64 at full matrix rate, 128 x 256 needs 48, 256 x 256 needs 32; and under matrix load the clock follows
+// the power drawn (2.4 GHz with the matrix cores idle, 1.7 in the loop below with all units at it), so
+// bytes moved per MFMA cost time even where they are hidden.  16 x 16 x 32 draws a tenth less than
+// 32 x 32 x 16 (2.03 against 1.85 PFLOP/s in a loop of MFMAs alone on N(0,0.25) operands) and gives the
+// same bits as two of those in a row, so the 128 x 128 kernels and these agree bit for bit.
+//
+// Operand tiles (64 reduction indices) go global -> LDS directly into rings that fill the 160 KB: FM = 8
+// three slots of A and two of B, FM = 4 four and three.  A is requested NB k tiles ahead half a turn
+// earlier than B.  A load is one buffer instruction with a per-lane offset that is fixed for the tile
+// and a scalar base that moves along k: issuing it costs two instructions, and the loop has no branch
+// around it (a wave that has to branch around its loads loses about 60 clocks for each).  The loads
+// run through the tile boundary: while a tile's last MFMAs and its store run, the first k tiles of the
+// block's next one are on their way, so only a block's first tile waits for memory.
+//
+// The eight waves run freely, two on each SIMD, and meet once per k tile; a fragment's register takes
+// the next half's as soon as the MFMAs that use it are issued.  K tile t, a wave's view:
+//     half 0 (32 indices)         :  MFMAs; reads of half 1; loads of A tile t + NB (slot of tile t - 1)
+//     half 1, the first quarter   :  MFMAs
+//     own loads of tile t + 1 have landed, own reads of tile t are done: all waves meet
+//     half 1, the rest            :  MFMAs; reads of tile t + 1, half 0; loads of B tile t + NB (slot of tile t)
+// FM = 8: 2450 clocks per k tile with everything in the L2, of which MFMAs alone take 2048, the meeting
+// about 200 and the fragment reads 100.
+//
+// A tile leaves the registers without LDS: the MFMA's operand roles are swapped (rows of B feed its
+// A side), so a lane holds 4 consecutive columns of one row, and a row's 16 columns lie in the lanes l,
+// l + 16, l + 32, l + 48.  One exchange between neighbouring groups of 16 lanes makes that 8 columns
+// (16 bytes of bf16), one between the halves of a group whole 128-byte lines per store instruction.
+// 12600 clocks a tile through LDS -> 3300.
+//
+// Measured with rotating operands on one box, against the tiles of 256 x 256 in 32 x 32 x 16 MFMAs with a
+// block per tile that this replaced (us): 65536 x 3072, K = 1024, bf16 401 -> 350; 65536 x 4096, K = 1024,
+// with GELU 712 -> 631; 65536 x 1024, K = 4096, fp32 with residual 481 -> 430; data gradients 65536 x 4096
+// K = 1024 523 -> 466, 65536 x 1024 K = 4096 471 -> 446.  1.45 us per 64 reduction indices, bound by power;
+// between tiles 5-9 us, bound by the stores' way into the L2 (starting some compute units or XCDs half a
+// tile later, or streaming stores, changed nothing).
+//
+// LDS layouts (16-byte chunks permuted so that fragment reads are conflict-free although a direct
+// load can only write 1 KB contiguously):
+//   k-major tile [rows][64 k], 128-byte rows : chunk kc of row r sits at kc ^ ((r >> 1) & 7)
+//   m-major tile [64 k][rows]               : chunk mc of k row q sits at mc ^ (4 * (q & 3) + 2 * ((q >> 3) & 1))
+// k-major fragments are one 16-byte read, m-major fragments two transposing 8-byte reads.
+// The reduction order over k is fixed by the shape alone (results reproducible bit for bit).
+#pragma once
+#include "gemm_device.h"
+
+#include <hip/hip_ext.h>
+
+#include <type_traits>
+
+namespace mk {
+
+namespace large {
+
+constexpr int LBN = 256;                         // tile columns
+constexpr int LBK = 64;                          // reduction indices per k tile
+constexpr int LGROUP_M = 4;                      // row panels per tile group (L2 reuse)
+constexpr int FN = 4;                            // 16 x 16 tiles of a wave across; down: FM = 8 or 4
+
+// Sizes of a variant: FM blocks of 16 rows per wave, tiles of 32 * FM rows.
+template <int FM>
+struct Sizes {
+  static constexpr int BM = 32 * FM;
+  static constexpr int NB = FM == 8 ? 2 : 3, NA = NB + 1;             // ring slots of B and A: 160 KB
+  static constexpr int A_TILE = BM * LBK, B_TILE = LBN * LBK;         // elements
+  static constexpr int A_LOADS = BM / 64, B_LOADS = LBN / 64;         // 1 KB direct loads per wave and operand tile
+  static constexpr int SMEM = (NA * A_TILE + NB * B_TILE) * 2;
+  static constexpr int MEET = FM / 4;                                 // rows of the second half multiplied before the waves meet
+  // loads younger than those of the next k tile when the waves meet: NB - 2 whole k tiles and an A tile
+  static constexpr int YOUNGER = (NB - 2) * (A_LOADS + B_LOADS) + A_LOADS;
+  static constexpr int STORES = 2 * FM;                               // 16-byte stores of a bf16 tile per lane
+};
+
+// Offsets from a buffer's size on lie outside: such a lane's 16 bytes of LDS are written with zeros.  No
+// buffer is larger than this.
+constexpr uint32_t kOutside = 0x80000000u;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void lds_void_l;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
+
+// One wave-level direct load: lane i's 16 bytes at base + offset land at lds + 16 * i.  Inline assembly,
+// so the compiler does not track it: the waits are placed by hand in the loop.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
+__device__ __forceinline__ void l_direct_load(uint64_t base, uint32_t bytes, uint32_t offset, uint32_t lds_byte_address) {
+  const u32x4 r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)base), (uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};          // raw buffer
+  asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(offset), "s"(r), "s"(lds_byte_address) : "memory", "m0");
+}
+// an address that is the same in all lanes, in scalar registers
+__device__ __forceinline__ uint64_t l_uniform(const void* p) {
+  const uint64_t a = (uint64_t)p;
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32;
+}
+__device__ __forceinline__ uint32_t l_lds_address(const void* p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_l*)p);
+}
+#pragma clang diagnostic pop
+
+// s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14)
+constexpr int kLdsDone = 15 | (7 << 4) | (0 << 8) | (3 << 14);      // LDS operations done, vector memory untouched
+constexpr int in_flight(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }   // at most n vector memory operations
+
+__device__ __forceinline__ void l_meet() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// R: rows of the operand's tiles
+template <bool KM, int R>
+struct LTileOf {
+  // Direct load j of a wave (a wave's loads follow each other, an even number or two) brings 64 chunks.
+  // Byte offset of the lane's from the tile's first element, j = 0 or 1; that of j + 2 is this and 2 * two(ld).
+  static __device__ __forceinline__ uint32_t src(int64_t ld, int rows, int j, int lane) {
+    if (KM) {
+      const int r = 8 * j + (lane >> 3), kc = (lane & 7) ^ ((r >> 1) & 7);
+      return (uint32_t)(r * (int)ld + kc * 8) * 2u;               // rows outside the matrix: behind the buffer's end
+    }
+    constexpr int RC = R / 8;                                     // chunks per k row
+    const int q = j * (64 / RC) + lane / RC, mc = (lane % RC) ^ (4 * (q & 3) + 2 * ((q >> 3) & 1));
+    return mc * 8 < rows ? (uint32_t)(q * (int)ld + mc * 8) * 2u : kOutside;
+  }
+  static __device__ __forceinline__ uint32_t two(int64_t ld) { return (uint32_t)(KM ? 16 : 2 * 64 / (R / 8)) * (uint32_t)ld * 2u; }
+  // size of the buffer that starts at the tile's first row and this k tile: the rows that exist end it
+  static __device__ __forceinline__ uint32_t bytes(int64_t ld, int rows) { return KM ? (uint32_t)min(rows, R) * (uint32_t)ld * 2u : kOutside; }
+  // whether that chunk lies behind the last of `left` reduction indices
+  static __device__ __forceinline__ bool behind(int left, int j, int lane) {
+    if (KM) return (((lane & 7) ^ ((4 * j + (lane >> 4)) & 7)) << 3) >= left;
+    return lane / (R / 8) >= left - j * (64 / (R / 8));
+  }
+  // this lane's place in the fragments of the 16-row blocks from first_block on (a multiple of 4)
+  int at[2];
+  __device__ __forceinline__ void init(int first_block, int lane) {
+    if (KM) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        at[h] = (first_block * 16 + (lane & 15)) * LBK + (((4 * h + (lane >> 4)) ^ ((lane >> 1) & 7)) << 3);
+    } else {
+      const int g = lane >> 4, kq = (lane & 15) >> 2;
+      at[0] = (8 * g + kq) * R + (((2 * first_block) ^ (((lane & 3) >> 1) + 4 * kq + 2 * (g & 1))) << 3) + (lane & 1) * 4;
+      at[1] = 0;
+    }
+  }
+  // fragment of block i, half h (both compile-time after unrolling): row lane % 16, indices 8 * (lane / 16) .. +7
+  __device__ __forceinline__ bf16x8 read(const bf16_t* ring, int slot, int i, int h) const {
+    if (KM) return *(const bf16x8*)(ring + slot + at[h] + i * 16 * LBK);
+    const bf16_t* p = ring + ((slot + at[0]) ^ (i * 16)) + h * 32 * R;      // block i: bits 1 .. 3 of the chunk number
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_l*)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_l*)(p + 4 * R));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
+
+// exchange of the odd groups of 16 lanes of a with the even ones of b: turns 4 + 4 columns of two column
+// tiles into 8 of one, and back
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  const auto s = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = s[0]; b = s[1];
+}
+
+// exchange between the halves of each group of 16 lanes: a's lanes 8 .. 15 with b's lanes 0 .. 7
+__device__ __forceinline__ void swap8(uint32_t& a, uint32_t& b) {
+  const uint32_t a0 = a;
+  a = __builtin_amdgcn_update_dpp(a, b, 0x128, 0xF, 0xC, false);         // row_ror:8 into lanes 8 .. 15
+  b = __builtin_amdgcn_update_dpp(b, a0, 0x128, 0xF, 0x3, false);        // into lanes 0 .. 7
+}
+
+}  // namespace large
+
+// GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH); a product without it stores bf16 or fp32,
+// with or without bias and residual.  p.vec is given.
+template <int FM, bool AK, bool BKM, bool KTAIL, int GE>
+__global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd) {
+  using namespace large;
+  typedef Sizes<FM> Z;
+  typedef LTileOf<AK, Z::BM> TA;
+  typedef LTileOf<BKM, LBN> TB;
+  constexpr int LA = Z::A_LOADS, LB = Z::B_LOADS, MEET = Z::MEET;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char l_smem[];
+  bf16_t* const ring = (bf16_t*)l_smem;
+  bf16_t* const ring_b = ring + Z::NA * Z::A_TILE;
+  // Block ids go to the 8 XCDs in turn: XCD x gets the run of per_xcd units from x * per_xcd on, its
+  // blocks (32, one per compute unit) every 32nd of them.  Units run part by part (all tiles of the
+  // first k range, then of the second, ...): a run then shares one k range of both operands in the L2.
+  const int stride = gridDim.x >> 3;
+  int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  const int u_end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, total);
+  if (unit >= u_end) return;
+  const int n_tiles = total / p.splits, tiles_m = (p.M + Z::BM - 1) / Z::BM;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: address arithmetic on it stays scalar
+  const int wm = wave >> 2, wn = wave & 3;
+  constexpr bool PARTS = !BKM, WG = !AK && !BKM;                  // reduction cut in parts; weight gradients: row sums, fp32
+
+  // ---- the loads' position: unit, its tile, the k tile
+  struct Place { int m0, n0, split; } cur, ahead;
+  int c_unit = unit, c_left, c_k;                                 // k tiles left; reduction indices left (KTAIL)
+  uint64_t base_a, base_b;
+  int64_t step_a = AK ? LBK * 2 : (int64_t)LBK * 2 * p.lda, step_b = BKM ? LBK * 2 : (int64_t)LBK * 2 * p.ldb;
+  uint32_t off_a[2], off_b[2], bytes_a, bytes_b;
+  auto enter = [&]() __attribute__((always_inline)) {                                            // first k tile of unit c_unit
+    const int split = PARTS ? c_unit / n_tiles : 0, t = c_unit - split * n_tiles;
+    const int group = t / (LGROUP_M * tiles_n), first_m = group * LGROUP_M;
+    const int gsize = min(tiles_m - first_m, LGROUP_M);
+    const int in_group = t - group * LGROUP_M * tiles_n;
+    ahead = {(first_m + in_group % gsize) * Z::BM, in_group / gsize * LBN, split};
+    const int k0 = p.kb[split];
+    c_k = p.kb[split + 1] - k0;
+    c_left = (c_k + LBK - 1) / LBK;
+    base_a = l_uniform((const bf16_t*)p.A + (AK ? (int64_t)ahead.m0 * p.lda + k0 : (int64_t)k0 * p.lda + ahead.m0));
+    base_b = l_uniform((const bf16_t*)p.B + (BKM ? (int64_t)ahead.n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + ahead.n0));
+    bytes_a = TA::bytes(p.lda, p.M - ahead.m0);
+    bytes_b = TB::bytes(p.ldb, p.N - ahead.n0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      off_a[j] = TA::src(p.lda, p.M - ahead.m0, wave * LA + j, lane);
+      off_b[j] = TB::src(p.ldb, p.N - ahead.n0, wave * LB + j, lane);
+    }
+  };
+  enter();
+  cur = ahead;
+  const uint32_t lds_a = l_lds_address(ring) + (uint32_t)wave * LA * 1024u;
+  const uint32_t lds_b = l_lds_address(ring_b) + (uint32_t)wave * LB * 1024u;
+  uint32_t fill_a = 0, fill_b = 0;                                // slots to fill, in bytes
+  const uint32_t two_a = TA::two(p.lda), two_b = TB::two(p.ldb);
+  auto load_a = [&](int j) __attribute__((always_inline)) {
+    const uint32_t at = off_a[j & 1] + (j >> 1) * two_a;
+    l_direct_load(base_a, bytes_a, KTAIL && TA::behind(c_k, wave * LA + j, lane) ? kOutside : at, lds_a + fill_a + j * 1024u);
+  };
+  auto load_b = [&](int j) __attribute__((always_inline)) {
+    const uint32_t at = off_b[j & 1] + (j >> 1) * two_b;
+    l_direct_load(base_b, bytes_b, KTAIL && TB::behind(c_k, wave * LB + j, lane) ? kOutside : at, lds_b + fill_b + j * 1024u);
+  };
+  // On to the next k tile, or the next unit's first.  Behind the block's last the same k tile is
+  // requested again, into slots that are not read any more.
+  auto advance = [&]() __attribute__((always_inline)) {
+    fill_a = fill_a == (Z::NA - 1) * Z::A_TILE * 2u ? 0 : fill_a + Z::A_TILE * 2u;
+    fill_b = fill_b == (Z::NB - 1) * Z::B_TILE * 2u ? 0 : fill_b + Z::B_TILE * 2u;
+    if (--c_left > 0) {
+      base_a += step_a; base_b += step_b;
+      c_k -= KTAIL ? LBK : 0;
+    } else if (c_unit + stride < u_end) {
+      c_unit += stride;
+      enter();
+    } else {
+      c_left = 1 << 30; step_a = step_b = 0; c_k = 1 << 30;
+      // c_k: with step 0 the k tile stays the unit's last; what lies behind its end is not looked at
+      if (KTAIL) c_k = 0;
+    }
+  };
+
+  // ---- fragments of the k tile being multiplied
+  TA fa;
+  TB fb;
+  fa.init(wm * FM, lane);
+  fb.init(wn * FN, lane);
+  int slot_a = 0, slot_b = 0;                                     // in elements
+  bf16x8 af[FM], bfr[2][FN];
+  auto read_a = [&](int i, int h) __attribute__((always_inline)) { af[i] = fa.read(ring, slot_a, i, h); };
+  auto read_b = [&](int j, int h) __attribute__((always_inline)) { bfr[h][j] = fb.read(ring_b, slot_b, j, h); };
+  f32x4 acc[FM][FN];
+  // Row sums of A (bias gradients): a wave owns FM / 2 chunks of 8 rows, a lane one of them and every 16th
+  // reduction index (the order of these sums is that of the other kernels, and leaving out 16 rows of zeros
+  // does not change it)
+  constexpr int CPW = FM / 2;
+  const int sum_pos = (lane / CPW) & 15, sum_chunk = CPW * wave + lane % CPW;
+  const int sum_at = sum_pos * Z::BM + ((sum_chunk ^ (4 * (sum_pos & 3) + 2 * ((sum_pos >> 3) & 1))) << 3);
+  float rs[8];
+  int stored = 0, young = 1;                                      // stores of the tile before, and for how many turns they are younger than the loads waited for
+
+  auto k_tile = [&](auto first_, auto sums_) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first_)::value, SUMS = decltype(sums_)::value;
+    auto row = [&](int i, int h) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[h][j], af[i], FIRST && h == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
+    };
+    bf16x8 sf;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      if (SUMS && i % (FM / 4) == 0) sf = *(const bf16x8*)(ring + slot_a + sum_at + i / (FM / 4) * 16 * Z::BM);
+      if (SUMS && i % (FM / 4) == FM / 4 - 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rs[e] += (float)sf[e];
+      row(i, 0);
+      read_a(i, 1);
+      if (i < FN) read_b(i, 1);
+      if (i % (FM / LA) == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(i / (FM / LA));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MEET; ++i) row(i, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kLdsDone);
+    // all but the loads of later k tiles and, in a tile's first turns, the stores of the tile before
+    if (stored == 2 * Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER + 2 * Z::STORES));
+    else if (stored == Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER + Z::STORES));
+    else __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER));
+    if (--young == 0) stored = 0;
+    l_meet();
+    slot_a = slot_a == (Z::NA - 1) * Z::A_TILE ? 0 : slot_a + Z::A_TILE;
+    slot_b = slot_b == (Z::NB - 1) * Z::B_TILE ? 0 : slot_b + Z::B_TILE;
+#pragma unroll
+    for (int i = 0; i < MEET; ++i) read_a(i, 0);
+#pragma unroll
+    for (int i = MEET; i < FM; ++i) {
+      row(i, 1);
+      read_a(i, 0);
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        if (j * (FM - MEET) / FN == i - MEET) {
+          read_b(j, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          load_b(j);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    advance();
+  };
+
+  // ---- a finished tile
+  // C and its leading dimension are the workspace's where the reduction is cut in parts
+  auto store = [&](auto edge_, auto f32_, auto resid_, void* C, int64_t ldc, bool bias) __attribute__((always_inline)) {
+    constexpr bool EDGE = decltype(edge_)::value, C32 = decltype(f32_)::value, RESID = decltype(resid_)::value;
+    // from a copy of the lane that the compiler takes for new: what the store computes from it would be held
+    // through the loop, which has no registers left
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int lr = l & 15, lq = l >> 4;
+    const int nw = cur.n0 + wn * 64, mw = cur.m0 + wm * FM * 16 + lr;
+    const int n4 = nw + 4 * lq, n8 = nw + (lq & 1) * 16 + (lq >> 1) * 8;      // a lane's first column in tile 0; in pair 0 after the exchange
+    u32x2 cb[FN];                                                 // bias of the lane's columns (the sums are never -0: adding 0 is no change)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      cb[j] = u32x2{0u, 0u};
+      const int n = n4 + j * 16;
+      if (bias) {
+        if (!EDGE || n + 4 <= p.N) cb[j] = *(const u32x2*)((const bf16_t*)p.bias + n);
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < p.N) cb[j][e >> 1] |= (uint32_t)((const bf16_t*)p.bias)[n + e] << (16 * (e & 1));
+      }
+    }
+    constexpr int DEPTH = FM < 4 ? FM : 4;                                      // rows of residuals requested ahead
+    u32x4 r[FM][FN / 2];                                          // in the order of the 16-byte stores
+    auto load = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int jp = 0; jp < FN / 2; ++jp) {
+        const int m = mw + i * 16, n = n8 + jp * 32;
+        const bf16_t* at = (const bf16_t*)p.resid + (int64_t)m * p.ldr + n;
+        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][jp] = *(const u32x4*)at;
+        else {
+          u32x4 w = {0u, 0u, 0u, 0u};
+          if (m < p.M)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (n + e < p.N) w[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
+          r[i][jp] = w;
+        }
+      }
+    };
+    // 16 rows of two column tiles as fp32; of all four as bf16.  Lanes 0 .. 7 of each 16 end up with a row
+    // of the first 8, lanes 8 .. 15 with the same row's other half: whole 128-byte lines per store.
+    const int up = lr >> 3;
+    auto put_f32 = [&](float* c, int i, int jp, const float (&x)[4], const float (&y)[4]) __attribute__((always_inline)) {
+      u32x4 a, b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { uint32_t s = __float_as_uint(x[e]), t = __float_as_uint(y[e]); swap8(s, t); a[e] = s; b[e] = t; }
+      const int n = n4 + jp * 32 + up * 16;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int m = mw + i * 16 + s * 8 - up * 8;
+        const u32x4 w = s ? b : a;
+        float* out = c + (int64_t)m * ldc + n;
+        if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4*)out = w;
+        else if (m < p.M)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < p.N) out[e] = __uint_as_float(w[e]);
+      }
+    };
+    auto put_bf16 = [&](bf16_t* c, int i, const float (&v)[4][4]) __attribute__((always_inline)) {
+      u32x4 ch[2];
+#pragma unroll
+      for (int jp = 0; jp < 2; ++jp) {
+        const float (&x)[4] = v[2 * jp], (&y)[4] = v[2 * jp + 1];
+        uint32_t x0 = pack_bf16x2(x[0], x[1]), x1 = pack_bf16x2(x[2], x[3]), y0 = pack_bf16x2(y[0], y[1]), y1 = pack_bf16x2(y[2], y[3]);
+        swap16(x0, y0); swap16(x1, y1);
+        ch[jp] = u32x4{x0, x1, y0, y1};
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { uint32_t s = ch[0][e], t = ch[1][e]; swap8(s, t); ch[0][e] = s; ch[1][e] = t; }
+      const int n = n8 + up * 32;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int m = mw + i * 16 + s * 8 - up * 8;
+        bf16_t* out = c + (int64_t)m * ldc + n;
+        if (!EDGE || (m < p.M && n + 8 <= p.N)) *(u32x4*)out = ch[s];
+        else if (m < p.M)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < p.N) out[e] = (bf16_t)(ch[s][e >> 1] >> (16 * (e & 1)));
+      }
+    };
+    if (RESID)
+#pragma unroll
+      for (int i = 0; i < DEPTH; ++i) load(i);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      float v[FN][4];
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        v[j][0] = acc[i][j][0] + __uint_as_float(cb[j][0] << 16);
+        v[j][1] = acc[i][j][1] + __uint_as_float(cb[j][0] & 0xFFFF0000u);
+        v[j][2] = acc[i][j][2] + __uint_as_float(cb[j][1] << 16);
+        v[j][3] = acc[i][j][3] + __uint_as_float(cb[j][1] & 0xFFFF0000u);
+      }
+      if (RESID) {
+#pragma unroll
+        for (int jp = 0; jp < FN / 2; ++jp) {
+          uint32_t w[2][2] = {{r[i][jp][0], r[i][jp][1]}, {r[i][jp][2], r[i][jp][3]}};
+          swap16(w[0][0], w[1][0]); swap16(w[0][1], w[1][1]);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            float (&x)[4] = v[2 * jp + s];
+            x[0] += __uint_as_float(w[s][0] << 16); x[1] += __uint_as_float(w[s][0] & 0xFFFF0000u);
+            x[2] += __uint_as_float(w[s][1] << 16); x[3] += __uint_as_float(w[s][1] & 0xFFFF0000u);
+          }
+        }
+      }
+      if (C32) {
+        put_f32((float*)C, i, 0, v[0], v[1]);
+        put_f32((float*)C, i, 1, v[2], v[3]);
+      } else {
+        put_bf16((bf16_t*)C, i, v);
+        if (GE != GELU_NONE) {
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[j][e] = GE == GELU_ERF ? gelu_erf_bf16(v[j][e]) : gelu_tanh_bf16(v[j][e]);
+          put_bf16((bf16_t*)p.gelu_out, i, v);
+        }
+      }
+      if (RESID && i + DEPTH < FM) load(i + DEPTH);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    stored = EDGE ? 0 : (GE != GELU_NONE || C32) ? 2 * Z::STORES : Z::STORES;
+    young = Z::NB - 1;
+  };
+
+  // ---- the block's tiles
+#pragma unroll
+  for (int t = 0; t < Z::NB; ++t) {
+#pragma unroll
+    for (int j = 0; j < LA; ++j) load_a(j);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) load_b(j);
+    advance();
+  }
+  __builtin_amdgcn_s_waitcnt(in_flight((Z::NB - 1) * (LA + LB)));
+  l_meet();
+  typedef std::true_type T;
+  typedef std::false_type F;
+  for (;;) {
+    // (read again where the tile before has read them ahead: kept through its store they cost registers)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) read_b(j, 0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) read_a(i, 0);
+    const int nk = (p.kb[cur.split + 1] - p.kb[cur.split] + LBK - 1) / LBK;
+    // raw fp32 tile and row sums of this k range, as a plain matrix [M][N] in the workspace; a
+    // second kernel adds the parts in order
+    const bool part = PARTS && p.splits > 1;
+    float* const rowsum = part ? p.partial + (int64_t)p.splits * p.M * p.N + (int64_t)cur.split * p.M : p.a_rowsum;
+    void* const C = part ? (void*)(p.partial + (int64_t)cur.split * p.M * p.N) : p.C;
+    const int64_t ldc = part ? p.N : p.ldc;
+    const bool c_f32 = part || p.c_f32;
+    if (WG && p.a_rowsum && cur.n0 == 0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rs[e] = 0.f;
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < nk; ++kt) k_tile(F(), T());
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float s = 0.f;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) s += __shfl(rs[e], g * CPW + lane % CPW, 64);
+        const int m = cur.m0 + sum_chunk * 8 + e;
+        if (lane < CPW && m < p.M) rowsum[m] = s;
+      }
+    } else {
+      k_tile(T(), F());
+      for (int kt = 1; kt < nk; ++kt) k_tile(F(), F());
+    }
+    const bool inside = cur.m0 + Z::BM <= p.M && cur.n0 + LBN <= p.N, bias = !WG && p.bias, resid = !WG && p.resid;
+    auto store_as = [&](auto f32_, auto resid_) __attribute__((always_inline)) {
+      if (inside) store(F(), f32_, resid_, C, ldc, bias);
+      else store(T(), f32_, resid_, C, ldc, bias);
+    };
+    if (GE != GELU_NONE) store_as(F(), F());
+    else if (WG) store_as(T(), F());
+    else if (c_f32 && resid) store_as(T(), T());
+    else if (c_f32) store_as(T(), F());
+    else if (resid) store_as(F(), T());
+    else store_as(F(), F());
+    unit += stride;
+    if (unit >= u_end) break;
+    cur = ahead;
+  }
+  __builtin_amdgcn_s_waitcnt(in_flight(0));           // no direct load may land in LDS that is another block's by then
+}
+
+template <int FM, bool AK, bool BKM, int GE>
+void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  static const bool configured = [] {
+    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, false, GE>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
+    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, true, GE>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
+    return true;
+  }();
+  (void)configured;
+  constexpr int BM = large::Sizes<FM>::BM;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + large::LBN - 1) / large::LBN;
+  const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
+  const dim3 grid(8 * (per < 32 ? per : 32)), block(512);
+  bool ktail = false;
+  for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % large::LBK != 0;
+  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+}
+
+// Requirements: 16-byte stores (p.vec); K % 8 == 0 when an operand is k-major (or zeros vouched for
+// behind a k-major A's last column, with B m-major); the leading dimension of an m-major operand
+// covers its row count rounded up to 8; both operands
+// m-major: fp32 output without bias or residual, and there alone row sums; a reduction in parts with B
+// m-major; parts of more
+// k tiles than the loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
+template <int FM>
+bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
+  if (!p.vec || (!p.a_k && p.b_k)) return false;
+  // a chunk of a k-major operand that straddles K is moved whole: allowed only where the caller
+  // vouches for zeros behind A's last column while B (m-major) reads zeros from row K on
+  if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
+  if (!p.a_k && p.lda < up8(p.M)) return false;
+  if (!p.b_k && p.ldb < up8(p.N)) return false;
+  if (p.a_k && p.a_rowsum) return false;
+  if (p.splits > 1 && (p.b_k || p.bias || p.resid)) return false;
+  if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;
+  for (int i = 0; i < p.splits; ++i)
+    if (p.kb[i + 1] - p.kb[i] <= large::Sizes<FM>::NB * large::LBK) return false;
+  if (p.a_k && p.b_k) {
+    if (p.gelu == GELU_ERF) launch_large_t<FM, true, true, GELU_ERF>(p, st, t0, t1);
+    else if (p.gelu == GELU_TANH) launch_large_t<FM, true, true, GELU_TANH>(p, st, t0, t1);
+    else launch_large_t<FM, true, true, GELU_NONE>(p, st, t0, t1);
+  } else {
+    if (p.gelu || (!p.a_k && (!p.c_f32 || p.bias || p.resid))) return false;
+    if (p.a_k) launch_large_t<FM, true, false, GELU_NONE>(p, st, t0, t1);
+    else launch_large_t<FM, false, false, GELU_NONE>(p, st, t0, t1);
+  }
+  return true;
+}
+
+}  // namespace mk

@@ -193,6 +193,44 @@ def test_gemm_large_tiles(a_k, b_k):
     assert np.array_equal(host(Cf), first)
 
 
+@pytest.mark.parametrize("M,N,K", [(5000, 4872, 776),    # 400 tiles of 256 x 256 in two rounds, ragged in each dimension
+                                   (4700, 4300, 520),    # 629 tiles of 128 x 256 in three rounds
+                                   (25600, 768, 640)])   # 300 tiles, whole in each dimension
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
+def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
+    """Blocks that take several tiles, in every form of the store: the bits are those of the same rows
+    multiplied alone, which other kernels do (the sum of an element is one chain over k in all of them)."""
+    g = torch.Generator(device=DEV).manual_seed(M + K + 2 * a_k + b_k)
+    up = lambda v: (v + 7) // 8 * 8
+    mk = lambda r, c: (torch.randn((r, c), generator=g, device=DEV) * 0.5).to(torch.bfloat16)
+    A, B = mk(M, K) if a_k else mk(K, up(M)), mk(N, K) if b_k else mk(K, up(N))
+    bias, resid = mk(1, N)[0], mk(M, up(N))
+    rows = 256                                                  # alone: 64 x 32 or 64 x 64 tiles
+    forms = [dict(c_f32=1), dict(c_f32=1, bias=1, resid=1), dict(c_f32=0, bias=1), dict(c_f32=0, resid=1),
+             dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, gelu=2)] if a_k else [dict(c_f32=1, rowsum=1)]
+    for form in forms:
+        if form.get("gelu") and N % 8:
+            continue                                            # the other kernels take the C library's erf there
+        def product(r0, n_rows):
+            kw = {}
+            C = torch.full((n_rows, up(N)), 7.0, dtype=torch.float32 if form["c_f32"] else torch.bfloat16, device=DEV)
+            G = torch.full_like(C, 7.0) if form.get("gelu") else None
+            rs = torch.zeros(n_rows, device=DEV) if form.get("rowsum") else None
+            if form.get("bias"): kw["bias"] = bias
+            if form.get("resid"): kw.update(resid=resid[r0:], ldr=up(N))
+            if G is not None: kw.update(gelu_out=G, gelu=form["gelu"])
+            if rs is not None: kw["a_rowsum"] = rs
+            mi.mimose_op_gemm(1, A[r0:] if a_k else A[:, r0:], K if a_k else up(M), a_k, B, K if b_k else up(N), b_k, C, up(N),
+                              form["c_f32"], n_rows, N, K, **kw)
+            sync()
+            return [x for x in (C, G, rs) if x is not None]
+        whole = product(0, M)
+        assert bool((whole[0][:, N:] == 7.0).all()), "wrote outside the N columns"
+        for r0 in (0, M // 2 // 8 * 8, (M - rows) // 8 * 8):
+            for full, alone in zip(whole, product(r0, rows)):
+                assert torch.equal(full[r0:r0 + rows], alone), (form, r0)
+
+
 def test_gemm_large_tiles_split_reduction():
     """Weight-gradient shape of the fused QKV projection with a ragged reduction length cut in
     parts, row sums included, and the same bits on a second run."""
