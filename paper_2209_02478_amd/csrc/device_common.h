@@ -87,11 +87,20 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ float gelu_erf(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f));
 }
+// 1 / x for x >= 1, rounded correctly up to 2^100 (compared with the division for every float there) and 2^-100
+// from there on, infinity included: the hardware's reciprocal and one Newton step, three operations
+// where the division takes eleven (GELU over all floats: the same bits).  65536 x 4096 outputs with GELU,
+// K = 1024: 667 -> 619 us; 6400 x 3072, K = 768: 63.5 -> 58.2.
+__device__ __forceinline__ float rcp_from_1(float x) {
+  x = fminf(x, 0x1p100f);
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
 // erf by the rational approximation of Abramowitz & Stegun 7.1.26 (absolute error < 1.5e-7),
 // one exponential and one reciprocal: used where the result is rounded to bf16 anyway
 __device__ __forceinline__ float erf_as(float x) {
   const float ax = fabsf(x);
-  const float t = __frcp_rn(fmaf(0.3275911f, ax, 1.0f));
+  const float t = rcp_from_1(fmaf(0.3275911f, ax, 1.0f));
   float p = fmaf(t, 1.061405429f, -1.453152027f);
   p = fmaf(t, p, 1.421413741f);
   p = fmaf(t, p, -0.284496736f);
@@ -106,7 +115,7 @@ __device__ __forceinline__ float gelu_erf_bf16(float x) {
 __device__ __forceinline__ float gelu_tanh_bf16(float x) {
   const float c = 0.79788456080286535588f;
   const float u = c * (x + 0.044715f * x * x * x);
-  const float t = 1.0f - 2.0f * __frcp_rn(1.0f + __expf(2.0f * u));
+  const float t = 1.0f - 2.0f * rcp_from_1(1.0f + __expf(2.0f * u));
   return 0.5f * x * (1.0f + t);
 }
 __device__ __forceinline__ float gelu_tanh(float x) {
@@ -122,7 +131,7 @@ __device__ __forceinline__ float gelu_erf_grad(float x) {
 // the derivative costs one exponential and one reciprocal (used where the result is rounded to bf16)
 __device__ __forceinline__ float gelu_erf_grad_bf16(float x) {
   const float ax = fabsf(x) * 0.70710678118654752440f;
-  const float t = __frcp_rn(fmaf(0.3275911f, ax, 1.0f));
+  const float t = rcp_from_1(fmaf(0.3275911f, ax, 1.0f));
   float p = fmaf(t, 1.061405429f, -1.453152027f);
   p = fmaf(t, p, 1.421413741f);
   p = fmaf(t, p, -0.284496736f);
