@@ -26,18 +26,23 @@
 // FM = 8: 2450 clocks per k tile with everything in the L2, of which MFMAs alone take 2048, the meeting
 // about 200 and the fragment reads 100.
 //
-// A tile leaves the registers without LDS: the MFMA's operand roles are swapped (rows of B feed its
-// A side), so a lane holds 4 consecutive columns of one row, and a row's 16 columns lie in the lanes l,
-// l + 16, l + 32, l + 48.  One exchange between neighbouring groups of 16 lanes makes that 8 columns
-// (16 bytes of bf16), one between the halves of a group whole 128-byte lines per store instruction.
-// 12600 clocks a tile through LDS -> 3300.
+// A tile's store: the MFMA's operand roles are swapped (rows of B feed its A side), so a lane holds 4
+// consecutive columns of one row.  16 rows of 128 bytes at a time go through 2 KB of LDS of the wave's own
+// (the part of the free ring slot that its next loads fill) and come back with 8 lanes along each row;
+// residuals take the same way in.  Whole lines with the lanes across the rows, by exchanges between
+// lanes, leave a unit at 31 bytes per clock, along the rows at 104.  Whole launches of 262144 x 1024, K = 512,
+// the one against the other (us): bf16 312 -> 293, with residual 340 -> 331, fp32 370 -> 346, with
+// residual 442 -> 424, data gradient 298 -> 277; between tiles 8.0 -> 6.6 us in bf16, 11.9 -> 10.2 in fp32.  The
+// loads of the first turn after a store wait at its end, so that its MFMAs are not held up behind the
+// stores on their way out (bert_base 32 x 200 iterations 0.5 %, 32 x 512 1.5, bert_stages 32 x 332 1.1).
 //
 // Measured with rotating operands on one box, against the tiles of 256 x 256 in 32 x 32 x 16 MFMAs with a
 // block per tile that this replaced (us): 65536 x 3072, K = 1024, bf16 401 -> 350; 65536 x 4096, K = 1024,
 // with GELU 712 -> 631; 65536 x 1024, K = 4096, fp32 with residual 481 -> 430; data gradients 65536 x 4096
-// K = 1024 523 -> 466, 65536 x 1024 K = 4096 471 -> 446.  1.45 us per 64 reduction indices, bound by power;
-// between tiles 5-9 us, bound by the stores' way into the L2 (starting some compute units or XCDs half a
-// tile later, or streaming stores, changed nothing).
+// K = 1024 523 -> 466, 65536 x 1024 K = 4096 471 -> 446 (before the store through LDS).  1.45 us per 64
+// reduction indices, bound by power; between tiles 5-10 us, bound by the stores' way into the L2, 15 with
+// residuals or GELU (starting some compute units or XCDs half a tile later, or streaming stores, changed
+// nothing).
 //
 // LDS layouts (16-byte chunks permuted so that fragment reads are conflict-free although a direct
 // load can only write 1 KB contiguously):
@@ -161,20 +166,6 @@ struct LTileOf {
   }
 };
 
-// exchange of the odd groups of 16 lanes of a with the even ones of b: turns 4 + 4 columns of two column
-// tiles into 8 of one, and back
-__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
-  const auto s = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = s[0]; b = s[1];
-}
-
-// exchange between the halves of each group of 16 lanes: a's lanes 8 .. 15 with b's lanes 0 .. 7
-__device__ __forceinline__ void swap8(uint32_t& a, uint32_t& b) {
-  const uint32_t a0 = a;
-  a = __builtin_amdgcn_update_dpp(a, b, 0x128, 0xF, 0xC, false);         // row_ror:8 into lanes 8 .. 15
-  b = __builtin_amdgcn_update_dpp(b, a0, 0x128, 0xF, 0x3, false);        // into lanes 0 .. 7
-}
-
 }  // namespace large
 
 // GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH); a product without it stores bf16 or fp32,
@@ -295,7 +286,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       row(i, 0);
       read_a(i, 1);
       if (i < FN) read_b(i, 1);
-      if (i % (FM / LA) == 0) {
+      if (!FIRST && i % (FM / LA) == 0) {
         __builtin_amdgcn_sched_barrier(0);
         load_a(i / (FM / LA));
         __builtin_amdgcn_sched_barrier(0);
@@ -306,9 +297,10 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(kLdsDone);
     // all but the loads of later k tiles and, in a tile's first turns, the stores of the tile before
-    if (stored == 2 * Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER + 2 * Z::STORES));
-    else if (stored == Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER + Z::STORES));
-    else __builtin_amdgcn_s_waitcnt(in_flight(Z::YOUNGER));
+    constexpr int YOUNGER = Z::YOUNGER - (FIRST ? LA : 0);        // (a tile's first turn has issued none yet)
+    if (stored == 2 * Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(YOUNGER + 2 * Z::STORES));
+    else if (stored == Z::STORES) __builtin_amdgcn_s_waitcnt(in_flight(YOUNGER + Z::STORES));
+    else __builtin_amdgcn_s_waitcnt(in_flight(YOUNGER));
     if (--young == 0) stored = 0;
     l_meet();
     slot_a = slot_a == (Z::NA - 1) * Z::A_TILE ? 0 : slot_a + Z::A_TILE;
@@ -323,31 +315,40 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       for (int j = 0; j < FN; ++j)
         if (j * (FM - MEET) / FN == i - MEET) {
           read_b(j, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          load_b(j);
-          __builtin_amdgcn_sched_barrier(0);
+          if (!FIRST) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_b(j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
+    }
+    if (FIRST) {                                                  // behind the stores of the tile before
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < LA; ++j) load_a(j);
+#pragma unroll
+      for (int j = 0; j < LB; ++j) load_b(j);
+      __builtin_amdgcn_sched_barrier(0);
     }
     advance();
   };
 
   // ---- a finished tile
   // C and its leading dimension are the workspace's where the reduction is cut in parts
-  auto store = [&](auto edge_, auto f32_, auto resid_, void* C, int64_t ldc, bool bias) __attribute__((always_inline)) {
-    constexpr bool EDGE = decltype(edge_)::value, C32 = decltype(f32_)::value, RESID = decltype(resid_)::value;
+  auto store = [&](auto edge_, auto f32_, auto resid_, auto bias_, void* C, int64_t ldc) __attribute__((always_inline)) {
+    constexpr bool EDGE = decltype(edge_)::value, C32 = decltype(f32_)::value, RESID = decltype(resid_)::value, BIAS = decltype(bias_)::value;
     // from a copy of the lane that the compiler takes for new: what the store computes from it would be held
     // through the loop, which has no registers left
     int l = lane;
     asm volatile("" : "+v"(l));
-    const int lr = l & 15, lq = l >> 4;
-    const int nw = cur.n0 + wn * 64, mw = cur.m0 + wm * FM * 16 + lr;
-    const int n4 = nw + 4 * lq, n8 = nw + (lq & 1) * 16 + (lq >> 1) * 8;      // a lane's first column in tile 0; in pair 0 after the exchange
+    const int lr = l & 15, lq = l >> 4, sr = l >> 3, sc = l & 7;   // place in a fragment: row, group of 4 columns; in memory: row, 16 bytes
+    const int nw = cur.n0 + wn * 64, mw = cur.m0 + wm * FM * 16 + sr;
     u32x2 cb[FN];                                                 // bias of the lane's columns (the sums are never -0: adding 0 is no change)
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       cb[j] = u32x2{0u, 0u};
-      const int n = n4 + j * 16;
-      if (bias) {
+      const int n = nw + 4 * lq + j * 16;
+      if (BIAS && p.bias) {
         if (!EDGE || n + 4 <= p.N) cb[j] = *(const u32x2*)((const bf16_t*)p.bias + n);
         else
 #pragma unroll
@@ -355,109 +356,125 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
             if (n + e < p.N) cb[j][e >> 1] |= (uint32_t)((const bf16_t*)p.bias)[n + e] << (16 * (e & 1));
       }
     }
-    constexpr int DEPTH = FM < 4 ? FM : 4;                                      // rows of residuals requested ahead
-    u32x4 r[FM][FN / 2];                                          // in the order of the 16-byte stores
+    // From fragment order to memory order through LDS, 16 rows of 128 bytes at a time: a store then takes whole
+    // rows with the lanes along them.  The place is what this wave's own loads of A fill in the next turn: nobody
+    // reads it any more, and nothing is on its way there.  The 16-byte chunks of a row are permuted by the row.
+    unsigned char* const turn = l_smem;
+    const uint32_t own = fill_a + (uint32_t)wave * LA * 1024u;
+    const uint32_t in16 = own + lr * 128 + (((lq >> 1) ^ (lr >> 1)) << 4) + (lq & 1) * 8;      // 4 columns of bf16; column tile j: ^ 32 j
+    const uint32_t in32 = own + lr * 128 + ((lq ^ (lr >> 1)) << 4);                           // of fp32; second of two tiles: ^ 64
+    const uint32_t out = own + sr * 128 + ((sc ^ (sr >> 1)) << 4);                            // rows 8 .. 15: + 1024 and ^ 64
+    auto fence = [&]() __attribute__((always_inline)) { asm volatile("" ::: "memory"); };
+    constexpr int DEPTH = 2;                                      // rows of residuals requested ahead (three spill)
+    u32x4 r[FM][2];                                               // in memory order
+    u32x2 rf[FN];                                                 // of one row, in fragment order
     auto load = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-      for (int jp = 0; jp < FN / 2; ++jp) {
-        const int m = mw + i * 16, n = n8 + jp * 32;
+      for (int s = 0; s < 2; ++s) {
+        const int m = mw + i * 16 + s * 8, n = nw + sc * 8;
         const bf16_t* at = (const bf16_t*)p.resid + (int64_t)m * p.ldr + n;
-        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][jp] = *(const u32x4*)at;
+        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][s] = *(const u32x4*)at;
         else {
           u32x4 w = {0u, 0u, 0u, 0u};
           if (m < p.M)
 #pragma unroll
             for (int e = 0; e < 8; ++e)
               if (n + e < p.N) w[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
-          r[i][jp] = w;
+          r[i][s] = w;
         }
       }
     };
-    // 16 rows of two column tiles as fp32; of all four as bf16.  Lanes 0 .. 7 of each 16 end up with a row
-    // of the first 8, lanes 8 .. 15 with the same row's other half: whole 128-byte lines per store.
-    const int up = lr >> 3;
-    auto put_f32 = [&](float* c, int i, int jp, const float (&x)[4], const float (&y)[4]) __attribute__((always_inline)) {
-      u32x4 a, b;
+    auto spread = [&](int i) __attribute__((always_inline)) {
+      fence();
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { uint32_t s = __float_as_uint(x[e]), t = __float_as_uint(y[e]); swap8(s, t); a[e] = s; b[e] = t; }
-      const int n = n4 + jp * 32 + up * 16;
+      for (int s = 0; s < 2; ++s) *(u32x4*)(turn + ((out + s * 1024) ^ (s * 64))) = r[i][s];
+      fence();
+#pragma unroll
+      for (int j = 0; j < FN; ++j) rf[j] = *(const u32x2*)(turn + (in16 ^ (j * 32)));
+      fence();
+    };
+    // Step t (row i = t / PER of fragments; of it the left or right columns in fp32, C or the GELU output) is
+    // read back when it is written, and stored a step later
+    constexpr int PER = C32 || GE != GELU_NONE ? 2 : 1;
+    u32x4 held[2];
+    auto send = [&](int t) __attribute__((always_inline)) {
+      const int n = C32 ? nw + (t % PER) * 32 + sc * 4 : nw + sc * 8;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        const int m = mw + i * 16 + s * 8 - up * 8;
-        const u32x4 w = s ? b : a;
-        float* out = c + (int64_t)m * ldc + n;
-        if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4*)out = w;
-        else if (m < p.M)
+        const int m = mw + t / PER * 16 + s * 8;
+        if (C32) {
+          float* to = (float*)C + (int64_t)m * ldc + n;
+          if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4*)to = held[s];
+          else if (m < p.M)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (n + e < p.N) out[e] = __uint_as_float(w[e]);
+            for (int e = 0; e < 4; ++e)
+              if (n + e < p.N) to[e] = __uint_as_float(held[s][e]);
+        } else {
+          bf16_t* to = (bf16_t*)(t % PER ? p.gelu_out : C) + (int64_t)m * ldc + n;
+          if (!EDGE || (m < p.M && n + 8 <= p.N)) *(u32x4*)to = held[s];
+          else if (m < p.M)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (n + e < p.N) to[e] = (bf16_t)(held[s][e >> 1] >> (16 * (e & 1)));
+        }
       }
     };
-    auto put_bf16 = [&](bf16_t* c, int i, const float (&v)[4][4]) __attribute__((always_inline)) {
-      u32x4 ch[2];
-#pragma unroll
-      for (int jp = 0; jp < 2; ++jp) {
-        const float (&x)[4] = v[2 * jp], (&y)[4] = v[2 * jp + 1];
-        uint32_t x0 = pack_bf16x2(x[0], x[1]), x1 = pack_bf16x2(x[2], x[3]), y0 = pack_bf16x2(y[0], y[1]), y1 = pack_bf16x2(y[2], y[3]);
-        swap16(x0, y0); swap16(x1, y1);
-        ch[jp] = u32x4{x0, x1, y0, y1};
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { uint32_t s = ch[0][e], t = ch[1][e]; swap8(s, t); ch[0][e] = s; ch[1][e] = t; }
-      const int n = n8 + up * 32;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const int m = mw + i * 16 + s * 8 - up * 8;
-        bf16_t* out = c + (int64_t)m * ldc + n;
-        if (!EDGE || (m < p.M && n + 8 <= p.N)) *(u32x4*)out = ch[s];
-        else if (m < p.M)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (n + e < p.N) out[e] = (bf16_t)(ch[s][e >> 1] >> (16 * (e & 1)));
-      }
+    auto back = [&](int t) __attribute__((always_inline)) {
+      fence();
+      const u32x4 w0 = *(const u32x4*)(turn + out), w1 = *(const u32x4*)(turn + ((out + 1024) ^ 64));
+      fence();
+      if (t > 0) send(t - 1);
+      held[0] = w0; held[1] = w1;
     };
-    if (RESID)
+    auto put_bf16 = [&](int t, const f32x4 (&v)[FN]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        *(u32x2*)(turn + (in16 ^ (j * 32))) = u32x2{pack_bf16x2(v[j][0], v[j][1]), pack_bf16x2(v[j][2], v[j][3])};
+      back(t);
+    };
+    auto put_f32 = [&](int t, const f32x4& x, const f32x4& y) __attribute__((always_inline)) {
+      *(f32x4*)(turn + in32) = x;
+      *(f32x4*)(turn + (in32 ^ 64)) = y;
+      back(t);
+    };
+    if (RESID) {
 #pragma unroll
       for (int i = 0; i < DEPTH; ++i) load(i);
+      spread(0);
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      float v[FN][4];
+      f32x4 v[FN];
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
-        v[j][0] = acc[i][j][0] + __uint_as_float(cb[j][0] << 16);
-        v[j][1] = acc[i][j][1] + __uint_as_float(cb[j][0] & 0xFFFF0000u);
-        v[j][2] = acc[i][j][2] + __uint_as_float(cb[j][1] << 16);
-        v[j][3] = acc[i][j][3] + __uint_as_float(cb[j][1] & 0xFFFF0000u);
-      }
-      if (RESID) {
-#pragma unroll
-        for (int jp = 0; jp < FN / 2; ++jp) {
-          uint32_t w[2][2] = {{r[i][jp][0], r[i][jp][1]}, {r[i][jp][2], r[i][jp][3]}};
-          swap16(w[0][0], w[1][0]); swap16(w[0][1], w[1][1]);
-#pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            float (&x)[4] = v[2 * jp + s];
-            x[0] += __uint_as_float(w[s][0] << 16); x[1] += __uint_as_float(w[s][0] & 0xFFFF0000u);
-            x[2] += __uint_as_float(w[s][1] << 16); x[3] += __uint_as_float(w[s][1] & 0xFFFF0000u);
-          }
+        v[j] = acc[i][j];
+        if (BIAS) {
+          v[j][0] += __uint_as_float(cb[j][0] << 16); v[j][1] += __uint_as_float(cb[j][0] & 0xFFFF0000u);
+          v[j][2] += __uint_as_float(cb[j][1] << 16); v[j][3] += __uint_as_float(cb[j][1] & 0xFFFF0000u);
+        }
+        if (RESID) {
+          v[j][0] += __uint_as_float(rf[j][0] << 16); v[j][1] += __uint_as_float(rf[j][0] & 0xFFFF0000u);
+          v[j][2] += __uint_as_float(rf[j][1] << 16); v[j][3] += __uint_as_float(rf[j][1] & 0xFFFF0000u);
         }
       }
       if (C32) {
-        put_f32((float*)C, i, 0, v[0], v[1]);
-        put_f32((float*)C, i, 1, v[2], v[3]);
+        put_f32(2 * i, v[0], v[1]);
+        put_f32(2 * i + 1, v[2], v[3]);
       } else {
-        put_bf16((bf16_t*)C, i, v);
+        put_bf16(PER * i, v);
         if (GE != GELU_NONE) {
 #pragma unroll
           for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[j][e] = GE == GELU_ERF ? gelu_erf_bf16(v[j][e]) : gelu_tanh_bf16(v[j][e]);
-          put_bf16((bf16_t*)p.gelu_out, i, v);
+          put_bf16(PER * i + 1, v);
         }
       }
       if (RESID && i + DEPTH < FM) load(i + DEPTH);
+      if (RESID && i + 1 < FM) spread(i + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
+    send(PER * FM - 1);
     stored = EDGE ? 0 : (GE != GELU_NONE || C32) ? 2 * Z::STORES : Z::STORES;
     young = Z::NB - 1;
   };
@@ -509,10 +526,14 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       k_tile(T(), F());
       for (int kt = 1; kt < nk; ++kt) k_tile(F(), F());
     }
-    const bool inside = cur.m0 + Z::BM <= p.M && cur.n0 + LBN <= p.N, bias = !WG && p.bias, resid = !WG && p.resid;
+    const bool inside = cur.m0 + Z::BM <= p.M && cur.n0 + LBN <= p.N, resid = !WG && p.resid;
     auto store_as = [&](auto f32_, auto resid_) __attribute__((always_inline)) {
-      if (inside) store(F(), f32_, resid_, C, ldc, bias);
-      else store(T(), f32_, resid_, C, ldc, bias);
+      auto with = [&](auto bias_) __attribute__((always_inline)) {
+        if (inside) store(F(), f32_, resid_, bias_, C, ldc);
+        else store(T(), f32_, resid_, bias_, C, ldc);
+      };
+      if (WG || (!BKM && !p.bias)) with(F());                     // (data gradients)
+      else with(T());
     };
     if (GE != GELU_NONE) store_as(F(), F());
     else if (WG) store_as(T(), F());
