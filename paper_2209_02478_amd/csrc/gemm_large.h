@@ -1,6 +1,6 @@
 // bf16 GEMM, large block tiles walked by persistent blocks.
 //
-// C[M,N] = sum_k A(m,k) B(n,k).  One block of 8 waves per compute unit takes tile after tile of 256 x 256
+// C[M,N] = sum_k A(m,k) B(n,k).  One block of 8 waves on a compute unit takes tile after tile of 256 x 256
 // (FM = 8) or 128 x 256 (FM = 4); a wave owns 16 * FM x 64 of it as MFMA tiles of 16 x 16 x 32.  Why these
 // sizes on gfx950: a compute unit draws about 54 bytes per clock from the L2, a 128 x 128 tile needs
 // 64 at full matrix rate, 128 x 256 needs 48, 256 x 256 needs 32; and under matrix load the clock follows
@@ -171,7 +171,7 @@ struct LTileOf {
 // GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH); a product without it stores bf16 or fp32,
 // with or without bias and residual.  p.vec is given.
 template <int FM, bool AK, bool BKM, bool KTAIL, int GE>
-__global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd) {
+__global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd, int turns) {
   using namespace large;
   typedef Sizes<FM> Z;
   typedef LTileOf<AK, Z::BM> TA;
@@ -180,12 +180,13 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   extern __shared__ __attribute__((aligned(1024))) unsigned char l_smem[];
   bf16_t* const ring = (bf16_t*)l_smem;
   bf16_t* const ring_b = ring + Z::NA * Z::A_TILE;
-  // Block ids go to the 8 XCDs in turn: XCD x gets the run of per_xcd units from x * per_xcd on, its
-  // blocks (32, one per compute unit) every 32nd of them.  Units run part by part (all tiles of the
-  // first k range, then of the second, ...): a run then shares one k range of both operands in the L2.
-  const int stride = gridDim.x >> 3;
-  int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  const int u_end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, total);
+  // Block ids go to the 8 XCDs in turn: XCD x gets the run of per_xcd units from x * per_xcd on, 32 of its
+  // blocks (one per compute unit) every 32nd of the next 32 * turns of them.  Units run part by part (all tiles of
+  // the first k range, then of the second, ...): a run then shares one k range of both operands in the L2.
+  constexpr int stride = 32;
+  const int first = (blockIdx.x >> 8) * stride * turns;
+  int unit = (blockIdx.x & 7) * per_xcd + first + ((blockIdx.x >> 3) & 31);
+  const int u_end = min((int)(blockIdx.x & 7) * per_xcd + min(per_xcd, first + stride * turns), total);
   if (unit >= u_end) return;
   const int n_tiles = total / p.splits, tiles_m = (p.M + Z::BM - 1) / Z::BM;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -559,11 +560,16 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   constexpr int BM = large::Sizes<FM>::BM;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + large::LBN - 1) / large::LBN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
-  const dim3 grid(8 * (per < 32 ? per : 32)), block(512);
+  // A block takes all its tiles, but two of a data gradient with six or more for each compute unit: the weight
+  // gradients on the other stream get their units sooner, for the price of a tile's first loads.  (Iterations of
+  // bert_large_stress 256 x 512 409.9 ms with all tiles in a block, 405.8 in twos, 408.0 in fours; with less than six
+  // 60.0 -> 60.2 and 19.93 -> 20.12 ms, gpt2_medium 16 x 1024 and bert_base 32 x 512.)
+  const int rounds = (per + 31) / 32, turns = AK && !BKM && rounds >= 6 ? 2 : rounds;
+  const dim3 grid(per < 32 ? 8 * per : 256 * ((rounds + turns - 1) / turns)), block(512);
   bool ktail = false;
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % large::LBK != 0;
-  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
-  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
+  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
 }
 
 // Requirements: 16-byte stores (p.vec); K % 8 == 0 when an operand is k-major (or zeros vouched for

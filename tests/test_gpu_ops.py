@@ -195,7 +195,8 @@ def test_gemm_large_tiles(a_k, b_k):
 
 @pytest.mark.parametrize("M,N,K", [(5000, 4872, 776),    # 400 tiles of 256 x 256 in two rounds, ragged in each dimension
                                    (4700, 4300, 520),    # 629 tiles of 128 x 256 in three rounds
-                                   (25600, 768, 640)])   # 300 tiles, whole in each dimension
+                                   (25600, 768, 640),    # 300 tiles, whole in each dimension
+                                   (9000, 9736, 328)])   # 1404 tiles: data gradients in blocks of two tiles
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
 def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     """Blocks that take several tiles, in every form of the store: the bits are those of the same rows
