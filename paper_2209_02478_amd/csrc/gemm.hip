@@ -504,7 +504,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   if (p.splits == 1) {
     const int rows = large_rows(g.M, g.N, g.K);
     if (rows == 256 && launch_bgemm_large(p, st, g.time_start, g.time_stop)) return true;
-    if (rows == 128 && launch_bgemm_large128(p, st, g.time_start, g.time_stop)) return true;
+    if (rows && launch_bgemm_large128(p, st, g.time_start, g.time_stop)) return true;   // (row sums of few columns too)
   }
   // B m-major (weight gradients, data gradients): the direct-to-LDS pipeline measures faster there;
   // the register-staged kernel below is ahead when both operands are k-major (forward)

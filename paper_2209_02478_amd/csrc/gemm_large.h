@@ -261,13 +261,16 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   auto read_a = [&](int i, int h) __attribute__((always_inline)) { af[i] = fa.read(ring, slot_a, i, h); };
   auto read_b = [&](int j, int h) __attribute__((always_inline)) { bfr[h][j] = fb.read(ring_b, slot_b, j, h); };
   f32x4 acc[FM][FN];
-  // Row sums of A (bias gradients): a wave owns FM / 2 chunks of 8 rows, a lane one of them and every 16th
-  // reduction index (the order of these sums is that of the other kernels, and leaving out 16 rows of zeros
-  // does not change it)
-  constexpr int CPW = FM / 2;
-  const int sum_pos = (lane / CPW) & 15, sum_chunk = CPW * wave + lane % CPW;
-  const int sum_at = sum_pos * Z::BM + ((sum_chunk ^ (4 * (sum_pos & 3) + 2 * ((sum_pos >> 3) & 1))) << 3);
-  float rs[8];
+  // Row sums of A (bias gradients): the first column tiles take 64 rows each; a lane sums two neighbouring rows,
+  // for each every 16th reduction index (the order of these sums is that of the other kernels, and leaving out
+  // 16 rows of zeros does not change it).  All waves of such a tile do the same share, 4 reads and 16 operations
+  // in a k tile, so that none is late where they meet.  All rows' sums in the first column tile, in half of the
+  // lanes, took a sixth of its time, and the first two waves of each column tile a seventh of everyone's.
+  // 20480 indices: 4096 x 1024 339 -> 303 us (without the sums 285), 1024 x 4096 314 -> 280, 30528 x 1024 1245 -> 1065.
+  constexpr int SUM_TILES = Z::BM / 64;
+  const int sum_pos = 2 * wave + (lane >> 5);
+  int sum_at = 0;
+  float rs[2];
   int stored = 0, young = 1;                                      // stores of the tile before, and for how many turns they are younger than the loads waited for
 
   auto k_tile = [&](auto first_, auto sums_) __attribute__((always_inline)) {
@@ -277,13 +280,16 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       for (int j = 0; j < FN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[h][j], af[i], FIRST && h == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
     };
-    bf16x8 sf;
+    uint32_t sf[4];
+    if (SUMS)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sf[u] = *(const uint32_t*)(ring + slot_a + sum_at + u * 16 * Z::BM);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      if (SUMS && i % (FM / 4) == 0) sf = *(const bf16x8*)(ring + slot_a + sum_at + i / (FM / 4) * 16 * Z::BM);
-      if (SUMS && i % (FM / 4) == FM / 4 - 1)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) rs[e] += (float)sf[e];
+      if (SUMS && i >= FM - 4) {
+        rs[0] += __uint_as_float(sf[i - (FM - 4)] << 16);
+        rs[1] += __uint_as_float(sf[i - (FM - 4)] & 0xFFFF0000u);
+      }
       row(i, 0);
       read_a(i, 1);
       if (i < FN) read_b(i, 1);
@@ -507,22 +513,31 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     void* const C = part ? (void*)(p.partial + (int64_t)cur.split * p.M * p.N) : p.C;
     const int64_t ldc = part ? p.N : p.ldc;
     const bool c_f32 = part || p.c_f32;
-    if (WG && p.a_rowsum && cur.n0 == 0) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) rs[e] = 0.f;
+    if (WG && p.a_rowsum && cur.n0 < SUM_TILES * LBN) {
+      const int chunk = cur.n0 / LBN * 8 + ((lane & 31) >> 2);
+      sum_at = sum_pos * Z::BM + ((chunk ^ (4 * (sum_pos & 3) + 2 * ((sum_pos >> 3) & 1))) << 3) + 2 * (lane & 3);
+      rs[0] = rs[1] = 0.f;
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int kt = 0; kt < nk; ++kt) k_tile(F(), T());
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      // the 16 sums of a row, in order, through the free slot of A (see the store)
+      auto place = [&](int pos, int r) __attribute__((always_inline)) {
+        return (float*)(l_smem + fill_a + (pos >> 1) * LA * 1024 + (pos & 1) * 256) + r;
+      };
+      *(float2*)place(sum_pos, 2 * (lane & 31)) = make_float2(rs[0], rs[1]);
+      __builtin_amdgcn_s_waitcnt(kLdsDone);
+      l_meet();
+      if (wave == 0) {
         float s = 0.f;
 #pragma unroll
-        for (int g = 0; g < 16; ++g) s += __shfl(rs[e], g * CPW + lane % CPW, 64);
-        const int m = cur.m0 + sum_chunk * 8 + e;
-        if (lane < CPW && m < p.M) rowsum[m] = s;
+        for (int g = 0; g < 16; ++g) s += *place(g, lane);
+        const int m = cur.m0 + cur.n0 / LBN * 64 + lane;
+        if (m < p.M) rowsum[m] = s;
       }
+      __builtin_amdgcn_s_waitcnt(kLdsDone);
+      l_meet();
     } else {
       k_tile(T(), F());
       for (int kt = 1; kt < nk; ++kt) k_tile(F(), F());
@@ -575,8 +590,8 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
 // Requirements: 16-byte stores (p.vec); K % 8 == 0 when an operand is k-major (or zeros vouched for
 // behind a k-major A's last column, with B m-major); the leading dimension of an m-major operand
 // covers its row count rounded up to 8; both operands
-// m-major: fp32 output without bias or residual, and there alone row sums; a reduction in parts with B
-// m-major; parts of more
+// m-major: fp32 output without bias or residual, and there alone row sums, shared by BM / 64 column tiles
+// (fewer are refused); a reduction in parts with B m-major; parts of more
 // k tiles than the loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
@@ -587,7 +602,7 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
   if (!p.a_k && p.lda < up8(p.M)) return false;
   if (!p.b_k && p.ldb < up8(p.N)) return false;
-  if (p.a_k && p.a_rowsum) return false;
+  if (p.a_rowsum && (p.a_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
   if (p.splits > 1 && (p.b_k || p.bias || p.resid)) return false;
   if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;
   for (int i = 0; i < p.splits; ++i)

@@ -196,7 +196,10 @@ def test_gemm_large_tiles(a_k, b_k):
 @pytest.mark.parametrize("M,N,K", [(5000, 4872, 776),    # 400 tiles of 256 x 256 in two rounds, ragged in each dimension
                                    (4700, 4300, 520),    # 629 tiles of 128 x 256 in three rounds
                                    (25600, 768, 640),    # 300 tiles, whole in each dimension
-                                   (9000, 9736, 328)])   # 1404 tiles: data gradients in blocks of two tiles
+                                   (9000, 9736, 328),    # 1404 tiles: data gradients in blocks of two tiles
+                                   (1000, 256, 1032),    # row sums: one column tile, which is too few
+                                   (3000, 300, 1096),    # two, the fewest
+                                   (20000, 768, 584)])   # three, of the four that 256 rows take
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
 def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     """Blocks that take several tiles, in every form of the store: the bits are those of the same rows
@@ -206,7 +209,7 @@ def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     mk = lambda r, c: (torch.randn((r, c), generator=g, device=DEV) * 0.5).to(torch.bfloat16)
     A, B = mk(M, K) if a_k else mk(K, up(M)), mk(N, K) if b_k else mk(K, up(N))
     bias, resid = mk(1, N)[0], mk(M, up(N))
-    rows = 256                                                  # alone: 64 x 32 or 64 x 64 tiles
+    rows = 256 if M > 4096 else 128                             # alone: 64 x 32 or 64 x 64 tiles
     forms = [dict(c_f32=1), dict(c_f32=1, bias=1, resid=1), dict(c_f32=0, bias=1), dict(c_f32=0, resid=1),
              dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, gelu=2)] if a_k else [dict(c_f32=1, rowsum=1)]
     for form in forms:
