@@ -32,7 +32,7 @@
 // residuals take the same way in.  Whole lines with the lanes across the rows, by exchanges between
 // lanes, leave a unit at 31 bytes per clock, along the rows at 104.  Whole launches of 262144 x 1024, K = 512,
 // the one against the other (us): bf16 312 -> 293, with residual 340 -> 331, fp32 370 -> 346, with
-// residual 442 -> 424, data gradient 298 -> 277; between tiles 8.0 -> 6.6 us in bf16, 11.9 -> 10.2 in fp32.  The
+// residual 442 -> 424, data gradient 298 -> 277 (with all its tiles in one block); between tiles 8.0 -> 6.6 us in bf16, 11.9 -> 10.2 in fp32.  The
 // loads of the first turn after a store wait at its end, so that its MFMAs are not held up behind the
 // stores on their way out (bert_base 32 x 200 iterations 0.5 %, 32 x 512 1.5, bert_stages 32 x 332 1.1).
 //
@@ -576,7 +576,8 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + large::LBN - 1) / large::LBN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
   // A block takes all its tiles, but two of a data gradient with six or more for each compute unit: the weight
-  // gradients on the other stream get their units sooner, for the price of a tile's first loads.  (Iterations of
+  // gradients on the other stream get their units sooner, for the price of a tile's first loads (262144 x 1024,
+  // K = 512 alone, the shortest: 277 -> 304 us; K = 4096 1610 -> 1660).  (Iterations of
   // bert_large_stress 256 x 512 409.9 ms with all tiles in a block, 405.8 in twos, 408.0 in fours; with less than six
   // 60.0 -> 60.2 and 19.93 -> 20.12 ms, gpt2_medium 16 x 1024 and bert_base 32 x 512.)
   const int rounds = (per + 31) / 32, turns = AK && !BKM && rounds >= 6 ? 2 : rounds;
