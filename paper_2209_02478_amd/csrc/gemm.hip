@@ -480,7 +480,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   }
   // Weight gradients: 128 x 256 tiles, also where they leave compute units idle (128 units at 4096 x 1024,
   // whose reduction is not cut; 144 at 3072 x 768 in two parts): alone that is slower (16384 x 4096 x 1024:
-  // 166 us on 256 units of 128 x 128, 250 on 128), but a unit's time is a quarter less and the other
+  // 166 us on 256 units of 128 x 128, 250 on 128, before their row sums were shared: 20480 x 4096 x 1024 339 -> 303), but a unit's time is a quarter less and the other
   // stream's kernels have the rest.  Iterations against the 128 x 128 kernels: bert_large_stress 256 x 512
   // 1.06 of the speed, bert_large 64 x 320 1.03, 16 x 256 1.02, 16 x 100 1.06, bert_base 32 x 512 1.01, 32 x 200
   // 1.01, 32 x 88 1.02, padded 12 x 397 1.02, gpt2_medium 16 x 1024 1.00, 4 x 400 1.05, 12 x 400 0.99.
