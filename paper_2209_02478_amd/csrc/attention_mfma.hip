@@ -99,11 +99,12 @@ struct FragAt {
 };
 
 // One wave-level direct load: lane i's 16 bytes at g land at lds + 16 * i.  Inline assembly, so the
-// compiler does not track it: landed() waits by hand.
+// compiler does not track it: landed() waits by hand.  The s_nop is the wait state between a write of M0
+// and the load that reads it, which the hardware leaves to the program.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
 __device__ __forceinline__ void direct_load(const bf16_t* g, uint32_t lds_byte_address) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_address(const void* p) {

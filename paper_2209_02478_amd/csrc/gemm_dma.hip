@@ -40,11 +40,12 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // One wave-level direct load: every lane's 16 bytes at `g` land at lds + 16 * lane.  Written as
 // inline assembly so that the compiler does not track it: the ring's waits are placed by hand
-// below (the compiler's own tracking drains the whole ring once per turn).
+// below (the compiler's own tracking drains the whole ring once per turn).  M0 is written one wait state
+// before a load to LDS reads it (the hardware does not wait for it): the s_nop.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
 __device__ __forceinline__ void direct_load(const bf16_t* g, uint32_t lds_byte_address) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 

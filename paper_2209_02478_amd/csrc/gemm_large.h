@@ -90,13 +90,14 @@ typedef __attribute__((address_space(3))) void lds_void_l;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
 
 // One wave-level direct load: lane i's 16 bytes at base + offset land at lds + 16 * i.  Inline assembly,
-// so the compiler does not track it: the waits are placed by hand in the loop.
+// so the compiler does not track it: the waits are placed by hand in the loop, and so is the wait state
+// between a write of M0 and the load that reads it (s_nop), which the hardware leaves to the program.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
 __device__ __forceinline__ void l_direct_load(uint64_t base, uint32_t bytes, uint32_t offset, uint32_t lds_byte_address) {
   const u32x4 r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)base), (uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)),
                    (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};          // raw buffer
-  asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(offset), "s"(r), "s"(lds_byte_address) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(offset), "s"(r), "s"(lds_byte_address) : "memory", "m0");
 }
 // an address that is the same in all lanes, in scalar registers
 __device__ __forceinline__ uint64_t l_uniform(const void* p) {

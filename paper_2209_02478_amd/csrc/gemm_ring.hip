@@ -30,10 +30,12 @@ __device__ __attribute__((aligned(16))) uint32_t g_zero16r[4] = {0u, 0u, 0u, 0u}
 typedef __attribute__((address_space(3))) void lds_void_r;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_r;
 
+// One wave-level direct load, its waits placed by hand.  The s_nop is the wait state between a write of M0 and
+// the load that reads it, which the hardware leaves to the program.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
 __device__ __forceinline__ void r_direct_load(const bf16_t* g, uint32_t lds_byte_address) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_byte_address) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // at most n loads in flight, no LDS operation pending
