@@ -12,8 +12,8 @@
 // Operand tiles (64 reduction indices) go global -> LDS directly into rings that fill the 160 KB: FM = 8
 // three slots of A and two of B, FM = 4 four and three.  A is requested NB k tiles ahead half a turn
 // earlier than B.  A load is one buffer instruction with a per-lane offset that is fixed for the tile
-// and a scalar base that moves along k: issuing it costs two instructions, and the loop has no branch
-// around it (a wave that has to branch around its loads loses about 60 clocks for each).  The loads
+// and a scalar base that moves along k: its descriptor stays in scalar registers, so issuing it takes the write
+// of M0, the wait state behind that and the load, and the loop has no branch around it (a wave that has to branch around its loads loses about 60 clocks for each).  The loads
 // run through the tile boundary: while a tile's last MFMAs and its store run, the first k tiles of the
 // block's next one are on their way, so only a block's first tile waits for memory.
 //
@@ -95,15 +95,22 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
 __device__ __forceinline__ void l_direct_load(uint64_t base, uint32_t bytes, uint32_t offset, uint32_t lds_byte_address) {
-  const u32x4 r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)base), (uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)),
-                   (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};          // raw buffer
+  const u32x4 r = {(uint32_t)base, (uint32_t)(base >> 32), bytes, 0x00020000u};                 // raw buffer
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(offset), "s"(r), "s"(lds_byte_address) : "memory", "m0");
 }
-// an address that is the same in all lanes, in scalar registers
-__device__ __forceinline__ uint64_t l_uniform(const void* p) {
+// A descriptor's address and size, the same in all lanes, settled in scalar registers: a scalar register that
+// a vector instruction (readfirstlane) wrote may be read by a load five wait states later, which the hardware
+// does not wait for either.  What comes out of the assembly counts as scalar from here on: moved and added to
+// by scalar instructions alone, which need no wait.
+__device__ __forceinline__ void l_descriptor(const void* p, uint32_t size, uint64_t& base, uint32_t& bytes) {
   const uint64_t a = (uint64_t)p;
-  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32;
+  uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32));
+  bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)size);
+  asm volatile("s_nop 4" : "+s"(lo), "+s"(hi), "+s"(bytes));
+  base = (uint64_t)lo | (uint64_t)hi << 32;
 }
+// a / b, the same in all lanes: vector instructions compute it, and without this all that follows from it
+__device__ __forceinline__ int l_div(int a, int b) { return __builtin_amdgcn_readfirstlane(a / b); }
 __device__ __forceinline__ uint32_t l_lds_address(const void* p) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_l*)p);
 }
@@ -202,18 +209,18 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   int64_t step_a = AK ? LBK * 2 : (int64_t)LBK * 2 * p.lda, step_b = BKM ? LBK * 2 : (int64_t)LBK * 2 * p.ldb;
   uint32_t off_a[2], off_b[2], bytes_a, bytes_b;
   auto enter = [&]() __attribute__((always_inline)) {                                            // first k tile of unit c_unit
-    const int split = PARTS ? c_unit / n_tiles : 0, t = c_unit - split * n_tiles;
-    const int group = t / (LGROUP_M * tiles_n), first_m = group * LGROUP_M;
+    const int split = PARTS ? l_div(c_unit, n_tiles) : 0, t = c_unit - split * n_tiles;
+    const int group = l_div(t, LGROUP_M * tiles_n), first_m = group * LGROUP_M;
     const int gsize = min(tiles_m - first_m, LGROUP_M);
-    const int in_group = t - group * LGROUP_M * tiles_n;
-    ahead = {(first_m + in_group % gsize) * Z::BM, in_group / gsize * LBN, split};
+    const int in_group = t - group * LGROUP_M * tiles_n, across = l_div(in_group, gsize);
+    ahead = {(first_m + in_group - across * gsize) * Z::BM, across * LBN, split};
     const int k0 = p.kb[split];
     c_k = p.kb[split + 1] - k0;
     c_left = (c_k + LBK - 1) / LBK;
-    base_a = l_uniform((const bf16_t*)p.A + (AK ? (int64_t)ahead.m0 * p.lda + k0 : (int64_t)k0 * p.lda + ahead.m0));
-    base_b = l_uniform((const bf16_t*)p.B + (BKM ? (int64_t)ahead.n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + ahead.n0));
-    bytes_a = TA::bytes(p.lda, p.M - ahead.m0);
-    bytes_b = TB::bytes(p.ldb, p.N - ahead.n0);
+    l_descriptor((const bf16_t*)p.A + (AK ? (int64_t)ahead.m0 * p.lda + k0 : (int64_t)k0 * p.lda + ahead.m0),
+                 TA::bytes(p.lda, p.M - ahead.m0), base_a, bytes_a);
+    l_descriptor((const bf16_t*)p.B + (BKM ? (int64_t)ahead.n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + ahead.n0),
+                 TB::bytes(p.ldb, p.N - ahead.n0), base_b, bytes_b);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       off_a[j] = TA::src(p.lda, p.M - ahead.m0, wave * LA + j, lane);
@@ -239,16 +246,17 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   auto advance = [&]() __attribute__((always_inline)) {
     fill_a = fill_a == (Z::NA - 1) * Z::A_TILE * 2u ? 0 : fill_a + Z::A_TILE * 2u;
     fill_b = fill_b == (Z::NB - 1) * Z::B_TILE * 2u ? 0 : fill_b + Z::B_TILE * 2u;
-    if (--c_left > 0) {
-      base_a += step_a; base_b += step_b;
-      c_k -= KTAIL ? LBK : 0;
-    } else if (c_unit + stride < u_end) {
-      c_unit += stride;
-      enter();
-    } else {
-      c_left = 1 << 30; step_a = step_b = 0; c_k = 1 << 30;
-      // c_k: with step 0 the k tile stays the unit's last; what lies behind its end is not looked at
-      if (KTAIL) c_k = 0;
+    base_a += step_a; base_b += step_b;
+    c_k -= KTAIL ? LBK : 0;
+    if (--c_left == 0) {                                          // (no else: its merge would leave the sizes in vector registers)
+      const bool more = c_unit + stride < u_end;
+      base_a -= more ? 0 : step_a; base_b -= more ? 0 : step_b;
+      step_a = more ? step_a : 0; step_b = more ? step_b : 0;
+      c_left = 1 << 30; c_k = 0;                                  // (no reduction index is left: zeros where KTAIL)
+      if (more) {
+        c_unit += stride;
+        enter();
+      }
     }
   };
 

@@ -143,3 +143,8 @@ def report(found):
 def test_m0_before_loads_to_lds(built):
     text = report({name: [f for f in bad if f[0] == "m0"] for name, bad in built.items()})
     assert not text, text
+
+
+def test_scalar_registers_before_vector_memory(built):
+    text = report({name: [f for f in bad if f[0] == "sgpr"] for name, bad in built.items()})
+    assert not text, text
