@@ -176,8 +176,8 @@ struct LTileOf {
 
 }  // namespace large
 
-// GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH); a product without it stores bf16 or fp32,
-// with or without bias and residual.  p.vec is given.
+// GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH), of the sum with bias and residual; a product
+// without it stores bf16 or fp32, with or without bias and residual.  p.vec is given.
 template <int FM, bool AK, bool BKM, bool KTAIL, int GE>
 __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd, int turns) {
   using namespace large;
@@ -560,7 +560,8 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       if (WG || (!BKM && !p.bias)) with(F());                     // (data gradients)
       else with(T());
     };
-    if (GE != GELU_NONE) store_as(F(), F());
+    if (GE != GELU_NONE && resid) store_as(F(), T());
+    else if (GE != GELU_NONE) store_as(F(), F());
     else if (WG) store_as(T(), F());
     else if (c_f32 && resid) store_as(T(), T());
     else if (c_f32) store_as(T(), F());

@@ -211,7 +211,8 @@ def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     bias, resid = mk(1, N)[0], mk(M, up(N))
     rows = 256 if M > 4096 else 128                             # alone: 64 x 32 or 64 x 64 tiles
     forms = [dict(c_f32=1), dict(c_f32=1, bias=1, resid=1), dict(c_f32=0, bias=1), dict(c_f32=0, resid=1),
-             dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, gelu=2)] if a_k else [dict(c_f32=1, rowsum=1)]
+             dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, gelu=2),
+             dict(c_f32=0, bias=1, resid=1, gelu=1), dict(c_f32=0, resid=1, gelu=2)] if a_k else [dict(c_f32=1, rowsum=1)]
     for form in forms:
         if form.get("gelu") and N % 8:
             continue                                            # the other kernels take the C library's erf there
@@ -233,6 +234,21 @@ def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
         for r0 in (0, M // 2 // 8 * 8, (M - rows) // 8 * 8):
             for full, alone in zip(whole, product(r0, rows)):
                 assert torch.equal(full[r0:r0 + rows], alone), (form, r0)
+
+
+@pytest.mark.parametrize("M,N,K", [(3500, 3800, 520), (2304, 2304, 512)])   # 256 x 256 and 128 x 256 tiles
+@pytest.mark.parametrize("form", [1, 2])
+def test_gemm_gelu_of_a_sum_with_residual(M, N, K, form):
+    rng = np.random.default_rng(M + form)
+    A, B = (rng.standard_normal(s).astype(np.float32) * 0.5 for s in ((M, K), (N, K)))
+    bias, resid = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32) * 4
+    C, G = (torch.zeros((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    mi.mimose_op_gemm(1, dev(A, 1), K, 1, dev(B, 1), K, 1, C, N, 0, M, N, K, bias=dev(bias, 1), resid=dev(resid, 1), ldr=N,
+                      gelu_out=G, gelu=form)
+    sync()
+    pre = quant(A, 1) @ quant(B, 1).T + quant(bias, 1) + quant(resid, 1)
+    close(host(C), pre, 1, k=2.0)
+    close(host(G), om.gelu_fwd(pre, form == 2), 1, scale=np.abs(pre).max(), k=3.0)
 
 
 def test_gemm_large_tiles_split_reduction():
