@@ -453,6 +453,10 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       *(f32x4*)(turn + (in32 ^ 64)) = y;
       back(t);
     };
+    // the last N % 8 columns take the C library's erf and tanh, as in the other kernels (tail: the first of them,
+    // from the wave's first column on)
+    const int tail = (p.N & ~7) - nw;
+    const bool ragged = EDGE && GE != GELU_NONE && (p.N & 7) && tail >= 0 && tail < 64;
     if (RESID) {
 #pragma unroll
       for (int i = 0; i < DEPTH; ++i) load(i);
@@ -479,10 +483,20 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       } else {
         put_bf16(PER * i, v);
         if (GE != GELU_NONE) {
+          f32x4 x = v[0];
+          if (ragged) {
 #pragma unroll
-          for (int j = 0; j < FN; ++j)
+            for (int j = 1; j < FN; ++j)
+              if (tail >> 4 == j) x = v[j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = GE == GELU_ERF ? gelu_erf(x[e]) : gelu_tanh(x[e]);
+          }
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[j][e] = GE == GELU_ERF ? gelu_erf_bf16(v[j][e]) : gelu_tanh_bf16(v[j][e]);
+            if (ragged && tail >> 4 == j && (tail >> 3 & 1) == lq >> 1) v[j] = x;
+          }
           put_bf16(PER * i + 1, v);
         }
       }
