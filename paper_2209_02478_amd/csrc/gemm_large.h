@@ -86,6 +86,7 @@ constexpr uint32_t kOutside = 0x80000000u;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes on any multiple of 4
 typedef __attribute__((address_space(3))) void lds_void_l;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
 
@@ -420,7 +421,8 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
         const int m = mw + t / PER * 16 + s * 8;
         if (C32) {
           float* to = (float*)C + (int64_t)m * ldc + n;
-          if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4*)to = held[s];
+          // (the rows of a part are N apart: on 16 bytes only where N % 4 == 0)
+          if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4_at4*)to = held[s];
           else if (m < p.M)
 #pragma unroll
             for (int e = 0; e < 4; ++e)

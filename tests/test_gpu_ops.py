@@ -273,6 +273,27 @@ def test_gemm_large_tiles_split_reduction():
     assert np.array_equal(host(W), first)
 
 
+@pytest.mark.parametrize("a_k,M,K", [(0, 1000, 2000), (0, 520, 2089), (1, 600, 8320)])
+@pytest.mark.parametrize("N", [1001, 1002, 1003])
+def test_gemm_parts_of_odd_columns(a_k, M, K, N):
+    """Parts whose rows do not lie on 16 bytes: the same bits as with the columns filled up."""
+    g = torch.Generator(device=DEV).manual_seed(N + M)
+    A = torch.randn((M, K) if a_k else (K, M), generator=g, device=DEV).to(torch.bfloat16)
+    B = torch.randn((K, 1008), generator=g, device=DEV).to(torch.bfloat16)
+    nws = mi.mimose_op_gemm_long_k_workspace_bytes(1008) if a_k else mi.mimose_op_gemm_workspace_bytes(M, 1008)
+    assert nws >= 2 * (M * 1008 + M) * 4
+    def product(n):
+        C, rs = torch.full((M, 1008), 7.0, device=DEV), torch.full((M,), 7.0, device=DEV)
+        ws = torch.zeros(nws, dtype=torch.uint8, device=DEV)
+        mi.mimose_op_gemm(1, A, K if a_k else M, a_k, B, 1008, 0, C, 1008, 1, M, n, K, a_rowsum=None if a_k else rs,
+                          workspace=ws, workspace_bytes=nws)
+        sync()
+        return C, rs
+    (C, rs), (whole, rs_whole) = product(N), product(1008)
+    assert torch.equal(C[:, :N], whole[:, :N]) and torch.equal(rs, rs_whole)
+    assert bool((C[:, N:] == 7.0).all()), "wrote outside the N columns"
+
+
 @pytest.mark.parametrize("c_f32", [0, 1])
 def test_gemm_long_reduction_in_parts(c_f32):
     """Data-gradient layout with a very long reduction and few output tiles (the shape class of the
