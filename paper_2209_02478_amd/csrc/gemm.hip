@@ -419,6 +419,15 @@ static int ring_variant(int M, int N) {
   return tiles(128, 128) <= 256 ? 3 : -1;
 }
 
+// Weight gradients that nothing runs beside keep the parts of their reduction (gemm_splits) and with them the
+// number of units.  The ring's 128 x 128 tiles are ahead where the units fill one round nearly (256 at
+// 4096 x 1024: 256 -> 207 us at K = 20480 against the 128 x 256 tiles on 128 units, 34 -> 27 at K = 2000) and
+// behind where they start a second one (288 at 768 x 3072), which leaves most of the chip idle in it.
+static bool ring_wgrad(int M, int N, int K, int splits) {
+  const int units = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * splits;
+  return K >= 1024 && units <= 256 && units >= 192;
+}
+
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
 bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
@@ -478,10 +487,16 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
     const int sp = splits_for(gemm_splits(g.M, g.N));
     if (sp > 1) { cut(sp, 32); p.partial = (float*)g.workspace; }
   }
+  // Weight gradients that nothing runs beside, where one round of small tiles holds them
+  if (!g.beside && !g.a_kmajor && !g.b_kmajor && ring_wgrad(g.M, g.N, rule_k, p.splits) &&
+      launch_bgemm_ring(p, 3, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
+    if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
+    return true;
+  }
   // Weight gradients: 128 x 256 tiles, also where they leave compute units idle (128 units at 4096 x 1024,
-  // whose reduction is not cut; 144 at 3072 x 768 in two parts): alone that is slower (16384 x 4096 x 1024:
-  // 166 us on 256 units of 128 x 128, 250 on 128, before their row sums were shared: 20480 x 4096 x 1024 339 -> 303), but a unit's time is a quarter less and the other
-  // stream's kernels have the rest.  Iterations against the 128 x 128 kernels: bert_large_stress 256 x 512
+  // whose reduction is not cut; 144 at 3072 x 768 in two parts).  Beside another product that pays although it
+  // is slower alone (see ring_wgrad): a unit's time is a quarter less and the other stream's kernels have
+  // the rest.  Iterations against the 128 x 128 kernels: bert_large_stress 256 x 512
   // 1.06 of the speed, bert_large 64 x 320 1.03, 16 x 256 1.02, 16 x 100 1.06, bert_base 32 x 512 1.01, 32 x 200
   // 1.01, 32 x 88 1.02, padded 12 x 397 1.02, gpt2_medium 16 x 1024 1.00, 4 x 400 1.05, 12 x 400 0.99.
   // Same parts and order of every sum, so the same bits.

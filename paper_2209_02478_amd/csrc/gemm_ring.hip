@@ -90,7 +90,11 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
   bf16_t* ring = (bf16_t*)r_smem;
   const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (unit >= total) return;
-  const int t = unit;
+  // weight gradients alone cut their reduction (units run part by part, see gemm_dma.hip) and carry
+  // the row sums of A
+  constexpr bool WG = !AK && !BKM;
+  const int n_tiles = WG ? total / p.splits : total;
+  const int split = WG ? unit / n_tiles : 0, t = unit - split * n_tiles;
   const int tiles_m = (p.M + BM - 1) / BM;
   const int group = t / (RGROUP_M * tiles_n), first_m = group * RGROUP_M;
   const int gsize = min(tiles_m - first_m, RGROUP_M);
@@ -109,8 +113,10 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int k_begin = 0, k_end = p.K;
+  const int k_begin = WG ? p.kb[split] : 0, k_end = WG ? p.kb[split + 1] : p.K;
   const int nk = (k_end - k_begin + RBK - 1) / RBK;
+  const bool do_rowsum = WG && p.a_rowsum && tile_n == 0;
+  float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const bf16_t *pa[LA], *pb[LB];
   int ka[LA], kb[LB];
 #pragma unroll
@@ -174,6 +180,19 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[S][ks][j], af[S][ks][i], acc[i][j], 0, 0, 0);
   };
+  // Row sums of the A tile: a thread owns 8 rows and every 16th reduction index, whatever the tile or
+  // stage size (the sums' order is that of the other kernels).
+  constexpr int RC = BM / 8;
+  auto rowsum_acc = [&](const bf16_t* at) {
+    if (RC * 16 < 64 * W && tid >= RC * 16) return;
+#pragma unroll
+    for (int j = 0; j < RBK / 16; ++j) {
+      const int q = tid / RC + 16 * j;
+      const bf16x8 v = *(const bf16x8*)(at + q * BM + (((tid % RC) ^ TA::swizzle(q)) << 3));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rs[e] += (float)v[e];
+    }
+  };
   constexpr int PER = LA + LB;
   static_assert(NS >= 3 && (NS - 2) * PER < 64, "loads in flight fit the counter");
 #pragma unroll
@@ -181,6 +200,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
   int cur = 0, fill = NS - 1;                         // slots of the next stage to read and to fill
   // Own loads of the next stage have landed (the younger NS - 2 stages stay in flight), own fragment
   // reads are done, all waves meet; its fragments are read, and the slot read a turn ago is refilled.
+  int sums_left = nk;                                 // an even count of stages ends with a turn behind the last
   auto turn = [&](auto set) {
     __builtin_amdgcn_sched_barrier(0);                // the other set's MFMAs stay behind the meeting
     __builtin_amdgcn_s_waitcnt(r_wait((NS - 2) * PER));
@@ -188,6 +208,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     fragments(set, cur);
+    if (WG && do_rowsum && sums_left > 0) { rowsum_acc(ring + cur * STAGE); --sums_left; }
     issue(fill);
     fill = cur;
     cur = cur == NS - 1 ? 0 : cur + 1;
@@ -205,7 +226,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
   __builtin_amdgcn_s_waitcnt(r_wait(0));
   // all residuals of the wave's tiles at once (one tile's after another's store cost a memory latency each)
   u32x4 resid[TM][TN][2];
-  if (resid_ahead(p))
+  if (!WG && resid_ahead(p))
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -218,6 +239,30 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
 
   // 32 x 32 tiles through LDS, so that the stores are rows: register r of a lane is row lane%32,
   // column 8*(r/4) + 4*(lane/32) + r%4; float4 chunk c of row r sits at c ^ (r & 7)
+  GemmDev q = p;
+  if (WG) {
+    float* rowsum = p.a_rowsum;
+    if (p.splits > 1) {                               // raw tile and row sums of this part, see gemm_dma.hip
+      q.C = p.partial + (int64_t)split * p.M * p.N;
+      q.ldc = p.N; q.c_f32 = 1; q.bias = nullptr; q.resid = nullptr; q.gelu = GELU_NONE;
+      q.vec = (p.N & 3) == 0;
+      rowsum = p.partial + (int64_t)p.splits * p.M * p.N + (int64_t)split * p.M;
+    }
+    if (do_rowsum) {                                  // sixteen threads hold parts of every row
+      float* red = (float*)ring;                      // [16][BM]
+      __syncthreads();
+      if (tid < RC * 16)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[(tid / RC) * BM + (tid % RC) * 8 + e] = rs[e];
+      __syncthreads();
+      if (tid < BM && m0 + tid < p.M) {
+        float tot = 0.f;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) tot += red[g * BM + tid];
+        rowsum[m0 + tid] = tot;
+      }
+    }
+  }
   __syncthreads();
   float* ws = (float*)ring + wave * 1024;
 #pragma unroll
@@ -234,7 +279,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
       const int mb = m0 + (wm * TM + i) * 32, nb = n0 + (wn * TN + j) * 32;
       const int n = nb + (lane & 3) * 8, c0 = 2 * (lane & 3);
       float cb[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (p.vec && p.bias && n + 8 <= p.N) unpack_bf16x8(*(const u32x4*)((const bf16_t*)p.bias + n), cb);
+      if (q.vec && q.bias && n + 8 <= p.N) unpack_bf16x8(*(const u32x4*)((const bf16_t*)q.bias + n), cb);
 #pragma unroll
       for (int it = 0; it < 2; ++it) {
         const int row = it * 16 + (lane >> 2), m = mb + row;
@@ -242,15 +287,15 @@ __global__ __launch_bounds__(64 * WM * WN) void bgemm_ring_kernel(GemmDev p, int
         const float4 hi = *(const float4*)&ws[row * 32 + (((c0 + 1) ^ (row & 7)) << 2)];
         float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         if (m >= p.M || n >= p.N) continue;
-        if (resid_ahead(p) && n + 8 <= p.N) {
+        if (!WG && resid_ahead(p) && n + 8 <= p.N) {
           float f[8];
           unpack_bf16x8(resid[i][j][it], f);
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = v[e] + cb[e] + f[e];
           put8(p, m, n, v);
-        } else if (p.vec) finish8(p, m, n, v, cb);
+        } else if (q.vec) finish8(q, m, n, v, cb);
         else
-          for (int e = 0; e < 8; ++e) epilogue<bf16_t>(p, m, n + e, v[e]);
+          for (int e = 0; e < 8; ++e) epilogue<bf16_t>(q, m, n + e, v[e]);
       }
       __builtin_amdgcn_wave_barrier();
     }
@@ -267,9 +312,11 @@ static void launch_ring_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEv
     return true;
   }();
   (void)configured;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, total = tiles_m * tiles_n, per = (total + 7) / 8;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
   const dim3 grid(per * 8), block(64 * WM * WN);
-  if (p.K % RBK != 0)
+  bool ktail = false;
+  for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % RBK != 0 || p.kb[i + 1] == p.kb[i];
+  if (ktail)
     hipExtLaunchKernelGGL((bgemm_ring_kernel<AK, BKM, true, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
   else
     hipExtLaunchKernelGGL((bgemm_ring_kernel<AK, BKM, false, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
@@ -286,7 +333,7 @@ static void launch_ring(const GemmDev& p, int which, hipStream_t st, hipEvent_t 
 
 bool launch_bgemm_ring(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
-  if (p.a_rowsum || p.splits > 1) return false;
+  if ((p.a_rowsum || p.splits > 1) && (p.a_k || p.b_k)) return false;
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
   if (!p.a_k && p.lda < up8(p.M)) return false;
   if (!p.b_k && p.ldb < up8(p.N)) return false;

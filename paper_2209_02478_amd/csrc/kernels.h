@@ -64,6 +64,8 @@ struct GemmArgs {
   // its blocks of kRowBlock rows (and one past the last) how many kept blocks lie before it (host)
   int k_padded = 0;
   const int32_t* k_blocks = nullptr;
+  // a weight gradient that other products run beside, on another stream: it may leave compute units to them
+  bool beside = false;
   void* workspace = nullptr;       // optional scratch of gemm_workspace_bytes(M, N) for split reductions
   size_t workspace_bytes = 0;
   // optional, both or neither: recorded by the product kernel's own start and end (not by markers

@@ -385,6 +385,7 @@ class Step {
   void with_workspace(mk::GemmArgs& a, bool late = false) {
     a.workspace = late ? late_ws_ : ws_;
     a.workspace_bytes = late ? late_ws_bytes_ : ws_bytes_;
+    a.beside = c_->side != nullptr;                 // (timed one by one they are the same kernels)
     if (dry_) return;
     // per-kernel timing brackets work on the main stream only, so it keeps everything there
     if (!c_->side || c_->prof_on) { gemm(a); return; }
