@@ -578,7 +578,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     };
     if (GE != GELU_NONE && resid) store_as(F(), T());
     else if (GE != GELU_NONE) store_as(F(), F());
-    else if (WG) store_as(T(), F());
+    else if (WG && c_f32) store_as(T(), F());
     else if (c_f32 && resid) store_as(T(), T());
     else if (c_f32) store_as(T(), F());
     else if (resid) store_as(F(), T());
@@ -623,13 +623,13 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
-  if (!p.vec || (!p.a_k && p.b_k)) return false;
+  if (!p.vec) return false;
   // a chunk of a k-major operand that straddles K is moved whole: allowed only where the caller
   // vouches for zeros behind A's last column while B (m-major) reads zeros from row K on
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
   if (!p.a_k && p.lda < up8(p.M)) return false;
   if (!p.b_k && p.ldb < up8(p.N)) return false;
-  if (p.a_rowsum && (p.a_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
+  if (p.a_rowsum && (p.a_k || p.b_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
   if (p.splits > 1 && (p.b_k || p.bias || p.resid)) return false;
   if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;
   for (int i = 0; i < p.splits; ++i)
@@ -639,8 +639,9 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
     else if (p.gelu == GELU_TANH) launch_large_t<FM, true, true, GELU_TANH>(p, st, t0, t1);
     else launch_large_t<FM, true, true, GELU_NONE>(p, st, t0, t1);
   } else {
-    if (p.gelu || (!p.a_k && (!p.c_f32 || p.bias || p.resid))) return false;
-    if (p.a_k) launch_large_t<FM, true, false, GELU_NONE>(p, st, t0, t1);
+    if (p.gelu || (!p.a_k && !p.b_k && (p.bias || p.resid))) return false;
+    if (p.b_k) launch_large_t<FM, false, true, GELU_NONE>(p, st, t0, t1);
+    else if (p.a_k) launch_large_t<FM, true, false, GELU_NONE>(p, st, t0, t1);
     else launch_large_t<FM, false, false, GELU_NONE>(p, st, t0, t1);
   }
   return true;

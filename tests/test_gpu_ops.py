@@ -201,7 +201,7 @@ def test_gemm_large_tiles(a_k, b_k):
                                    (1000, 256, 1032),    # row sums: one column tile, which is too few
                                    (3000, 300, 1096),    # two, the fewest
                                    (20000, 768, 584)])   # three, of the four that 256 rows take
-@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0), (0, 1)])
 def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     """Blocks that take several tiles, in every form of the store: the bits are those of the same rows
     multiplied alone, which other kernels do (the sum of an element is one chain over k in all of them)."""
@@ -213,7 +213,9 @@ def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
     rows = 256 if M > 4096 else 128                             # alone: 64 x 32 or 64 x 64 tiles
     forms = [dict(c_f32=1), dict(c_f32=1, bias=1, resid=1), dict(c_f32=0, bias=1), dict(c_f32=0, resid=1),
              dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, gelu=2),
-             dict(c_f32=0, bias=1, resid=1, gelu=1), dict(c_f32=0, resid=1, gelu=2)] if a_k else [dict(c_f32=1, rowsum=1)]
+             dict(c_f32=0, bias=1, resid=1, gelu=1), dict(c_f32=0, resid=1, gelu=2)]
+    if not a_k:
+        forms = forms[:4] if b_k else [dict(c_f32=1, rowsum=1), dict(c_f32=1), dict(c_f32=0)]
     for form in forms:
         def product(r0, n_rows):
             kw = {}
