@@ -86,7 +86,10 @@ constexpr uint32_t kOutside = 0x80000000u;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes on any multiple of 4
+// 16 and 8 bytes wherever an element may lie: the same instructions, at full speed where they are aligned
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_at2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_at2 __attribute__((ext_vector_type(2), aligned(2)));
 typedef __attribute__((address_space(3))) void lds_void_l;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
 
@@ -178,7 +181,7 @@ struct LTileOf {
 }  // namespace large
 
 // GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH), of the sum with bias and residual; a product
-// without it stores bf16 or fp32, with or without bias and residual.  p.vec is given.
+// without it stores bf16 or fp32, with or without bias and residual.
 template <int FM, bool AK, bool BKM, bool KTAIL, int GE>
 __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd, int turns) {
   using namespace large;
@@ -366,7 +369,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       cb[j] = u32x2{0u, 0u};
       const int n = nw + 4 * lq + j * 16;
       if (BIAS && p.bias) {
-        if (!EDGE || n + 4 <= p.N) cb[j] = *(const u32x2*)((const bf16_t*)p.bias + n);
+        if (!EDGE || n + 4 <= p.N) cb[j] = *(const u32x2_at2*)((const bf16_t*)p.bias + n);
         else
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       for (int s = 0; s < 2; ++s) {
         const int m = mw + i * 16 + s * 8, n = nw + sc * 8;
         const bf16_t* at = (const bf16_t*)p.resid + (int64_t)m * p.ldr + n;
-        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][s] = *(const u32x4*)at;
+        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][s] = *(const u32x4_at2*)at;
         else {
           u32x4 w = {0u, 0u, 0u, 0u};
           if (m < p.M)
@@ -421,7 +424,6 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
         const int m = mw + t / PER * 16 + s * 8;
         if (C32) {
           float* to = (float*)C + (int64_t)m * ldc + n;
-          // (the rows of a part are N apart: on 16 bytes only where N % 4 == 0)
           if (!EDGE || (m < p.M && n + 4 <= p.N)) *(u32x4_at4*)to = held[s];
           else if (m < p.M)
 #pragma unroll
@@ -429,7 +431,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
               if (n + e < p.N) to[e] = __uint_as_float(held[s][e]);
         } else {
           bf16_t* to = (bf16_t*)(t % PER ? p.gelu_out : C) + (int64_t)m * ldc + n;
-          if (!EDGE || (m < p.M && n + 8 <= p.N)) *(u32x4*)to = held[s];
+          if (!EDGE || (m < p.M && n + 8 <= p.N)) *(u32x4_at2*)to = held[s];
           else if (m < p.M)
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -614,16 +616,16 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
 }
 
-// Requirements: 16-byte stores (p.vec); K % 8 == 0 when an operand is k-major (or zeros vouched for
-// behind a k-major A's last column, with B m-major); the leading dimension of an m-major operand
-// covers its row count rounded up to 8; both operands
-// m-major: fp32 output without bias or residual, and there alone row sums, shared by BM / 64 column tiles
-// (fewer are refused); a reduction in parts with B m-major; parts of more
+// Requirements: K % 8 == 0 when an operand is k-major (or zeros vouched for behind a k-major A's last column,
+// with B m-major); the leading dimension of an m-major operand covers its row count rounded up to 8; GELU with
+// both operands k-major and where C and all that comes with it lies on 16 bytes (elsewhere the other kernels take
+// the C library's functions for every column); both operands m-major: no bias or residual, and there alone row
+// sums, shared by BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more
 // k tiles than the loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
-  if (!p.vec) return false;
+  if (!p.vec && p.gelu) return false;
   // a chunk of a k-major operand that straddles K is moved whole: allowed only where the caller
   // vouches for zeros behind A's last column while B (m-major) reads zeros from row K on
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;

@@ -237,6 +237,33 @@ def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
                 assert torch.equal(full[r0:r0 + rows], alone), (form, r0)
 
 
+@pytest.mark.parametrize("M,N,K", [(3500, 3801, 520), (2304, 2306, 512)])   # 256 x 256 and 128 x 256 tiles
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_gemm_large_tiles_off_16_bytes(M, N, K, a_k, b_k):
+    """C, bias and residual wherever an element may lie: the bits are those of the aligned product."""
+    g = torch.Generator(device=DEV).manual_seed(N + 2 * a_k + b_k)
+    up = lambda v: (v + 7) // 8 * 8
+    mk = lambda r, c: (torch.randn((r, c), generator=g, device=DEV) * 0.5).to(torch.bfloat16)
+    A, B = mk(M, K) if a_k else mk(K, up(M)), mk(N, K) if b_k else mk(K, up(N))
+    bias, resid = mk(1, up(N))[0], mk(M, up(N))
+    def place(x, pitch):                                        # rows `pitch` apart, from the second element on
+        out = torch.full((M * pitch + 8,), 7.0, dtype=x.dtype, device=DEV)[1:M * pitch + 1].view(M, pitch)
+        out[:, :N] = x[:, :N]
+        return out
+    for dt, epilogue in ((torch.bfloat16, True), (torch.float32, True), (torch.bfloat16, False), (torch.float32, False)):
+        if epilogue and not (a_k or b_k):
+            continue
+        def product(C, r, b):
+            mi.mimose_op_gemm(1, A, K if a_k else up(M), a_k, B, K if b_k else up(N), b_k, C, C.stride(0), int(dt == torch.float32),
+                              M, N, K, **(dict(bias=b, resid=r, ldr=r.stride(0)) if epilogue else {}))
+            sync()
+            return C
+        blank = torch.full((M, up(N)), 7.0, dtype=dt, device=DEV)
+        off = product(place(blank, N + 4), place(resid, N + 2), torch.cat([bias[:1], bias])[1:])
+        assert torch.equal(off[:, :N], product(blank, resid, bias)[:, :N]), (dt, epilogue)
+        assert bool((off[:, N:] == 7.0).all()), "wrote outside the N columns"
+
+
 @pytest.mark.parametrize("M,N,K", [(3500, 3800, 520), (2304, 2304, 512)])   # 256 x 256 and 128 x 256 tiles
 @pytest.mark.parametrize("form", [1, 2])
 def test_gemm_gelu_of_a_sum_with_residual(M, N, K, form):
