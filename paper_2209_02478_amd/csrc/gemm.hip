@@ -420,12 +420,13 @@ static int ring_variant(int M, int N) {
 }
 
 // Weight gradients that nothing runs beside keep the parts of their reduction (gemm_splits) and with them the
-// number of units.  The ring's 128 x 128 tiles are ahead where the units fill one round nearly (256 at
-// 4096 x 1024: 256 -> 207 us at K = 20480 against the 128 x 256 tiles on 128 units, 34 -> 27 at K = 2000) and
-// behind where they start a second one (288 at 768 x 3072), which leaves most of the chip idle in it.
-static bool ring_wgrad(int M, int N, int K, int splits) {
-  const int units = ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * splits;
-  return K >= 1024 && units <= 256 && units >= 192;
+// number of units.  Where these fit one round the ring's 128 x 128 tiles are ahead of the 128 x 256 tiles, which
+// leave half of it idle (256 units at 4096 x 1024: 208 us against 257 at K = 20480, 28.9 against 34.9 at K = 2000;
+// 36 at 768 x 768 in one part 178 against 253), and of the 128 x 128 kernel without the ring (245, 35.6;
+// 228).  From where a second round starts they are behind both (288 at 768 x 3072: 60 us against 52 and 54 at
+// K = 6400).
+static bool ring_wgrad(int M, int N, int splits) {
+  return ((M + BM - 1) / BM) * ((N + BN - 1) / BN) * splits <= 256;
 }
 
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
@@ -487,8 +488,10 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
     const int sp = splits_for(gemm_splits(g.M, g.N));
     if (sp > 1) { cut(sp, 32); p.partial = (float*)g.workspace; }
   }
-  // Weight gradients that nothing runs beside, where one round of small tiles holds them
-  if (!g.beside && !g.a_kmajor && !g.b_kmajor && ring_wgrad(g.M, g.N, rule_k, p.splits) &&
+  // Weight gradients, which are what has parts or row sums, and those of the iteration without a bias; what is left
+  // of products with both operands m-major goes by its output tiles as the others do
+  const bool wgrad = !g.a_kmajor && !g.b_kmajor && rule_k >= 1024 && (g.beside || g.a_rowsum || p.splits > 1);
+  if (wgrad && !g.beside && ring_wgrad(g.M, g.N, p.splits) &&
       launch_bgemm_ring(p, 3, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
     if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
     return true;
@@ -500,7 +503,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   // 1.06 of the speed, bert_large 64 x 320 1.03, 16 x 256 1.02, 16 x 100 1.06, bert_base 32 x 512 1.01, 32 x 200
   // 1.01, 32 x 88 1.02, padded 12 x 397 1.02, gpt2_medium 16 x 1024 1.00, 4 x 400 1.05, 12 x 400 0.99.
   // Same parts and order of every sum, so the same bits.
-  if (!g.a_kmajor && !g.b_kmajor && rule_k >= 1024 && g.M >= 256 && g.N >= 256 && tiles128(g.M, g.N) <= 256 &&
+  if (wgrad && g.M >= 256 && g.N >= 256 && tiles128(g.M, g.N) <= 256 &&
       launch_bgemm_large128(p, st, g.time_start, p.splits > 1 ? nullptr : g.time_stop)) {
     if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
     return true;

@@ -359,7 +359,7 @@ def test_gemm_long_reduction_in_parts(c_f32):
 # rows, columns and reduction lengths (one, an odd and an even count of 64-deep stages)
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
 @pytest.mark.parametrize("M,N,K", [(70, 96, 64), (33, 8, 200), (130, 4104, 136), (640, 776, 192), (1700, 768, 72),
-                                   (1536, 1600, 320), (2500, 776, 264)])
+                                   (1536, 1600, 320), (2500, 776, 264), (300, 600, 1096)])
 def test_gemm_ring_tiles(a_k, b_k, M, N, K):
     dtype = 1
     rng = np.random.default_rng(M + N + K)
@@ -388,17 +388,20 @@ def test_gemm_ring_tiles(a_k, b_k, M, N, K):
     close(host(G)[:, :N], om.gelu_fwd(pre, False), dtype, scale=np.abs(pre).max(), k=3.0)
 
 
-# weight gradients on the ring: parts with an odd and an even count of stages, a ragged last part
+# weight gradients on the ring: parts with an odd and an even count of stages, a ragged last part; a round of
+# units and a few
+@pytest.mark.parametrize("M,N", [(1024, 1024), (300, 600), (8, 40)])
 @pytest.mark.parametrize("T", [1024, 1100, 2000, 2089])
-def test_gemm_ring_weight_gradient(T):
-    dtype, M, N = 1, 1024, 1024
+def test_gemm_ring_weight_gradient(T, M, N):
+    dtype, ld = 1, lambda v: (v + 7) // 8 * 8
     rng = np.random.default_rng(T)
     dY, X = rng.standard_normal((T, M)).astype(np.float32), rng.standard_normal((T, N)).astype(np.float32)
     nws = mi.mimose_op_gemm_workspace_bytes(M, N)
     ws = torch.zeros(nws, dtype=torch.uint8, device=DEV)
     W = torch.full((M, N), 9.0, dtype=torch.float32, device=DEV)
     rs = torch.full((M,), 9.0, dtype=torch.float32, device=DEV)
-    mi.mimose_op_gemm(dtype, dev(dY, dtype), M, 0, dev(X, dtype), N, 0, W, N, 1, M, N, T, a_rowsum=rs, workspace=ws,
+    pad = lambda X: np.ascontiguousarray(np.pad(X, ((0, 0), (0, ld(X.shape[1]) - X.shape[1]))))
+    mi.mimose_op_gemm(dtype, dev(pad(dY), dtype), ld(M), 0, dev(pad(X), dtype), ld(N), 0, W, N, 1, M, N, T, a_rowsum=rs, workspace=ws,
                       workspace_bytes=nws)
     sync()
     close(host(W), quant(dY, dtype).T @ quant(X, dtype), 0, k=40.0)
