@@ -181,8 +181,10 @@ struct LTileOf {
 }  // namespace large
 
 // GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH), of the sum with bias and residual; a product
-// without it stores bf16 or fp32, with or without bias and residual.
-template <int FM, bool AK, bool BKM, bool KTAIL, int GE>
+// without it stores bf16 or fp32, with or without bias and residual.  SUMS: row sums with B k-major; a loop with and
+// one without them do not fit the registers there, and reloads in the loop wait for its loads to LDS (10624 x 1024,
+// K = 4096: 110 us and, without sums, 105; apart 86 and 80), so every tile takes them.
+template <int FM, bool AK, bool BKM, bool KTAIL, int GE, bool SUMS>
 __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd, int turns) {
   using namespace large;
   typedef Sizes<FM> Z;
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: address arithmetic on it stays scalar
   const int wm = wave >> 2, wn = wave & 3;
-  constexpr bool PARTS = !BKM, WG = !AK && !BKM;                  // reduction cut in parts; weight gradients: row sums, fp32
+  constexpr bool PARTS = !BKM, WG = !AK && !BKM;                  // reduction cut in parts; weight gradients: no bias, no residual
 
   // ---- the loads' position: unit, its tile, the k tile
   struct Place { int m0, n0, split; } cur, ahead;
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   auto read_b = [&](int j, int h) __attribute__((always_inline)) { bfr[h][j] = fb.read(ring_b, slot_b, j, h); };
   f32x4 acc[FM][FN];
   // Row sums of A (bias gradients): the first column tiles take 64 rows each; a lane sums two neighbouring rows,
-  // for each every 16th reduction index (the order of these sums is that of the other kernels, and leaving out
+  // for each every 16th reduction index (the order of these sums is that of the other kernels with direct loads, and leaving out
   // 16 rows of zeros does not change it).  All waves of such a tile do the same share, 4 reads and 16 operations
   // in a k tile, so that none is late where they meet.  All rows' sums in the first column tile, in half of the
   // lanes, took a sixth of its time, and the first two waves of each column tile a seventh of everyone's.
@@ -287,19 +289,19 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   int stored = 0, young = 1;                                      // stores of the tile before, and for how many turns they are younger than the loads waited for
 
   auto k_tile = [&](auto first_, auto sums_) __attribute__((always_inline)) {
-    constexpr bool FIRST = decltype(first_)::value, SUMS = decltype(sums_)::value;
+    constexpr bool FIRST = decltype(first_)::value, SUM = decltype(sums_)::value;
     auto row = [&](int i, int h) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[h][j], af[i], FIRST && h == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
     };
     uint32_t sf[4];
-    if (SUMS)
+    if (SUM)
 #pragma unroll
       for (int u = 0; u < 4; ++u) sf[u] = *(const uint32_t*)(ring + slot_a + sum_at + u * 16 * Z::BM);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      if (SUMS && i >= FM - 4) {
+      if (SUM && i >= FM - 4) {
         rs[0] += __uint_as_float(sf[i - (FM - 4)] << 16);
         rs[1] += __uint_as_float(sf[i - (FM - 4)] & 0xFFFF0000u);
       }
@@ -540,8 +542,9 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     void* const C = part ? (void*)(p.partial + (int64_t)cur.split * p.M * p.N) : p.C;
     const int64_t ldc = part ? p.N : p.ldc;
     const bool c_f32 = part || p.c_f32;
-    if (WG && p.a_rowsum && cur.n0 < SUM_TILES * LBN) {
-      const int chunk = cur.n0 / LBN * 8 + ((lane & 31) >> 2);
+    const bool sum_tile = (WG || SUMS) && p.a_rowsum && cur.n0 < SUM_TILES * LBN;
+    if (SUMS || sum_tile) {
+      const int chunk = (sum_tile ? cur.n0 / LBN * 8 : 0) + ((lane & 31) >> 2);
       sum_at = sum_pos * Z::BM + ((chunk ^ (4 * (sum_pos & 3) + 2 * ((sum_pos >> 3) & 1))) << 3) + 2 * (lane & 3);
       rs[0] = rs[1] = 0.f;
 #pragma unroll
@@ -553,18 +556,20 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
       auto place = [&](int pos, int r) __attribute__((always_inline)) {
         return (float*)(l_smem + fill_a + (pos >> 1) * LA * 1024 + (pos & 1) * 256) + r;
       };
-      *(float2*)place(sum_pos, 2 * (lane & 31)) = make_float2(rs[0], rs[1]);
-      __builtin_amdgcn_s_waitcnt(kLdsDone);
-      l_meet();
-      if (wave == 0) {
-        float s = 0.f;
+      if (sum_tile) {
+        *(float2*)place(sum_pos, 2 * (lane & 31)) = make_float2(rs[0], rs[1]);
+        __builtin_amdgcn_s_waitcnt(kLdsDone);
+        l_meet();
+        if (wave == 0) {
+          float s = 0.f;
 #pragma unroll
-        for (int g = 0; g < 16; ++g) s += *place(g, lane);
-        const int m = cur.m0 + cur.n0 / LBN * 64 + lane;
-        if (m < p.M) rowsum[m] = s;
+          for (int g = 0; g < 16; ++g) s += *place(g, lane);
+          const int m = cur.m0 + cur.n0 / LBN * 64 + lane;
+          if (m < p.M) rowsum[m] = s;
+        }
+        __builtin_amdgcn_s_waitcnt(kLdsDone);
+        l_meet();
       }
-      __builtin_amdgcn_s_waitcnt(kLdsDone);
-      l_meet();
     } else {
       k_tile(T(), F());
       for (int kt = 1; kt < nk; ++kt) k_tile(F(), F());
@@ -592,11 +597,11 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   __builtin_amdgcn_s_waitcnt(in_flight(0));           // no direct load may land in LDS that is another block's by then
 }
 
-template <int FM, bool AK, bool BKM, int GE>
+template <int FM, bool AK, bool BKM, int GE, bool SUMS = false>
 void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   static const bool configured = [] {
-    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, false, GE>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
-    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, true, GE>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
+    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
+    (void)hipFuncSetAttribute((const void*)bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>, hipFuncAttributeMaxDynamicSharedMemorySize, large::Sizes<FM>::SMEM);
     return true;
   }();
   (void)configured;
@@ -612,15 +617,15 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   const dim3 grid(per < 32 ? 8 * per : 256 * ((rounds + turns - 1) / turns)), block(512);
   bool ktail = false;
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % large::LBK != 0;
-  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
-  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
+  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
+  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
 }
 
 // Requirements: K % 8 == 0 when an operand is k-major (or zeros vouched for behind a k-major A's last column,
 // with B m-major); the leading dimension of an m-major operand covers its row count rounded up to 8; GELU with
 // both operands k-major and where C and all that comes with it lies on 16 bytes (elsewhere the other kernels take
-// the C library's functions for every column); both operands m-major: no bias or residual, and there alone row
-// sums, shared by BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more
+// the C library's functions for every column); both operands m-major: no bias or residual; row sums with A
+// m-major, shared by BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more
 // k tiles than the loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
@@ -631,7 +636,7 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
   if (!p.a_k && p.lda < up8(p.M)) return false;
   if (!p.b_k && p.ldb < up8(p.N)) return false;
-  if (p.a_rowsum && (p.a_k || p.b_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
+  if (p.a_rowsum && (p.a_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
   if (p.splits > 1 && (p.b_k || p.bias || p.resid)) return false;
   if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;
   for (int i = 0; i < p.splits; ++i)
@@ -642,7 +647,8 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
     else launch_large_t<FM, true, true, GELU_NONE>(p, st, t0, t1);
   } else {
     if (p.gelu || (!p.a_k && !p.b_k && (p.bias || p.resid))) return false;
-    if (p.b_k) launch_large_t<FM, false, true, GELU_NONE>(p, st, t0, t1);
+    if (p.b_k && p.a_rowsum) launch_large_t<FM, false, true, GELU_NONE, true>(p, st, t0, t1);
+    else if (p.b_k) launch_large_t<FM, false, true, GELU_NONE>(p, st, t0, t1);
     else if (p.a_k) launch_large_t<FM, true, false, GELU_NONE>(p, st, t0, t1);
     else launch_large_t<FM, false, false, GELU_NONE>(p, st, t0, t1);
   }
