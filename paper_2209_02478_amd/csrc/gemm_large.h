@@ -84,6 +84,8 @@ struct Sizes {
 // buffer is larger than this.
 constexpr uint32_t kOutside = 0x80000000u;
 
+constexpr int kLibrary = 4;                      // on top of the GELU's form
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // 16 and 8 bytes wherever an element may lie: the same instructions, at full speed where they are aligned
@@ -180,7 +182,8 @@ struct LTileOf {
 
 }  // namespace large
 
-// GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH), of the sum with bias and residual; a product
+// GE: GELU in the store (GELU_NONE, GELU_ERF, GELU_TANH), of the sum with bias and residual, by the C library's
+// functions in every column with kLibrary on top (C not on 16 bytes, as in the other kernels); a product
 // without it stores bf16 or fp32, with or without bias and residual.  SUMS: row sums with B k-major; a loop with and
 // one without them do not fit the registers there, and reloads in the loop wait for its loads to LDS (10624 x 1024,
 // K = 4096: 110 us and, without sums, 105; apart 86 and 80), so every tile takes them.
@@ -191,6 +194,8 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   typedef LTileOf<AK, Z::BM> TA;
   typedef LTileOf<BKM, LBN> TB;
   constexpr int LA = Z::A_LOADS, LB = Z::B_LOADS, MEET = Z::MEET;
+  constexpr bool LIBRARY = GE & kLibrary;
+  constexpr int FORM = GE & (kLibrary - 1);
   extern __shared__ __attribute__((aligned(1024))) unsigned char l_smem[];
   bf16_t* const ring = (bf16_t*)l_smem;
   bf16_t* const ring_b = ring + Z::NA * Z::A_TILE;
@@ -462,7 +467,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     // the last N % 8 columns take the C library's erf and tanh, as in the other kernels (tail: the first of them,
     // from the wave's first column on)
     const int tail = (p.N & ~7) - nw;
-    const bool ragged = EDGE && GE != GELU_NONE && (p.N & 7) && tail >= 0 && tail < 64;
+    const bool ragged = EDGE && GE != GELU_NONE && !LIBRARY && (p.N & 7) && tail >= 0 && tail < 64;
     if (RESID) {
 #pragma unroll
       for (int i = 0; i < DEPTH; ++i) load(i);
@@ -495,12 +500,14 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
             for (int j = 1; j < FN; ++j)
               if (tail >> 4 == j) x = v[j];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = GE == GELU_ERF ? gelu_erf(x[e]) : gelu_tanh(x[e]);
+            for (int e = 0; e < 4; ++e) x[e] = FORM == GELU_ERF ? gelu_erf(x[e]) : gelu_tanh(x[e]);
           }
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[j][e] = GE == GELU_ERF ? gelu_erf_bf16(v[j][e]) : gelu_tanh_bf16(v[j][e]);
+            for (int e = 0; e < 4; ++e)
+              if (LIBRARY) v[j][e] = FORM == GELU_ERF ? gelu_erf(v[j][e]) : gelu_tanh(v[j][e]);
+              else v[j][e] = FORM == GELU_ERF ? gelu_erf_bf16(v[j][e]) : gelu_tanh_bf16(v[j][e]);
             if (ragged && tail >> 4 == j && (tail >> 3 & 1) == lq >> 1) v[j] = x;
           }
           put_bf16(PER * i + 1, v);
@@ -577,7 +584,7 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
     const bool inside = cur.m0 + Z::BM <= p.M && cur.n0 + LBN <= p.N, resid = !WG && p.resid;
     auto store_as = [&](auto f32_, auto resid_) __attribute__((always_inline)) {
       auto with = [&](auto bias_) __attribute__((always_inline)) {
-        if (inside) store(F(), f32_, resid_, bias_, C, ldc);
+        if (!LIBRARY && inside) store(F(), f32_, resid_, bias_, C, ldc);
         else store(T(), f32_, resid_, bias_, C, ldc);
       };
       if (WG || (!BKM && !p.bias)) with(F());                     // (data gradients)
@@ -623,14 +630,12 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
 
 // Requirements: K % 8 == 0 when an operand is k-major (or zeros vouched for behind a k-major A's last column,
 // with B m-major); the leading dimension of an m-major operand covers its row count rounded up to 8; GELU with
-// both operands k-major and where C and all that comes with it lies on 16 bytes (elsewhere the other kernels take
-// the C library's functions for every column); both operands m-major: no bias or residual; row sums with A
-// m-major, shared by BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more
-// k tiles than the loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
+// both operands k-major; both operands m-major: no bias or residual; row sums with A m-major, shared by
+// BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more k tiles than the
+// loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
-  if (!p.vec && p.gelu) return false;
   // a chunk of a k-major operand that straddles K is moved whole: allowed only where the caller
   // vouches for zeros behind A's last column while B (m-major) reads zeros from row K on
   if ((p.a_k || p.b_k) && (p.K & 7) && !(p.a_tail_zero && p.a_k && !p.b_k && p.lda >= up8(p.K))) return false;
@@ -642,7 +647,9 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
   for (int i = 0; i < p.splits; ++i)
     if (p.kb[i + 1] - p.kb[i] <= large::Sizes<FM>::NB * large::LBK) return false;
   if (p.a_k && p.b_k) {
-    if (p.gelu == GELU_ERF) launch_large_t<FM, true, true, GELU_ERF>(p, st, t0, t1);
+    if (p.gelu == GELU_ERF && !p.vec) launch_large_t<FM, true, true, GELU_ERF | large::kLibrary>(p, st, t0, t1);
+    else if (p.gelu == GELU_TANH && !p.vec) launch_large_t<FM, true, true, GELU_TANH | large::kLibrary>(p, st, t0, t1);
+    else if (p.gelu == GELU_ERF) launch_large_t<FM, true, true, GELU_ERF>(p, st, t0, t1);
     else if (p.gelu == GELU_TANH) launch_large_t<FM, true, true, GELU_TANH>(p, st, t0, t1);
     else launch_large_t<FM, true, true, GELU_NONE>(p, st, t0, t1);
   } else {

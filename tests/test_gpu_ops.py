@@ -268,6 +268,26 @@ def test_gemm_large_tiles_off_16_bytes(M, N, K, a_k, b_k):
         assert bool((off[:, N:] == 7.0).all()), "wrote outside the N columns"
 
 
+@pytest.mark.parametrize("M,N,K", [(3500, 3801, 520), (2304, 2306, 512)])   # 256 x 256 and 128 x 256 tiles
+@pytest.mark.parametrize("form,resid", [(1, 0), (2, 0), (1, 1), (2, 1)])
+def test_gemm_gelu_off_16_bytes(M, N, K, form, resid):
+    """The C library's functions in every column: the bits are those of the same rows multiplied alone, which
+    another kernel does."""
+    g = torch.Generator(device=DEV).manual_seed(N + form)
+    A, B, bias, r = ((torch.randn(s, generator=g, device=DEV) * k).to(torch.bfloat16)
+                     for s, k in (((M, K), 0.5), ((N, K), 0.5), ((N,), 1.0), ((M, N), 4.0)))
+    def product(r0, rows):
+        C, G = (torch.full((rows * N + 1,), 7.0, dtype=torch.bfloat16, device=DEV)[1:].view(rows, N) for _ in range(2))
+        kw = dict(resid=r[r0:], ldr=N) if resid else {}
+        mi.mimose_op_gemm(1, A[r0:], K, 1, B, K, 1, C, N, 0, rows, N, K, bias=bias, gelu_out=G, gelu=form, **kw)
+        sync()
+        return C, G
+    whole = product(0, M)
+    for r0 in (0, 1000, M - 128):
+        for full, alone in zip(whole, product(r0, 128)):
+            assert torch.equal(full[r0:r0 + 128], alone), r0
+
+
 @pytest.mark.parametrize("M,N,K", [(3500, 3800, 520), (2304, 2304, 512)])   # 256 x 256 and 128 x 256 tiles
 @pytest.mark.parametrize("form", [1, 2])
 def test_gemm_gelu_of_a_sum_with_residual(M, N, K, form):
