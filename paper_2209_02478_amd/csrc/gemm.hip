@@ -335,17 +335,25 @@ bool launch_bgemm_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEven
 bool launch_bgemm_large128(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
 static int tiles128(int M, int N) { return ((M + 127) / 128) * ((N + 255) / 256); }
 static int rounds(int tiles) { return (tiles + 255) / 256; }
-// Rows of the tiles (256 or 128) of a forward or data-gradient product, or 0: the kernels with 128 x 128.
+// Rows of the tiles (256 or 128) of a product that is not cut in parts, or 0: the kernels with 128 x 128.
 // One block per compute unit, so the time is a whole number of rounds of 256 tiles; a round of the
 // smaller tiles takes about two thirds of one of the larger (0.95 against 1.5 us per 64 reduction indices,
 // and 6-8 us of start and store).  One round against two thirds: ahead by 20-28 % at 88-128 large tiles
 // (8192 x 768 K = 3072: 74 -> 54 us; 6352 x 1024 K = 4096: 88 -> 64), three against two (320 large tiles)
-// by 0-6 %; from there on the larger are ahead by up to a fifth.  The 128 x 128 kernels are left where a
-// second round of large tiles has just begun (264 tiles of 768 reduction indices: 40 against 43 us).
-static int large_rows(int M, int N, int K) {
+// by 0-6 %; from there on the larger are ahead by up to a fifth.  Left to the kernels with 128 x 128, of which a
+// compute unit holds two or three, times of the large tiles over theirs:
+// - fewer than 66 large tiles
+// - B m-major where a second round of large tiles has just begun (257-280): 0.91-1.10 for data gradients and
+//   1.00-1.14 for both operands m-major, K = 512-6400.  With B k-major the tiles of 128 rows are ahead there too,
+//   0.70-0.97 from K = 768 on and 0.73-1.02 at 512
+// - one round of their own, 512, where tiles of 128 rows have begun a second one (a last column tile at most half
+//   full, as in 2816 x 2944 or 16391 x 257): 0.95-1.88 with B m-major; with B k-major 0.84-1.70 up to K = 1024, 1.2 in
+//   the mean, 0.80-1.30 at 2048 and 0.78-1.14 at 4096
+static int large_rows(int M, int N, int K, bool b_k) {
   if (M < 256 || N < 256 || K < 512) return 0;
   const int large = gemm_large_tiles(M, N), r = rounds(large), r128 = rounds(tiles128(M, N));
-  if (large < 66 || (large > 256 && large <= 280)) return 0;
+  if (large < 66 || (!b_k && large > 256 && large <= 280)) return 0;
+  if (r == 1 && r128 == 2 && ((M + BM - 1) / BM) * ((N + BN - 1) / BN) <= 512 && (!b_k || K < 4096)) return 0;
   return 2 * r128 <= 3 * r ? 128 : 256;
 }
 
@@ -520,7 +528,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   }
   // large tiles (a choice made from the shape alone)
   if (p.splits == 1) {
-    const int rows = large_rows(g.M, g.N, g.K);
+    const int rows = large_rows(g.M, g.N, g.K, g.b_kmajor);
     if (rows == 256 && launch_bgemm_large(p, st, g.time_start, g.time_stop)) return true;
     if (rows && launch_bgemm_large128(p, st, g.time_start, g.time_stop)) return true;   // (row sums of few columns too)
   }
