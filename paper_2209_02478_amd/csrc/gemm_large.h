@@ -399,22 +399,27 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int m = mw + i * 16 + s * 8, n = nw + sc * 8;
-        const bf16_t* at = (const bf16_t*)p.resid + (int64_t)m * p.ldr + n;
-        if (!EDGE || (m < p.M && n + 8 <= p.N)) r[i][s] = *(const u32x4_at2*)at;
-        else {
-          u32x4 w = {0u, 0u, 0u, 0u};
-          if (m < p.M)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < p.N) w[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
-          r[i][s] = w;
-        }
+        // where the row ends within these 8 columns, its last 8, shifted when they are used (an element at a time each
+        // row waits for memory: 1300 x 6500, K = 1024 data gradient with residual 40 us against 28)
+        const bf16_t* at = (const bf16_t*)p.resid + (int64_t)m * p.ldr + (EDGE && n + 8 > p.N ? p.N - 8 : n);
+        r[i][s] = u32x4{0u, 0u, 0u, 0u};
+        if (!EDGE || (m < p.M && n < p.N)) r[i][s] = *(const u32x4_at2*)at;
       }
+    };
+    // the last N & 7 of 8 columns, in front
+    auto shift = [&](const u32x4& w) __attribute__((always_inline)) {
+      const uint64_t lo = (uint64_t)w[1] << 32 | w[0], hi = (uint64_t)w[3] << 32 | w[2];
+      const int bits = 16 * (8 - (p.N & 7));
+      const uint64_t x = bits < 64 ? lo >> bits | hi << (64 - bits) : hi >> ((bits - 64) & 63), y = bits < 64 ? hi >> bits : 0;
+      return u32x4{(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
     };
     auto spread = [&](int i) __attribute__((always_inline)) {
       fence();
 #pragma unroll
-      for (int s = 0; s < 2; ++s) *(u32x4*)(turn + ((out + s * 1024) ^ (s * 64))) = r[i][s];
+      for (int s = 0; s < 2; ++s) {
+        if (EDGE && nw + sc * 8 + 8 > p.N) r[i][s] = shift(r[i][s]);
+        *(u32x4*)(turn + ((out + s * 1024) ^ (s * 64))) = r[i][s];
+      }
       fence();
 #pragma unroll
       for (int j = 0; j < FN; ++j) rf[j] = *(const u32x2*)(turn + (in16 ^ (j * 32)));
@@ -632,7 +637,7 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
 // with B m-major); the leading dimension of an m-major operand covers its row count rounded up to 8; GELU with
 // both operands k-major; both operands m-major: no bias or residual; row sums with A m-major, shared by
 // BM / 64 column tiles (fewer are refused); a reduction in parts with B m-major; parts of more k tiles than the
-// loads run ahead (into the block's next unit at most); 2 GB for a tile's rows.
+// loads run ahead (into the block's next unit at most); 2 GB for a tile's rows; N >= 8 with a residual.
 template <int FM>
 bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
@@ -643,7 +648,7 @@ bool launch_large(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1
   if (!p.b_k && p.ldb < up8(p.N)) return false;
   if (p.a_rowsum && (p.a_k || p.N <= (large::Sizes<FM>::BM / 64 - 1) * large::LBN)) return false;
   if (p.splits > 1 && (p.b_k || p.bias || p.resid)) return false;
-  if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;
+  if (p.lda >= (1 << 21) || p.ldb >= (1 << 21) || (p.resid && p.N < 8)) return false;
   for (int i = 0; i < p.splits; ++i)
     if (p.kb[i + 1] - p.kb[i] <= large::Sizes<FM>::NB * large::LBK) return false;
   if (p.a_k && p.b_k) {
