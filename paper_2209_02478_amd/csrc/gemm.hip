@@ -343,16 +343,16 @@ static int rounds(int tiles) { return (tiles + 255) / 256; }
 // by 0-6 %; from there on the larger are ahead by up to a fifth.  Left to the kernels with 128 x 128, of which a
 // compute unit holds two or three, times of the large tiles over theirs:
 // - fewer than 66 large tiles
-// - B m-major where a second round of large tiles has just begun (257-280): 0.91-1.10 for data gradients and
-//   1.00-1.14 for both operands m-major, K = 512-6400.  With B k-major the tiles of 128 rows are ahead there too,
+// - B m-major where a second round of large tiles has just begun: 0.91-1.10 for data gradients (257-280) and
+//   0.95-1.14 for both operands m-major (257-300), K = 512-6400.  With B k-major the tiles of 128 rows are ahead there too,
 //   0.70-0.97 from K = 768 on and 0.73-1.02 at 512
 // - one round of their own, 512, where tiles of 128 rows have begun a second one (a last column tile at most half
 //   full, as in 2816 x 2944 or 16391 x 257): 0.95-1.88 with B m-major; with B k-major 0.84-1.70 up to K = 1024, 1.2 in
 //   the mean, 0.80-1.30 at 2048 and 0.78-1.14 at 4096
-static int large_rows(int M, int N, int K, bool b_k) {
+static int large_rows(int M, int N, int K, bool a_k, bool b_k) {
   if (M < 256 || N < 256 || K < 512) return 0;
   const int large = gemm_large_tiles(M, N), r = rounds(large), r128 = rounds(tiles128(M, N));
-  if (large < 66 || (!b_k && large > 256 && large <= 280)) return 0;
+  if (large < 66 || (!b_k && large > 256 && large <= (a_k ? 280 : 300))) return 0;
   if (r == 1 && r128 == 2 && ((M + BM - 1) / BM) * ((N + BN - 1) / BN) <= 512 && (!b_k || K < 4096)) return 0;
   return 2 * r128 <= 3 * r ? 128 : 256;
 }
@@ -528,7 +528,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   }
   // large tiles (a choice made from the shape alone)
   if (p.splits == 1) {
-    const int rows = large_rows(g.M, g.N, g.K, g.b_kmajor);
+    const int rows = large_rows(g.M, g.N, g.K, g.a_kmajor, g.b_kmajor);
     if (rows == 256 && launch_bgemm_large(p, st, g.time_start, g.time_stop)) return true;
     if (rows && launch_bgemm_large128(p, st, g.time_start, g.time_stop)) return true;   // (row sums of few columns too)
   }
