@@ -13,9 +13,10 @@
 // three slots of A and two of B, FM = 4 four and three.  A is requested NB k tiles ahead half a turn
 // earlier than B.  A load is one buffer instruction with a per-lane offset that is fixed for the tile
 // and a scalar base that moves along k: its descriptor stays in scalar registers, so issuing it takes the write
-// of M0, the wait state behind that and the load, and the loop has no branch around it (a wave that has to branch around its loads loses about 60 clocks for each).  The loads
-// run through the tile boundary: while a tile's last MFMAs and its store run, the first k tiles of the
-// block's next one are on their way, so only a block's first tile waits for memory.
+// of M0, the wait state behind that and the load, and the loop has no branch around it (a wave that has to
+// branch around its loads loses about 60 clocks for each).  The loads run through the tile boundary: while a tile's
+// last MFMAs and its store run, the first k tiles of the block's next one are on their way, so only a block's first
+// tile waits for memory.
 //
 // The eight waves run freely, two on each SIMD, and meet once per k tile; a fragment's register takes
 // the next half's as soon as the MFMAs that use it are issued.  K tile t, a wave's view:
@@ -32,7 +33,7 @@
 // residuals take the same way in.  Whole lines with the lanes across the rows, by exchanges between
 // lanes, leave a unit at 31 bytes per clock, along the rows at 104.  Whole launches of 262144 x 1024, K = 512,
 // the one against the other (us): bf16 312 -> 293, with residual 340 -> 331, fp32 370 -> 346, with
-// residual 442 -> 424, data gradient 298 -> 277 (with all its tiles in one block); between tiles 8.0 -> 6.6 us in bf16, 11.9 -> 10.2 in fp32.  The
+// residual 442 -> 424, data gradient 298 -> 277; between tiles 8.0 -> 6.6 us in bf16, 11.9 -> 10.2 in fp32.  The
 // loads of the first turn after a store wait at its end, so that its MFMAs are not held up behind the
 // stores on their way out (bert_base 32 x 200 iterations 0.5 %, 32 x 512 1.5, bert_stages 32 x 332 1.1).
 //
@@ -188,7 +189,7 @@ struct LTileOf {
 // one without them do not fit the registers there, and reloads in the loop wait for its loads to LDS (10624 x 1024,
 // K = 4096: 110 us and, without sums, 105; apart 86 and 80), so every tile takes them.
 template <int FM, bool AK, bool BKM, bool KTAIL, int GE, bool SUMS>
-__global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd, int turns) {
+__global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n, int total, int per_xcd) {
   using namespace large;
   typedef Sizes<FM> Z;
   typedef LTileOf<AK, Z::BM> TA;
@@ -199,13 +200,12 @@ __global__ __launch_bounds__(512) void bgemm_large_kernel(GemmDev p, int tiles_n
   extern __shared__ __attribute__((aligned(1024))) unsigned char l_smem[];
   bf16_t* const ring = (bf16_t*)l_smem;
   bf16_t* const ring_b = ring + Z::NA * Z::A_TILE;
-  // Block ids go to the 8 XCDs in turn: XCD x gets the run of per_xcd units from x * per_xcd on, 32 of its
-  // blocks (one per compute unit) every 32nd of the next 32 * turns of them.  Units run part by part (all tiles of
+  // Block ids go to the 8 XCDs in turn: XCD x gets the run of per_xcd units from x * per_xcd on, each of its 32
+  // blocks (one per compute unit) every 32nd of them.  Units run part by part (all tiles of
   // the first k range, then of the second, ...): a run then shares one k range of both operands in the L2.
   constexpr int stride = 32;
-  const int first = (blockIdx.x >> 8) * stride * turns;
-  int unit = (blockIdx.x & 7) * per_xcd + first + ((blockIdx.x >> 3) & 31);
-  const int u_end = min((int)(blockIdx.x & 7) * per_xcd + min(per_xcd, first + stride * turns), total);
+  int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  const int u_end = min((int)(blockIdx.x & 7) * per_xcd + per_xcd, total);
   if (unit >= u_end) return;
   const int n_tiles = total / p.splits, tiles_m = (p.M + Z::BM - 1) / Z::BM;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -620,17 +620,14 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   constexpr int BM = large::Sizes<FM>::BM;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + large::LBN - 1) / large::LBN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
-  // A block takes all its tiles, but two of a data gradient with six or more for each compute unit: the weight
-  // gradients on the other stream get their units sooner, for the price of a tile's first loads (262144 x 1024,
-  // K = 512 alone, the shortest: 277 -> 304 us; K = 4096 1610 -> 1660).  (Iterations of
-  // bert_large_stress 256 x 512 409.9 ms with all tiles in a block, 405.8 in twos, 408.0 in fours; with less than six
-  // 60.0 -> 60.2 and 19.93 -> 20.12 ms, gpt2_medium 16 x 1024 and bert_base 32 x 512.)
-  const int rounds = (per + 31) / 32, turns = AK && !BKM && rounds >= 6 ? 2 : rounds;
-  const dim3 grid(per < 32 ? 8 * per : 256 * ((rounds + turns - 1) / turns)), block(512);
+  // A block takes all its tiles.  Two of a data gradient's to a block where each unit gets six or more (the weight
+  // gradients on the other stream get their units sooner) are behind: alone 262144 x 1024, K = 512 277 -> 304 us,
+  // iterations of bert_large 64 x 512 93.1 -> 93.9 ms, bert_large_stress 256 x 512 393.5 -> 394.5, 192 x 512 292.8 -> 294.4.
+  const dim3 grid(8 * (per < 32 ? per : 32)), block(512);
   bool ktail = false;
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % large::LBK != 0;
-  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
-  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per, turns);
+  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
 }
 
 // Requirements: K % 8 == 0 when an operand is k-major (or zeros vouched for behind a k-major A's last column,

@@ -196,7 +196,7 @@ def test_gemm_large_tiles(a_k, b_k):
 @pytest.mark.parametrize("M,N,K", [(5000, 4872, 776),    # 400 tiles of 256 x 256 in two rounds, ragged in each dimension
                                    (4700, 4300, 520),    # 629 tiles of 128 x 256 in three rounds
                                    (25600, 768, 640),    # 600 of them, whole in each dimension
-                                   (9000, 9736, 520),    # 1404 tiles of 256 x 256 in six rounds: data gradients in blocks of two tiles
+                                   (9000, 9736, 520),    # 1404 tiles of 256 x 256 in six rounds
                                    (9216, 9472, 576),    # 1332, whole in each dimension
                                    (1000, 256, 1032),    # row sums: one column tile, which is too few
                                    (3000, 300, 1096),    # two, the fewest
