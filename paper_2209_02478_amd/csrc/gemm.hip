@@ -339,7 +339,7 @@ static int rounds(int tiles) { return (tiles + 255) / 256; }
 // One block per compute unit, so the time is a whole number of rounds of 256 tiles; a round of the
 // smaller tiles takes about two thirds of one of the larger (0.95 against 1.5 us per 64 reduction indices,
 // and 6-8 us of start and store).  One round against two thirds: ahead by 20-28 % at 88-128 large tiles
-// (8192 x 768 K = 3072: 74 -> 54 us; 6352 x 1024 K = 4096: 88 -> 64), three against two (320 large tiles)
+// (8192 x 768, K = 3072: 74 -> 49 us; 6352 x 1024, K = 4096: 87 -> 57), three against two (320 large tiles)
 // by 0-6 %; from there on the larger are ahead by up to a fifth.  Left to the kernels with 128 x 128, of which a
 // compute unit holds two or three, times of the large tiles over theirs:
 // - fewer than 66 large tiles

@@ -24,7 +24,7 @@
 //     half 1, the first quarter   :  MFMAs
 //     own loads of tile t + 1 have landed, own reads of tile t are done: all waves meet
 //     half 1, the rest            :  MFMAs; reads of tile t + 1, half 0; loads of B tile t + NB (slot of tile t)
-// FM = 8: 2450 clocks per k tile with everything in the L2, of which MFMAs alone take 2048, the meeting
+// FM = 8, before the descriptors stayed in scalar registers: 2450 clocks per k tile with everything in the L2, of which MFMAs alone take 2048, the meeting
 // about 200 and the fragment reads 100.
 //
 // A tile's store: the MFMA's operand roles are swapped (rows of B feed its A side), so a lane holds 4
@@ -37,13 +37,13 @@
 // loads of the first turn after a store wait at its end, so that its MFMAs are not held up behind the
 // stores on their way out (bert_base 32 x 200 iterations 0.5 %, 32 x 512 1.5, bert_stages 32 x 332 1.1).
 //
-// Measured with rotating operands on one box, against the tiles of 256 x 256 in 32 x 32 x 16 MFMAs with a
-// block per tile that this replaced (us): 65536 x 3072, K = 1024, bf16 401 -> 350; 65536 x 4096, K = 1024,
-// with GELU 712 -> 631; 65536 x 1024, K = 4096, fp32 with residual 481 -> 430; data gradients 65536 x 4096
-// K = 1024 523 -> 466, 65536 x 1024 K = 4096 471 -> 446 (before the store through LDS).  1.45 us per 64
-// reduction indices, bound by power; between tiles 5-10 us, bound by the stores' way into the L2, 15 with
-// residuals or GELU (starting some compute units or XCDs half a tile later, or streaming stores, changed
-// nothing).
+// Measured with rotating operands in one run, against the tiles of 256 x 256 in 32 x 32 x 16 MFMAs with a
+// block per tile that this replaced (us): 65536 x 3072, K = 1024, bf16 454 -> 387; 65536 x 4096, K = 1024,
+// with GELU 746 -> 624; 65536 x 1024, K = 4096, fp32 with residual 488 -> 449; data gradients 65536 x 4096,
+// K = 1024 545 -> 462, 65536 x 1024, K = 4096 454 -> 410; weight gradient 30528 x 1024, K = 20480 with row sums
+// 1164 -> 1076.  1.45 us per 64 reduction indices, bound by power; between tiles 5-10 us, bound by the stores'
+// way into the L2, 15 with residuals or GELU (starting some compute units or XCDs half a tile later, or
+// streaming stores, changed nothing).
 //
 // LDS layouts (16-byte chunks permuted so that fragment reads are conflict-free although a direct
 // load can only write 1 KB contiguously):

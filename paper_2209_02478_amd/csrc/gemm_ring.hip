@@ -8,6 +8,10 @@
 // same chain of MFMAs over ascending k as in the kernels with larger tiles, so which
 // kernel a product gets does not change a bit of it.
 //
+// All four layouts in all four tile sizes: forward, data gradients, and through the kernel-level entry point products with
+// both operands m-major that are no weight gradient (768 x 768, K = 20480 in bf16: 66 us, 228 on 128 x 256 tiles).
+// Weight gradients that nothing runs beside come in 128 x 128, with parts and row sums (ring_wgrad in gemm.hip).
+//
 // LDS tiles: a k-major tile
 // [rows][64 k] keeps chunk kc of row r at kc ^ ((r >> 1) & 7); an m-major tile [64 k][R rows] keeps
 // chunk mc of k row q at mc ^ s(q), with s so that four k rows read together meet different banks:

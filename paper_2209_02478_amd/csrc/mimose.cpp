@@ -646,8 +646,8 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
 //   by 0.7-3.4 % at 96-150 tiles and from 320 on (3.2 % there, 0.2 % at 1024).  At 160 tiles (one
 //   measurement, causal) it was ahead by 1.5 % too: the line at 192 is on the safe side.
 // - a forward of a few thousand elements per tensor is its launches: 2 layers of 64 columns in one
-//   piece are ahead by 18-20 % at 2048 to 16896 elements per tensor and by 13 % at 32768.  Above, the
-//   line is not a sharp one: 12 bf16 layers of 768 columns in one piece are behind by 3 % at 24576 and
+//   piece are ahead by 18-20 % at 2048 to 16896 elements per tensor and by 13 % at 32768, where the line is.
+//   Above it there is no one line for all models: 12 bf16 layers of 768 columns in one piece are behind by 3 % at 24576 and
 //   36864 elements, ahead by 10 % at 56832, by 4-6 % at 98304-196608, behind by 0.5-1.3 % at
 //   294912-393216 and level at 786432; in fp32 ahead by 1-2 % at 24576-122880 and behind by 4 % at
 //   393216; 24 causal layers of 1024 columns ahead by 1-3 % at 131072-262144.
@@ -726,7 +726,9 @@ void Step::layer_backward(int l, LayerActs& A) {
   if (guard_gA && hipEventRecord(c_->ev_w2, c_->side) != hipSuccess)
     throw StepError{MIMOSE_ERR_HIP, "marking the weight-gradient stream failed"};
   // behind the product: in front of it this small kernel waits for a compute unit beside the main stream's
-  // next product and the weight gradient with it (padded 12 x 397 with dropout 8.65 -> 8.49 ms an iteration)
+  // next product and the weight gradient with it (padded 12 x 397 with dropout 8.75 -> 8.62 ms an iteration;
+  // bert_base 32 x 200 7.96 -> 7.93, 32 x 88 5.06 -> 5.08, bert_stages 32 x 332 padded 9.04 -> 9.07, the fp32
+  // one of 2 layers 0.474 -> 0.473)
   if (part2) ln_bwd_reduce(part2, p.ln2g, p.ln2b);
   void* dact = talloc(TF);
   dgrad(dffn, H, H, p.w2, dact, F);
