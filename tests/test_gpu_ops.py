@@ -198,8 +198,9 @@ def test_gemm_large_tiles(a_k, b_k):
                                    (25600, 768, 640),    # 600 of them, whole in each dimension
                                    (9000, 9736, 520),    # 1404 tiles of 256 x 256 in six rounds
                                    (9216, 9472, 576),    # 1332, whole in each dimension
-                                   (1000, 256, 1032),    # row sums: one column tile, which is too few
-                                   (3000, 300, 1096),    # two, the fewest
+                                   (17000, 256, 1032),   # row sums: one column tile, which is too few (266 units: past the ring's round)
+                                   (11000, 300, 1096),   # two, the fewest (258 units)
+                                   (3000, 300, 1096),    # 72 units: the ring
                                    (20000, 768, 584)])   # three, of the four that 256 rows take
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0), (0, 1)])
 def test_gemm_large_tiles_bits(M, N, K, a_k, b_k):
