@@ -409,7 +409,7 @@ static void launch_bgemm(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEve
 // direct-to-LDS pipeline (gemm_dma.hip); false when the operands do not meet its alignment rules
 bool launch_bgemm_dma(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
 
-// fp32 on the matrix cores (gemm_f32.hip)
+// fp32 on the bf16 matrix cores (gemm_f32.hip)
 void launch_sgemm(const GemmDev& p, int rows, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
 
 // small tiles, deep ring (gemm_ring.hip); false when the operands do not meet its alignment rules

@@ -1,0 +1,96 @@
+"""fp32 products, whose operands are split in three bf16 parts, against 64-bit products: every block
+tile and number of ways the launcher chooses, at ragged ends, in every layout."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2209_02478_amd as mi
+from oracle import model as om
+from gpu_util import DEV, host, sync
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24                        # unit roundoff of fp32
+
+# (M, N, K) -> block tile and ways it gets; remainders of tiles, of slices and of ways' turns
+SHAPES = [(1, 1, 1), (33, 65, 31), (130, 129, 100), (130, 70, 515),       # 32 x 32, four ways
+          (130, 2300, 250), (129, 2305, 32),                              # 32 x 32, two
+          (260, 2300, 99), (520, 1030, 1000),                             # 64 x 64, two
+          (900, 900, 70), (1100, 1030, 260),                              # 64 x 64, one
+          (1500, 1500, 70), (1410, 3000, 130)]                            # 128 x 128
+
+
+def put(X, kmajor, pad):
+    """X [rows, K] as the operand lies on the device, and its leading dimension (pad 3: no 16-byte rows)."""
+    Y = X if kmajor else X.T
+    buf = np.full((Y.shape[0], (Y.shape[1] + 3) // 4 * 4 + pad), np.nan, np.float32)    # the padding is not read
+    buf[:, :Y.shape[1]] = Y
+    return torch.from_numpy(buf).to(DEV), buf.shape[1]
+
+
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_split_products(M, N, K, a_k, b_k):
+    rng = np.random.default_rng(M + 3 * N + 5 * K + a_k + 2 * b_k)
+    A, B = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    bias, resid = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    a64, b64 = A.astype(np.float64), B.astype(np.float64)
+    prod, mag = a64 @ b64.T, np.abs(a64) @ np.abs(b64).T
+    # three left-out products of 2^-27, 32 products of a slice in one rounding, one rounding a slice in
+    # the large sum (the small ones' are 2^-8 of it), the ways' sums, bias and residual
+    bound = (K / 32 + 16) * U * (mag + np.abs(bias) + np.abs(resid)) + 1e-30
+    for pad in (0, 3):
+        dA, lda = put(A, a_k, pad)
+        dB, ldb = put(B, b_k, pad)
+        C = torch.full((M, N + 5), 7.0, device=DEV)
+        G = torch.full((M, N + 5), 7.0, device=DEV)
+        rs = torch.full((M + 1,), 9.0, device=DEV)
+        mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C, N + 5, 0, M, N, K, bias=torch.from_numpy(bias).to(DEV),
+                          resid=torch.from_numpy(resid).to(DEV), ldr=N, gelu_out=G, gelu=1, a_rowsum=rs)
+        sync()
+        got = host(C)
+        pre = prod + bias + resid
+        assert np.all(np.abs(got[:, :N] - pre) <= bound)
+        assert np.all(got[:, N:] == 7.0) and np.all(host(G)[:, N:] == 7.0), "wrote outside the N columns"
+        # GELU's slope is at most 1.13; its own evaluation a few roundings
+        assert np.all(np.abs(host(G)[:, :N] - om.gelu_fwd(pre, False)) <= 1.13 * bound + 16 * U * (1 + np.abs(pre)))
+        s = host(rs)
+        assert np.all(np.abs(s[:M] - a64.sum(1)) <= (K / 4 + 16) * U * np.abs(a64).sum(1)) and s[M] == 9.0
+        # aligned rows of C: the same bits through 8-byte stores
+        C2 = torch.full((M, (N + 3) // 4 * 4), 7.0, device=DEV)
+        mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C2, C2.shape[1], 0, M, N, K, bias=torch.from_numpy(bias).to(DEV))
+        C3 = torch.full((M, N + 5), 7.0, device=DEV)
+        mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C3, N + 5, 0, M, N, K, bias=torch.from_numpy(bias).to(DEV))
+        sync()
+        assert torch.equal(C2[:, :N], C3[:, :N])
+
+
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K", [(130, 129, 100), (130, 2300, 250), (260, 2300, 99), (900, 900, 70), (1500, 1500, 70)])
+def test_infinities_and_nan(M, N, K, a_k, b_k):
+    """Values the split cannot carry come out as fp32 arithmetic has them, and disturb no other output."""
+    rng = np.random.default_rng(K)
+    A, B = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    A[3, 5] = np.inf
+    A[70, 9] = np.nan
+    B[11, 2] = -np.inf
+    B[20, 5] = 0.0                                                 # inf * 0
+    A[100, 7] = np.finfo(np.float32).max                           # rounds to infinity as bf16
+    B[:, 7] *= 0.125
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = A.astype(np.float64) @ B.astype(np.float64).T
+        want = ref.astype(np.float32)
+    dA, lda = put(A, a_k, 0)
+    dB, ldb = put(B, b_k, 0)
+    C = torch.zeros((M, N), device=DEV)
+    mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C, N, 0, M, N, K)
+    sync()
+    got = C.cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    with np.errstate(invalid="ignore", over="ignore"):
+        mag = np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64)).T
+    # the tiles taken again round for every two indices
+    assert np.all(np.abs(got[fin] - ref[fin]) <= (K / 2 + 16) * U * mag[fin])
