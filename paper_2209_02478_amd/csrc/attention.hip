@@ -316,20 +316,11 @@ __global__ __launch_bounds__(128) void attn_bwd_dkv_kernel(const T* __restrict__
       const float lss[4] = {ls.x, ls.y, ls.z, ls.w}, dls[4] = {dl.x, dl.y, dl.z, dl.w};
       // Dropout: a lane holds one key and four queries, a generator block four keys of one query.
       // The four lanes of a quad (four neighbouring keys) each make the block of one of the four
-      // queries and pass its words round.
+      // queries and pass its decisions round.
       bool keep[4] = {true, true, true, true};
       if (drop.thr) {
-        const int c = lane & 3;
-        const int qmine = min(q0 + qq + c, sm.n - 1);
-        const uint4 w = attn_drop_words(drop, (int64_t)bh * L + qmine, (L + 3) >> 2, ki & ~3);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const uint32_t got = __shfl(pick_word(w, (c - t) & 3), (lane & ~3) | ((c + t) & 3), 64);
-          const bool kp = got >= drop.thr;
-          const int e = (c + t) & 3;
-          keep[0] = e == 0 ? kp : keep[0]; keep[1] = e == 1 ? kp : keep[1];
-          keep[2] = e == 2 ? kp : keep[2]; keep[3] = e == 3 ? kp : keep[3];
-        }
+        const int qmine = min(q0 + qq + (lane & 3), sm.n - 1);
+        quad_keep(attn_drop_words(drop, (int64_t)bh * L + qmine, (L + 3) >> 2, ki & ~3), drop.thr, lane, keep);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {

@@ -456,21 +456,11 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dkv_kernel(const bf16_t* __rest
         const float nls[4] = {nl.x, nl.y, nl.z, nl.w}, dls[4] = {dl.x, dl.y, dl.z, dl.w};
         // Dropout: this lane holds one key and four queries; a generator block covers four keys
         // of one query.  The four lanes of a quad (four neighbouring keys) each make the block of
-        // one of the four queries and pass its words round: in turn t a lane receives, from the
-        // lane t places on, the word of its own key for that lane's query.
+        // one of the four queries and pass its decisions round.
         bool keep[4] = {true, true, true, true};
         if (DROP) {
-          const int c = lane & 3;
-          const int qmine = min(q0 + qq + c, sm.n - 1);
-          const uint4 w = attn_drop_words(drop, (int64_t)bh * L + qmine, (L + 3) >> 2, ki & ~3);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const uint32_t got = __shfl(pick_word(w, (c - t) & 3), (lane & ~3) | ((c + t) & 3), 64);
-            const bool k = got >= drop.thr;
-            const int e = (c + t) & 3;
-            keep[0] = e == 0 ? k : keep[0]; keep[1] = e == 1 ? k : keep[1];
-            keep[2] = e == 2 ? k : keep[2]; keep[3] = e == 3 ? k : keep[3];
-          }
+          const int qmine = min(q0 + qq + (lane & 3), sm.n - 1);
+          quad_keep(attn_drop_words(drop, (int64_t)bh * L + qmine, (L + 3) >> 2, ki & ~3), drop.thr, lane, keep);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
