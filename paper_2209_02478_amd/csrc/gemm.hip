@@ -427,6 +427,21 @@ static int ring_variant(int M, int N) {
   return tiles(128, 128) <= 256 ? 3 : -1;
 }
 
+// small tiles behind long reductions (gemm_tiles.hip); false when the operands do not meet its rules
+bool launch_bgemm_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+// From K = 1536 on its k steps pay (K = 768: level, the launch and the first loads are most of the time).  Its tiles are
+// 32 x 32, 64 x 64, 96 x 64 and 128 x 64 (variants 0..3); 64 x 32 and 128 x 128 stay with the ring (350 x 768, K = 3072
+// on 64 x 64 12.0 us, 11.3 there; 3312 x 768 on 128 x 128 level).
+static int tiles_variant(int M, int N, int K) {
+  if (K < 1536) return -1;
+  auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
+  if (tiles(32, 32) <= 256) return 0;
+  if (tiles(64, 32) <= 256) return -1;
+  if (tiles(64, 64) <= 256) return 1;
+  if (tiles(96, 64) <= 256) return 2;
+  return tiles(128, 64) <= 256 ? 3 : -1;
+}
+
 // Weight gradients that nothing runs beside keep the parts of their reduction (gemm_splits) and with them the
 // number of units.  Where these fit one round the ring's 128 x 128 tiles are ahead of the 128 x 256 tiles, which
 // leave half of it idle (256 units at 4096 x 1024: 208 us against 257 at K = 20480, 28.9 against 34.9 at K = 2000;
@@ -523,7 +538,8 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   // (gpt2_medium 16 x 397), 1.002-1.004 (bert_base 32 x 88, 200, 256), 1.000 (padded 12 x 397 with
   // dropout) and 0.995 (bert_large 16 x 256).
   if (p.splits == 1 && !g.a_rowsum) {
-    const int which = ring_variant(rule_rows, g.N);
+    const int small = tiles_variant(rule_rows, g.N, g.K), which = ring_variant(rule_rows, g.N);
+    if (small >= 0 && launch_bgemm_tiles(p, small, st, g.time_start, g.time_stop)) return true;
     if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
   }
   // large tiles (a choice made from the shape alone)

@@ -11,6 +11,41 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers
 
 
+// ---- direct loads from memory to LDS through buffer descriptors --------------------------------
+typedef __attribute__((address_space(3))) void lds_void_l;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4_l;
+
+// Offsets from a buffer's size on lie outside: such a lane's 16 bytes of LDS are written with zeros.  No
+// buffer is larger than this.
+constexpr uint32_t kOutside = 0x80000000u;
+
+// One wave-level direct load: lane i's 16 bytes at base + offset land at lds + 16 * i.  Inline assembly,
+// so the compiler does not track it: the waits are placed by hand in the loop, and so is the wait state
+// between a write of M0 and the load that reads it (s_nop), which the hardware leaves to the program.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // m0 is a reserved register: named as clobbered on purpose
+__device__ __forceinline__ void l_direct_load(uint64_t base, uint32_t bytes, uint32_t offset, uint32_t lds_byte_address) {
+  const u32x4 r = {(uint32_t)base, (uint32_t)(base >> 32), bytes, 0x00020000u};                 // raw buffer
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(offset), "s"(r), "s"(lds_byte_address) : "memory", "m0");
+}
+// A descriptor's address and size, the same in all lanes, settled in scalar registers: a scalar register that
+// a vector instruction (readfirstlane) wrote may be read by a load five wait states later, which the hardware
+// does not wait for either.  What comes out of the assembly counts as scalar from here on: moved and added to
+// by scalar instructions alone, which need no wait.
+__device__ __forceinline__ void l_descriptor(const void* p, uint32_t size, uint64_t& base, uint32_t& bytes) {
+  const uint64_t a = (uint64_t)p;
+  uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32));
+  bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)size);
+  asm volatile("s_nop 4" : "+s"(lo), "+s"(hi), "+s"(bytes));
+  base = (uint64_t)lo | (uint64_t)hi << 32;
+}
+// a / b, the same in all lanes: vector instructions compute it, and without this all that follows from it
+__device__ __forceinline__ int l_div(int a, int b) { return __builtin_amdgcn_readfirstlane(a / b); }
+__device__ __forceinline__ uint32_t l_lds_address(const void* p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_l*)p);
+}
+#pragma clang diagnostic pop
+
 struct GemmDev {
   const void* A; const void* B; void* C;
   const void* bias; const void* resid; void* gelu_out; float* a_rowsum;

@@ -765,3 +765,37 @@ def test_dropout_inside_layernorm(dtype, wide, T, H, shift):
         with pytest.raises(mi.MimoseError):
             mi.mimose_op_layernorm_bwd_dropout(dtype, ddy, wide, xs, wide, dg_, out, dadd, alias, dgam, dbet, partial, T, H,
                                                1e-5, p, seed, site, step)
+
+
+@pytest.mark.parametrize("rows,N,K", [(1, 8, 1536), (74, 768, 1544), (300, 776, 3072),          # 32 x 32 tiles: one, a tail, ragged
+                                      (700, 1000, 1600), (640, 1024, 1656),                     # 64 x 64: a stage half full, a tail in its first half
+                                      (1500, 1032, 1664), (1441, 1024, 1736),                   # 96 x 64
+                                      (2000, 1032, 1536), (2048, 1000, 1592)])                  # 128 x 64
+@pytest.mark.parametrize("b_k", [1, 0])
+def test_gemm_long_reductions_bits(rows, N, K, b_k):
+    """Few rows behind a long reduction: the bits are those of the same rows in a product of more,
+    which other kernels do, in every form of the store."""
+    g = torch.Generator(device=DEV).manual_seed(rows + K + b_k)
+    up = lambda v: (v + 7) // 8 * 8
+    mk = lambda r, c: (torch.randn((r, c), generator=g, device=DEV) * 0.5).to(torch.bfloat16)
+    M = rows + 6000
+    A, B, bias, resid = mk(M, K), mk(N, K) if b_k else mk(K, up(N)), mk(1, up(N))[0], mk(M, up(N))
+    forms = [dict(c_f32=1), dict(c_f32=1, bias=1, resid=1), dict(c_f32=0, resid=1), dict(c_f32=0, bias=1),
+             dict(c_f32=0, bias=1, gelu=1), dict(c_f32=0, bias=1, resid=1, gelu=2)]
+    for form in forms:
+        for pitch in (up(N) + 8, N + 3):                        # rows of C on 16 bytes, and not
+            if form.get("gelu") and pitch != up(N) + 8:         # (off 16 bytes GELU is the C library's in every kernel but the store of 8 columns)
+                continue
+            def product(r0, n_rows):
+                C = torch.full((n_rows, pitch), 7.0, dtype=torch.float32 if form["c_f32"] else torch.bfloat16, device=DEV)
+                G = torch.full_like(C, 7.0) if form.get("gelu") else None
+                kw = {}
+                if form.get("bias"): kw["bias"] = bias
+                if form.get("resid"): kw.update(resid=resid[r0:], ldr=up(N))
+                if G is not None: kw.update(gelu_out=G, gelu=form["gelu"])
+                mi.mimose_op_gemm(1, A[r0:], K, 1, B, K if b_k else up(N), b_k, C, pitch, form["c_f32"], n_rows, N, K, **kw)
+                sync()
+                return [x for x in (C, G) if x is not None]
+            for full, alone in zip(product(0, M), product(0, rows)):
+                assert bool((alone[:, N:] == 7.0).all()), "wrote outside the N columns"
+                assert torch.equal(full[:rows, :N], alone[:, :N]), form
