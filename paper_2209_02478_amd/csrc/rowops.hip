@@ -330,14 +330,15 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
   }
 }
 
-// Backward: block = 4 waves = kRowsPerChunk rows, every wave takes 4 rows one after the other and
-// loads the next one's elements before the arithmetic of a row: three waves' registers fit a SIMD, where
-// all four rows' elements at once leave two (bf16 131072 x 1024 with the reduction 296 -> 241 us, 6400 x 768 19.7 ->
-// 18.5; with fp32 rows 20.8 -> 19.1, 300 -> 296, the copy rate).  All four rows' sums side by side gained
+// Backward: block = 4 waves = kRowsPerChunk rows, every wave takes 4 rows one after the other, AHEAD rows'
+// elements in registers.  Two where there are blocks for more than two to a unit: three waves then fit a SIMD,
+// where four rows' elements leave two (bf16 131072 x 1024 with the reduction 296 -> 241 us, 16384 x 768 39.7 -> 36.5;
+// with fp32 rows 300 -> 296, the copy rate, 38.3 -> 35.5).  Four for fewer blocks, which wait for memory
+// and not for each other (bert_base 32 x 88 with two: 0.5 % on the iteration).  All four rows' sums side by side gained
 // nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order of the sums over
 // rows; the sums over a row's columns run over other columns per lane.
-template <typename TD, typename TX, typename T, int NC>
-__global__ __launch_bounds__(256, 3) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
+template <typename TD, typename TX, typename T, int NC, int AHEAD>
+__global__ __launch_bounds__(256, AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
                                                          const T* __restrict__ gamma, T* __restrict__ dx,
                                                          const T* __restrict__ add, float* __restrict__ partial,
                                                          T* __restrict__ masked, DropRows dr, int Trows, int H, float eps) {
@@ -354,42 +355,42 @@ __global__ __launch_bounds__(256, 3) void ln_bwd_vec_kernel(const TD* __restrict
 #pragma unroll
     for (int e = 0; e < E; ++e) { if (c >= nchunks) g[i][e] = 0.f; sg[i][e] = 0.f; sb[i][e] = 0.f; }
   }
-  // rows in turn, the next one's elements on their way while one is worked on
-  float v[2][NC][E], d[2][NC][E];
+  float v[AHEAD][NC][E], d[AHEAD][NC][E];
   auto fetch = [&](int rr) {
     const int row = blockIdx.x * kRowsPerChunk + rr * 4 + wave;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int c = lane + 64 * i;
       if (row < Trows && c < nchunks) {
-        load_elems<TX, E>(x + (int64_t)row * H + c * E, v[rr & 1][i]);
-        load_elems<TD, E>(dy + (int64_t)row * H + c * E, d[rr & 1][i]);
+        load_elems<TX, E>(x + (int64_t)row * H + c * E, v[rr % AHEAD][i]);
+        load_elems<TD, E>(dy + (int64_t)row * H + c * E, d[rr % AHEAD][i]);
       } else {
 #pragma unroll
-        for (int e = 0; e < E; ++e) { v[rr & 1][i][e] = 0.f; d[rr & 1][i][e] = 0.f; }
+        for (int e = 0; e < E; ++e) { v[rr % AHEAD][i][e] = 0.f; d[rr % AHEAD][i][e] = 0.f; }
       }
     }
   };
-  fetch(0);
+#pragma unroll
+  for (int rr = 0; rr < AHEAD - 1; ++rr) fetch(rr);
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
     const int row = blockIdx.x * kRowsPerChunk + rr * 4 + wave;
     if (row >= Trows) break;
-    if (rr + 1 < R) fetch(rr + 1);
+    if (rr + AHEAD - 1 < R) fetch(rr + AHEAD - 1);
     float mean, rstd;
-    chunk_stats<NC, E>(v[rr & 1], nchunks, lane, H, eps, mean, rstd);
+    chunk_stats<NC, E>(v[rr % AHEAD], nchunks, lane, H, eps, mean, rstd);
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < NC; ++i)
       if (lane + 64 * i < nchunks)
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          const float xh = (v[rr & 1][i][e] - mean) * rstd;
-          v[rr & 1][i][e] = xh;
-          sg[i][e] += d[rr & 1][i][e] * xh;
-          sb[i][e] += d[rr & 1][i][e];
-          const float dxh = d[rr & 1][i][e] * g[i][e];
-          d[rr & 1][i][e] = dxh;
+          const float xh = (v[rr % AHEAD][i][e] - mean) * rstd;
+          v[rr % AHEAD][i][e] = xh;
+          sg[i][e] += d[rr % AHEAD][i][e] * xh;
+          sb[i][e] += d[rr % AHEAD][i][e];
+          const float dxh = d[rr % AHEAD][i][e] * g[i][e];
+          d[rr % AHEAD][i][e] = dxh;
           s1 += dxh;
           s2 += dxh * xh;
         }
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(256, 3) void ln_bwd_vec_kernel(const TD* __restrict
       if (c < nchunks) {
         float o[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) o[e] = rstd * (d[rr & 1][i][e] - s1 - v[rr & 1][i][e] * s2);
+        for (int e = 0; e < E; ++e) o[e] = rstd * (d[rr % AHEAD][i][e] - s1 - v[rr % AHEAD][i][e] * s2);
         if (add) {
           float a[E];
           Chunk<T>::load(add + (int64_t)row * H + c * E, a);
@@ -905,9 +906,11 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-#define V_(NC) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC>), grid, dim3(256), 0, st, (const TD*)dy, \
+    const bool many = grid.x > 512;
+#define A_(NC, AHEAD) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD>), grid, dim3(256), 0, st, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
+#define V_(NC) do { if (many) A_(NC, 2); else A_(NC, 4); } while (0)
     if (nc <= 1) { V_(1); return; }
     if (nc <= 2) { V_(2); return; }
     if constexpr (sizeof(T) == 4) {                   // (bf16 rows of 1024 are two chunks a lane)
@@ -917,6 +920,7 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
       return;
     }
 #undef V_
+#undef A_
   }
 #define M_(NPL) hipLaunchKernelGGL((ln_bwd_kernel<TD, TX, T, NPL>), grid, dim3(256), 0, st, (const TD*)dy,    \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, T_, H, eps)
