@@ -429,11 +429,12 @@ static int ring_variant(int M, int N) {
 
 // small tiles behind long reductions (gemm_tiles.hip); false when the operands do not meet its rules
 bool launch_bgemm_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1);
+constexpr int kLongSteps = 1536;
 // From K = 1536 on its k steps pay (K = 768: level, the launch and the first loads are most of the time).  Its tiles are
 // 32 x 32, 64 x 64, 96 x 64 and 128 x 64 (variants 0..3); 64 x 32 and 128 x 128 stay with the ring (350 x 768, K = 3072
 // on 64 x 64 12.0 us, 11.3 there; 3312 x 768 on 128 x 128 level).
 static int tiles_variant(int M, int N, int K) {
-  if (K < 1536) return -1;
+  if (K < kLongSteps) return -1;
   auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
   if (tiles(32, 32) <= 256) return 0;
   if (tiles(64, 32) <= 256) return -1;
@@ -531,16 +532,21 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
     if (p.splits > 1) launch_splitk_reduce(p, st, g.time_stop);
     return true;
   }
-  // Forward and data-gradient products that one round of smaller tiles covers.  Judged by the whole
-  // batch's rows, as in the products above, not by those of a half or of a batch without its padding:
-  // by a product's own rows more of them would come here, with the same bits and the iteration at
-  // 1.018 of its speed at 32 x 128 (bert_base), 1.017 (bert_stages, padded 32 x 332), 1.011
-  // (gpt2_medium 16 x 397), 1.002-1.004 (bert_base 32 x 88, 200, 256), 1.000 (padded 12 x 397 with
-  // dropout) and 0.995 (bert_large 16 x 256).
+  // Forward and data-gradient products that one round of smaller tiles covers, by the rows that are left of the batch;
+  // of a product run in two halves on two streams by the whole batch's, so that the halves share the round,
+  // and only where it has too many and the reduction is long, by the half's own.  No bit depends on it.  By the
+  // padded batch's rows padded iterations take 1.02-1.11 of the time (bert_stages 32 x 332, bert_large 40 x 300,
+  // bert_base 20 x 150, gpt2_medium 10 x 500).  Without the halves' own rows bert_large 32 x 150 takes 1.038,
+  // bert_base 32 x 180 1.028, 32 x 200 and 32 x 256 1.011-1.013, gpt2_medium 16 x 397 1.020; with them for short
+  // reductions too bert_stages 16 x 200 and gpt2_medium 8 x 300 1.014, bert_base 32 x 88 1.004; by them
+  // alone bert_stages 16 x 200 1.006, bert_large 16 x 256 1.004.
   if (p.splits == 1 && !g.a_rowsum) {
-    const int small = tiles_variant(rule_rows, g.N, g.K), which = ring_variant(rule_rows, g.N);
-    if (small >= 0 && launch_bgemm_tiles(p, small, st, g.time_start, g.time_stop)) return true;
-    if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
+    for (const int rows : {g.whole_rows > 0 ? g.whole_rows : g.M, g.M}) {
+      if (rows < g.whole_rows && g.K < kLongSteps) break;
+      const int small = tiles_variant(rows, g.N, g.K), which = ring_variant(rows, g.N);
+      if (small >= 0 && launch_bgemm_tiles(p, small, st, g.time_start, g.time_stop)) return true;
+      if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
+    }
   }
   // large tiles (a choice made from the shape alone)
   if (p.splits == 1) {

@@ -55,11 +55,12 @@ struct GemmArgs {
   // A k-major with K not a multiple of 8: its columns [K, K rounded up to 8) exist (lda covers
   // them) and hold zeros, so a kernel that moves whole 16-byte chunks may read them
   bool a_tail_zero = false;
-  // rows the choice of kernel is made from (0: M): a product issued in row ranges, or with padding
-  // left out of its rows, names the whole here.  A bf16 reduction long enough to be cut in parts and
-  // fp32's two tile sizes need it, because there the choice orders the sums; the small tiles of
-  // gemm_ring.hip go by it too, though no sum depends on them (see gemm)
+  // rows the choice of kernel is made from where the choice orders the sums (0: M): a bf16 reduction long
+  // enough to be cut in parts, fp32's tiles and ways.  A product issued in row ranges, or with padding left out
+  // of its rows, names the whole padded batch here
   int rule_rows = 0;
+  // rows of the whole that a product issued in row ranges is a part of (0: M), for choices that order no sum
+  int whole_rows = 0;
   // reduction over the rows of a batch with padding left out: the padded row count, and for each of
   // its blocks of kRowBlock rows (and one past the last) how many kept blocks lie before it (host)
   int k_padded = 0;

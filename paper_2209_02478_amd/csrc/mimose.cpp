@@ -613,6 +613,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
     a.resid = resid; a.ldr = out;
     a.gelu_out = act; a.gelu = ge;
     a.rule_rows = rule_rows();
+    a.whole_rows = T_;
     if (!mk::gemm(dt_, a, s)) throw StepError{MIMOSE_ERR_INVALID_ARG, "gemm: unsupported alignment"};
   };
   auto ln = [&](const void* x, int gi, int bi, void* y, bool x_f32) {
