@@ -330,21 +330,27 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
   }
 }
 
-// Backward: block = 4 waves = kRowsPerChunk rows, every wave takes 4 rows one after the other, AHEAD rows'
+// Backward: a block takes kRowsPerChunk rows.  Where every block has a compute unit of its own (256 blocks at most)
+// it has 16 waves, one for each row: a row is a chain of four sums over its columns, and one wave's four rows are
+// four chains (with the reduction, rows in bf16: 74 x 768 10.4 -> 8.3 us, 3312 x 768 14.3 -> 10.6; in fp32 with bf16 results
+// 9.4 -> 8.6 and 12.4 -> 11.1; 4096 x 1024 in fp32 15.6 -> 13.7).  From the 257th block on a unit gets a second
+// one, which waits for memory as the first does, and 16 waves are behind (10000 x 768 25.9 us against 21.3; level at 4400-8192 rows):
+// 4 waves take 4 rows each one after the other, AHEAD rows'
 // elements in registers.  Two where there are blocks for more than two to a unit: three waves then fit a SIMD,
 // where four rows' elements leave two (bf16 131072 x 1024 with the reduction 296 -> 241 us, 16384 x 768 39.7 -> 36.5;
 // with fp32 rows 300 -> 296, the copy rate, 38.3 -> 35.5).  Four for fewer blocks, which wait for memory
-// and not for each other (bert_base 32 x 88 with two: 0.5 % on the iteration).  All four rows' sums side by side gained
+// and not for each other.  All four rows' sums side by side gained
 // nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order of the sums over
 // rows; the sums over a row's columns run over other columns per lane.
-template <typename TD, typename TX, typename T, int NC, int AHEAD>
-__global__ __launch_bounds__(256, AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
+template <typename TD, typename TX, typename T, int NC, int AHEAD, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 16 ? 4 : AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
                                                          const T* __restrict__ gamma, T* __restrict__ dx,
                                                          const T* __restrict__ add, float* __restrict__ partial,
                                                          T* __restrict__ masked, DropRows dr, int Trows, int H, float eps) {
   constexpr int E = Chunk<T>::N;
-  constexpr int R = kRowsPerChunk / 4;
-  __shared__ float red[4][2][64 * NC * E];
+  constexpr int R = kRowsPerChunk / WAVES, Q = E / 4, COLS = 64 * NC * E;
+  static_assert((WAVES == 4 || R == 1) && AHEAD <= R, "rows of a wave");
+  __shared__ __attribute__((aligned(16))) float red[4][2][COLS];   // a lane's four columns e, .. e + 3 of chunk c at ((e / 4) (64 NC) + c) 4
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nchunks = H / E;
   float g[NC][E], sg[NC][E], sb[NC][E];
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(256, AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(con
   }
   float v[AHEAD][NC][E], d[AHEAD][NC][E];
   auto fetch = [&](int rr) {
-    const int row = blockIdx.x * kRowsPerChunk + rr * 4 + wave;
+    const int row = blockIdx.x * kRowsPerChunk + rr * WAVES + wave;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int c = lane + 64 * i;
@@ -371,12 +377,12 @@ __global__ __launch_bounds__(256, AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(con
     }
   };
 #pragma unroll
-  for (int rr = 0; rr < AHEAD - 1; ++rr) fetch(rr);
+  for (int rr = 0; rr < (AHEAD > 1 ? AHEAD - 1 : 1); ++rr) fetch(rr);
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
-    const int row = blockIdx.x * kRowsPerChunk + rr * 4 + wave;
+    const int row = blockIdx.x * kRowsPerChunk + rr * WAVES + wave;
     if (row >= Trows) break;
-    if (rr + AHEAD - 1 < R) fetch(rr + AHEAD - 1);
+    if (AHEAD > 1 && rr + AHEAD - 1 < R) fetch(rr + AHEAD - 1);
     float mean, rstd;
     chunk_stats<NC, E>(v[rr % AHEAD], nchunks, lane, H, eps, mean, rstd);
     float s1 = 0.f, s2 = 0.f;
@@ -419,22 +425,47 @@ __global__ __launch_bounds__(256, AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(con
       }
     }
   }
+  // A wave's sums: four waves hold four rows' each; of sixteen, four at a time add their row's to those
+  // of the four rows before, in the order in which one wave would.
+  float4* mine[2] = {(float4*)red[wave & 3][0] + lane, (float4*)red[wave & 3][1] + lane};
+  if (WAVES == 4 || wave < 4) {
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
+    for (int i = 0; i < NC; ++i)
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      red[wave][0][(lane + 64 * i) * E + e] = sg[i][e];
-      red[wave][1][(lane + 64 * i) * E + e] = sb[i][e];
-    }
+      for (int q = 0; q < Q; ++q) {
+        mine[0][64 * (q * NC + i)] = make_float4(sg[i][4 * q], sg[i][4 * q + 1], sg[i][4 * q + 2], sg[i][4 * q + 3]);
+        mine[1][64 * (q * NC + i)] = make_float4(sb[i][4 * q], sb[i][4 * q + 1], sb[i][4 * q + 2], sb[i][4 * q + 3]);
+      }
+  }
   __syncthreads();
+  if (WAVES > 4) {
+    for (int turn = 1; turn < WAVES / 4; ++turn) {
+      if (wave >> 2 == turn) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            float4 a = mine[0][64 * (q * NC + i)], b = mine[1][64 * (q * NC + i)];
+            const float(&xh)[E] = v[0][i];
+            a.x += sb[i][4 * q] * xh[4 * q]; a.y += sb[i][4 * q + 1] * xh[4 * q + 1];
+            a.z += sb[i][4 * q + 2] * xh[4 * q + 2]; a.w += sb[i][4 * q + 3] * xh[4 * q + 3];
+            b.x += sb[i][4 * q]; b.y += sb[i][4 * q + 1]; b.z += sb[i][4 * q + 2]; b.w += sb[i][4 * q + 3];
+            mine[0][64 * (q * NC + i)] = a;
+            mine[1][64 * (q * NC + i)] = b;
+          }
+      }
+      __syncthreads();
+    }
+  }
   float* prow = partial + (int64_t)blockIdx.x * 2 * H;
-  for (int c = threadIdx.x; c < 2 * H; c += 256) {
-    const int which = c / H, col = c - which * H;
-    float s = red[0][which][col];
-    s += red[1][which][col];
-    s += red[2][which][col];
-    s += red[3][which][col];
-    prow[c] = s;
+  for (int t = threadIdx.x; t < 2 * COLS; t += 64 * WAVES) {
+    const int which = t / COLS, at = t % COLS, col = at / 4 % (64 * NC) * E + at / (256 * NC) * 4 + at % 4;
+    if (col >= H) continue;
+    float s = red[0][which][at];
+    s += red[1][which][at];
+    s += red[2][which][at];
+    s += red[3][which][at];
+    prow[which * H + col] = s;
   }
 }
 
@@ -913,11 +944,11 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-    const bool many = grid.x > 512;
-#define A_(NC, AHEAD) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD>), grid, dim3(256), 0, st, (const TD*)dy, \
+    const bool many = grid.x > 512, few = grid.x <= 256;
+#define A_(NC, AHEAD, WAVES) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), 0, st, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
-#define V_(NC) do { if (many) A_(NC, 2); else A_(NC, 4); } while (0)
+#define V_(NC) do { if (few) A_(NC, 1, 16); else if (many) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
     if (nc <= 1) { V_(1); return; }
     if (nc <= 2) { V_(2); return; }
     if constexpr (sizeof(T) == 4) {                   // (bf16 rows of 1024 are two chunks a lane)

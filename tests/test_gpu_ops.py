@@ -483,6 +483,35 @@ def test_layernorm_fwd_bwd(dtype, x_f32, dy_f32, T, H):
             mi.mimose_op_layernorm_bwd(dtype, ddy, dy_f32, dx_, x_f32, dg_, ddy, None, dgam, dbet, partial, T, H, 1e-5)
 
 
+# 256 blocks of 16 rows have a wave for each row, 257 four: both add in the same order
+@pytest.mark.parametrize("dtype,wide", [(0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("H", [8, 768, 1024])
+def test_layernorm_bwd_waves_of_a_block(dtype, wide, H):
+    few, many = 4088, 4104                                   # the last of the 256 blocks is half full
+    g = torch.Generator(device=DEV).manual_seed(H)
+    storage = torch.bfloat16 if dtype else torch.float32
+    x = (torch.randn(many, H, generator=g, device=DEV) * 2 + 0.5).to(torch.float32 if wide else storage)
+    dy = torch.randn(many, H, generator=g, device=DEV).to(x.dtype)
+    dy[few:] = 0.0                                           # what the larger one adds to the sums
+    gamma = torch.randn(H, generator=g, device=DEV).to(storage)
+
+    def run(T):
+        dx = torch.zeros(T, H, dtype=storage, device=DEV)
+        partial = torch.zeros(mi.mimose_op_partial_rows(T) * 2 * H, device=DEV)
+        dgam, dbet = torch.zeros(H, device=DEV), torch.zeros(H, device=DEV)
+        mi.mimose_op_layernorm_bwd(dtype, dy, wide, x, wide, gamma, dx, None, dgam, dbet, partial, T, H, 1e-5)
+        sync()
+        return dx[:few], partial[:256 * 2 * H], dgam, dbet
+
+    a, b = run(few), run(many)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    _, saved = om.layernorm_fwd(host(x[:few]), host(gamma), host(gamma), 1e-5)
+    dx_ref, dg_ref, db_ref = om.layernorm_bwd(host(dy[:few]), saved, host(gamma))
+    close(host(a[0]), dx_ref, dtype, k=3.0)
+    close(host(a[2]), dg_ref, 0, k=50.0)
+    close(host(a[3]), db_ref, 0, k=50.0)
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 @pytest.mark.parametrize("form", [0, 1])
 def test_gelu_bwd(dtype, form):
