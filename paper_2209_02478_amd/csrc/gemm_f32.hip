@@ -22,14 +22,17 @@
 // and NaN come out as fp32 arithmetic has them (some 20 times slower).  Below 2^-109 the third part is
 // a bf16 denormal and loses bits, from 2^-118 on the second.
 //
-// Block tiles are TB x TB with 8 TB threads for each of WK ways of sharing the reduction: k way g takes
-// the 32-index slices g, g + WK, ... and the ways' accumulators are added in order at the end.
-// Half of a way's threads bring its A slice, half its B slice: 8 floats each, loaded ND slices ahead into
+// Block tiles are BM x BN with one thread or more for 8 floats of a slice, and WK ways of sharing the reduction: k way
+// g takes the 32-index slices g, g + WK, ... and the ways' accumulators are added in order at the end.
+// A way's first 4 BM threads bring its A slice, the next 4 BN its B slice: 8 floats each, loaded ND slices ahead into
 // registers, split there (11 vector instructions for two values) and stored as three bf16 planes into
-// one of two buffers while the MFMAs work on the other.  A wave issues one vector instruction in 8 clocks,
+// one of two buffers while the MFMAs work on the other; any that are left only multiply.  A wave issues one vector instruction in 8 clocks,
 // a SIMD one in 4, and splitting takes about two for each MFMA: hence many waves with small parts of
 // the tile each, four on every SIMD.  128 x 128 tiles: 16 waves of 32 x 32; 64 x 64: 8 waves of 16 x 32
-// a way; 32 x 32: 4 waves of 16 x 16 a way.
+// a way; 32 x 32: 4 waves of 16 x 16 a way; 96 x 64 and 128 x 64, 12 and 16 waves of 16 x 32, where the squares have just
+// begun a second round or leave units idle (us, the squares' best -> these): 1408 x 768, K = 3072 77 -> 57, K = 768
+// 23.7 -> 18.7; 1408 x 3072 58 -> 54; 360 x 3072 24.4 -> 18.9; data gradient 1408 x 768, K = 30522 722 -> 614;
+// 704 x 2304 24.4 -> 21.1; weight gradient 2304 x 768 over 2256 rows 69 -> 59; 2256 x 768, K = 3072 84 -> 69.
 //
 // LDS plane of an operand slice: slots of 64 bytes (32 indices), their four 16-byte chunks turned
 // against bank conflicts.  Which row a fragment's lane holds is free, as it only renames outputs: lane l of
@@ -129,26 +132,28 @@ template <bool KM> __device__ __forceinline__ float get(const float (&v)[8], int
 template <bool AK, bool BKM, int WM, int WN, int TM, int TN, int WK, int ND>
 __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev p, int vec_in, int vec_out, int tiles_n,
                                                                        int total, int per_xcd) {
-  constexpr int TB = 16 * WM * TM, GT = 64 * WM * WN, HALF = GT / 2;
-  static_assert(16 * WN * TN == TB && GT == 8 * TB, "square tiles, 8 floats of a slice for each thread of a way");
-  constexpr int PLANE = TB * 64, OPERAND = 3 * PLANE, SLICE = 2 * OPERAND;   // bytes
+  constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, GT = 64 * WM * WN;
+  constexpr int FIRST_B = 4 * BM, FIRST_IDLE = FIRST_B + 4 * BN;             // threads of a way: 8 floats of a slice each
+  static_assert(FIRST_IDLE <= GT && BM % 16 == 0 && BN % 16 == 0, "enough threads, whole waves for either operand");
+  constexpr int PLANE_A = BM * 64, PLANE_B = BN * 64, OPERAND = 3 * PLANE_A, SLICE = OPERAND + 3 * PLANE_B;   // bytes
   constexpr int SMEM = 2 * WK * SLICE;
-  static_assert(SMEM >= WK * TB * TB * 4 && SMEM >= WK * 8 * TB * 4, "space for the ways' accumulators and row sums");
+  static_assert(SMEM >= (WK > 1 ? WK * BM * BN * 4 : 0) && SMEM >= WK * 8 * BM * 4, "space for the ways' accumulators and row sums");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   // block id -> XCD-contiguous runs of tiles, in groups of SGROUP_M row panels
   const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (tile >= total) return;
-  const int tiles_m = (p.M + TB - 1) / TB;
+  const int tiles_m = (p.M + BM - 1) / BM;
   const int tgroup = tile / (SGROUP_M * tiles_n), first_m = tgroup * SGROUP_M;
   const int gsize = min(tiles_m - first_m, SGROUP_M);
   const int in_group = tile - tgroup * SGROUP_M * tiles_n;
   const int tile_m = first_m + in_group % gsize, tile_n = in_group / gsize;
-  const int m0 = tile_m * TB, n0 = tile_n * TB;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int way = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
   const int gt = tid % GT, l16 = lane & 15, q = lane >> 4;
-  const bool mine_a = wave % (WM * WN) < WM * WN / 2;                // this wave brings A (else B)
+  const bool mine_a = wave % (WM * WN) < FIRST_B / 64;               // this wave brings A, else B,
+  const bool idle = wave % (WM * WN) >= FIRST_IDLE / 64;             // else nothing
   const float* A = (const float*)p.A;
   const float* B = (const float*)p.B;
 
@@ -156,12 +161,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
   float raw[ND][8];
   float rs[2] = {0.f, 0.f};
   const bool do_rowsum = p.a_rowsum && tile_n == 0 && mine_a;
-  if (mine_a) init_share<AK, TB, TM>(sh, A, p.lda, p.M, m0, gt, way * SK, WK * SK);
-  else init_share<BKM, TB, TN>(sh, B, p.ldb, p.N, n0, gt - HALF, way * SK, WK * SK);
+  if (mine_a) init_share<AK, BM, TM>(sh, A, p.lda, p.M, m0, gt, way * SK, WK * SK);
+  else if (!idle) init_share<BKM, BN, TN>(sh, B, p.ldb, p.N, n0, gt - FIRST_B, way * SK, WK * SK);
   const bool km = mine_a ? AK : BKM;
   const int rows = mine_a ? p.M : p.N;
   // an m-major operand is read along its rows, so its tile has to be whole; a k-major one is not
-  const bool whole = vec_in && (km || (mine_a ? m0 : n0) + TB <= rows);
+  const bool whole = vec_in && (km || (mine_a ? m0 + BM : n0 + BN) <= rows);
   const int64_t ld = mine_a ? p.lda : p.ldb;
   auto load = [&](float (&v)[8], auto kmajor) {      // a slice inside K, of a whole tile
     if (decltype(kmajor)::value) {
@@ -187,7 +192,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
     const int r0 = mine_a ? m0 : n0, kl = p.K - kb - sh.k;            // indices left from this share's first
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int row = KM ? r0 + (mine_a ? row_of<TB, TM>(i, gt) : row_of<TB, TN>(i, gt - HALF)) : sh.row + i;
+      const int row = KM ? r0 + (mine_a ? row_of<BM, TM>(i, gt) : row_of<BN, TN>(i, gt - FIRST_B)) : sh.row + i;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         v[KM ? 4 * i + e : 2 * e + i] = e < kl && row < rows ? X[KM ? (int64_t)row * ld + kb + sh.k + e : (int64_t)(kb + sh.k + e) * ld + row] : 0.f;
@@ -196,6 +201,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
   };
   char* mine = smem + way * SLICE;
   char* to = mine + (mine_a ? 0 : OPERAND);
+  const int plane = mine_a ? PLANE_A : PLANE_B;
   // half a row split; behind the second half the row's indices are stored
   uint32_t lo[3], hi[3];
   auto split_half = [&](const float (&v)[8], int half, int buf, auto kmajor) {
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
     if (half % 2 == 0) { split2(get<KM>(v, i, 0), get<KM>(v, i, 1), lo); return; }
     split2(get<KM>(v, i, 2), get<KM>(v, i, 3), hi);
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) *(uint2*)(to + buf * (WK * SLICE) + pl * PLANE + sh.at[i]) = make_uint2(lo[pl], hi[pl]);
+    for (int pl = 0; pl < 3; ++pl) *(uint2*)(to + buf * (WK * SLICE) + pl * plane + sh.at[i]) = make_uint2(lo[pl], hi[pl]);
   };
   auto add_rows = [&](const float (&v)[8], auto kmajor) {            // (weight gradients have row sums, others hardly ever)
     constexpr bool KM = decltype(kmajor)::value;
@@ -231,9 +237,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[pl][i] = *(const bf16x8*)(at + pl * PLANE + i * 1024 + a_at);
+      for (int i = 0; i < TM; ++i) fa[pl][i] = *(const bf16x8*)(at + pl * PLANE_A + i * 1024 + a_at);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[pl][j] = *(const bf16x8*)(at + pl * PLANE + j * 1024 + b_at);
+      for (int j = 0; j < TN; ++j) fb[pl][j] = *(const bf16x8*)(at + pl * PLANE_B + j * 1024 + b_at);
     }
   };
   auto multiply = [&](int x) {                      // one of the six products
@@ -250,12 +256,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
   // vector instructions of the split dealt out between the MFMAs.  Slice t waits in raw[t % ND].
   const int n_slices = (p.K + WK * SK - 1) / (WK * SK);
   const int n_whole = whole ? max(0, (p.K / SK - way + WK - 1) / WK) : 0;    // of this way, inside K
-  auto work = [&](auto kmajor) {
-    fetch(0, raw[0], kmajor);
-    stash(raw[0], 0, kmajor);
+  auto work = [&](auto kmajor, auto loads) {
+    constexpr bool LOADS = decltype(loads)::value;
+    if (LOADS) {
+      fetch(0, raw[0], kmajor);
+      stash(raw[0], 0, kmajor);
 #pragma unroll
-    for (int u = 1; u <= ND; ++u)
-      if (u < n_slices) fetch(u, raw[u % ND], kmajor);
+      for (int u = 1; u <= ND; ++u)
+        if (u < n_slices) fetch(u, raw[u % ND], kmajor);
+    }
     __syncthreads();
     int t = 0;
     if (!AK || !p.a_rowsum)
@@ -268,8 +277,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int x = 0; x < 6; ++x) {
-            if (x >= 1 && x <= 4) split_half(v, x - 1, buf ^ 1, kmajor);
-            if (x == 5) { add_rows(v, kmajor); load(v, kmajor); }
+            if (LOADS && x >= 1 && x <= 4) split_half(v, x - 1, buf ^ 1, kmajor);
+            if (LOADS && x == 5) { add_rows(v, kmajor); load(v, kmajor); }
             multiply(x);
 #pragma unroll
             for (int f = 0; f < TM * TN; ++f) {
@@ -288,7 +297,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
         if (t >= n_slices) break;
         float (&v)[8] = raw[(u + 1) % ND];
         read(t & 1);
-        if (t + 1 < n_slices) {
+        if (LOADS && t + 1 < n_slices) {
           stash(v, (t + 1) & 1, kmajor);
           if (t + 1 + ND < n_slices) fetch(t + 1 + ND, v, kmajor);
         }
@@ -299,25 +308,26 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
     }
   };
   // every wave meets the others n_slices + 1 times, whichever of the two it runs
-  if (AK == BKM || mine_a) work(std::integral_constant<bool, AK>());
-  else work(std::integral_constant<bool, BKM>());
+  if (FIRST_IDLE < GT && idle) work(std::true_type(), std::false_type());
+  else if (AK == BKM || mine_a) work(std::integral_constant<bool, AK>(), std::true_type());
+  else work(std::integral_constant<bool, BKM>(), std::true_type());
 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
   if (p.a_rowsum && tile_n == 0) {                    // the shares of a row, in order
-    float* red = (float*)smem;                        // [8 WK shares][TB rows]
+    float* red = (float*)smem;                        // [8 WK shares][BM rows]
     if (mine_a) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        red[(way * 8 + sh.k / 4) * TB + (AK ? row_of<TB, TM>(i, gt) : sh.row - m0 + i)] = rs[i];
+        red[(way * 8 + sh.k / 4) * BM + (AK ? row_of<BM, TM>(i, gt) : sh.row - m0 + i)] = rs[i];
     }
     __syncthreads();
-    if (tid < TB && m0 + tid < p.M) {
+    if (tid < BM && m0 + tid < p.M) {
       float s = red[tid];
 #pragma unroll
-      for (int i = 1; i < 8 * WK; ++i) s += red[i * TB + tid];
+      for (int i = 1; i < 8 * WK; ++i) s += red[i * BM + tid];
       p.a_rowsum[m0 + tid] = s;
     }
     __syncthreads();
@@ -408,31 +418,34 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
 // The block tiles and ways of the reduction a product may get, and about what it then takes in units of 10 ns:
 // `rounds` of 256 tiles (one for each compute unit), each with a start and end and `slices` of 32 indices.
 // The one-way 64 x 64 and the two-way 32 x 32 tiles leave room for others on their unit, so from the
-// second round on rounds overlap.  Fitted to 16-4096 rows or indices of 768, 2304, 3072 and 30528 columns; where two are
-// close the estimate may take the second by up to 10 %.
-constexpr int kVariants = 5;
+// second round on rounds overlap; the 128 x 128 ones on all units get in each other's way.  Fitted to 16-4096 rows or
+// indices of 768, 2304, 3072 and 30528 columns; where two are close the estimate may take the second by up to 10 %.
+constexpr int kVariants = 7;
 static int64_t estimate(int which, int64_t M, int64_t N, int64_t K) {
-  constexpr int kTile[kVariants] = {128, 64, 64, 32, 32};
-  constexpr int kAlone[kVariants] = {500, 460, 500, 460, 460}, kAloneSlice[kVariants] = {95, 46, 35, 19, 15};
-  constexpr int kMany[kVariants] = {500, 230, 500, 240, 400}, kManySlice[kVariants] = {95, 40, 35, 16, 15};
-  const int64_t b = kTile[which], rounds = ((M + b - 1) / b * ((N + b - 1) / b) + 255) / 256, slices = (K + SK - 1) / SK;
+  constexpr int kM[kVariants] = {128, 64, 64, 32, 32, 96, 128}, kN[kVariants] = {128, 64, 64, 32, 32, 64, 64};
+  constexpr int kAlone[kVariants] = {500, 460, 500, 460, 460, 520, 550}, kAloneSlice[kVariants] = {95, 46, 35, 19, 15, 54, 66};
+  constexpr int kMany[kVariants] = {600, 230, 500, 240, 400, 480, 500}, kManySlice[kVariants] = {115, 40, 35, 16, 15, 56, 68};
+  const int64_t m = kM[which], n = kN[which], rounds = ((M + m - 1) / m * ((N + n - 1) / n) + 255) / 256, slices = (K + SK - 1) / SK;
   return rounds == 1 ? kAlone[which] + slices * kAloneSlice[which] : rounds * (kMany[which] + slices * kManySlice[which]);
 }
 
 template <bool AK, bool BKM>
 static void launch_f32(const GemmDev& p, int which, int vec_in, int vec_out, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-#define GO_(TB, WM, WN, TM, TN, WK, ND)                                                                                   \
+#define GO_(WM, WN, TM, TN, WK, ND)                                                                                       \
   {                                                                                                                       \
-    const int tiles_n = (p.N + TB - 1) / TB, total = (p.M + TB - 1) / TB * tiles_n, per = (total + 7) / 8;                \
+    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN;                                                                   \
+    const int tiles_n = (p.N + BN - 1) / BN, total = (p.M + BM - 1) / BM * tiles_n, per = (total + 7) / 8;                \
     hipExtLaunchKernelGGL((sgemm_split_kernel<AK, BKM, WM, WN, TM, TN, WK, ND>), dim3(per * 8), dim3(64 * WM * WN * WK),  \
                           0, st, t0, t1, 0, p, vec_in, vec_out, tiles_n, total, per);                                     \
   }
   switch (which) {
-    case 0: GO_(128, 4, 4, 2, 2, 1, 1) break;
-    case 1: GO_(64, 4, 2, 1, 2, 1, 2) break;
-    case 2: GO_(64, 4, 2, 1, 2, 2, 2) break;
-    case 3: GO_(32, 2, 2, 1, 1, 2, 3) break;
-    default: GO_(32, 2, 2, 1, 1, 4, 2) break;
+    case 0: GO_(4, 4, 2, 2, 1, 1) break;
+    case 1: GO_(4, 2, 1, 2, 1, 2) break;
+    case 2: GO_(4, 2, 1, 2, 2, 2) break;
+    case 3: GO_(2, 2, 1, 1, 2, 3) break;
+    case 4: GO_(2, 2, 1, 1, 4, 2) break;
+    case 5: GO_(6, 2, 1, 2, 1, 2) break;
+    default: GO_(8, 2, 1, 2, 1, 2) break;
   }
 #undef GO_
 }

@@ -16,8 +16,10 @@ U = 2.0 ** -24                        # unit roundoff of fp32
 SHAPES = [(1, 1, 1), (33, 65, 31), (130, 129, 100), (130, 70, 515),       # 32 x 32, four ways
           (130, 2300, 250), (129, 2305, 32),                              # 32 x 32, two
           (260, 2300, 99), (520, 1030, 1000),                             # 64 x 64, two
-          (900, 900, 70), (1100, 1030, 260),                              # 64 x 64, one
-          (1500, 1500, 70), (1410, 3000, 130)]                            # 128 x 128
+          (900, 900, 70), (1410, 3000, 130),                              # 64 x 64, one
+          (1100, 1030, 260), (1409, 770, 515),                            # 96 x 64
+          (700, 2300, 300), (2305, 750, 515),                             # 128 x 64
+          (1500, 1500, 70), (1345, 2300, 99)]                             # 128 x 128
 
 
 def put(X, kmajor, pad):
@@ -66,7 +68,8 @@ def test_split_products(M, N, K, a_k, b_k):
 
 
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
-@pytest.mark.parametrize("M,N,K", [(130, 129, 100), (130, 2300, 250), (260, 2300, 99), (900, 900, 70), (1500, 1500, 70)])
+@pytest.mark.parametrize("M,N,K", [(130, 129, 100), (130, 2300, 250), (260, 2300, 99), (900, 900, 70), (1409, 770, 515),
+                                   (700, 2300, 300), (1500, 1500, 70)])
 def test_infinities_and_nan(M, N, K, a_k, b_k):
     """Values the split cannot carry come out as fp32 arithmetic has them, and disturb no other output."""
     rng = np.random.default_rng(K)
