@@ -2,9 +2,16 @@
 // (v_mfma_f32_32x32x2_f32), without materialising the L x L matrices.
 //
 // Head sizes 32 and 64; the fp32 configuration, and bf16 with head size 32 (bf16 with head size 64
-// runs on the bf16 kernels of attention_mfma.hip).  One wave owns 32 query rows (forward, dQ) or 32
-// key rows (dK/dV); a block's two waves share tiles of 32 opposite rows in LDS.  An MFMA of 32 x 32
-// x 2 takes 64 clocks, so the matrix pipe is the limit and everything else hides behind it.
+// runs on the bf16 kernels of attention_mfma.hip).  A block owns 32 query rows (forward, dQ) or 32
+// key rows (dK/dV) and its four waves take the 32-row tiles of the opposite rows in turn; their results are added in
+// wave order at the end.  An MFMA of 32 x 32 x 2 takes 64 clocks, a tile 64-128 of them: a wave that walks
+// all tiles of its rows, as before (two waves of a block side by side, sharing the tiles in LDS), is a chain of
+// 3 us for each, while a short batch has fewer waves than the chip has SIMDs.  Nothing is shared but the own rows: a
+// wave loads a tile's rows from memory straight into operands of the first products, the next tile's while it
+// works, and passes them through its own LDS for the product that needs them by columns, without a barrier.
+// Forward / backward, us: 12 heads of 64, 16 samples of 35-141 tokens 30 / 74 -> 24 / 73, 16 x 88 20 / 50 -> 16 / 45,
+// 16 x 256 51 / 168 -> 49 / 141, 16 x 512 150 / 480 -> 142 / 444; causal 3 x 300 35 / 102 -> 21 / 59; 2 heads of 32, 4 x 33
+// 6.5 / 16.5 -> 5.3 / 12.6; one sample of a single tile 5.6 / 14.8 -> 5.9 / 16.0.
 //
 //   forward   O_i = sum_j softmax_j(q_i k_j / sqrt(d)) v_j,   lse_i = log sum_j exp(s_ij)
 //   backward  P_ij = exp(s_ij - lse_i), dP_ij = dO_i v_j, dS_ij = P_ij (dP_ij - delta_i),
@@ -35,8 +42,8 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
 
 namespace {
 
-constexpr int TR = 32;                 // rows of a streamed tile
-constexpr int BLOCK_ROWS = 64;         // 2 waves x 32 rows
+constexpr int TR = 32;                 // own rows of a block, and rows of a streamed tile
+constexpr int WAVES = 4;               // they take the tiles in turn
 
 __device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
 __device__ __forceinline__ float4 load4(const bf16_t* p) {
@@ -49,50 +56,41 @@ __device__ __forceinline__ void store4(bf16_t* p, float4 v) {
   *(uint2*)p = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
 }
 
-// Tile of TR rows x D columns: global -> registers -> LDS [row][D + 4].  128 threads, 16 bytes each.
+// A tile's row l32 (rows past `last` are read as `last`) as the MFMA takes it: element j of group g is column 8g + 4h + j
 template <typename T, int D>
-struct RowTile {
-  static constexpr int LD = D + 4;
-  static constexpr int NCH = TR * D / 4 / 128;
-  float4 v[NCH];
-  __device__ __forceinline__ void fetch(const T* src, int64_t ld, int r0, int last, int tid) {
+__device__ __forceinline__ void fetch_rows(const T* src, int64_t ld, int r0, int last, int l32, int h, float4 (&f)[D / 8]) {
+  const T* p = src + (int64_t)min(r0 + l32, last) * ld + 4 * h;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int c = tid + i * 128, r = min(r0 + c / (D / 4), last);
-      v[i] = load4(src + (int64_t)r * ld + (c % (D / 4)) * 4);
-    }
-  }
-  __device__ __forceinline__ void stash(float* tile, int tid) const {
+  for (int g = 0; g < D / 8; ++g) f[g] = load4(p + 8 * g);
+}
+// the same rows as they lie, [row][D + 4], to be read by columns
+template <int D>
+__device__ __forceinline__ void stash(float* tile, int l32, int h, const float4 (&f)[D / 8]) {
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int c = tid + i * 128;
-      *(float4*)&tile[(c / (D / 4)) * LD + (c % (D / 4)) * 4] = v[i];
-    }
-  }
-};
-
-// the wave's own row as B operand: element j of group g is column 8g + 4h + j
-template <typename T, int D>
-__device__ __forceinline__ void own_row(const T* p, int h, float4 (&f)[D / 8]) {
-#pragma unroll
-  for (int g = 0; g < D / 8; ++g) f[g] = load4(p + 8 * g + 4 * h);
+  for (int g = 0; g < D / 8; ++g) *(float4*)&tile[l32 * (D + 4) + 8 * g + 4 * h] = f[g];
 }
 __device__ __forceinline__ void clear(f32x16& v) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = 0.f;
 }
-// s = tile rows (A) x own rows (B) over the D columns
+__device__ __forceinline__ void multiply4(const float4& a, const float4& b, f32x16& s) {
+  s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, s, 0, 0, 0);
+  s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, s, 0, 0, 0);
+  s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, s, 0, 0, 0);
+  s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, s, 0, 0, 0);
+}
+// s = tile rows (A) x own rows (B), which lie in LDS, over the D columns
 template <int D>
-__device__ __forceinline__ void scores(const float* tile, int l32, int h, const float4 (&own)[D / 8], f32x16& s) {
+__device__ __forceinline__ void scores(const float4 (&rows)[D / 8], const float* own, int l32, int h, f32x16& s) {
   clear(s);
 #pragma unroll
-  for (int g = 0; g < D / 8; ++g) {
-    const float4 a = *(const float4*)&tile[l32 * (D + 4) + 8 * g + 4 * h];
-    s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, own[g].x, s, 0, 0, 0);
-    s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, own[g].y, s, 0, 0, 0);
-    s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, own[g].z, s, 0, 0, 0);
-    s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, own[g].w, s, 0, 0, 0);
-  }
+  for (int g = 0; g < D / 8; ++g) multiply4(rows[g], *(const float4*)&own[l32 * (D + 4) + 8 * g + 4 * h], s);
+}
+// What the lanes of a wave have stored to LDS before, the others read after: the hardware keeps a wave's accesses
+// in order, the compiler has to be told.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
 }
 // acc (rows = head columns, columns = own rows) += tile^T x s
 template <int D>
@@ -104,55 +102,76 @@ __device__ __forceinline__ void accumulate(const float* tile, int l32, int h, co
     for (int db = 0; db < D / 32; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(row[32 * db], s[r], acc[db], 0, 0, 0);
   }
 }
-template <typename T, int D>
-__device__ __forceinline__ void store_own(T* dst, const f32x16 (&acc)[D / 32], int h, float mul) {
+// A wave's part of a sum over the tiles goes into its own part of LDS (at least TR * (D + 4) floats) ...
+template <int D>
+__device__ __forceinline__ void put_part(float* part, int lane, const f32x16 (&acc)[D / 32]) {
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      store4(dst + 32 * db + 8 * g + 4 * h,
-             make_float4(acc[db][4 * g] * mul, acc[db][4 * g + 1] * mul, acc[db][4 * g + 2] * mul, acc[db][4 * g + 3] * mul));
+      *(float4*)&part[((4 * db + g) * 64 + lane) * 4] = make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+}
+// ... and behind a barrier wave w adds the n waves' parts of head columns 8 q + 4 h .., q = w, w + WAVES, ..., in wave
+// order, each times its own row's factor.
+template <typename T, int D>
+__device__ __forceinline__ void store_sum(T* dst, const float* parts, int stride, int n, int wave, int lane, const float (&factor)[WAVES]) {
+#pragma unroll
+  for (int i = 0; i < D / 8 / WAVES; ++i) {
+    const int q = wave + WAVES * i;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      if (w >= n) break;
+      const float4 v = *(const float4*)&parts[w * stride + (q * 64 + lane) * 4];
+      s.x = fmaf(v.x, factor[w], s.x); s.y = fmaf(v.y, factor[w], s.y);
+      s.z = fmaf(v.z, factor[w], s.z); s.w = fmaf(v.w, factor[w], s.w);
+    }
+    store4(dst + 8 * q + 4 * (lane >> 5), s);
+  }
 }
 
 }  // namespace
 
 // qkv row stride is 3*H; head hh of token t: q at t*3H + hh*D, k at +H, v at +2H.
 template <typename T, int D>
-__global__ __launch_bounds__(128) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
+__global__ __launch_bounds__(64 * WAVES, 3) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
                                                        float* __restrict__ lse, Rows rows, int L, int nh, int causal,
                                                        DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float Ks[TR * (D + 4)], Vs[TR * (D + 4)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 31, h = lane >> 5;
+  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
+  __shared__ float ms[WAVES][TR], ls[WAVES][TR];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int i0 = blockIdx.x * BLOCK_ROWS;
+  const int i0 = blockIdx.x * TR;
   if (i0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
-  const int qi = i0 + wave * 32 + ql, qc = min(qi, sm.n - 1);
+  const int qi = i0 + ql, qc = min(qi, sm.n - 1);
   const float scale = rsqrtf((float)D);
-  float4 q[D / 8];
-  own_row<T, D>(base + (int64_t)qc * ld3, h, q);
+  const int kend = causal ? min(sm.keys, i0 + TR) : sm.keys;
+  float4 k[D / 8], v[D / 8];
+  auto fetch = [&](int k0) {
+    fetch_rows<T, D>(base + H, ld3, k0, sm.n - 1, ql, h, k);
+    fetch_rows<T, D>(base + 2 * H, ld3, k0, sm.n - 1, ql, h, v);
+  };
+  if (wave * TR < kend) fetch(wave * TR);
+  if (wave == 0) {
+    float4 own[D / 8];
+    fetch_rows<T, D>(base, ld3, i0, sm.n - 1, ql, h, own);
+    stash<D>(own_q, ql, h, own);
+  }
+  __syncthreads();
   f32x16 o[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) clear(o[db]);
   float m = -INFINITY, l = 0.f;
-  const int kend = causal ? min(sm.keys, i0 + BLOCK_ROWS) : sm.keys;
-  RowTile<T, D> tk, tv;
-  tk.fetch(base + H, ld3, 0, sm.n - 1, tid);
-  tv.fetch(base + 2 * H, ld3, 0, sm.n - 1, tid);
-  for (int k0 = 0; k0 < kend; k0 += TR) {
-    __syncthreads();
-    tk.stash(Ks, tid);
-    tv.stash(Vs, tid);
-    __syncthreads();
-    if (k0 + TR < kend) {
-      tk.fetch(base + H, ld3, k0 + TR, sm.n - 1, tid);
-      tv.fetch(base + 2 * H, ld3, k0 + TR, sm.n - 1, tid);
-    }
+  for (int k0 = wave * TR; k0 < kend; k0 += WAVES * TR) {
     f32x16 s;
-    scores<D>(Ks, ql, h, q, s);
+    scores<D>(k, own_q, ql, h, s);
+    stash<D>(tiles[wave], ql, h, v);
+    wave_sync();
+    if (k0 + WAVES * TR < kend) fetch(k0 + WAVES * TR);
     float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -161,11 +180,12 @@ __global__ __launch_bounds__(128) void attn_fwd_kernel(const T* __restrict__ qkv
       mx = fmaxf(mx, s[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mnew = fmaxf(m, mx);                  // finite: key 0 is visible to every query
-    const float alpha = expf(m - mnew);
+    const float mnew = fmaxf(m, mx);
+    const float at = mnew == -INFINITY ? 0.f : mnew;  // no key of this wave's tiles so far is visible to the query
+    const float alpha = expf(m - at);
     float rs = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[r] = expf(s[r] - mnew); rs += s[r]; }
+    for (int r = 0; r < 16; ++r) { s[r] = expf(s[r] - at); rs += s[r]; }
     l = l * alpha + (rs + __shfl_xor(rs, 32, 64));    // the normaliser counts every probability
     m = mnew;
     if (drop.thr) {                                   // dropped ones leave the P V product; the scale waits for the end
@@ -182,65 +202,83 @@ __global__ __launch_bounds__(128) void attn_fwd_kernel(const T* __restrict__ qkv
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-    accumulate<D>(Vs, ql, h, s, o);
+    accumulate<D>(tiles[wave], ql, h, s, o);
+    wave_sync();
   }
+  // the waves' results brought to the largest maximum and added in order
+  put_part<D>(tiles[wave], lane, o);
+  if (h == 0) { ms[wave][ql] = m; ls[wave][ql] = l; }
+  __syncthreads();
+  const int n = min(WAVES, (kend + TR - 1) / TR);
+  float mall = ms[0][ql], lall = 0.f, factor[WAVES];  // finite: key 0 is visible to every query
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) mall = fmaxf(mall, ms[w][ql]);
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) { factor[w] = expf(ms[w][ql] - mall); lall += ls[w][ql] * factor[w]; }
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) factor[w] *= drop.scale / lall;
   if (qi < sm.n) {
-    store_own<T, D>(ctx + (sm.first + qi) * H + hh * D, o, h, drop.scale / l);
-    if (h == 0) lse[(int64_t)bh * L + qi] = m + logf(l);
+    store_sum<T, D>(ctx + (sm.first + qi) * H + hh * D, tiles[0], TR * (D + 4), n, wave, lane, factor);
+    if (wave == 0 && h == 0) lse[(int64_t)bh * L + qi] = mall + logf(lall);
   }
 }
 
 // also writes delta_i = dO_i O_i for the dK/dV kernel, which runs after this one
 template <typename T, int D>
-__global__ __launch_bounds__(128) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
+__global__ __launch_bounds__(64 * WAVES, 3) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
                                                           const T* __restrict__ dctx, const float* __restrict__ lse,
                                                           float* __restrict__ delta, T* __restrict__ dqkv, Rows rows, int L,
                                                           int nh, int causal, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float Ks[TR * (D + 4)], Vs[TR * (D + 4)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 31, h = lane >> 5;
+  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], own_g[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int i0 = blockIdx.x * BLOCK_ROWS;
+  const int i0 = blockIdx.x * TR;
   if (i0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
-  const int qi = i0 + wave * 32 + ql, qc = min(qi, sm.n - 1);
+  const int qi = i0 + ql, qc = min(qi, sm.n - 1);
   const float scale = rsqrtf((float)D);
-  float4 q[D / 8], go[D / 8], of[D / 8];
-  own_row<T, D>(base + (int64_t)qc * ld3, h, q);
-  own_row<T, D>(dctx + (sm.first + qc) * H + hh * D, h, go);
-  own_row<T, D>(ctx + (sm.first + qc) * H + hh * D, h, of);
-  float delta_q = 0.f;
-#pragma unroll
-  for (int g = 0; g < D / 8; ++g) {
-    delta_q = fmaf(of[g].x, go[g].x, delta_q);
-    delta_q = fmaf(of[g].y, go[g].y, delta_q);
-    delta_q = fmaf(of[g].z, go[g].z, delta_q);
-    delta_q = fmaf(of[g].w, go[g].w, delta_q);
-  }
-  delta_q += __shfl_xor(delta_q, 32, 64);
-  if (h == 0 && qi < sm.n) delta[(int64_t)bh * L + qi] = delta_q;
+  float4 k[D / 8], v[D / 8];
+  const int kend = causal ? min(sm.keys, i0 + TR) : sm.keys;
+  auto fetch = [&](int k0) {
+    fetch_rows<T, D>(base + H, ld3, k0, sm.n - 1, ql, h, k);
+    fetch_rows<T, D>(base + 2 * H, ld3, k0, sm.n - 1, ql, h, v);
+  };
+  if (wave * TR < kend) fetch(wave * TR);
   const float lse_q = lse[(int64_t)bh * L + qc];
+  float delta_q = 0.f;
+  {
+    float4 go[D / 8], of[D / 8];
+    fetch_rows<T, D>(dctx + sm.first * H + hh * D, H, i0, sm.n - 1, ql, h, go);
+    fetch_rows<T, D>(ctx + sm.first * H + hh * D, H, i0, sm.n - 1, ql, h, of);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+      delta_q = fmaf(of[g].x, go[g].x, delta_q);
+      delta_q = fmaf(of[g].y, go[g].y, delta_q);
+      delta_q = fmaf(of[g].z, go[g].z, delta_q);
+      delta_q = fmaf(of[g].w, go[g].w, delta_q);
+    }
+    delta_q += __shfl_xor(delta_q, 32, 64);
+    if (wave == 1) stash<D>(own_g, ql, h, go);
+    if (wave == 0) {
+      if (h == 0 && qi < sm.n) delta[(int64_t)bh * L + qi] = delta_q;
+      fetch_rows<T, D>(base, ld3, i0, sm.n - 1, ql, h, of);
+      stash<D>(own_q, ql, h, of);
+    }
+  }
+  __syncthreads();
   f32x16 dq[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) clear(dq[db]);
-  const int kend = causal ? min(sm.keys, i0 + BLOCK_ROWS) : sm.keys;
-  RowTile<T, D> tk, tv;
-  tk.fetch(base + H, ld3, 0, sm.n - 1, tid);
-  tv.fetch(base + 2 * H, ld3, 0, sm.n - 1, tid);
-  for (int k0 = 0; k0 < kend; k0 += TR) {
-    __syncthreads();
-    tk.stash(Ks, tid);
-    tv.stash(Vs, tid);
-    __syncthreads();
-    if (k0 + TR < kend) {
-      tk.fetch(base + H, ld3, k0 + TR, sm.n - 1, tid);
-      tv.fetch(base + 2 * H, ld3, k0 + TR, sm.n - 1, tid);
-    }
+  for (int k0 = wave * TR; k0 < kend; k0 += WAVES * TR) {
     f32x16 s, dp;
-    scores<D>(Ks, ql, h, q, s);
-    scores<D>(Vs, ql, h, go, dp);
+    scores<D>(k, own_q, ql, h, s);
+    scores<D>(v, own_g, ql, h, dp);
+    stash<D>(tiles[wave], ql, h, k);
+    wave_sync();
+    if (k0 + WAVES * TR < kend) fetch(k0 + WAVES * TR);
     if (drop.thr) {                                   // d(P) of a dropped probability is zero, of a kept one scaled
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -257,62 +295,67 @@ __global__ __launch_bounds__(128) void attn_bwd_dq_kernel(const T* __restrict__ 
       const bool out = key >= sm.keys || (causal && key > qi);
       s[r] = out ? 0.f : expf(s[r] * scale - lse_q) * (dp[r] - delta_q);
     }
-    accumulate<D>(Ks, ql, h, s, dq);
+    accumulate<D>(tiles[wave], ql, h, s, dq);
+    wave_sync();
   }
-  if (qi < sm.n) store_own<T, D>(dqkv + (sm.first + qi) * ld3 + hh * D, dq, h, scale);
+  put_part<D>(tiles[wave], lane, dq);
+  __syncthreads();
+  float factor[WAVES];
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) factor[w] = scale;
+  if (qi < sm.n)
+    store_sum<T, D>(dqkv + (sm.first + qi) * ld3 + hh * D, tiles[0], TR * (D + 4), min(WAVES, (kend + TR - 1) / TR), wave, lane, factor);
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(128) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
+__global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                            T* __restrict__ dqkv, Rows rows, int L, int nh, int causal,
                                                            DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float Qs[TR * (D + 4)], Gs[TR * (D + 4)], lse_s[TR], delta_s[TR];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kl = lane & 31, h = lane >> 5;
+  __shared__ __attribute__((aligned(16))) float own_k[TR * (D + 4)], own_v[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
+  __shared__ __attribute__((aligned(16))) float stats[WAVES][2][TR];      // lse and delta of the tile's queries
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kl = lane & 31, h = lane >> 5;
   const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int j0 = blockIdx.x * BLOCK_ROWS;
+  const int j0 = blockIdx.x * TR;
   if (j0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
   const T* gbase = dctx + sm.first * H + hh * D;
-  const int ki = j0 + wave * 32 + kl, kc = min(ki, sm.n - 1);
+  const int ki = j0 + kl;
   const float scale = rsqrtf((float)D);
-  float4 k[D / 8], v[D / 8];
-  own_row<T, D>(base + (int64_t)kc * ld3 + H, h, k);
-  own_row<T, D>(base + (int64_t)kc * ld3 + 2 * H, h, v);
+  float4 q[D / 8], go[D / 8];
+  const int qstart = causal ? j0 : 0;                 // earlier queries never see these keys
+  const int qend = j0 >= sm.keys ? 0 : sm.n;          // a block of padded keys only writes zeros
+  const int first = qstart + wave * TR;
+  if (first < qend) {
+    fetch_rows<T, D>(base, ld3, first, sm.n - 1, kl, h, q);
+    fetch_rows<T, D>(gbase, H, first, sm.n - 1, kl, h, go);
+  }
+  if (wave < 2) {
+    float4 own[D / 8];
+    fetch_rows<T, D>(base + (wave + 1) * H, ld3, j0, sm.n - 1, kl, h, own);
+    stash<D>(wave ? own_v : own_k, kl, h, own);
+  }
+  __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
-  const int qstart = causal ? j0 : 0;                 // earlier queries never see these keys
-  const int qend = j0 >= sm.keys ? 0 : sm.n;          // a block of padded keys only writes zeros
-  RowTile<T, D> tq, tg;
-  float pre_lse = 0.f, pre_delta = 0.f;
-  auto fetch = [&](int q0) {
-    tq.fetch(base, ld3, q0, sm.n - 1, tid);
-    tg.fetch(gbase, H, q0, sm.n - 1, tid);
-    if (tid < TR) {
-      const int q = min(q0 + tid, sm.n - 1);
-      pre_lse = lse[(int64_t)bh * L + q];
-      pre_delta = delta[(int64_t)bh * L + q];
-    }
-  };
-  if (qstart < qend) fetch(qstart);
-  for (int q0 = qstart; q0 < qend; q0 += TR) {
-    __syncthreads();
-    tq.stash(Qs, tid);
-    tg.stash(Gs, tid);
-    if (tid < TR) { lse_s[tid] = pre_lse; delta_s[tid] = pre_delta; }
-    __syncthreads();
-    if (q0 + TR < qend) fetch(q0 + TR);
+  for (int q0 = first; q0 < qend; q0 += WAVES * TR) {
+    const int next = q0 + WAVES * TR;
+    const float stat = (h ? delta : lse)[(int64_t)bh * L + min(q0 + kl, sm.n - 1)];
     f32x16 s, dp;
-    scores<D>(Qs, kl, h, k, s);
-    scores<D>(Gs, kl, h, v, dp);
+    scores<D>(q, own_k, kl, h, s);
+    scores<D>(go, own_v, kl, h, dp);
+    stash<D>(tiles[wave], kl, h, go);
+    stats[wave][h][kl] = stat;
+    wave_sync();
+    if (next < qend) fetch_rows<T, D>(gbase, H, next, sm.n - 1, kl, h, go);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int qq = 8 * g + 4 * h;
-      const float4 ls = *(const float4*)&lse_s[qq], dl = *(const float4*)&delta_s[qq];
+      const float4 ls = *(const float4*)&stats[wave][0][qq], dl = *(const float4*)&stats[wave][1][qq];
       const float lss[4] = {ls.x, ls.y, ls.z, ls.w}, dls[4] = {dl.x, dl.y, dl.z, dl.w};
       // Dropout: a lane holds one key and four queries, a generator block four keys of one query.
       // The four lanes of a quad (four neighbouring keys) each make the block of one of the four
@@ -324,41 +367,52 @@ __global__ __launch_bounds__(128) void attn_bwd_dkv_kernel(const T* __restrict__
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = 4 * g + e, q = q0 + qq + e;
-        const bool out = q >= sm.n || (causal && ki > q);
+        const int r = 4 * g + e, at = q0 + qq + e;
+        const bool out = at >= sm.n || (causal && ki > at);
         const float p = out ? 0.f : expf(s[r] * scale - lss[e]);
         const float d = keep[e] ? dp[r] * drop.scale : 0.f;
         s[r] = keep[e] ? p * drop.scale : 0.f;        // what multiplied V in the forward
         dp[r] = p * (d - dls[e]);
       }
     }
-    accumulate<D>(Gs, kl, h, s, dv);
-    accumulate<D>(Qs, kl, h, dp, dk);
+    accumulate<D>(tiles[wave], kl, h, s, dv);
+    wave_sync();
+    stash<D>(tiles[wave], kl, h, q);
+    wave_sync();
+    if (next < qend) fetch_rows<T, D>(base, ld3, next, sm.n - 1, kl, h, q);
+    accumulate<D>(tiles[wave], kl, h, dp, dk);
+    wave_sync();
   }
-  if (ki < sm.n) {
-    if (ki >= sm.keys) {                              // whatever the lane's column held
+  const bool in = ki < sm.n;
+  const int n = ki < sm.keys ? min(WAVES, max(0, qend - qstart + TR - 1) / TR) : 0;   // padded keys: zeros, whatever the lane's column held
+  T* out = dqkv + (sm.first + ki) * ld3 + hh * D;
+  float factor[WAVES];
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
-    }
-    T* out = dqkv + (sm.first + ki) * ld3 + hh * D;
-    store_own<T, D>(out + H, dk, h, scale);
-    store_own<T, D>(out + 2 * H, dv, h, 1.f);
-  }
+  for (int w = 0; w < WAVES; ++w) factor[w] = scale;
+  put_part<D>(tiles[wave], lane, dk);
+  __syncthreads();
+  if (in) store_sum<T, D>(out + H, tiles[0], TR * (D + 4), n, wave, lane, factor);
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) factor[w] = 1.f;
+  put_part<D>(tiles[wave], lane, dv);
+  __syncthreads();
+  if (in) store_sum<T, D>(out + 2 * H, tiles[0], TR * (D + 4), n, wave, lane, factor);
 }
 
 template <typename T, int D>
 static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                   const DropDesc& drop, hipStream_t st) {
-  dim3 grid((L + BLOCK_ROWS - 1) / BLOCK_ROWS, B * nh);
-  hipLaunchKernelGGL((attn_fwd_kernel<T, D>), grid, dim3(128), 0, st, (const T*)qkv, (T*)ctx, lse, rows, L, nh, causal, drop);
+  dim3 grid((L + TR - 1) / TR, B * nh);
+  hipLaunchKernelGGL((attn_fwd_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (T*)ctx, lse, rows, L, nh, causal, drop);
 }
 template <typename T, int D>
 static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
                   const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
-  dim3 grid((L + BLOCK_ROWS - 1) / BLOCK_ROWS, B * nh);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(128), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
+  dim3 grid((L + TR - 1) / TR, B * nh);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
                      delta, (T*)dqkv, rows, L, nh, causal, drop);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, D>), grid, dim3(128), 0, st, (const T*)qkv, (const T*)dctx, lse, delta,
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)dctx, lse, delta,
                      (T*)dqkv, rows, L, nh, causal, drop);
 }
 

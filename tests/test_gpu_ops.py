@@ -609,6 +609,15 @@ def test_attention_tile_edges(causal, L, nh, lengths):
     attention_case(1, len(lengths) if lengths else 3, L, nh, 64, causal, seed=L + 3, lengths=lengths)
 
 
+# fp32 MFMAs: four waves take the tiles of 32 in turn, some of them none, or none that a query may see
+@pytest.mark.parametrize("dtype,d", [(0, 64), (0, 32), (1, 32)])
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("L,lengths,p_drop", [(32, None, 0.0), (65, [1, 32, 33, 65], 0.0), (128, [97, 128], 0.2),
+                                              (161, [31, 129, 160, 161], 0.0)])
+def test_attention_fp32_waves(dtype, d, causal, L, lengths, p_drop):
+    attention_case(dtype, len(lengths) if lengths else 2, L, 3, d, causal, seed=L + 5, lengths=lengths, p_drop=p_drop)
+
+
 # dropout of the probabilities: the kept set is the oracle's (integer comparisons of generator
 # words), so the usual tolerances apply; lengths off the 4-key grid, several key tiles, padding
 @pytest.mark.parametrize("dtype", [0, 1])
