@@ -368,6 +368,14 @@ class Step {
     over_rows(a);
     with_workspace(a, late);
   }
+  // A step of a few thousand elements per tensor is its launches: an event handed from one stream to the other costs
+  // the host 8-10 us, two launches' worth, and the device as much as a small kernel.  All on one stream against two, ms: 2 fp32 layers
+  // of 64 columns 0.45 -> 0.26-0.28 at 1024-8448 elements, 0.48 -> 0.31 at 16384, 0.63 -> 0.46 at 32768, 0.63 -> 0.50 at
+  // 65536, 0.72 -> 0.76 at 262144; 12 layers of 768 columns in bf16 2.46 -> 2.40 at 12288, 2.54 -> 2.48 at 24576,
+  // 2.52 -> 2.71 at 56832, in fp32 3.22 -> 3.11, 3.29 -> 3.20 and, at 98304, 3.41 -> 3.68; 24 causal layers of 1024
+  // columns 6.82 -> 6.56 at 65536, 7.11 -> 7.32 at 262144.  Same bits.
+  bool one_stream() const { return (int64_t)T_ * f_.hidden <= 1 << 15; }
+  bool second_stream() const { return c_->side && !one_stream(); }
   // Weight-gradient products may cut their reduction in parts; the scratch for that is taken
   // once per layer backward / head (a size fixed by the weight shapes), so that every
   // component of the step's memory stays a polynomial of the input size.
@@ -385,10 +393,10 @@ class Step {
   void with_workspace(mk::GemmArgs& a, bool late = false) {
     a.workspace = late ? late_ws_ : ws_;
     a.workspace_bytes = late ? late_ws_bytes_ : ws_bytes_;
-    a.beside = c_->side != nullptr;                 // (timed one by one they are the same kernels)
+    a.beside = second_stream();                     // (timed one by one they are the same kernels)
     if (dry_) return;
     // per-kernel timing brackets work on the main stream only, so it keeps everything there
-    if (!c_->side || c_->prof_on) { gemm(a); return; }
+    if (!second_stream() || c_->prof_on) { gemm(a); return; }
     if (!forked_) fork();
     if (late && hipEventRecord(c_->ev_early, c_->side) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "marking the weight-gradient stream failed"};
@@ -470,7 +478,7 @@ class Step {
   }
   void ln_bwd_reduce(const float* partial, int gi, int bi) {
     if (dry_) return;
-    const bool aside = c_->side && !c_->prof_on;
+    const bool aside = second_stream() && !c_->prof_on;
     mk::layernorm_bwd_reduce(partial, g(gi), g(bi), chunk_at_, chunk_at_ ? Tpad_ : T_, f_.hidden, aside ? c_->side : st_);
     if (aside) side_busy_ = true;
   }
@@ -478,7 +486,7 @@ class Step {
   // launches its next product (every group of side work here is followed by one).
   bool forked_ = false;
   void fork() {
-    if (dry_ || !c_->side || c_->prof_on) return;
+    if (dry_ || !second_stream() || c_->prof_on) return;
     if (hipEventRecord(c_->ev_fork, st_) != hipSuccess || hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "fork to the weight-gradient stream failed"};
     forked_ = true;
@@ -654,7 +662,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
 //   393216; 24 causal layers of 1024 columns ahead by 1-3 % at 131072-262144.
 bool Step::split_forward() const {
   const int tiles = dt_ == mk::BF16 ? mk::gemm_large_tiles(T_, f_.hidden) : 0;
-  if ((tiles >= 192 && tiles <= 256) || (int64_t)T_ * f_.hidden < (1 << 15)) return false;
+  if ((tiles >= 192 && tiles <= 256) || one_stream()) return false;
   return !dry_ && c_->side && !c_->prof_on && !collect_ && !drop_on() && c_->p_attn <= 0.f && B_ >= 2;
 }
 

@@ -447,6 +447,30 @@ def test_halves_of_the_batch_change_no_bits(name, B, L):
     m.close()
 
 
+@pytest.mark.parametrize("name", ["fp32_postln", "bf16_postln", "bf16_preln_causal"])
+def test_one_and_two_streams_in_turn(name):
+    """Up to 2^15 elements per tensor a step stays on one stream.  Queued steps on either side of the line
+    leave the bits that each has alone, with its kernels timed one by one."""
+    shape = SMALL[name]
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=256 * MiB)
+    m.load_params(synthdata.make_params(shape, 95, perturb=True))
+    m.force_plan(0b10)
+    rows = (1 << 15) // shape.hidden                               # the line, one sample more, and few
+    L = max(l for l in range(1, shape.max_seq + 1) if rows % l == 0)
+    batches = [synthdata.make_batch(shape, n, L, 96 + n) for n in (rows // L, rows // L + 1, 1)]
+    mi.mimose_profile_enable(m.ctx, 1)
+    alone = [(m.train_step(*b)[0], m.grads()) for b in batches]
+    mi.mimose_profile_enable(m.ctx, 0)
+    for turns in ((1, 0), (0, 1), (1, 2), (2, 1, 2, 0)):
+        for i in turns:
+            m.train_step(*batches[i], wait=False)
+        assert m.sync_loss() == alone[turns[-1]][0]
+        G = m.grads()
+        for k in G:
+            assert np.array_equal(G[k], alone[turns[-1]][1][k]), (turns, k)
+    m.close()
+
+
 @pytest.mark.parametrize("H,F,lengths", [(128, 512, [512, 3, 512, 17]),       # reductions in 8 parts of 256 rows
                                          (128, 256, [1536, 40, 1536, 700]),   # 384 chunks of partial LayerNorm sums
                                          (1024, 1024, [1024, 100])])          # in 4 of 512, one round of units
