@@ -16,8 +16,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_HBM_GBS = 8000.0
-GEMM_SOURCES = ("gemm.hip", "gemm_dma.hip", "gemm_large.h", "gemm_large.hip", "gemm_large128.hip", "gemm_ring.hip", "gemm_device.h")
-GEMM_KERNELS = {"bf16": "bgemm_kernel / bgemm_dma_kernel / bgemm_large_kernel / bgemm_ring_kernel", "fp32": "sgemm_mfma_kernel"}
+GEMM_SOURCES = ("gemm.hip", "gemm_dma.hip", "gemm_large.h", "gemm_large.hip", "gemm_large128.hip", "gemm_ring.hip", "gemm_tiles.hip", "gemm_device.h")
+GEMM_KERNELS = {"bf16": "bgemm_kernel / bgemm_dma_kernel / bgemm_large_kernel / bgemm_ring_kernel / bgemm_tiles_kernel", "fp32": "sgemm_split_kernel"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bert_base_gemm_hbm_traffic.txt")
 
 

@@ -27,6 +27,7 @@
 //
 // Every output element is produced by one wave in a fixed order: reproducible bit for bit.
 #include "device_common.h"
+#include <hip/hip_ext.h>
 #include "kernels.h"
 #include "philox.h"
 
@@ -38,7 +39,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                         const DropDesc& drop, hipStream_t st);
 void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
-                        const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st);
+                        const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done);
 
 namespace {
 
@@ -408,11 +409,11 @@ static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int 
 }
 template <typename T, int D>
 static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
-                  const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
+                  const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
   dim3 grid((L + TR - 1) / TR, B * nh);
   hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
                      delta, (T*)dqkv, rows, L, nh, causal, drop);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)dctx, lse, delta,
+  hipExtLaunchKernelGGL((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, nullptr, done, 0, (const T*)qkv, (const T*)dctx, lse, delta,
                      (T*)dqkv, rows, L, nh, causal, drop);
 }
 
@@ -427,12 +428,12 @@ void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows
 
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta,
                    void* dqkv, const Rows& rows, int B, int L, int nh, int d, int causal, const DropDesc& drop,
-                   hipStream_t st) {
+                   hipStream_t st, hipEvent_t done) {
   if (B * L <= 0) return;
-  if (dtype == BF16 && d == 64) attention_bwd_mfma(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st);
-  else if (dtype == BF16) bwd_t<bf16_t, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st);
-  else if (d == 32) bwd_t<float, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st);
-  else bwd_t<float, 64>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st);
+  if (dtype == BF16 && d == 64) attention_bwd_mfma(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else if (dtype == BF16) bwd_t<bf16_t, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else if (d == 32) bwd_t<float, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else bwd_t<float, 64>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
 }
 
 }  // namespace mk

@@ -25,6 +25,7 @@
 //
 // No atomics: dQ comes from a kernel that owns query rows, dK/dV from one that owns key rows.
 #include "device_common.h"
+#include <hip/hip_ext.h>
 #include "kernels.h"
 #include "philox.h"
 
@@ -512,13 +513,13 @@ void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, const Rows& rows
 }
 
 void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
-                        const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st) {
+                        const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
   const int pairs = B * nh;
   const dim3 grid((unsigned)((L + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) * 8u * (unsigned)((pairs + 7) / 8));
 #define BWD_(C, D)                                                                                               \
   hipLaunchKernelGGL((fa_bwd_dq_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)ctx,  \
                      (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop);                          \
-  hipLaunchKernelGGL((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
+  hipExtLaunchKernelGGL((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), 0, st, nullptr, done, 0, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
                      delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop)
   if (drop.thr) { if (causal) { BWD_(true, true); } else { BWD_(false, true); } }
   else { if (causal) { BWD_(true, false); } else { BWD_(false, false); } }

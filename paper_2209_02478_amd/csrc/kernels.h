@@ -112,8 +112,10 @@ struct LnBwdMasked {
   Rows rows;
   int B = 0, L = 0;
 };
+// done (optional; of gelu_bwd and attention_bwd too): an event for the end of the last kernel, bound to its launch
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
-                        const void* add, float* partial, int T, int H, float eps, const LnBwdMasked& extra, hipStream_t st);
+                        const void* add, float* partial, int T, int H, float eps, const LnBwdMasked& extra, hipStream_t st,
+                        hipEvent_t done = nullptr);
 // chunk_at (optional, device): T is the padded row count, and chunk_at[c] says which of the partial
 // rows belongs to its rows c * kRowBlock .. (-1: left out, they would add zeros)
 void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T, int H,
@@ -127,14 +129,14 @@ constexpr size_t kStaticPartialFloats = (size_t)2 << 20;   // 8 MiB
 int layernorm_bwd_static(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma,
                          void* dx, const void* add, float* dgamma, float* dbeta, int T, int H, float eps,
                          hipStream_t st);
-void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st);
+void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st, hipEvent_t done = nullptr);
 // drop: dropout of the probabilities (the
 // softmax normaliser counts all of them; ctx = (mask * scale * P) V).
 void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,
                    int causal, const DropDesc& drop, hipStream_t st);
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse,
                    float* delta, void* dqkv, const Rows& rows, int B, int L, int nh, int d, int causal,
-                   const DropDesc& drop, hipStream_t st);
+                   const DropDesc& drop, hipStream_t st, hipEvent_t done = nullptr);
 void softmax_xent(int dtype, void* logits, int64_t ld, const int32_t* labels, float* row_loss,
                   float* loss, int T, int V, int n_valid, hipStream_t st);
 // T: rows (B * L, or the real ones when rows.ends is given)

@@ -93,7 +93,7 @@ struct mimose_ctx {
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // the last weight-gradient product of a layer is waited for one layer later: ev_early marks
-  // the side stream just before it, ev_late just after it
+  // the end of the product before it on the side stream, ev_late its own
   hipEvent_t ev_early = nullptr, ev_late = nullptr;
   // end of a layer's first weight-gradient product, which reads the incoming gradient where the
   // layer's last data-gradient product writes when the carriers have the storage type
@@ -362,11 +362,13 @@ class Step {
     if (packed_ && dt_ == mk::BF16) { a.k_padded = Tpad_; a.k_blocks = blocks_.data(); }
   }
   // dW[out,in] = dY^T X, db[out] = column sums of dY
-  void wgrad(const void* dY, int64_t ldy, int out, const void* X, int in, int wi, int bi, bool late = false) {
+  // done (optional): marks its end on the weight-gradient stream, bound to its last kernel
+  void wgrad(const void* dY, int64_t ldy, int out, const void* X, int in, int wi, int bi, bool late = false,
+             hipEvent_t done = nullptr) {
     mk::GemmArgs a{dY, ldy, false, X, in, false, g(wi), in, true, out, in, T_};
     a.a_rowsum = bi >= 0 ? g(bi) : nullptr;
     over_rows(a);
-    with_workspace(a, late);
+    with_workspace(a, late, done);
   }
   // A step of a few thousand elements per tensor is its launches: an event handed from one stream to the other costs
   // the host 8-10 us, two launches' worth, and the device as much as a small kernel.  All on one stream against two, ms: 2 fp32 layers
@@ -390,7 +392,7 @@ class Step {
   }
   // late: the product reads and writes nothing that the layer's pop frees (its operand and its
   // scratch live in the step-long slot), so the layer's end need not wait for it
-  void with_workspace(mk::GemmArgs& a, bool late = false) {
+  void with_workspace(mk::GemmArgs& a, bool late = false, hipEvent_t done = nullptr) {
     a.workspace = late ? late_ws_ : ws_;
     a.workspace_bytes = late ? late_ws_bytes_ : ws_bytes_;
     a.beside = second_stream();                     // (timed one by one they are the same kernels)
@@ -398,14 +400,9 @@ class Step {
     // per-kernel timing brackets work on the main stream only, so it keeps everything there
     if (!second_stream() || c_->prof_on) { gemm(a); return; }
     if (!forked_) fork();
-    if (late && hipEventRecord(c_->ev_early, c_->side) != hipSuccess)
-      throw StepError{MIMOSE_ERR_HIP, "marking the weight-gradient stream failed"};
+    a.time_stop = late ? c_->ev_late : done;
     if (!mk::gemm(dt_, a, c_->side)) throw StepError{MIMOSE_ERR_INVALID_ARG, "gemm: unsupported alignment"};
-    if (late) {
-      if (hipEventRecord(c_->ev_late, c_->side) != hipSuccess)
-        throw StepError{MIMOSE_ERR_HIP, "marking the weight-gradient stream failed"};
-      late_pending_ = early_marked_ = true;
-    }
+    if (late) late_pending_ = early_marked_ = true;
     side_busy_ = true;
   }
   // Step-long slot for the gradient of the fused QKV projection and the scratch of its
@@ -468,14 +465,15 @@ class Step {
   // partial sums stay allocated until the layer's end), the small reduction to dgamma, dbeta on
   // the weight-gradient stream after the next fork, off the chain of data gradients.
   // masked (optional): dx behind the dropout mask of `site`.
-  float* ln_bwd_rows(const void* dy, const void* x, int gi, void* dx, const void* add, void* masked, uint32_t site) {
+  float* ln_bwd_rows(const void* dy, const void* x, int gi, void* dx, const void* add, void* masked, uint32_t site,
+                     hipEvent_t done = nullptr) {
     const bool dy_f32 = wide_, x_f32 = wide_;
     float* partial = (float*)c_->arena.alloc(partial_bytes());
     const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * ((add ? 2.0 : 1.0) + (masked ? 1.0 : 0.0));
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
     mk::LnBwdMasked ex;
     if (masked) { ex.masked = masked; ex.d = drop_desc(site); ex.rows = rows(); ex.B = B_; ex.L = L_; }
-    if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, ex, st_);
+    if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, ex, st_, done);
     return partial;
   }
   void ln_bwd_reduce(const float* partial, int gi, int bi) {
@@ -490,6 +488,17 @@ class Step {
   void fork() {
     if (dry_ || !second_stream() || c_->prof_on) return;
     if (hipEventRecord(c_->ev_fork, st_) != hipSuccess || hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
+      throw StepError{MIMOSE_ERR_HIP, "fork to the weight-gradient stream failed"};
+    forked_ = true;
+  }
+  // The same behind a kernel that is given the event with its launch (done_event): a record between two kernels is a
+  // packet of its own, behind which the second starts 2 us later.  With those of the other stream below, ms: bert_base 2 x 37
+  // 2.53 -> 2.40, 32 x 88 4.98 -> 4.88, 32 x 200 7.81 -> 7.71, padded 12 x 397 7.96 -> 7.88, bert_stages 32 x 332 padded
+  // 8.89 -> 8.77, bert_large 64 x 320 55.3 -> 55.1.
+  hipEvent_t done_event() const { return dry_ || !second_stream() || c_->prof_on ? nullptr : c_->ev_fork; }
+  void fork_behind_kernel() {
+    if (!done_event()) return;
+    if (hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "fork to the weight-gradient stream failed"};
     forked_ = true;
   }
@@ -726,16 +735,14 @@ void Step::layer_backward(int l, LayerActs& A) {
   const bool drop = drop_on();
   const uint32_t site_o = 4 * (uint32_t)(l + 1) + 1, site_f = site_o + 1;
   void* masked2 = drop ? talloc(TH) : nullptr;
-  float* part2 = f_.pre_ln ? nullptr : ln_bwd_rows(gA_, A.s2, p.ln2g, oA_, nullptr, masked2, site_f);
+  float* part2 = f_.pre_ln ? nullptr : ln_bwd_rows(gA_, A.s2, p.ln2g, oA_, nullptr, masked2, site_f, done_event());
   if (drop && f_.pre_ln) dropout(masked2, oA_, false, nullptr, site_f);
   const void* dffn = drop ? masked2 : oA_;
-  fork();
-  wgrad(dffn, H, H, A.act, F, p.w2, p.b2);
+  if (f_.pre_ln) fork(); else fork_behind_kernel();
+  wgrad(dffn, H, H, A.act, F, p.w2, p.b2, false, dffn == gA_ ? c_->ev_w2 : nullptr);
   // Carriers of the storage type: that product reads gA_ (dffn is oA_, which is gA_), and the
   // layer's last data gradient writes gA_ before the streams join, so it is ordered by an event.
   const bool guard_gA = !dry_ && side_busy_ && dffn == gA_;
-  if (guard_gA && hipEventRecord(c_->ev_w2, c_->side) != hipSuccess)
-    throw StepError{MIMOSE_ERR_HIP, "marking the weight-gradient stream failed"};
   // behind the product: in front of it this small kernel waits for a compute unit beside the main stream's
   // next product and the weight gradient with it (padded 12 x 397 with dropout 8.75 -> 8.62 ms an iteration;
   // bert_base 32 x 200 7.96 -> 7.93, 32 x 88 5.06 -> 5.08, bert_stages 32 x 332 padded 9.04 -> 9.07, the fp32
@@ -746,8 +753,9 @@ void Step::layer_backward(int l, LayerActs& A) {
   {
     const int64_t n = (int64_t)T_ * F;
     Timed t(this, MIMOSE_K_GELU_BWD, 3.0 * n * es_d());
-    if (!dry_) mk::gelu_bwd(dt_, dact, A.pre, n, f_.gelu_tanh, st_);        // dact = d pre
+    if (!dry_) mk::gelu_bwd(dt_, dact, A.pre, n, f_.gelu_tanh, st_, done_event());        // dact = d pre
   }
+  fork_behind_kernel();
   wgrad(dact, F, F, A.u, H, p.w1, p.b1);
   // dact stays allocated until the end of the layer: the weight-gradient stream may still read
   // it, and waiting for that stream here would idle the chip for the length of the hand-over
@@ -755,16 +763,16 @@ void Step::layer_backward(int l, LayerActs& A) {
   void* masked1 = drop ? talloc(TH) : nullptr;
   if (f_.pre_ln) {
     dgrad(dact, F, F, p.w1, gB_, H);                                          // gB = d LN2(u)
-    part1 = ln_bwd_rows(gB_, A.s1, p.ln2g, gB_, gA_, masked1, site_o);        // gB = d u
+    part1 = ln_bwd_rows(gB_, A.s1, p.ln2g, gB_, gA_, masked1, site_o, done_event());        // gB = d u
   } else {
     dgrad(dact, F, F, p.w1, gB_, H, oA_, wide_);                              // gB = d u = d s2 + FFN path
-    part1 = ln_bwd_rows(gB_, A.s1, p.ln1g, oB_, nullptr, masked1, site_o);    // oB = d s1
+    part1 = ln_bwd_rows(gB_, A.s1, p.ln1g, oB_, nullptr, masked1, site_o, done_event());    // oB = d s1
   }
   const void* dproj = drop ? masked1 : oB_;
-  fork();
+  fork_behind_kernel();
   if (f_.pre_ln) ln_bwd_reduce(part1, p.ln2g, p.ln2b);
   else ln_bwd_reduce(part1, p.ln1g, p.ln1b);
-  wgrad(dproj, H, H, A.ctx, H, p.wo, p.bo);
+  wgrad(dproj, H, H, A.ctx, H, p.wo, p.bo, false, late_ok() ? c_->ev_early : nullptr);   // the last but the late one
   void* dctx = talloc(TH);
   dgrad(dproj, H, H, p.wo, dctx, H);
   // Post-LN: the QKV weight gradient is the last product of the layer, issued when the main
@@ -779,8 +787,9 @@ void Step::layer_backward(int l, LayerActs& A) {
     Timed t(this, MIMOSE_K_ATTN_BWD, 8.0 * attention_pairs(B_, L_, lens_host) * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
       mk::attention_bwd(dt_, A.qkv, A.ctx, dctx, A.lse, delta, dqkv, rows(), B_, L_, nh, d, f_.causal,
-                        drop_desc(4 * (uint32_t)(l + 1), true), st_);
+                        drop_desc(4 * (uint32_t)(l + 1), true), st_, done_event());
   }
+  fork_behind_kernel();
   const void* a = f_.pre_ln ? A.n1 : A.x;
   wgrad(dqkv, 3 * H, 3 * H, a, H, p.wqkv, p.bqkv, late_ok());
   if (guard_gA && hipStreamWaitEvent(st_, c_->ev_w2, 0) != hipSuccess)

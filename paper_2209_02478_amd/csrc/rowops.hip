@@ -6,6 +6,7 @@
 // Column reductions over rows (LayerNorm's dgamma/dbeta) are two-stage with a row ->
 // chunk mapping fixed by the shape, so they are reproducible bit for bit (no atomics).
 #include "device_common.h"
+#include <hip/hip_ext.h>
 #include <initializer_list>
 
 #include "kernels.h"
@@ -940,12 +941,12 @@ void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, co
 
 template <typename TD, typename TX, typename T>
 static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, const void* add, float* partial,
-                     int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {
+                     int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st, hipEvent_t done) {
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
     const bool many = grid.x > 512, few = grid.x <= 256;
-#define A_(NC, AHEAD, WAVES) hipLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), 0, st, (const TD*)dy, \
+#define A_(NC, AHEAD, WAVES) hipExtLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), 0, st, nullptr, done, 0, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
 #define V_(NC) do { if (few) A_(NC, 1, 16); else if (many) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
@@ -966,15 +967,17 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
 #undef M_
   if (ex.masked)                                      // dx is stored: the mask in a pass of its own
     dropout_apply(sizeof(T) == 2 ? BF16 : F32, ex.masked, dx, false, nullptr, (int64_t)T_ * H, ex.d, ex.rows, ex.B, ex.L, H, st);
+  if (done) (void)hipEventRecord(done, st);
 }
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
-                        const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st) {
+                        const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st,
+                        hipEvent_t done) {
   if (T_ <= 0) return;
-  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
-  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
-  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
-  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
-  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st);
+  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
+  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
+  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
+  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
+  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
 }
 static_assert(kRowsPerChunk == kRowBlock, "padding is left out in whole chunks");
 void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T_, int H,
@@ -1020,15 +1023,15 @@ int layernorm_bwd_static(int dtype, const void* dy, bool dy_f32, const void* x, 
   return 0;
 }
 
-void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st) {
+void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st, hipEvent_t done) {
   if (n <= 0) return;
   dim3 grid((unsigned)((n + 2047) / 2048));
-  if (dtype == BF16) hipLaunchKernelGGL(gelu_bwd_bf16_kernel, grid, dim3(256), 0, st, (bf16_t*)d, (const bf16_t*)pre, n, tanh_form);
+  if (dtype == BF16) hipExtLaunchKernelGGL(gelu_bwd_bf16_kernel, grid, dim3(256), 0, st, nullptr, done, 0, (bf16_t*)d, (const bf16_t*)pre, n, tanh_form);
   else {
     const dim3 grid4((unsigned)((n + 1023) / 1024));
     if ((((uintptr_t)d | (uintptr_t)pre) & 15) == 0)
-      hipLaunchKernelGGL(gelu_bwd_f32_kernel<true>, grid4, dim3(256), 0, st, (float*)d, (const float*)pre, n, tanh_form);
-    else hipLaunchKernelGGL(gelu_bwd_f32_kernel<false>, grid4, dim3(256), 0, st, (float*)d, (const float*)pre, n, tanh_form);
+      hipExtLaunchKernelGGL(gelu_bwd_f32_kernel<true>, grid4, dim3(256), 0, st, nullptr, done, 0, (float*)d, (const float*)pre, n, tanh_form);
+    else hipExtLaunchKernelGGL(gelu_bwd_f32_kernel<false>, grid4, dim3(256), 0, st, nullptr, done, 0, (float*)d, (const float*)pre, n, tanh_form);
   }
 }
 
