@@ -340,7 +340,9 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
 // elements in registers.  Two where there are blocks for more than two to a unit: three waves then fit a SIMD,
 // where four rows' elements leave two (bf16 131072 x 1024 with the reduction 296 -> 241 us, 16384 x 768 39.7 -> 36.5;
 // with fp32 rows 300 -> 296, the copy rate, 38.3 -> 35.5).  Four for fewer blocks, which wait for memory
-// and not for each other.  All four rows' sums side by side gained
+// and not for each other, and from 14 blocks to a unit on, where alone it is behind but leaves more to the weight gradients
+// beside it: iterations with two against four, ms: 16384 rows 19.05 / 19.12, 20480 54.5 / 54.7, 51200 160.1 / 160.4; 65536
+// 198.5 / 196.6, 98304 293.1 / 291.4, 131072 388.2 / 386.6.  All four rows' sums side by side gained
 // nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order of the sums over
 // rows; the sums over a row's columns run over other columns per lane.
 template <typename TD, typename TX, typename T, int NC, int AHEAD, int WAVES>
@@ -945,11 +947,11 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-    const bool many = grid.x > 512, few = grid.x <= 256;
+    const bool few = grid.x <= 256, ahead2 = grid.x > 512 && grid.x <= 3584;
 #define A_(NC, AHEAD, WAVES) hipExtLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), 0, st, nullptr, done, 0, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
-#define V_(NC) do { if (few) A_(NC, 1, 16); else if (many) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
+#define V_(NC) do { if (few) A_(NC, 1, 16); else if (ahead2) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
     if (nc <= 1) { V_(1); return; }
     if (nc <= 2) { V_(2); return; }
     if constexpr (sizeof(T) == 4) {                   // (bf16 rows of 1024 are two chunks a lane)
