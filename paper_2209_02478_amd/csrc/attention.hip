@@ -27,7 +27,6 @@
 //
 // Every output element is produced by one wave in a fixed order: reproducible bit for bit.
 #include "device_common.h"
-#include <hip/hip_ext.h>
 #include "kernels.h"
 #include "philox.h"
 
@@ -413,7 +412,7 @@ static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const floa
   dim3 grid((L + TR - 1) / TR, B * nh);
   hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
                      delta, (T*)dqkv, rows, L, nh, causal, drop);
-  hipExtLaunchKernelGGL((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, nullptr, done, 0, (const T*)qkv, (const T*)dctx, lse, delta,
+  LAUNCH_MARKED_((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), st, done, (const T*)qkv, (const T*)dctx, lse, delta,
                      (T*)dqkv, rows, L, nh, causal, drop);
 }
 

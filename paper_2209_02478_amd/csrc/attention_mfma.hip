@@ -25,7 +25,6 @@
 //
 // No atomics: dQ comes from a kernel that owns query rows, dK/dV from one that owns key rows.
 #include "device_common.h"
-#include <hip/hip_ext.h>
 #include "kernels.h"
 #include "philox.h"
 
@@ -519,7 +518,7 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
 #define BWD_(C, D)                                                                                               \
   hipLaunchKernelGGL((fa_bwd_dq_kernel<C, D>), grid, dim3(256), 0, st, (const bf16_t*)qkv, (const bf16_t*)ctx,  \
                      (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop);                          \
-  hipExtLaunchKernelGGL((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), 0, st, nullptr, done, 0, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
+  LAUNCH_MARKED_((fa_bwd_dkv_kernel<C, D>), grid, dim3(256), st, done, (const bf16_t*)qkv, (const bf16_t*)dctx, lse, \
                      delta, (bf16_t*)dqkv, rows, L, nh, pairs, drop)
   if (drop.thr) { if (causal) { BWD_(true, true); } else { BWD_(false, true); } }
   else { if (causal) { BWD_(true, false); } else { BWD_(false, false); } }

@@ -1,9 +1,17 @@
 // Device-side helpers shared by the kernels: storage types, conversions, wave reductions.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 #include <stdint.h>
 
 #include "kernels.h"
+
+// Launches K without dynamic LDS; DONE (may be null) is bound to its end.
+#define LAUNCH_MARKED_(K, GRID, BLOCK, STREAM, DONE, ...)                                              \
+  do {                                                                                                 \
+    if (DONE) hipExtLaunchKernelGGL(K, GRID, BLOCK, 0, STREAM, nullptr, DONE, 0, __VA_ARGS__);         \
+    else hipLaunchKernelGGL(K, GRID, BLOCK, 0, STREAM, __VA_ARGS__);                                   \
+  } while (0)
 
 namespace mk {
 

@@ -6,7 +6,6 @@
 // Column reductions over rows (LayerNorm's dgamma/dbeta) are two-stage with a row ->
 // chunk mapping fixed by the shape, so they are reproducible bit for bit (no atomics).
 #include "device_common.h"
-#include <hip/hip_ext.h>
 #include <initializer_list>
 
 #include "kernels.h"
@@ -948,7 +947,7 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
     const bool few = grid.x <= 256, ahead2 = grid.x > 512 && grid.x <= 3584;
-#define A_(NC, AHEAD, WAVES) hipExtLaunchKernelGGL((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), 0, st, nullptr, done, 0, (const TD*)dy, \
+#define A_(NC, AHEAD, WAVES) LAUNCH_MARKED_((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), st, done, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
 #define V_(NC) do { if (few) A_(NC, 1, 16); else if (ahead2) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
@@ -1028,12 +1027,12 @@ int layernorm_bwd_static(int dtype, const void* dy, bool dy_f32, const void* x, 
 void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st, hipEvent_t done) {
   if (n <= 0) return;
   dim3 grid((unsigned)((n + 2047) / 2048));
-  if (dtype == BF16) hipExtLaunchKernelGGL(gelu_bwd_bf16_kernel, grid, dim3(256), 0, st, nullptr, done, 0, (bf16_t*)d, (const bf16_t*)pre, n, tanh_form);
+  if (dtype == BF16) LAUNCH_MARKED_(gelu_bwd_bf16_kernel, grid, dim3(256), st, done, (bf16_t*)d, (const bf16_t*)pre, n, tanh_form);
   else {
     const dim3 grid4((unsigned)((n + 1023) / 1024));
     if ((((uintptr_t)d | (uintptr_t)pre) & 15) == 0)
-      hipExtLaunchKernelGGL(gelu_bwd_f32_kernel<true>, grid4, dim3(256), 0, st, nullptr, done, 0, (float*)d, (const float*)pre, n, tanh_form);
-    else hipExtLaunchKernelGGL(gelu_bwd_f32_kernel<false>, grid4, dim3(256), 0, st, nullptr, done, 0, (float*)d, (const float*)pre, n, tanh_form);
+      LAUNCH_MARKED_(gelu_bwd_f32_kernel<true>, grid4, dim3(256), st, done, (float*)d, (const float*)pre, n, tanh_form);
+    else LAUNCH_MARKED_(gelu_bwd_f32_kernel<false>, grid4, dim3(256), st, done, (float*)d, (const float*)pre, n, tanh_form);
   }
 }
 
