@@ -4,28 +4,32 @@
 // both differences are exact in fp32, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|, and what x2's own rounding
 // leaves is below 2^-27 |x|.  Of the nine products of a pair the six down to 2^-18 are multiplied
 // (v_mfma_f32_16x16x32_bf16: products exact, sums in fp32); the other three are below 2^-26 of the
-// product, under the 2^-24 that one fp32 rounding costs.  x0 y0 has accumulators of its own, rounded once
-// for 32 indices where fp32 MFMAs (32 x 32 x 2) round sixteen times; the other five, 2^-8 of it, share a second
-// set, added at the end.  (In one set the small products lose their last bits against a large sum:
-// 1.7 times the error of fp32 MFMAs instead of two thirds.)  Errors against 64 bits on N(0,1) operands, 2-norm
-// over the result's, fp32 MFMAs -> here: 768 indices 2.5e-7 -> 0.9-1.6e-7, 3072 5.0e-7 -> 1.7-3.4e-7, 30522
-// 1.6e-6 -> 0.6-1.1e-6 (the smaller with four ways of the reduction).
+// product, under the 2^-24 that one fp32 rounding costs.  x0 y0 has accumulators of its own; the other five, 2^-8
+// of it, share a second set, added at the end.  (In one set the small products lose their last bits against a large
+// sum: 1.7 times the error of fp32 MFMAs instead of two thirds.)  Errors against 64 bits, 2-norm over the result's,
+// fp32 MFMAs -> here, on N(0,1) operands: 768 indices 2.5-5.0e-7 -> 0.9-1.6e-7, 3072 5.0e-7 -> 1.6-3.4e-7, 30522
+// 1.6e-6 -> 0.8e-6 (the smaller with four ways of the reduction); with a GELU's outputs times N(0,1) the same.
+// With both operands of one sign, whose errors are a third of those, there is no bias, and 0.4-0.7 times the error,
+// or 1.4 times it where the fp32 MFMAs had four partial sums and this has one (1408 x 768, K = 3072 2.1e-7 -> 3.0e-7).
 // The matrix cores multiply bf16 at 16 times their fp32 rate, so six products leave 2.7.  Against the kernel
 // with fp32 MFMAs (32 x 32 and 64 x 64 tiles), us: 1408 x 768, K = 768 27 -> 22, K = 3072 87 -> 77; 1408 x 3072
 // 78 -> 57; data gradient 704 x 768, K = 3072 58 -> 40; weight gradients over 1408 rows, 768 x 768 27 -> 24,
 // 3072 x 768 74 -> 51, 30528 x 768 926 -> 371; 4096 x 3072, K = 768 173 -> 105 (185 TFLOP/s); 1408 x 30522
-// 590 -> 372; 64 x 768, K = 3072 27 -> 19; from a few slices of a few tiles on (64 columns) level.
+// 590 -> 372; 64 x 768, K = 3072 27 -> 19; from a few slices of a few tiles on (64 columns) level.  (All of this file's
+// times are without the scale below, which costs 2-3 %, 5 % at K = 3072 on 96 x 64 tiles, 56 -> 59 us.)
 //
-// What the split cannot carry are values that are not finite or round to infinity as bf16 (above
-// 0x1.ffp127): their differences are NaN, and so is every output they reach.  A wave that finds an
-// output that is not finite takes its tile again with fp32 MFMAs straight from memory, so infinities
-// and NaN come out as fp32 arithmetic has them (some 20 times slower).  Below 2^-109 the third part is
-// a bf16 denormal and loses bits, from 2^-118 on the second.
+// What is split is the value times 2^16, and sums are times 2^32 until the end: every part is then a bf16 number, denormal
+// ones included, for every fp32 value down to 2^-149.  (Unscaled, the third part loses bits from 2^-109 on and the
+// second from 2^-118.  To look for lost bits and take such tiles again costs half of it, and 20 times the time for a
+// single small value that matters nothing.)
+// What the split cannot carry are values that are not finite or above 2^112, and sums above 2^96: they leave
+// an output that is infinite or NaN.  A wave that finds one takes its tile again with fp32 MFMAs straight from memory,
+// so infinities, NaN and large values come out as fp32 arithmetic has them (some 20 times slower).
 //
 // Block tiles are BM x BN with one thread or more for 8 floats of a slice, and WK ways of sharing the reduction: k way
 // g takes the 32-index slices g, g + WK, ... and the ways' accumulators are added in order at the end.
 // A way's first 4 BM threads bring its A slice, the next 4 BN its B slice: 8 floats each, loaded ND slices ahead into
-// registers, split there (11 vector instructions for two values) and stored as three bf16 planes into
+// registers, split there (13 vector instructions for two values) and stored as three bf16 planes into
 // one of two buffers while the MFMAs work on the other; any that are left only multiply.  A wave issues one vector instruction in 8 clocks,
 // a SIMD one in 4, and splitting takes about two for each MFMA: hence many waves with small parts of
 // the tile each, four on every SIMD.  128 x 128 tiles: 16 waves of 32 x 32; 64 x 64: 8 waves of 16 x 32
@@ -66,8 +70,11 @@ template <int F> __device__ __forceinline__ int slot_at(int slot, int k8) {
   return slot * 64 + ((k8 ^ turn) << 4);
 }
 
-// two values -> their three bf16 parts, a's in the low halves
+// Two values -> the three bf16 parts of each times kUp, a's in the low halves
+constexpr float kUp = 0x1p16f, kDown = 0x1p-32f;
 __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[3]) {
+  a *= kUp;
+  b *= kUp;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     w[p] = pack_bf16x2(a, b);
@@ -350,6 +357,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
         acc[i][j] = s;
       }
   }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] *= kDown;  // (infinities stay what they are)
   // register r of fragment (i, j): row TM * (4 q + r) + i, column TN * l16 + j of the wave's part
   const int mw = m0 + wm * 16 * TM, nw = n0 + wn * 16 * TN;
   bool finite = true;

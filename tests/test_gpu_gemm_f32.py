@@ -97,3 +97,29 @@ def test_infinities_and_nan(M, N, K, a_k, b_k):
         mag = np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64)).T
     # the tiles taken again round for every two indices
     assert np.all(np.abs(got[fin] - ref[fin]) <= (K / 2 + 16) * U * mag[fin])
+
+
+# A's and B's values around 2^ea and 2^eb: where parts of a value would be bf16 denormals or vanish (below 2^-109),
+# fp32 denormals; and operands above 2^112 and sums above 2^96, which the split's scale takes out of fp32's range
+@pytest.mark.parametrize("ea,eb", [(-112, 0), (-116, 90), (60, -124), (-133, 100), (-145, 100), (90, -149), (-60, -60), (50, 50), (-20, 114)])
+@pytest.mark.parametrize("M,N,K,a_k,b_k", [(33, 65, 131, 1, 1), (260, 2300, 99, 0, 0), (1410, 1300, 200, 1, 0), (1409, 770, 515, 1, 1)])
+def test_small_and_large_operands(M, N, K, a_k, b_k, ea, eb):
+    rng = np.random.default_rng(M + K + 1000 * (ea + 200) + eb + 200)
+    A, B = rng.standard_normal((M, K)), rng.standard_normal((N, K))
+    A, B = (A * 2.0 ** ea).astype(np.float32), (B * 2.0 ** eb).astype(np.float32)
+    # every fourth column of B sees the small or large values alone, its others stand beside common ones
+    A[:, : K // 2] = rng.standard_normal((M, K // 2))
+    B[:, : K // 2] = rng.standard_normal((N, K // 2)) * 2.0 ** min(0, ea + eb)
+    B[::4, : K // 2] = 0.0
+    a64, b64 = A.astype(np.float64), B.astype(np.float64)
+    ref, mag = a64 @ b64.T, np.abs(a64) @ np.abs(b64).T
+    dA, lda = put(A, a_k, 0)
+    dB, ldb = put(B, b_k, 0)
+    C = torch.zeros((M, N), device=DEV)
+    mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C, N, 0, M, N, K)
+    sync()
+    # as above, or one rounding for every two indices where a tile is taken again; sums below 2^-126 round to 2^-149
+    per = 2 if ea + eb > 80 or max(ea, eb) > 105 else 32
+    bound = (K / per + 16) * U * mag + 2.0 ** -149 * K
+    err = np.abs(host(C).astype(np.float64) - ref)
+    assert np.all(err <= bound), (err / np.maximum(mag, 1e-300)).max()
