@@ -3,15 +3,12 @@
 //
 // Head sizes 32 and 64; the fp32 configuration, and bf16 with head size 32 (bf16 with head size 64
 // runs on the bf16 kernels of attention_mfma.hip).  A block owns 32 query rows (forward, dQ) or 32
-// key rows (dK/dV) and its four waves take the 32-row tiles of the opposite rows in turn; their results are added in
-// wave order at the end.  An MFMA of 32 x 32 x 2 takes 64 clocks, a tile 64-128 of them: a wave that walks
-// all tiles of its rows, as before (two waves of a block side by side, sharing the tiles in LDS), is a chain of
-// 3 us for each, while a short batch has fewer waves than the chip has SIMDs.  Nothing is shared but the own rows: a
-// wave loads a tile's rows from memory straight into operands of the first products, the next tile's while it
-// works, and passes them through its own LDS for the product that needs them by columns, without a barrier.
-// Forward / backward, us: 12 heads of 64, 16 samples of 35-141 tokens 30 / 74 -> 24 / 73, 16 x 88 20 / 50 -> 16 / 45,
-// 16 x 256 51 / 168 -> 49 / 141, 16 x 512 150 / 480 -> 142 / 444; causal 3 x 300 35 / 102 -> 21 / 59; 2 heads of 32, 4 x 33
-// 6.5 / 16.5 -> 5.3 / 12.6; one sample of a single tile 5.6 / 14.8 -> 5.9 / 16.0.
+// key rows (dK/dV) and its W waves (one, two or four, see waves_of_block) take the 32-row tiles of the opposite rows
+// in turn; their results are added in wave order at the end.  An MFMA of 32 x 32 x 2 takes 64 clocks, a tile 64-128 of
+// them: a wave that walks all tiles of its rows is a chain of 3 us for each, while a short batch has fewer waves than
+// the chip has SIMDs.  Nothing is shared but the own rows: a wave loads a tile's rows from memory straight into
+// operands of the first products, the next tile's while it works, and passes them through its own LDS for the
+// product that needs them by columns, without a barrier.
 //
 //   forward   O_i = sum_j softmax_j(q_i k_j / sqrt(d)) v_j,   lse_i = log sum_j exp(s_ij)
 //   backward  P_ij = exp(s_ij - lse_i), dP_ij = dO_i v_j, dS_ij = P_ij (dP_ij - delta_i),
@@ -22,7 +19,7 @@
 // computed with the wave's own rows as columns, so a lane's 16 registers belong to one of its rows,
 // and register r is, as it stands, the B operand of the next product for the index pair
 // (8*(r/4) + r%4, the same + 4): the probabilities never leave their registers.
-// (One wave per row with a shuffle per key, as before: 222, 407 and 391 us per layer for forward, dQ
+// (One wave per row with a shuffle per key: 222, 407 and 391 us per layer for forward, dQ
 // and dK/dV at B = 16, L = 141, 12 heads of 64.)
 //
 // Every output element is produced by one wave in a fixed order: reproducible bit for bit.
@@ -43,7 +40,6 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
 namespace {
 
 constexpr int TR = 32;                 // own rows of a block, and rows of a streamed tile
-constexpr int WAVES = 4;               // they take the tiles in turn
 
 __device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
 __device__ __forceinline__ float4 load4(const bf16_t* p) {
@@ -111,16 +107,16 @@ __device__ __forceinline__ void put_part(float* part, int lane, const f32x16 (&a
     for (int g = 0; g < 4; ++g)
       *(float4*)&part[((4 * db + g) * 64 + lane) * 4] = make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
 }
-// ... and behind a barrier wave w adds the n waves' parts of head columns 8 q + 4 h .., q = w, w + WAVES, ..., in wave
+// ... and behind a barrier wave w adds the n waves' parts of head columns 8 q + 4 h .., q = w, w + W, ..., in wave
 // order, each times its own row's factor.
-template <typename T, int D>
-__device__ __forceinline__ void store_sum(T* dst, const float* parts, int stride, int n, int wave, int lane, const float (&factor)[WAVES]) {
+template <typename T, int D, int W>
+__device__ __forceinline__ void store_sum(T* dst, const float* parts, int stride, int n, int wave, int lane, const float (&factor)[W]) {
 #pragma unroll
-  for (int i = 0; i < D / 8 / WAVES; ++i) {
-    const int q = wave + WAVES * i;
+  for (int i = 0; i < D / 8 / W; ++i) {
+    const int q = wave + W * i;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
+    for (int w = 0; w < W; ++w) {
       if (w >= n) break;
       const float4 v = *(const float4*)&parts[w * stride + (q * 64 + lane) * 4];
       s.x = fmaf(v.x, factor[w], s.x); s.y = fmaf(v.y, factor[w], s.y);
@@ -129,22 +125,39 @@ __device__ __forceinline__ void store_sum(T* dst, const float* parts, int stride
     store4(dst + 8 * q + 4 * (lane >> 5), s);
   }
 }
+// a single wave's sums straight from its registers, times factor (zeros where there is none)
+template <typename T, int D>
+__device__ __forceinline__ void store_own(T* dst, int lane, const f32x16 (&acc)[D / 32], bool any, float factor) {
+#pragma unroll
+  for (int q = 0; q < D / 8; ++q) {
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    const f32x16& a = acc[q / 4];
+    const int r = 4 * (q % 4);
+    if (any) s = make_float4(a[r] * factor, a[r + 1] * factor, a[r + 2] * factor, a[r + 3] * factor);
+    store4(dst + 8 * q + 4 * (lane >> 5), s);
+  }
+}
+
+// The grid is 8 x blocks of a pair x groups of 8 pairs, so that the blocks of a (sample, head) pair run on one XCD and
+// its keys and values (or queries) reach that XCD's L2 once.
+__device__ __forceinline__ int pair_of_block() { return blockIdx.z * 8 + blockIdx.x; }
 
 }  // namespace
 
 // qkv row stride is 3*H; head hh of token t: q at t*3H + hh*D, k at +H, v at +2H.
-template <typename T, int D>
-__global__ __launch_bounds__(64 * WAVES, 3) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
-                                                       float* __restrict__ lse, Rows rows, int L, int nh, int causal,
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W, 3) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
+                                                       float* __restrict__ lse, Rows rows, int L, int nh, int pairs, int causal,
                                                        DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
-  __shared__ float ms[WAVES][TR], ls[WAVES][TR];
+  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], tiles[W][TR * (D + 4)];
+  __shared__ float ms[W][TR], ls[W][TR];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int i0 = blockIdx.y * TR, bh = pair_of_block();
+  if (bh >= pairs) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int i0 = blockIdx.x * TR;
   if (i0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
   const int qi = i0 + ql, qc = min(qi, sm.n - 1);
@@ -166,12 +179,12 @@ __global__ __launch_bounds__(64 * WAVES, 3) void attn_fwd_kernel(const T* __rest
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) clear(o[db]);
   float m = -INFINITY, l = 0.f;
-  for (int k0 = wave * TR; k0 < kend; k0 += WAVES * TR) {
+  for (int k0 = wave * TR; k0 < kend; k0 += W * TR) {
     f32x16 s;
     scores<D>(k, own_q, ql, h, s);
     stash<D>(tiles[wave], ql, h, v);
     wave_sync();
-    if (k0 + WAVES * TR < kend) fetch(k0 + WAVES * TR);
+    if (k0 + W * TR < kend) fetch(k0 + W * TR);
     float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -205,37 +218,46 @@ __global__ __launch_bounds__(64 * WAVES, 3) void attn_fwd_kernel(const T* __rest
     accumulate<D>(tiles[wave], ql, h, s, o);
     wave_sync();
   }
+  T* out = ctx + (sm.first + qi) * H + hh * D;
+  if (W == 1) {
+    if (qi < sm.n) {
+      store_own<T, D>(out, lane, o, true, drop.scale / l);
+      if (h == 0) lse[(int64_t)bh * L + qi] = m + logf(l);
+    }
+    return;
+  }
   // the waves' results brought to the largest maximum and added in order
   put_part<D>(tiles[wave], lane, o);
   if (h == 0) { ms[wave][ql] = m; ls[wave][ql] = l; }
   __syncthreads();
-  const int n = min(WAVES, (kend + TR - 1) / TR);
-  float mall = ms[0][ql], lall = 0.f, factor[WAVES];  // finite: key 0 is visible to every query
+  const int n = min(W, (kend + TR - 1) / TR);
+  float mall = ms[0][ql], lall = 0.f, factor[W];      // finite: key 0 is visible to every query
 #pragma unroll
-  for (int w = 1; w < WAVES; ++w) mall = fmaxf(mall, ms[w][ql]);
+  for (int w = 1; w < W; ++w) mall = fmaxf(mall, ms[w][ql]);
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) { factor[w] = expf(ms[w][ql] - mall); lall += ls[w][ql] * factor[w]; }
+  for (int w = 0; w < W; ++w) { factor[w] = expf(ms[w][ql] - mall); lall += ls[w][ql] * factor[w]; }
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) factor[w] *= drop.scale / lall;
+  for (int w = 0; w < W; ++w) factor[w] *= drop.scale / lall;
   if (qi < sm.n) {
-    store_sum<T, D>(ctx + (sm.first + qi) * H + hh * D, tiles[0], TR * (D + 4), n, wave, lane, factor);
+    store_sum<T, D, W>(out, tiles[0], TR * (D + 4), n, wave, lane, factor);
     if (wave == 0 && h == 0) lse[(int64_t)bh * L + qi] = mall + logf(lall);
   }
 }
 
 // also writes delta_i = dO_i O_i for the dK/dV kernel, which runs after this one
-template <typename T, int D>
-__global__ __launch_bounds__(64 * WAVES, 3) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W, 3) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
                                                           const T* __restrict__ dctx, const float* __restrict__ lse,
                                                           float* __restrict__ delta, T* __restrict__ dqkv, Rows rows, int L,
-                                                          int nh, int causal, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], own_g[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
+                                                          int nh, int pairs, int causal, DropDesc drop) {
+  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], own_g[TR * (D + 4)], tiles[W][TR * (D + 4)];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int i0 = blockIdx.y * TR, bh = pair_of_block();
+  if (bh >= pairs) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int i0 = blockIdx.x * TR;
   if (i0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
   const int qi = i0 + ql, qc = min(qi, sm.n - 1);
@@ -261,7 +283,7 @@ __global__ __launch_bounds__(64 * WAVES, 3) void attn_bwd_dq_kernel(const T* __r
       delta_q = fmaf(of[g].w, go[g].w, delta_q);
     }
     delta_q += __shfl_xor(delta_q, 32, 64);
-    if (wave == 1) stash<D>(own_g, ql, h, go);
+    if (wave == (W > 1 ? 1 : 0)) stash<D>(own_g, ql, h, go);
     if (wave == 0) {
       if (h == 0 && qi < sm.n) delta[(int64_t)bh * L + qi] = delta_q;
       fetch_rows<T, D>(base, ld3, i0, sm.n - 1, ql, h, of);
@@ -272,13 +294,13 @@ __global__ __launch_bounds__(64 * WAVES, 3) void attn_bwd_dq_kernel(const T* __r
   f32x16 dq[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) clear(dq[db]);
-  for (int k0 = wave * TR; k0 < kend; k0 += WAVES * TR) {
+  for (int k0 = wave * TR; k0 < kend; k0 += W * TR) {
     f32x16 s, dp;
     scores<D>(k, own_q, ql, h, s);
     scores<D>(v, own_g, ql, h, dp);
     stash<D>(tiles[wave], ql, h, k);
     wave_sync();
-    if (k0 + WAVES * TR < kend) fetch(k0 + WAVES * TR);
+    if (k0 + W * TR < kend) fetch(k0 + W * TR);
     if (drop.thr) {                                   // d(P) of a dropped probability is zero, of a kept one scaled
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -298,28 +320,33 @@ __global__ __launch_bounds__(64 * WAVES, 3) void attn_bwd_dq_kernel(const T* __r
     accumulate<D>(tiles[wave], ql, h, s, dq);
     wave_sync();
   }
+  T* out = dqkv + (sm.first + qi) * ld3 + hh * D;
+  if (W == 1) {
+    if (qi < sm.n) store_own<T, D>(out, lane, dq, true, scale);
+    return;
+  }
   put_part<D>(tiles[wave], lane, dq);
   __syncthreads();
-  float factor[WAVES];
+  float factor[W];
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) factor[w] = scale;
-  if (qi < sm.n)
-    store_sum<T, D>(dqkv + (sm.first + qi) * ld3 + hh * D, tiles[0], TR * (D + 4), min(WAVES, (kend + TR - 1) / TR), wave, lane, factor);
+  for (int w = 0; w < W; ++w) factor[w] = scale;
+  if (qi < sm.n) store_sum<T, D, W>(out, tiles[0], TR * (D + 4), min(W, (kend + TR - 1) / TR), wave, lane, factor);
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
-                                                           T* __restrict__ dqkv, Rows rows, int L, int nh, int causal,
+                                                           T* __restrict__ dqkv, Rows rows, int L, int nh, int pairs, int causal,
                                                            DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_k[TR * (D + 4)], own_v[TR * (D + 4)], tiles[WAVES][TR * (D + 4)];
-  __shared__ __attribute__((aligned(16))) float stats[WAVES][2][TR];      // lse and delta of the tile's queries
+  __shared__ __attribute__((aligned(16))) float own_k[TR * (D + 4)], own_v[TR * (D + 4)], tiles[W][TR * (D + 4)];
+  __shared__ __attribute__((aligned(16))) float stats[W][2][TR];      // lse and delta of the tile's queries
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kl = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y, b = bh / nh, hh = bh - b * nh;
+  const int j0 = blockIdx.y * TR, bh = pair_of_block();
+  if (bh >= pairs) return;
+  const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  const int j0 = blockIdx.x * TR;
   if (j0 >= sm.n) return;
   const T* base = qkv + sm.first * ld3 + hh * D;
   const T* gbase = dctx + sm.first * H + hh * D;
@@ -333,17 +360,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dkv_kernel(const T* __
     fetch_rows<T, D>(base, ld3, first, sm.n - 1, kl, h, q);
     fetch_rows<T, D>(gbase, H, first, sm.n - 1, kl, h, go);
   }
-  if (wave < 2) {
-    float4 own[D / 8];
-    fetch_rows<T, D>(base + (wave + 1) * H, ld3, j0, sm.n - 1, kl, h, own);
-    stash<D>(wave ? own_v : own_k, kl, h, own);
-  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (wave == (W > 1 ? i : 0)) {
+      float4 own[D / 8];
+      fetch_rows<T, D>(base + (i + 1) * H, ld3, j0, sm.n - 1, kl, h, own);
+      stash<D>(i ? own_v : own_k, kl, h, own);
+    }
   __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) { clear(dk[db]); clear(dv[db]); }
-  for (int q0 = first; q0 < qend; q0 += WAVES * TR) {
-    const int next = q0 + WAVES * TR;
+  for (int q0 = first; q0 < qend; q0 += W * TR) {
+    const int next = q0 + W * TR;
     const float stat = (h ? delta : lse)[(int64_t)bh * L + min(q0 + kl, sm.n - 1)];
     f32x16 s, dp;
     scores<D>(q, own_k, kl, h, s);
@@ -384,45 +413,93 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dkv_kernel(const T* __
     wave_sync();
   }
   const bool in = ki < sm.n;
-  const int n = ki < sm.keys ? min(WAVES, max(0, qend - qstart + TR - 1) / TR) : 0;   // padded keys: zeros, whatever the lane's column held
+  const int n = ki < sm.keys ? min(W, max(0, qend - qstart + TR - 1) / TR) : 0;   // padded keys: zeros, whatever the lane's column held
   T* out = dqkv + (sm.first + ki) * ld3 + hh * D;
-  float factor[WAVES];
+  if (W == 1) {
+    if (in) {
+      store_own<T, D>(out + H, lane, dk, n > 0, scale);
+      store_own<T, D>(out + 2 * H, lane, dv, n > 0, 1.f);
+    }
+    return;
+  }
+  float factor[W];
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) factor[w] = scale;
+  for (int w = 0; w < W; ++w) factor[w] = scale;
   put_part<D>(tiles[wave], lane, dk);
   __syncthreads();
-  if (in) store_sum<T, D>(out + H, tiles[0], TR * (D + 4), n, wave, lane, factor);
+  if (in) store_sum<T, D, W>(out + H, tiles[0], TR * (D + 4), n, wave, lane, factor);
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) factor[w] = 1.f;
+  for (int w = 0; w < W; ++w) factor[w] = 1.f;
   put_part<D>(tiles[wave], lane, dv);
   __syncthreads();
-  if (in) store_sum<T, D>(out + 2 * H, tiles[0], TR * (D + 4), n, wave, lane, factor);
+  if (in) store_sum<T, D, W>(out + 2 * H, tiles[0], TR * (D + 4), n, wave, lane, factor);
 }
 
-template <typename T, int D>
-static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
+// Waves of a block, for `tiles` tiles of a sample and `blocks` blocks of the whole batch.  Four make the chain of a
+// sample's tiles a quarter as long; a wave without a tile only takes LDS and a place, and every further one's sums
+// have to be added.  So four where the blocks alone do not fill the chip: up to 512 of them for each tile of a
+// sample, and up to 768 where of four waves' last turn two or three would idle; one where a sample has two tiles
+// or three and the blocks do fill it.  Forward + backward in us with one / two / four
+// waves, 12 heads of 64 in fp32 (heads of 32 alike), against two waves of a block on 64 rows that share tiles in LDS:
+//   512 x 32 tokens 180 / 213 / 279 against 231    128 x 64 127 / 133 / 176 against 133    16 x 64 40 / 40 / 42 against 37
+//   8 x 64 35 / 26.5 / 27 against 36               128 x 96 239 / 262 / 277 against 287    8 x 128 65 / 62 / 48 against 61
+//   32 x 128 115 / 126 / 114 against 121           16 x 141 padded 93 / 86 / 103 against 123
+//   32 x 256 379 / 349 / 333 against 348           16 x 512 causal 575 / 459 / 433 against 606
+// (One tile of 12-192 pairs stays 3-7 % behind that, a microsecond for the three kernels, 257-512 blocks of two tiles of
+// head size 64 10 % and 1536-3072 of head size 32 2-6 %, whatever the waves.)
+static int waves_of_block(int tiles, int64_t blocks) {
+  if (tiles == 1 || (tiles <= 3 && blocks >= 768 * (tiles - 1))) return 1;
+  const bool idle = tiles == 3 || tiles == 5 || tiles == 6;   // (behind more turns the last weighs little)
+  return tiles == 2 || blocks >= (idle ? 768 : 512 * (int64_t)tiles) ? 2 : 4;
+}
+
+template <typename T, int D, int W>
+static void fwd_w(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                   const DropDesc& drop, hipStream_t st) {
-  dim3 grid((L + TR - 1) / TR, B * nh);
-  hipLaunchKernelGGL((attn_fwd_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (T*)ctx, lse, rows, L, nh, causal, drop);
+  const int pairs = B * nh;
+  hipLaunchKernelGGL((attn_fwd_kernel<T, D, W>), dim3(8, (L + TR - 1) / TR, (pairs + 7) / 8), dim3(64 * W), 0, st, (const T*)qkv,
+                     (T*)ctx, lse, rows, L, nh, pairs, causal, drop);
+}
+template <typename T, int D>
+static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int whole, int L, int nh, int causal,
+                  const DropDesc& drop, hipStream_t st) {
+  const int tiles = (L + TR - 1) / TR;
+  switch (waves_of_block(tiles, (int64_t)whole * nh * tiles)) {
+    case 1: fwd_w<T, D, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
+    case 2: fwd_w<T, D, 2>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
+    default: fwd_w<T, D, 4>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
+  }
+}
+template <typename T, int D, int W>
+static void bwd_w(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
+                  const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
+  const int pairs = B * nh;
+  const dim3 grid(8, (L + TR - 1) / TR, (pairs + 7) / 8);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D, W>), grid, dim3(64 * W), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
+                     delta, (T*)dqkv, rows, L, nh, pairs, causal, drop);
+  LAUNCH_MARKED_((attn_bwd_dkv_kernel<T, D, W>), grid, dim3(64 * W), st, done, (const T*)qkv, (const T*)dctx, lse, delta,
+                 (T*)dqkv, rows, L, nh, pairs, causal, drop);
 }
 template <typename T, int D>
 static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
                   const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
-  dim3 grid((L + TR - 1) / TR, B * nh);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(64 * WAVES), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
-                     delta, (T*)dqkv, rows, L, nh, causal, drop);
-  LAUNCH_MARKED_((attn_bwd_dkv_kernel<T, D>), grid, dim3(64 * WAVES), st, done, (const T*)qkv, (const T*)dctx, lse, delta,
-                     (T*)dqkv, rows, L, nh, causal, drop);
+  const int tiles = (L + TR - 1) / TR;
+  switch (waves_of_block(tiles, (int64_t)B * nh * tiles)) {
+    case 1: bwd_w<T, D, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
+    case 2: bwd_w<T, D, 2>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
+    default: bwd_w<T, D, 4>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
+  }
 }
 
 void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,
-                   int causal, const DropDesc& drop, hipStream_t st) {
+                   int causal, const DropDesc& drop, hipStream_t st, int whole) {
   if (B * L <= 0) return;
+  if (whole <= 0) whole = B;
   if (dtype == BF16 && d == 64) attention_fwd_mfma(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
-  else if (dtype == BF16) fwd_t<bf16_t, 32>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
-  else if (d == 32) fwd_t<float, 32>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
-  else fwd_t<float, 64>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
+  else if (dtype == BF16) fwd_t<bf16_t, 32>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
+  else if (d == 32) fwd_t<float, 32>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
+  else fwd_t<float, 64>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
 }
 
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta,

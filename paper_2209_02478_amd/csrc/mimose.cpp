@@ -643,7 +643,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   if (f_.pre_ln) { ln(x, p.ln1g, p.ln1b, at(A.n1, H), false); a = at(A.n1, H); }
   lin(a, H, p.wqkv, p.bqkv, at(A.qkv, 3 * H), 3 * H, nullptr, nullptr, 0, false);
   mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_,
-                    mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s);
+                    mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s, B_);
   lin(at(A.ctx, H), H, p.wo, p.bo, at(A.s1, H, wide_), H, x, nullptr, 0, wide_);
   if (f_.pre_ln) {
     ln(at(A.s1, H), p.ln2g, p.ln2b, at(A.u, H), false);

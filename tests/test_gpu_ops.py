@@ -618,6 +618,19 @@ def test_attention_fp32_waves(dtype, d, causal, L, lengths, p_drop):
     attention_case(dtype, len(lengths) if lengths else 2, L, 3, d, causal, seed=L + 5, lengths=lengths, p_drop=p_drop)
 
 
+# Waves of a block by tiles of 32 rows and by blocks of the batch (samples x heads x tiles): one, two or four
+@pytest.mark.parametrize("dtype,d", [(0, 64), (0, 32), (1, 32)])
+@pytest.mark.parametrize("B,L,nh,causal,p_drop", [(3, 31, 3, 0, 0.2), (5, 32, 2, 1, 0.0),        # one tile: one wave
+                                                  (127, 64, 3, 0, 0.0), (128, 64, 3, 1, 0.0),    # 762, 768 blocks of two: two, one
+                                                  (129, 33, 3, 0, 0.2),                          # 774, the last of one row
+                                                  (170, 96, 3, 0, 0.0), (171, 70, 3, 0, 0.2),    # 1530, 1539 of three: two, one
+                                                  (52, 129, 3, 1, 0.2),                          # 780 of five: two
+                                                  (171, 97, 3, 0, 0.0)])                         # 2052 of four: two
+def test_attention_waves_of_a_block(dtype, d, B, L, nh, causal, p_drop):
+    lengths = [(1, L, max(1, L - 1), min(L, 32), min(L, 33), max(1, L // 2))[b % 6] for b in range(B)]
+    attention_case(dtype, B, L, nh, d, causal, seed=L + B, lengths=lengths, p_drop=p_drop)
+
+
 # dropout of the probabilities: the kept set is the oracle's (integer comparisons of generator
 # words), so the usual tolerances apply; lengths off the 4-key grid, several key tiles, padding
 @pytest.mark.parametrize("dtype", [0, 1])

@@ -423,7 +423,8 @@ def test_stream_layout_does_not_change_the_bits(name):
 
 
 @pytest.mark.parametrize("name,B,L", [("fp32_postln", 11, 48), ("bf16_postln", 4, 90), ("bf16_preln_causal", 3, 80),
-                                      ("bf16_stages", 5, 96)])
+                                      ("bf16_stages", 5, 96),
+                                      ("fp32_postln", 200, 64)])      # half of it alone has other waves of an attention block
 def test_halves_of_the_batch_change_no_bits(name, B, L):
     """The same for batches large enough (2^15 elements per tensor) to run the forward in halves."""
     shape = SMALL[name]
