@@ -4,16 +4,32 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include <tuple>
+
 #include "kernels.h"
 
 // Launches K without dynamic LDS; DONE (may be null) is bound to its end.
 #define LAUNCH_MARKED_(K, GRID, BLOCK, STREAM, DONE, ...)                                              \
   do {                                                                                                 \
-    if (DONE) hipExtLaunchKernelGGL(K, GRID, BLOCK, 0, STREAM, nullptr, DONE, 0, __VA_ARGS__);         \
+    if (DONE) launch_marked(K, GRID, BLOCK, 0, STREAM, nullptr, DONE, __VA_ARGS__);                    \
     else hipLaunchKernelGGL(K, GRID, BLOCK, 0, STREAM, __VA_ARGS__);                                   \
   } while (0)
 
 namespace mk {
+
+void note_marking(hipError_t e);   // kept for marking_error()
+
+// Launches a kernel with events bound to its start and end (either may be null), through the call that says
+// whether the launch succeeded.
+template <typename... P, typename... A>
+inline void launch_marked(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t start, hipEvent_t stop,
+                          A... a) {
+  std::tuple<P...> params(a...);
+  std::apply([&](P&... p) {
+    void* args[] = {(void*)&p...};
+    note_marking(hipExtLaunchKernel((const void*)kernel, grid, block, args, lds, st, start, stop, 0));
+  }, params);
+}
 
 typedef uint16_t bf16_t;   // raw bfloat16 bits
 

@@ -17,8 +17,6 @@
 #include "device_common.h"
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 
 #include "kernels.h"
@@ -384,10 +382,10 @@ static void launch_splitk_reduce(const GemmDev& p, hipStream_t st, hipEvent_t t1
   const int64_t MN = (int64_t)p.M * p.N;
   const dim3 grid((unsigned)((MN / 4 + 256) / 256));
   if (p.c_f32)
-    hipExtLaunchKernelGGL(splitk_reduce_kernel<false>, grid, dim3(256), 0, st, nullptr, t1, 0, p.partial, p.C, p.ldc,
+    launch_marked(splitk_reduce_kernel<false>, grid, dim3(256), 0, st, nullptr, t1, p.partial, p.C, p.ldc,
                           p.a_rowsum, p.M, p.N, p.splits);
   else
-    hipExtLaunchKernelGGL(splitk_reduce_kernel<true>, grid, dim3(256), 0, st, nullptr, t1, 0, p.partial, p.C, p.ldc,
+    launch_marked(splitk_reduce_kernel<true>, grid, dim3(256), 0, st, nullptr, t1, p.partial, p.C, p.ldc,
                           p.a_rowsum, p.M, p.N, p.splits);
 }
 
@@ -401,7 +399,7 @@ static void launch_bgemm(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEve
   }
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int total = tiles_m * tiles_n * p.splits, per = (total + 7) / 8;
-  hipExtLaunchKernelGGL((bgemm_kernel<AK, BKM>), dim3(per * 8), dim3(256), smem, st, t0, p.splits > 1 ? nullptr : t1, 0, p,
+  launch_marked((bgemm_kernel<AK, BKM>), dim3(per * 8), dim3(256), smem, st, t0, p.splits > 1 ? nullptr : t1, p,
                         tiles_n, total, per);
   if (p.splits > 1) launch_splitk_reduce(p, st, t1);
 }

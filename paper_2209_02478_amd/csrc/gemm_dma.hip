@@ -21,8 +21,6 @@
 // with tile t+2.  The reduction order over k is fixed by the shape alone.
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 namespace mk {
 
 namespace {
@@ -305,8 +303,8 @@ static void launch_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % BK != 0;
   dim3 grid(per * 8), block(256);
   // t0, t1 (optional): events bound to this kernel's own start and end
-  if (ktail) hipExtLaunchKernelGGL((bgemm_dma_kernel<AK, BKM, true>), grid, block, 0, st, t0, t1, 0, p, tiles_n, total, per);
-  else hipExtLaunchKernelGGL((bgemm_dma_kernel<AK, BKM, false>), grid, block, 0, st, t0, t1, 0, p, tiles_n, total, per);
+  if (ktail) launch_marked((bgemm_dma_kernel<AK, BKM, true>), grid, block, 0, st, t0, t1, p, tiles_n, total, per);
+  else launch_marked((bgemm_dma_kernel<AK, BKM, false>), grid, block, 0, st, t0, t1, p, tiles_n, total, per);
 }
 
 // Requirements: 16-byte chunks must be wholly inside or wholly outside the matrix along the

@@ -46,8 +46,6 @@
 // row's four indices.
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 #include <type_traits>
 
@@ -446,8 +444,8 @@ static void launch_f32(const GemmDev& p, int which, int vec_in, int vec_out, hip
   {                                                                                                                       \
     constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN;                                                                   \
     const int tiles_n = (p.N + BN - 1) / BN, total = (p.M + BM - 1) / BM * tiles_n, per = (total + 7) / 8;                \
-    hipExtLaunchKernelGGL((sgemm_split_kernel<AK, BKM, WM, WN, TM, TN, WK, ND>), dim3(per * 8), dim3(64 * WM * WN * WK),  \
-                          0, st, t0, t1, 0, p, vec_in, vec_out, tiles_n, total, per);                                     \
+    launch_marked((sgemm_split_kernel<AK, BKM, WM, WN, TM, TN, WK, ND>), dim3(per * 8), dim3(64 * WM * WN * WK),  \
+                          0, st, t0, t1, p, vec_in, vec_out, tiles_n, total, per);                                     \
   }
   switch (which) {
     case 0: GO_(4, 4, 2, 2, 1, 1) break;

@@ -54,8 +54,6 @@
 #pragma once
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <type_traits>
 
 namespace mk {
@@ -593,8 +591,8 @@ void launch_large_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEvent_t 
   const dim3 grid(8 * (per < 32 ? per : 32)), block(512);
   bool ktail = false;
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % large::LBK != 0;
-  if (ktail) hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
-  else hipExtLaunchKernelGGL((bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+  if (ktail) launch_marked((bgemm_large_kernel<FM, AK, BKM, true, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, p, tiles_n, total, per);
+  else launch_marked((bgemm_large_kernel<FM, AK, BKM, false, GE, SUMS>), grid, block, large::Sizes<FM>::SMEM, st, t0, t1, p, tiles_n, total, per);
 }
 
 // Requirements: K % 8 == 0 when an operand is k-major (or zeros vouched for behind a k-major A's last column,

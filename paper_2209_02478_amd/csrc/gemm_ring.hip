@@ -18,8 +18,6 @@
 // 256 bytes hold 128/R k rows, so s(q) = 4 * ((q & 3) / (128/R)).
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <type_traits>
 
 namespace mk {
@@ -321,9 +319,9 @@ static void launch_ring_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipEv
   bool ktail = false;
   for (int i = 0; i < p.splits; ++i) ktail |= (p.kb[i + 1] - p.kb[i]) % RBK != 0 || p.kb[i + 1] == p.kb[i];
   if (ktail)
-    hipExtLaunchKernelGGL((bgemm_ring_kernel<AK, BKM, true, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+    launch_marked((bgemm_ring_kernel<AK, BKM, true, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, p, tiles_n, total, per);
   else
-    hipExtLaunchKernelGGL((bgemm_ring_kernel<AK, BKM, false, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+    launch_marked((bgemm_ring_kernel<AK, BKM, false, WM, WN, TM, TN, NS>), grid, block, SMEM, st, t0, t1, p, tiles_n, total, per);
 }
 template <bool AK, bool BKM>
 static void launch_ring(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {

@@ -18,8 +18,6 @@
 // a fixed per-lane offset and a scalar base that moves along k.
 #include "gemm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <type_traits>
 
 namespace mk {
@@ -282,9 +280,9 @@ static void launch_tiles_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipE
   const int tiles_n = (p.N + BN - 1) / BN, total = (p.M + BM - 1) / BM * tiles_n, per = (total + 7) / 8;
   const dim3 grid(per * 8), block(64 * WM * WN);
   if (p.K % (KB * TBK))
-    hipExtLaunchKernelGGL((bgemm_tiles_kernel<BKM, true, WM, WN, TM, TN, KB, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+    launch_marked((bgemm_tiles_kernel<BKM, true, WM, WN, TM, TN, KB, NS>), grid, block, SMEM, st, t0, t1, p, tiles_n, total, per);
   else
-    hipExtLaunchKernelGGL((bgemm_tiles_kernel<BKM, false, WM, WN, TM, TN, KB, NS>), grid, block, SMEM, st, t0, t1, 0, p, tiles_n, total, per);
+    launch_marked((bgemm_tiles_kernel<BKM, false, WM, WN, TM, TN, KB, NS>), grid, block, SMEM, st, t0, t1, p, tiles_n, total, per);
 }
 template <bool BKM>
 static void launch_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {

@@ -11,6 +11,10 @@ enum Gelu : int { GELU_NONE = 0, GELU_ERF = 1, GELU_TANH = 2 };
 
 constexpr int kMaxRowWidth = 1024;  // widest row the row-wise kernels accept (hidden size)
 
+// Launches take events that are bound to a kernel's start or end.  A launch that fails leaves its event where it was,
+// and nothing may wait for it: the first such failure on this thread since the last call, or success.
+hipError_t marking_error();
+
 inline size_t elt_size(int dtype) { return dtype == BF16 ? 2 : 4; }
 
 // Dropout mask descriptor, passed by value to kernels.  thr == 0: dropout off.

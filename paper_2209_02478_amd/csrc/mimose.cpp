@@ -402,6 +402,7 @@ class Step {
     if (!forked_) fork();
     a.time_stop = late ? c_->ev_late : done;
     if (!mk::gemm(dt_, a, c_->side)) throw StepError{MIMOSE_ERR_INVALID_ARG, "gemm: unsupported alignment"};
+    if (a.time_stop) check_marking();
     if (late) late_pending_ = early_marked_ = true;
     side_busy_ = true;
   }
@@ -482,6 +483,11 @@ class Step {
     mk::layernorm_bwd_reduce(partial, g(gi), g(bi), chunk_at_, chunk_at_ ? Tpad_ : T_, f_.hidden, aside ? c_->side : st_);
     if (aside) side_busy_ = true;
   }
+  // behind a launch that an event is bound to, before anything waits for the event
+  void check_marking() {
+    if (mk::marking_error() != hipSuccess)
+      throw StepError{MIMOSE_ERR_HIP, "launch of a kernel that another stream waits for failed"};
+  }
   // One fork serves everything issued on the weight-gradient stream until the main stream
   // launches its next product (every group of side work here is followed by one).
   bool forked_ = false;
@@ -498,6 +504,7 @@ class Step {
   hipEvent_t done_event() const { return dry_ || !second_stream() || c_->prof_on ? nullptr : c_->ev_fork; }
   void fork_behind_kernel() {
     if (!done_event()) return;
+    check_marking();
     if (hipStreamWaitEvent(c_->side, c_->ev_fork, 0) != hipSuccess)
       throw StepError{MIMOSE_ERR_HIP, "fork to the weight-gradient stream failed"};
     forked_ = true;
@@ -915,6 +922,7 @@ void Step::embed_backward() {
 void Step::run(const int32_t* tokens, const int32_t* labels, float* loss_out, bool wait) {
   Arena& ar = c_->arena;
   const int N = f_.n_layers;
+  (void)mk::marking_error();              // (of a profiled step, whose events only time)
   a_bytes.assign(N, 0); b_bytes.assign(N, 0); w_bytes.assign(N, 0);
   ar.pop_to(c_->fixed_top);
   ar.reset_high();
@@ -1128,6 +1136,7 @@ int do_step(mimose_ctx* c, const int32_t* tokens, const int32_t* labels, const i
     c->prof_pending.clear(); c->ev_used = 0;
     c->arena.pop_to(c->fixed_top);
     if (!dry && c->has_device) { if (c->side) (void)hipStreamSynchronize(c->side); (void)hipStreamSynchronize(c->stream); }
+    if (e.code == MIMOSE_ERR_HIP) (void)hipGetLastError();        // reported here, not by the next step too
     return fail(c, e.code, e.msg);
   }
   const uint64_t pk = c->arena.high();

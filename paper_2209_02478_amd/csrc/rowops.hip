@@ -968,7 +968,7 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
 #undef M_
   if (ex.masked)                                      // dx is stored: the mask in a pass of its own
     dropout_apply(sizeof(T) == 2 ? BF16 : F32, ex.masked, dx, false, nullptr, (int64_t)T_ * H, ex.d, ex.rows, ex.B, ex.L, H, st);
-  if (done) (void)hipEventRecord(done, st);
+  if (done) note_marking(hipEventRecord(done, st));
 }
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
                         const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st,
@@ -1132,6 +1132,10 @@ void adamw_update(int lowp_dtype, const AdamTensor* tensors, const AdamChunk* ch
   if (n_chunks <= 0) return;
   hipLaunchKernelGGL(adamw_kernel, dim3((unsigned)n_chunks * kAdamBlocks), dim3(kAdamThreads), 0, st, tensors, chunks, h);
 }
+
+static thread_local hipError_t first_marking_error = hipSuccess;
+void note_marking(hipError_t e) { if (first_marking_error == hipSuccess) first_marking_error = e; }
+hipError_t marking_error() { const hipError_t e = first_marking_error; first_marking_error = hipSuccess; return e; }
 
 void fill_zero(void* p, int64_t bytes, hipStream_t st) {
   int64_t n = bytes / 4;
