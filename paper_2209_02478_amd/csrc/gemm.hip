@@ -454,7 +454,11 @@ static bool ring_wgrad(int M, int N, int splits) {
 static bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
 bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return true;
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0) {             // nothing to launch that could carry the events
+    for (hipEvent_t e : {g.time_start, g.time_stop})
+      if (e) note_marking(hipEventRecord(e, st));
+    return true;
+  }
   GemmDev p;
   p.A = g.A; p.B = g.B; p.C = g.C; p.bias = g.bias; p.resid = g.resid; p.gelu_out = g.gelu_out; p.a_rowsum = g.a_rowsum;
   p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.ldr = g.ldr;

@@ -73,8 +73,9 @@ struct GemmArgs {
   bool beside = false;
   void* workspace = nullptr;       // optional scratch of gemm_workspace_bytes(M, N) for split reductions
   size_t workspace_bytes = 0;
-  // optional, both or neither: recorded by the product kernel's own start and end (not by markers
-  // around the launch), for per-kernel timing; a split product ends with its reduction kernel
+  // optional: events bound to the start of the product's first kernel and to the end of its last (a split product's
+  // reduction).  time_stop alone marks the end for another stream that waits for it, so every path has to bind
+  // it; together they time the product by its kernels and not by markers around the launch.
   hipEvent_t time_start = nullptr, time_stop = nullptr;
 };
 

@@ -57,6 +57,17 @@ int hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, void*, void* sta
 }
 """
 
+# a product without elements, with events
+EMPTY = r"""
+#include "kernels.h"
+extern "C" int empty_product(void* gemm, void* start, void* stop) {
+  mk::GemmArgs g{nullptr, 8, true, nullptr, 8, true, nullptr, 8, true, 0, 8, 8};
+  g.time_start = (hipEvent_t)start;
+  g.time_stop = (hipEvent_t)stop;
+  return ((bool (*)(int, const mk::GemmArgs&, hipStream_t))gemm)(mk::BF16, g, nullptr);
+}
+"""
+
 STEP = """
     import ctypes, sys
     runtime = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
@@ -71,19 +82,19 @@ STEP = """
     mi.mimose_set_dropout(ctx, float(sys.argv[4]), 0.0, 5, 0)
     batch = synthdata.make_batch(shape, 4, 96, 3)
     assert batch[0].size * shape.hidden > 1 << 15                 # two streams
-    runtime.shim_fail_at(-1)
+    runtime.shim_fail_at(ctypes.c_long(-1))
     mi.mimose_train_step(ctx, *batch, wait=False)
     n = runtime.shim_marks()
     assert n > 12, n
     for k in range(n):
-        runtime.shim_fail_at(k)
+        runtime.shim_fail_at(ctypes.c_long(k))
         try:
             mi.mimose_train_step(ctx, *batch, wait=False)
             raise SystemExit("marking %d of %d failed and the step did not say so" % (k, n))
         except mi.MimoseError as e:
             assert e.code == mi.MIMOSE_ERR_HIP, e
         assert runtime.shim_bad_waits() == 0, "a stream waits for marking %d of %d, which failed" % (k, n)
-        runtime.shim_fail_at(-1)
+        runtime.shim_fail_at(ctypes.c_long(-1))
         mi.mimose_train_step(ctx, *batch, wait=True)
 """
 
@@ -92,7 +103,10 @@ STEP = """
 def runtime(tmp_path_factory):
     d = tmp_path_factory.mktemp("runtime")
     (d / "runtime.cpp").write_text(RUNTIME)
-    subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", "-o", str(d / "runtime.so"), str(d / "runtime.cpp")])
+    (d / "empty.cpp").write_text(EMPTY)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", str(d / "runtime.so"), str(d / "runtime.cpp"),
+                           str(d / "empty.cpp"), "-D__HIP_PLATFORM_AMD__", "-I" + os.environ.get("ROCM_PATH", "/opt/rocm") + "/include",
+                           "-I" + os.path.join(ROOT, "paper_2209_02478_amd", "csrc")])
     return str(d / "runtime.so")
 
 
@@ -100,4 +114,20 @@ def runtime(tmp_path_factory):
 def test_failed_markings_reach_the_caller(runtime, dtype, pre_ln, p_drop):
     r = subprocess.run([sys.executable, "-c", textwrap.dedent(STEP), runtime, dtype, str(pre_ln), str(p_drop)], cwd=ROOT,
                        capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_empty_product_marks_its_events(runtime):
+    """Whoever waits for a product's end waits for the event, also where there was nothing to launch."""
+    code = """
+        import ctypes, sys
+        runtime = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+        import paper_2209_02478_amd as mi
+        gemm = ctypes.cast(getattr(mi.load_library(), "_ZN2mk4gemmEiRKNS_8GemmArgsEP12ihipStream_t"), ctypes.c_void_p)
+        for start, stop in ((0, 0), (0, 7), (6, 7)):
+            runtime.shim_fail_at(ctypes.c_long(-1))
+            assert runtime.empty_product(gemm, ctypes.c_void_p(start), ctypes.c_void_p(stop)) == 1
+            assert runtime.shim_marks() == (start != 0) + (stop != 0), (start, stop, runtime.shim_marks())
+    """
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(code), runtime], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
