@@ -430,15 +430,18 @@ bool launch_bgemm_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t 
 constexpr int kLongSteps = 1536;
 // From K = 1536 on its k steps pay (K = 768: level, the launch and the first loads are most of the time).  Its tiles are
 // 32 x 32, 64 x 64, 96 x 64 and 128 x 64 (variants 0..3); 64 x 32 and 128 x 128 stay with the ring (350 x 768, K = 3072
-// on 64 x 64 12.0 us, 11.3 there; 3312 x 768 on 128 x 128 level).
-static int tiles_variant(int M, int N, int K) {
+// on 64 x 64 12.0 us, 11.3 there; 3312 x 768 on 128 x 128 level), and so do the second and fourth with an m-major B, whose
+// fragments take two transposing reads each: of the ring's time, operands in the caches / from memory, k-major B 0.95-1.05 /
+// 0.92-1.01 (64 x 64) and 0.94-0.99 / 0.96-1.03 (128 x 64), m-major 1.00-1.08 / 0.98-1.03 and 0.99-1.03 / 1.00-1.04
+// (1000 x 768, K = 1536-3072 7.7-12.1 us in the ring, 8.3-12.8 here); 32 x 32 and 96 x 64 0.76-0.98 and 0.82-1.05 either way.
+static int tiles_variant(int M, int N, int K, bool b_kmajor) {
   if (K < kLongSteps) return -1;
   auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
   if (tiles(32, 32) <= 256) return 0;
   if (tiles(64, 32) <= 256) return -1;
-  if (tiles(64, 64) <= 256) return 1;
+  if (tiles(64, 64) <= 256) return b_kmajor ? 1 : -1;
   if (tiles(96, 64) <= 256) return 2;
-  return tiles(128, 64) <= 256 ? 3 : -1;
+  return b_kmajor && tiles(128, 64) <= 256 ? 3 : -1;
 }
 
 // Weight gradients that nothing runs beside keep the parts of their reduction (gemm_splits) and with them the
@@ -545,7 +548,7 @@ bool gemm(int dtype, const GemmArgs& g, hipStream_t st) {
   if (p.splits == 1 && !g.a_rowsum) {
     for (const int rows : {g.whole_rows > 0 ? g.whole_rows : g.M, g.M}) {
       if (rows < g.whole_rows && g.K < kLongSteps) break;
-      const int small = tiles_variant(rows, g.N, g.K), which = ring_variant(rows, g.N);
+      const int small = tiles_variant(rows, g.N, g.K, g.b_kmajor), which = ring_variant(rows, g.N);
       if (small >= 0 && launch_bgemm_tiles(p, small, st, g.time_start, g.time_stop)) return true;
       if (which >= 0 && launch_bgemm_ring(p, which, st, g.time_start, g.time_stop)) return true;
     }

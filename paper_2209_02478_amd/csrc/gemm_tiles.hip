@@ -10,7 +10,7 @@
 // kernels, so which kernel a product gets does not change a bit of it.  us, ring kernel -> here, operands from
 // memory: 74, 150, 300 x 768, K = 3072 11.0 -> 8.5-9.0 (data gradient 11.2-11.7 -> 9.3-10.5), 74 x 768,
 // K = 30528 94 -> 63 (119 -> 98); 1500 x 1024, K = 4096 on 96 x 64 29.1 -> 23.3 (27.9 -> 23.6); 2048 x 768, K = 3072 on
-// 128 x 64 20.0 -> 17.8 (21.0 -> 20.3); 700 x 1024, K = 4096 on 64 x 64 16.3 -> 15.4.
+// 128 x 64 20.0 -> 17.8; 700 x 1024, K = 4096 on 64 x 64 16.3 -> 15.4 (both with a k-major B alone, see tiles_variant).
 //
 // LDS tiles: a k-major tile [rows][64 k] keeps chunk kc of row r at kc ^ ((r >> 1) & 7); an m-major tile
 // [64 k][R rows] keeps chunk mc of k row q at mc ^ f(q), with f so that the four k rows and two groups of
@@ -286,22 +286,22 @@ static void launch_tiles_t(const GemmDev& p, hipStream_t st, hipEvent_t t0, hipE
 }
 template <bool BKM>
 static void launch_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-  switch (which) {
-    case 0: launch_tiles_t<BKM, 2, 1, 1, 2, 1, 8>(p, st, t0, t1); break;     // 32 x 32
-    case 1: launch_tiles_t<BKM, 2, 2, 2, 2, 2, 5>(p, st, t0, t1); break;     // 64 x 64
-    case 2: launch_tiles_t<BKM, 2, 2, 3, 2, 2, 4>(p, st, t0, t1); break;     // 96 x 64
-    default: launch_tiles_t<BKM, 4, 2, 2, 2, 1, 6>(p, st, t0, t1); break;    // 128 x 64
+  if (which == 0) launch_tiles_t<BKM, 2, 1, 1, 2, 1, 8>(p, st, t0, t1);        // 32 x 32
+  else if (which == 2) launch_tiles_t<BKM, 2, 2, 3, 2, 2, 4>(p, st, t0, t1);   // 96 x 64
+  else if constexpr (BKM) {
+    if (which == 1) launch_tiles_t<true, 2, 2, 2, 2, 2, 5>(p, st, t0, t1);     // 64 x 64
+    else launch_tiles_t<true, 4, 2, 2, 2, 1, 6>(p, st, t0, t1);                // 128 x 64
   }
 }
 
 // Requirements: A k-major; K % 8 == 0 or zeros vouched for behind A's last column, with B m-major; the leading
-// dimension of an m-major B covers N rounded up to 8; 2 GB for a tile's rows.
+// dimension of an m-major B covers N rounded up to 8; a tile's 128 rows or indices span 512 MB at most.
 bool launch_bgemm_tiles(const GemmDev& p, int which, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   auto up8 = [](int64_t v) { return (v + 7) / 8 * 8; };
   if (!p.a_k || p.a_rowsum || p.splits > 1) return false;
   if ((p.K & 7) && !(p.a_tail_zero && !p.b_k && p.lda >= up8(p.K))) return false;
-  if (!p.b_k && p.ldb < up8(p.N)) return false;
-  if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;          // 2 GB for a tile's rows
+  if (!p.b_k && (p.ldb < up8(p.N) || which == 1 || which == 3)) return false;
+  if (p.lda >= (1 << 21) || p.ldb >= (1 << 21)) return false;          // 128 of them: 512 MB
   if (p.b_k) launch_tiles<true>(p, which, st, t0, t1);
   else launch_tiles<false>(p, which, st, t0, t1);
   return true;

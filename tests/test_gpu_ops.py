@@ -819,9 +819,9 @@ def test_dropout_inside_layernorm(dtype, wide, T, H, shift):
 
 
 @pytest.mark.parametrize("rows,N,K", [(1, 8, 1536), (74, 768, 1544), (300, 776, 3072),          # 32 x 32 tiles: one, a tail, ragged
-                                      (700, 1000, 1600), (640, 1024, 1656),                     # 64 x 64: a stage half full, a tail in its first half
+                                      (700, 1000, 1600), (640, 1024, 1656),                     # 64 x 64 (k-major B): a stage half full, a tail in its first half
                                       (1500, 1032, 1664), (1441, 1024, 1736),                   # 96 x 64
-                                      (2000, 1032, 1536), (2048, 1000, 1592)])                  # 128 x 64
+                                      (2000, 1032, 1536), (2048, 1000, 1592)])                  # 128 x 64 (k-major B)
 @pytest.mark.parametrize("b_k", [1, 0])
 def test_gemm_long_reductions_bits(rows, N, K, b_k):
     """Few rows behind a long reduction: the bits are those of the same rows in a product of more,
