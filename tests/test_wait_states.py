@@ -43,7 +43,8 @@ class Instruction:
         """Scalar registers that a vector instruction writes."""
         if not self.name.startswith("v_"):
             return set()
-        return set().union(*[registers(o) for o in self.operands[:2 if "_co_" in self.name or "div_scale" in self.name else 1]])
+        two = any(part in self.name for part in ("_co_", "div_scale", "mad_u64_u32", "mad_i64_i32"))    # a carry too
+        return set().union(*[registers(o) for o in self.operands[:2 if two else 1]])
 
 
 def parse(disassembly):
@@ -122,6 +123,9 @@ def test_checker():
     assert faults(sample("v_readfirstlane_b32 s10, v2", "s_mov_b32 m0, s1", "s_nop 2", load))
     assert not faults(sample("v_readfirstlane_b32 s10, v2", "s_mov_b32 m0, s1", "s_nop 3", load))
     assert not faults(sample("v_readfirstlane_b32 s12, v2", "s_mov_b32 m0, s1", "s_nop 0", load))
+    assert faults(sample("v_mad_u64_u32 v[2:3], s[10:11], v4, s20, 0", "s_nop 3", load))              # its carry
+    assert not faults(sample("v_mad_u64_u32 v[2:3], s[10:11], v4, s20, 0", "s_nop 4", load))
+    assert not faults(sample("v_mad_u64_u32 v[2:3], s[20:21], v4, s10, 0", load))
     # around a loop: the writer stands behind the load
     assert faults(sample("s_nop 4", "s_mov_b32 m0, s1", "s_nop 0", load, "v_readlane_b32 s9, v2, 1", ("s_cbranch_scc1 1", 4)))
 
