@@ -1,5 +1,9 @@
 """fp32 products, whose operands are split in three bf16 parts, against 64-bit products: every block
-tile and number of ways the launcher chooses, at ragged ends, in every layout."""
+tile and number of ways the launcher chooses, with the reduction's end alone and with the pipelined loop before
+it, at ragged ends, in every layout."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -12,14 +16,47 @@ pytestmark = pytest.mark.gpu
 
 U = 2.0 ** -24                        # unit roundoff of fp32
 
-# (M, N, K) -> block tile and ways it gets; remainders of tiles, of slices and of ways' turns
-SHAPES = [(1, 1, 1), (33, 65, 31), (130, 129, 100), (130, 70, 515),       # 32 x 32, four ways
-          (130, 2300, 250), (129, 2305, 32),                              # 32 x 32, two
-          (260, 2300, 99), (520, 1030, 1000),                             # 64 x 64, two
-          (900, 900, 70), (1410, 3000, 130),                              # 64 x 64, one
-          (1100, 1030, 260), (1409, 770, 515),                            # 96 x 64
-          (700, 2300, 300), (2305, 750, 515),                             # 128 x 64
-          (1500, 1500, 70), (1345, 2300, 99)]                             # 128 x 128
+# block tile, ways and slices requested ahead of the launcher's variants
+TILES = [(128, 128, 1, 1), (64, 64, 1, 2), (64, 64, 2, 2), (32, 32, 2, 3), (32, 32, 4, 2), (96, 64, 1, 2), (128, 64, 1, 2)]
+
+
+def variant(M, N, K):
+    """The variant `estimate` picks, by the constants in the source."""
+    src = open(os.path.join(os.path.dirname(mi.__file__), "csrc", "gemm_f32.hip")).read()
+    table = {k: [int(x) for x in v.split(",")] for k, v in re.findall(r"(k\w+)\[kVariants\] = \{([-0-9, ]+)\}", src)}
+    assert [t[:2] for t in TILES] == list(zip(table["kM"], table["kN"]))
+
+    def estimate(w):
+        rounds = -(-(-(-M // table["kM"][w]) * -(-N // table["kN"][w])) // 256)
+        slices = -(-K // 32)
+        return (table["kAlone"][w] + slices * table["kAloneSlice"][w] if rounds == 1 else
+                rounds * (table["kMany"][w] + slices * table["kManySlice"][w]))
+    return min(range(len(TILES)), key=estimate)
+
+
+# (M, N, K) -> variant it gets; remainders of tiles, of slices and of ways' turns
+SHAPES = {(1, 1, 1): 4, (33, 65, 31): 4, (130, 129, 100): 4, (130, 70, 515): 4,        # 32 x 32, four ways
+          (130, 2300, 250): 3, (130, 1867, 99): 3,                                     # 32 x 32, two
+          (260, 2300, 99): 2, (520, 1030, 1000): 2,                                    # 64 x 64, two
+          (129, 2305, 32): 1, (900, 900, 70): 1, (1410, 3000, 130): 1,                 # 64 x 64, one
+          (1100, 1030, 260): 5, (1409, 770, 515): 5,                                   # 96 x 64
+          (700, 2300, 300): 6, (2305, 750, 515): 6,                                    # 128 x 64
+          (1500, 1500, 70): 0, (1345, 2300, 99): 0}                                    # 128 x 128
+# every variant with a reduction that its pipelined loop takes several turns of, and a ragged end
+LONG = {(227, 130, 1300): 4, (130, 1736, 1030): 3, (325, 1474, 850): 2, (906, 2129, 515): 1, (325, 2784, 515): 5,
+        (615, 2391, 515): 6, (712, 2784, 303): 0}
+
+
+def test_shapes_reach_every_variant():
+    for shapes in (SHAPES, LONG):
+        assert set(shapes.values()) == set(range(len(TILES)))
+        for shape, which in shapes.items():
+            assert variant(*shape) == which, shape
+    for (M, N, K), which in LONG.items():
+        ways, ahead = TILES[which][2:]
+        for way in range(ways):
+            whole = (K // 32 - way + ways - 1) // ways          # slices of the way that lie inside K
+            assert whole > 2 * ahead + 2 * ahead and K % 32, (M, N, K)
 
 
 def put(X, kmajor, pad):
@@ -38,8 +75,8 @@ def test_split_products(M, N, K, a_k, b_k):
     bias, resid = rng.standard_normal(N).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
     a64, b64 = A.astype(np.float64), B.astype(np.float64)
     prod, mag = a64 @ b64.T, np.abs(a64) @ np.abs(b64).T
-    # three left-out products of 2^-27, 32 products of a slice in one rounding, one rounding a slice in
-    # the large sum (the small ones' are 2^-8 of it), the ways' sums, bias and residual
+    # three left-out products of 2^-27, a rounding or a few for the 32 products of a slice (at most half the
+    # largest sum each, on average far less), the ways' sums, bias and residual
     bound = (K / 32 + 16) * U * (mag + np.abs(bias) + np.abs(resid)) + 1e-30
     for pad in (0, 3):
         dA, lda = put(A, a_k, pad)
@@ -65,6 +102,34 @@ def test_split_products(M, N, K, a_k, b_k):
         mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C3, N + 5, 0, M, N, K, bias=torch.from_numpy(bias).to(DEV))
         sync()
         assert torch.equal(C2[:, :N], C3[:, :N])
+
+
+@pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", LONG)
+def test_pipelined_loop(M, N, K, a_k, b_k):
+    """Aligned operands, without row sums as forward and data gradients have them, and with the row sums of weight
+    gradients (both operands m-major); values of both signs, and of one (a rounding that always goes one way adds up)."""
+    rng = np.random.default_rng(M + 3 * N + 5 * K + a_k + 2 * b_k)
+    for one_sign in (False, True):
+        A, B = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+        if one_sign:
+            A, B = np.abs(A), np.abs(B)
+        a64, b64 = A.astype(np.float64), B.astype(np.float64)
+        prod, mag = a64 @ b64.T, np.abs(a64) @ np.abs(b64).T
+        dA, lda = put(A, a_k, 0)
+        dB, ldb = put(B, b_k, 0)
+        C = torch.full((M, (N + 3) // 4 * 4), 7.0, device=DEV)
+        rs = torch.zeros(M, device=DEV) if not a_k and not b_k else None
+        mi.mimose_op_gemm(0, dA, lda, a_k, dB, ldb, b_k, C, C.shape[1], 0, M, N, K, a_rowsum=rs)
+        sync()
+        if rs is not None:
+            assert np.all(np.abs(host(rs) - a64.sum(1)) <= (K / 4 + 16) * U * np.abs(a64).sum(1))
+        err = host(C)[:, :N] - prod
+        assert np.all(np.abs(err) <= (K / 32 + 16) * U * mag) and bool((C[:, N:] == 7.0).all())
+        if one_sign:
+            # Independent errors of at most that size have a mean of its 1 / sqrt(M N) (four times that here), and the last rounding
+            # of a sum may lean to one side by a quarter; one that went down in each of K / 32 slices would be K / 64 roundings.
+            assert abs((err / mag).mean()) <= U / 4 + 4 * (K / 32 + 16) * U / np.sqrt(M * N)
 
 
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
