@@ -483,33 +483,54 @@ def test_layernorm_fwd_bwd(dtype, x_f32, dy_f32, T, H):
             mi.mimose_op_layernorm_bwd(dtype, ddy, dy_f32, dx_, x_f32, dg_, ddy, None, dgam, dbet, partial, T, H, 1e-5)
 
 
-# 256 blocks of 16 rows have a wave for each row, 257 four: both add in the same order
+# 256 blocks of 16 rows have a wave for each row, 257 four waves with four rows' elements at a time, 513 with two;
+# 768 and 1024 columns are three and four chunks a lane in fp32.  All add in the same order.
 @pytest.mark.parametrize("dtype,wide", [(0, 0), (1, 0), (1, 1)])
 @pytest.mark.parametrize("H", [8, 768, 1024])
 def test_layernorm_bwd_waves_of_a_block(dtype, wide, H):
-    few, many = 4088, 4104                                   # the last of the 256 blocks is half full
+    few, sizes = 4088, (4104, 8200)                          # the last block half full
     g = torch.Generator(device=DEV).manual_seed(H)
     storage = torch.bfloat16 if dtype else torch.float32
-    x = (torch.randn(many, H, generator=g, device=DEV) * 2 + 0.5).to(torch.float32 if wide else storage)
-    dy = torch.randn(many, H, generator=g, device=DEV).to(x.dtype)
-    dy[few:] = 0.0                                           # what the larger one adds to the sums
+    x = (torch.randn(sizes[-1], H, generator=g, device=DEV) * 2 + 0.5).to(torch.float32 if wide else storage)
+    dy = torch.randn(sizes[-1], H, generator=g, device=DEV).to(x.dtype)
+    dy[few:] = 0.0                                           # what the larger ones add to the sums
     gamma = torch.randn(H, generator=g, device=DEV).to(storage)
+    add = torch.randn(sizes[-1], H, generator=g, device=DEV).to(storage)
 
-    def run(T):
-        dx = torch.zeros(T, H, dtype=storage, device=DEV)
+    def run(T, residual, form):
+        dx, masked = (torch.zeros(T, H, dtype=storage, device=DEV) for _ in range(2))
+        d = dy[:T]
+        if form == "in place":                               # later rows are loaded after earlier ones are stored
+            d = dx = dy[:T].clone()
         partial = torch.zeros(mi.mimose_op_partial_rows(T) * 2 * H, device=DEV)
         dgam, dbet = torch.zeros(H, device=DEV), torch.zeros(H, device=DEV)
-        mi.mimose_op_layernorm_bwd(dtype, dy, wide, x, wide, gamma, dx, None, dgam, dbet, partial, T, H, 1e-5)
+        a = add if residual else None
+        if form == "masked":
+            mi.mimose_op_layernorm_bwd_dropout(dtype, d, wide, x, wide, gamma, dx, a, masked, dgam, dbet, partial, T, H, 1e-5,
+                                               0.2, 0xA5A5A5A5DEADBEEF, 14, 77)
+        else:
+            mi.mimose_op_layernorm_bwd(dtype, d, wide, x, wide, gamma, dx, a, dgam, dbet, partial, T, H, 1e-5)
         sync()
-        return dx[:few], partial[:256 * 2 * H], dgam, dbet
+        return dx[:few], masked[:few], partial[:256 * 2 * H], dgam, dbet
 
-    a, b = run(few), run(many)
-    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    first = None
+    for residual in (0, 1):
+        for form in ("plain", "masked") + (() if wide else ("in place",)):
+            a = run(few, residual, form)
+            first = first or a
+            for T in sizes:
+                b = run(T, residual, form)
+                assert all(torch.equal(a[i], b[i]) for i in range(3)), (residual, form, T)
+            assert torch.equal(a[2], first[2])               # the sums are those of the plain form
+            if residual:
+                continue
+            assert torch.equal(a[0], first[0])
     _, saved = om.layernorm_fwd(host(x[:few]), host(gamma), host(gamma), 1e-5)
     dx_ref, dg_ref, db_ref = om.layernorm_bwd(host(dy[:few]), saved, host(gamma))
-    close(host(a[0]), dx_ref, dtype, k=3.0)
-    close(host(a[2]), dg_ref, 0, k=50.0)
-    close(host(a[3]), db_ref, 0, k=50.0)
+    close(host(first[0]), dx_ref, dtype, k=3.0)
+    close(host(a[0]), dx_ref + host(add[:few]), dtype, k=3.0)
+    close(host(first[3]), dg_ref, 0, k=50.0)
+    close(host(first[4]), db_ref, 0, k=50.0)
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
@@ -524,6 +545,24 @@ def test_gelu_bwd(dtype, form):
     mi.mimose_op_gelu_bwd(dtype, dd, dp, n, form)
     sync()
     close(host(dd), ref, dtype, k=2.0)
+
+
+@pytest.mark.parametrize("n", [1, 4, 1023, 1027])
+def test_gelu_bwd_fp32_off_16_bytes(n):
+    """Operands that do not lie on 16 bytes give the bits of those that do."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    pre, d = (torch.randn(n, generator=g, device=DEV) * 2 for _ in range(2))
+    for form in (0, 1):
+        out = []
+        for shift in (0, 1):
+            buf, p = torch.full((2, n + 8), 9.0, device=DEV)
+            buf[shift:shift + n], p[shift:shift + n] = d, pre
+            mi.mimose_op_gelu_bwd(0, buf[shift:], p[shift:], n, form)
+            sync()
+            assert bool((buf[shift + n:] == 9.0).all()) and bool((buf[:shift] == 9.0).all())
+            out.append(buf[shift:shift + n].clone())
+        assert torch.equal(out[0], out[1])
+        close(host(out[0]), host(d) * om.gelu_grad(host(pre), form), 0, k=2.0)
 
 
 # ---------------------------------------------------------------- attention
