@@ -387,38 +387,37 @@ def test_dropout_parity_and_replay(name):
 
 
 @pytest.mark.parametrize("name", ["fp32_postln", "bf16_postln", "bf16_preln_causal", "bf16_stages"])
-def test_stream_layout_does_not_change_the_bits(name):
+@pytest.mark.parametrize("p_drop", [0.0, 0.15])
+def test_stream_layout_does_not_change_the_bits(name, p_drop):
     """With per-kernel timing on, every kernel runs on the caller's stream over the whole batch;
-    without it the forward runs as two halves of the batch on two streams and the weight
-    gradients on the second one.  Same loss and gradients, bit for bit, also for an odd batch
-    and for a padded one."""
+    without it the forward runs as two halves of the batch on two streams (not with dropout) and the weight
+    gradients on the second one, where a tensor has more than 2^15 elements.  Same loss and gradients, bit for
+    bit, also for an odd batch and for a padded one."""
     shape = SMALL[name]
     params = synthdata.make_params(shape, 91, perturb=True)
     m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=256 * MiB)
     m.load_params(params)
-    for B, L, plan in ((4, 33, 0), (5, 40, 0b101 & ((1 << shape.n_layers) - 1)), (2, 7, 1), (1, 16, 0)):
-        tokens, labels = synthdata.make_batch(shape, B, L, 92 + B)
+    line = (1 << 15) // shape.hidden                              # rows up to which a step stays on one stream
+    some = 0b101 & ((1 << shape.n_layers) - 1)
+    batches = [synthdata.make_batch(shape, line // L + more, L, 92 + L) + (None, plan)
+               for L, more, plan in ((33, 1, 0), (40, 2, some), (7, 1, 1), (shape.max_seq, 3, some))]
+    assert {b[0].shape[0] % 2 for b in batches} == {0, 1}
+    n = 3 * line // 40 + 3
+    padded = synthdata.make_padded_batch(shape, [(20, 7, 13)[b % 3] for b in range(n)], 93) + (0,)
+    batches.append(padded)
+    # two streams: more than the line, of the rows that are left (at least the real tokens)
+    assert all((b[0].size if b[2] is None else int(b[2].sum())) > line for b in batches)
+    batches.append(synthdata.make_batch(shape, 1, 16, 94) + (None, 0))                   # and one on one
+    for tokens, labels, lens, plan in batches:
         m.force_plan(plan)
-        mi.mimose_profile_enable(m.ctx, 1)
-        loss0, _, _ = m.train_step(tokens, labels)
-        G0 = m.grads()
-        mi.mimose_profile_enable(m.ctx, 0)
-        loss1, _, _ = m.train_step(tokens, labels)
-        G1 = m.grads()
-        assert loss0 == loss1
-        for k in G0:
-            assert np.array_equal(G0[k], G1[k]), (B, L, k)
-    tk, lb, lens = synthdata.make_padded_batch(shape, [20, 7, 13], 93)
-    m.force_plan(0)
-    mi.mimose_profile_enable(m.ctx, 1)
-    loss0, _, _ = m.train_step(tk, lb, lengths=lens)
-    G0 = m.grads()
-    mi.mimose_profile_enable(m.ctx, 0)
-    loss1, _, _ = m.train_step(tk, lb, lengths=lens)
-    G1 = m.grads()
-    assert loss0 == loss1
-    for k in G0:
-        assert np.array_equal(G0[k], G1[k]), k
+        out = []
+        for timed in (1, 0):
+            m.set_dropout(float(np.float32(p_drop)), float(np.float32(p_drop)), 0xC0FFEE1234567, 5)
+            mi.mimose_profile_enable(m.ctx, timed)
+            out.append((m.train_step(tokens, labels, lengths=lens)[0], m.grads()))
+        assert out[0][0] == out[1][0]
+        for k in out[0][1]:
+            assert np.array_equal(out[0][1][k], out[1][1][k]), (tokens.shape, k)
     m.close()
 
 
