@@ -330,29 +330,30 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
   }
 }
 
-// Backward: a block takes kRowsPerChunk rows.  Where every block has a compute unit of its own (256 blocks at most)
-// it has 16 waves, one for each row: a row is a chain of four sums over its columns, and one wave's four rows are
-// four chains (with the reduction, rows in bf16: 74 x 768 10.4 -> 8.3 us, 3312 x 768 14.3 -> 10.6; in fp32 with bf16 results
-// 9.4 -> 8.6 and 12.4 -> 11.1; 4096 x 1024 in fp32 15.6 -> 13.7).  From the 257th block on a unit gets a second
-// one, which waits for memory as the first does, and 16 waves are behind (10000 x 768 25.9 us against 21.3; level at 4400-8192 rows):
-// 4 waves take 4 rows each one after the other, AHEAD rows'
-// elements in registers.  Two where there are blocks for more than two to a unit: three waves then fit a SIMD,
-// where four rows' elements leave two (bf16 131072 x 1024 with the reduction 296 -> 241 us, 16384 x 768 39.7 -> 36.5;
-// with fp32 rows 300 -> 296, the copy rate, 38.3 -> 35.5).  Four for fewer blocks, which wait for memory
-// and not for each other, and from 14 blocks to a unit on, where alone it is behind but leaves more to the weight gradients
-// beside it: iterations with two against four, ms: 16384 rows 19.05 / 19.12, 20480 54.5 / 54.7, 51200 160.1 / 160.4; 65536
-// 198.5 / 196.6, 98304 293.1 / 291.4, 131072 388.2 / 386.6.  All four rows' sums side by side gained
-// nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order of the sums over
-// rows; the sums over a row's columns run over other columns per lane.
+// Backward: a block takes kRowsPerChunk rows, WAVES waves of it a row each in turn, with AHEAD rows' elements in registers.
+// A row is a chain of four sums over its columns.  Up to 256 blocks, one to a compute unit, 16 waves take a row each instead
+// of four rows one after the other (with the reduction, bf16: 74 x 768 10.4 -> 8.3 us, 3312 x 768 14.3 -> 10.6; fp32 rows
+// 9.4 -> 8.6, 12.4 -> 11.1; 4096 x 1024 in fp32 15.6 -> 13.7).  A second block on a unit waits for memory while the first
+// works, and 16 waves fall behind 4 (level at 4400-8192 rows, 10000 x 768 25.9 us against 21.3).
+// Of 4 waves' rows two are ahead from the third block to a unit on: three waves then fit a SIMD, where four rows'
+// elements leave two (bf16 16384 x 768 39.7 -> 36.5 us, 131072 x 1024 296 -> 241; fp32 rows 38.3 -> 35.5, 300 -> 296).
+// Four for fewer blocks, which wait for memory and not for each other, and from 14 blocks to a unit on, where in bf16
+// four are behind alone but leave more to the weight gradients beside: iterations with two against four, ms:
+// 16384 rows 19.05 / 19.12, 51200 160.1 / 160.4, 65536 198.5 / 196.6, 131072 388.2 / 386.6.  Wide rows in fp32
+// (three chunks a lane and more), of which no step measured has that many, stay with two: 57360 x 1024 alone 160 -> 153
+// us, with a residual 229 -> 202, 131072 x 1024 351 -> 340, 131072 x 768 267 -> 263.
+// All four rows' sums side by side gained nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order
+// of the sums over rows; the sums over a row's columns run over other columns per lane.
 template <typename TD, typename TX, typename T, int NC, int AHEAD, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 16 ? 4 : AHEAD == 2 ? 3 : 2) void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x,
-                                                         const T* __restrict__ gamma, T* __restrict__ dx,
-                                                         const T* __restrict__ add, float* __restrict__ partial,
-                                                         T* __restrict__ masked, DropRows dr, int Trows, int H, float eps) {
+__global__ __launch_bounds__(64 * WAVES, WAVES == 16 ? 4 : AHEAD == 2 ? 3 : 2)
+void ln_bwd_vec_kernel(const TD* __restrict__ dy, const TX* __restrict__ x, const T* __restrict__ gamma, T* __restrict__ dx,
+                       const T* __restrict__ add, float* __restrict__ partial, T* __restrict__ masked, DropRows dr, int Trows,
+                       int H, float eps) {
   constexpr int E = Chunk<T>::N;
   constexpr int R = kRowsPerChunk / WAVES, Q = E / 4, COLS = 64 * NC * E;
   static_assert((WAVES == 4 || R == 1) && AHEAD <= R, "rows of a wave");
-  __shared__ __attribute__((aligned(16))) float red[4][2][COLS];   // a lane's four columns e, .. e + 3 of chunk c at ((e / 4) (64 NC) + c) 4
+  // a lane's four columns e, .. e + 3 of chunk c are at ((e / 4) (64 NC) + c) 4
+  __shared__ __attribute__((aligned(16))) float red[4][2][COLS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nchunks = H / E;
   float g[NC][E], sg[NC][E], sb[NC][E];
@@ -946,7 +947,7 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-    const bool few = grid.x <= 256, ahead2 = grid.x > 512 && grid.x <= 3584;
+    const bool few = grid.x <= 256, ahead2 = grid.x > 512 && (grid.x <= 3584 || nc > 2);
 #define A_(NC, AHEAD, WAVES) LAUNCH_MARKED_((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), st, done, (const TD*)dy, \
                                    (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
