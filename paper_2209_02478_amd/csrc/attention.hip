@@ -105,7 +105,8 @@ __device__ __forceinline__ void put_part(float* part, int lane, const f32x16 (&a
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      *(float4*)&part[((4 * db + g) * 64 + lane) * 4] = make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+      *(float4*)&part[((4 * db + g) * 64 + lane) * 4] =
+          make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
 }
 // ... and behind a barrier wave w adds the n waves' parts of head columns 8 q + 4 h .., q = w, w + W, ..., in wave
 // order, each times its own row's factor.

@@ -6,37 +6,36 @@
 // (v_mfma_f32_16x16x32_bf16: products exact, sums in fp32); the other three are below 2^-26 of the
 // product, under the 2^-24 that one fp32 rounding costs.  x0 y0 has accumulators of its own; the other five, 2^-8
 // of it, share a second set, added at the end.  (In one set the small products lose their last bits against a large
-// sum: 1.7 times the error of fp32 MFMAs instead of two thirds.)  Errors against 64 bits, 2-norm over the result's,
-// fp32 MFMAs -> here, on N(0,1) operands: 768 indices 2.5-5.0e-7 -> 0.9-1.6e-7, 3072 5.0e-7 -> 1.6-3.4e-7, 30522
-// 1.6e-6 -> 0.8e-6 (the smaller with four ways of the reduction); with a GELU's outputs times N(0,1) the same.
-// With both operands of one sign, whose errors are a third of those, there is no bias, and 0.4-0.7 times the error,
-// or 1.4 times it where the fp32 MFMAs had four partial sums and this has one (1408 x 768, K = 3072 2.1e-7 -> 3.0e-7).
-// The matrix cores multiply bf16 at 16 times their fp32 rate, so six products leave 2.7.  Against the kernel
-// with fp32 MFMAs (32 x 32 and 64 x 64 tiles), us: 1408 x 768, K = 768 27 -> 22, K = 3072 87 -> 77; 1408 x 3072
-// 78 -> 57; data gradient 704 x 768, K = 3072 58 -> 40; weight gradients over 1408 rows, 768 x 768 27 -> 24,
-// 3072 x 768 74 -> 51, 30528 x 768 926 -> 371; 4096 x 3072, K = 768 173 -> 105 (185 TFLOP/s); 1408 x 30522
-// 590 -> 372; 64 x 768, K = 3072 27 -> 19; from a few slices of a few tiles on (64 columns) level.  (All of this file's
-// times are without the scale below, which costs 2-3 %, 5 % at K = 3072 on 96 x 64 tiles, 56 -> 59 us.)
+// sum, 1.7 times the error of fp32 MFMAs.)  Errors against 64 bits, 2-norm over the result's, fp32 MFMAs -> here, on
+// N(0,1) operands: 768 indices 2.5-5.0e-7 -> 0.9-1.6e-7, 3072 5.0e-7 -> 1.6-3.4e-7, 30522 1.6e-6 -> 0.8e-6.  With both
+// operands of one sign, whose errors are a third of those, there is no bias, and 0.4-0.7 times the error, or 1.4
+// times it where the fp32 MFMAs had four partial sums and this has one (1408 x 768, K = 3072 2.1e-7 -> 3.0e-7).
 //
 // What is split is the value times 2^16, and sums are times 2^32 until the end: every part is then a bf16 number, denormal
 // ones included, for every fp32 value down to 2^-149.  (Unscaled, the third part loses bits from 2^-109 on and the
-// second from 2^-118.  To look for lost bits and take such tiles again costs half of it, and 20 times the time for a
-// single small value that matters nothing.)
+// second from 2^-118.  The scale costs 2-3 %, 5 % at K = 3072 on 96 x 64 tiles; to look for lost bits instead, an OR for
+// every two values, and take such tiles again 1-3 %.)
 // What the split cannot carry are values that are not finite or above 2^112, and sums above 2^96: they leave
 // an output that is infinite or NaN.  A wave that finds one takes its tile again with fp32 MFMAs straight from memory,
 // so infinities, NaN and large values come out as fp32 arithmetic has them (some 20 times slower).
+//
+// The matrix cores multiply bf16 at 16 times their fp32 rate, so six products leave 2.7; the split takes the rest.  On
+// 128 x 128 tiles the matrix pipes are busy for 53-58 % of the time and vector instructions issue in 52-59 %, on 96 x 64
+// (three waves to a SIMD) 34-38 and 48.  Against 64 x 64 and 32 x 32 tiles of fp32 MFMAs, us, without the scale: 1408 x 768,
+// K = 768 27 -> 19, K = 3072 87 -> 57; 1408 x 3072 78 -> 54; weight gradients over 1408 rows, 3072 x 768 74 -> 51,
+// 30528 x 768 926 -> 371; 4096 x 3072, K = 768 173 -> 105; 64 x 768, K = 3072 27 -> 19; 64 columns and indices level.
 //
 // Block tiles are BM x BN with one thread or more for 8 floats of a slice, and WK ways of sharing the reduction: k way
 // g takes the 32-index slices g, g + WK, ... and the ways' accumulators are added in order at the end.
 // A way's first 4 BM threads bring its A slice, the next 4 BN its B slice: 8 floats each, loaded ND slices ahead into
 // registers, split there (13 vector instructions for two values) and stored as three bf16 planes into
-// one of two buffers while the MFMAs work on the other; any that are left only multiply.  A wave issues one vector instruction in 8 clocks,
-// a SIMD one in 4, and splitting takes about two for each MFMA: hence many waves with small parts of
-// the tile each, four on every SIMD.  128 x 128 tiles: 16 waves of 32 x 32; 64 x 64: 8 waves of 16 x 32
-// a way; 32 x 32: 4 waves of 16 x 16 a way; 96 x 64 and 128 x 64, 12 and 16 waves of 16 x 32, where the squares have just
-// begun a second round or leave units idle (us, the squares' best -> these): 1408 x 768, K = 3072 77 -> 57, K = 768
-// 23.7 -> 18.7; 1408 x 3072 58 -> 54; 360 x 3072 24.4 -> 18.9; data gradient 1408 x 768, K = 30522 722 -> 614;
-// 704 x 2304 24.4 -> 21.1; weight gradient 2304 x 768 over 2256 rows 69 -> 59; 2256 x 768, K = 3072 84 -> 69.
+// one of two buffers while the MFMAs work on the other; any that are left only multiply.  A wave issues one vector
+// instruction in 8 clocks, a SIMD one in 4, and splitting takes two or more for each MFMA: hence many waves with small
+// parts of the tile each, three or four on every SIMD.  128 x 128 tiles: 16 waves of 32 x 32; 64 x 64: 8 waves of
+// 16 x 32 a way; 32 x 32: 4 waves of 16 x 16 a way; 96 x 64 and 128 x 64, 12 and 16 waves of 16 x 32, where the squares
+// have just begun a second round or leave units idle (us, the squares' best -> these): 1408 x 768, K = 3072 77 -> 57;
+// 1408 x 3072 58 -> 54; 360 x 3072 24.4 -> 18.9; data gradient 1408 x 768, K = 30522 722 -> 614; weight gradient
+// 2304 x 768 over 2256 rows 69 -> 59.
 //
 // LDS plane of an operand slice: slots of 64 bytes (32 indices), their four 16-byte chunks turned
 // against bank conflicts.  Which row a fragment's lane holds is free, as it only renames outputs: lane l of
@@ -200,7 +199,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
       const int row = KM ? r0 + (mine_a ? row_of<BM, TM>(i, gt) : row_of<BN, TN>(i, gt - FIRST_B)) : sh.row + i;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        v[KM ? 4 * i + e : 2 * e + i] = e < kl && row < rows ? X[KM ? (int64_t)row * ld + kb + sh.k + e : (int64_t)(kb + sh.k + e) * ld + row] : 0.f;
+        v[KM ? 4 * i + e : 2 * e + i] =
+            e < kl && row < rows ? X[KM ? (int64_t)row * ld + kb + sh.k + e : (int64_t)(kb + sh.k + e) * ld + row] : 0.f;
     }
     sh.base += sh.step;
   };

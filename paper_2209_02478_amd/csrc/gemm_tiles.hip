@@ -50,7 +50,9 @@ struct TTile {
     const int q = index(j, lane), mc = (lane % RC) ^ turn(q);
     return mc * 8 < rows ? (uint32_t)(q * (int)ld + mc * 8) * 2u : kOutside;
   }
-  static __device__ __forceinline__ uint32_t bytes(int64_t ld, int rows) { return KM ? (uint32_t)min(rows, R) * (uint32_t)ld * 2u : kOutside; }
+  static __device__ __forceinline__ uint32_t bytes(int64_t ld, int rows) {
+    return KM ? (uint32_t)min(rows, R) * (uint32_t)ld * 2u : kOutside;
+  }
   // fragment of the 16 rows from `row` on, indices 32 h ..: element offset of its (first) read
   static __device__ __forceinline__ int frag_at(int row, int h, int lane) {
     if (KM) return (row + (lane & 15)) * TBK + (((4 * h + (lane >> 4)) ^ ((lane >> 1) & 7)) << 3);

@@ -650,7 +650,8 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   if (f_.pre_ln) { ln(x, p.ln1g, p.ln1b, at(A.n1, H), false); a = at(A.n1, H); }
   lin(a, H, p.wqkv, p.bqkv, at(A.qkv, 3 * H), 3 * H, nullptr, nullptr, 0, false);
   mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_,
-                    mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal, mk::DropDesc(), s, B_);
+                    mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal,
+                    mk::DropDesc(), s, B_);
   lin(at(A.ctx, H), H, p.wo, p.bo, at(A.s1, H, wide_), H, x, nullptr, 0, wide_);
   if (f_.pre_ln) {
     ln(at(A.s1, H), p.ln2g, p.ln2b, at(A.u, H), false);
@@ -672,12 +673,10 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
 //   The whole batch in one piece is ahead by 0.1-1.6 % at 192-200 tiles, 1.6-3.1 % at 224-256, behind
 //   by 0.7-3.4 % at 96-150 tiles and from 320 on (3.2 % there, 0.2 % at 1024).  At 160 tiles (one
 //   measurement, causal) it was ahead by 1.5 % too: the line at 192 is on the safe side.
-// - a forward of a few thousand elements per tensor is its launches: 2 layers of 64 columns in one
-//   piece are ahead by 18-20 % at 2048 to 16896 elements per tensor and by 13 % at 32768, where the line is.
-//   Above it there is no one line for all models: 12 bf16 layers of 768 columns in one piece are behind by 3 % at 24576 and
-//   36864 elements, ahead by 10 % at 56832, by 4-6 % at 98304-196608, behind by 0.5-1.3 % at
-//   294912-393216 and level at 786432; in fp32 ahead by 1-2 % at 24576-122880 and behind by 4 % at
-//   393216; 24 causal layers of 1024 columns ahead by 1-3 % at 131072-262144.
+// - a step of a few thousand elements per tensor is its launches (one_stream).  Above that line no one line suits all
+//   models, and little depends on it: one piece takes, of the halves' time, 0.98-0.99 at 36864-98304 elements
+//   per tensor (12 bf16 layers of 768 columns), 1.00-1.01 at 196608-1.2 M and 1.02-1.03 at 2.2-4.9 M; in fp32
+//   1.01 at 49152-1.7 M; with 24 causal layers of 1024 columns 0.98 at 131072 and 1.2 M and 1.00 between.
 bool Step::split_forward() const {
   const int tiles = dt_ == mk::BF16 ? mk::gemm_large_tiles(T_, f_.hidden) : 0;
   if ((tiles >= 192 && tiles <= 256) || one_stream()) return false;

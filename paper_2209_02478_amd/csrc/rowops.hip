@@ -817,8 +817,9 @@ __global__ __launch_bounds__(256) void dropout_kernel(TIO* __restrict__ dst, con
 // Bound by memory: 28 or 30 bytes an element in seven or eight streams, none of which fits a cache until it is
 // touched again, so all but the low-precision copy, which the next forward reads, go past the caches (non-temporal
 // loads and stores; either alone gains nothing).  kAdamBlocks blocks share a chunk of kAdamChunk elements of one
-// tensor, four elements a thread and no loop: stretches of 8 KB that start together.  110 M parameters, bf16: a
-// block for a chunk 645 us (5.1 TB/s), non-temporal 584, so 531 (6.2).
+// tensor, four elements a thread and no loop: stretches of 8 KB that start together.  110 M parameters in bf16, call
+// behind call: a block for a chunk, through the caches, 650 us (5.05 TB/s), so 616 (5.3); behind an iteration's
+// backward, which leaves some of the gradients in the last cache, 645 and 550-570.
 constexpr int kAdamThreads = 512, kAdamBlocks = kAdamChunk / (4 * kAdamThreads);
 __global__ __launch_bounds__(kAdamThreads) void adamw_kernel(const AdamTensor* __restrict__ tensors,
                                                              const AdamChunk* __restrict__ chunks, AdamHyper h) {
