@@ -300,7 +300,8 @@ void mimose_destroy(mimose_ctx* ctx);
  * a_rowsum (optional, fp32[M]) receives sum_k A(m,k) (the bias gradient of a weight-gradient
  * product).  gelu: 0 none, 1 erf, 2 tanh.  bf16: lda, ldb must be multiples of 8 and A, B
  * 16-byte aligned, otherwise INVALID_ARG.  workspace: optional device scratch, see
- * mimose_op_gemm_workspace_bytes. */
+ * mimose_op_gemm_workspace_bytes.  fp32: any values; tiles that meet operands above 2^112, sums
+ * above 2^96, infinities or NaN take some 20 times as long. */
 int mimose_op_gemm(int32_t dtype, const void* A, int64_t lda, int32_t a_kmajor, const void* B,
                    int64_t ldb, int32_t b_kmajor, void* C, int64_t ldc, int32_t c_f32, int32_t M,
                    int32_t N, int32_t K, const void* bias, const void* resid, int64_t ldr,

@@ -437,19 +437,23 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bwd_dkv_kernel(const T* __rest
   if (in) store_sum<T, D, W>(out + 2 * H, tiles[0], TR * (D + 4), n, wave, lane, factor);
 }
 
-// Waves of a block, for `tiles` tiles of a sample and `blocks` blocks of the whole batch.  Four make the chain of a
-// sample's tiles a quarter as long; a wave without a tile only takes LDS and a place, and every further one's sums
-// have to be added.  So four where the blocks alone do not fill the chip: up to 512 of them for each tile of a
-// sample, and up to 768 where of four waves' last turn two or three would idle; one where a sample has two tiles
-// or three and the blocks do fill it.  Forward + backward in us with one / two / four
-// waves, 12 heads of 64 in fp32 (heads of 32 alike), against two waves of a block on 64 rows that share tiles in LDS:
+// Waves of a block, by the tiles of a sample and the blocks that the rows of the batch make (without padding that was left
+// out of them; of halves on two streams the whole batch's).  Four make the chain of a sample's tiles a quarter as
+// long; a wave without a tile only takes LDS and a place, and every further one's sums have to be added.  So four
+// where the blocks alone do not fill the chip: up to 512 of them for each tile of a sample, and up to 768 where of four
+// waves' last turn two or three would idle; one where a sample has two tiles or three and the blocks do fill it.
+// Iterations go by it too (12 layers in fp32, 16 x 141 padded to 88 on average: 9.47 / 9.10 / 8.98 ms with one / two / four).
+// Forward + backward in us with one / two / four waves, 12 heads of 64 in fp32 (heads of 32 alike), against two waves of
+// a block on 64 rows that share tiles in LDS:
 //   512 x 32 tokens 180 / 213 / 279 against 231    128 x 64 127 / 133 / 176 against 133    16 x 64 40 / 40 / 42 against 37
 //   8 x 64 35 / 26.5 / 27 against 36               128 x 96 239 / 262 / 277 against 287    8 x 128 65 / 62 / 48 against 61
-//   32 x 128 115 / 126 / 114 against 121           16 x 141 padded 93 / 86 / 103 against 123
+//   32 x 128 115 / 126 / 114 against 121           32 x 141 188 / 171 / 196 against 204
 //   32 x 256 379 / 349 / 333 against 348           16 x 512 causal 575 / 459 / 433 against 606
 // (One tile of 12-192 pairs stays 3-7 % behind that, a microsecond for the three kernels, 257-512 blocks of two tiles of
 // head size 64 10 % and 1536-3072 of head size 32 2-6 %, whatever the waves.)
-static int waves_of_block(int tiles, int64_t blocks) {
+static int waves_of_block(int L, int nh, int64_t rule_rows) {
+  const int tiles = (L + TR - 1) / TR;
+  const int64_t blocks = (rule_rows + L - 1) / L * nh * tiles;
   if (tiles == 1 || (tiles <= 3 && blocks >= 768 * (tiles - 1))) return 1;
   const bool idle = tiles == 3 || tiles == 5 || tiles == 6;   // (behind more turns the last weighs little)
   return tiles == 2 || blocks >= (idle ? 768 : 512 * (int64_t)tiles) ? 2 : 4;
@@ -463,10 +467,9 @@ static void fwd_w(const void* qkv, void* ctx, float* lse, const Rows& rows, int 
                      (T*)ctx, lse, rows, L, nh, pairs, causal, drop);
 }
 template <typename T, int D>
-static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int whole, int L, int nh, int causal,
+static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int64_t rule_rows, int L, int nh, int causal,
                   const DropDesc& drop, hipStream_t st) {
-  const int tiles = (L + TR - 1) / TR;
-  switch (waves_of_block(tiles, (int64_t)whole * nh * tiles)) {
+  switch (waves_of_block(L, nh, rule_rows)) {
     case 1: fwd_w<T, D, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
     case 2: fwd_w<T, D, 2>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
     default: fwd_w<T, D, 4>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
@@ -483,10 +486,9 @@ static void bwd_w(const void* qkv, const void* ctx, const void* dctx, const floa
                  (T*)dqkv, rows, L, nh, pairs, causal, drop);
 }
 template <typename T, int D>
-static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
-                  const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
-  const int tiles = (L + TR - 1) / TR;
-  switch (waves_of_block(tiles, (int64_t)B * nh * tiles)) {
+static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv, const Rows& rows,
+                  int B, int64_t rule_rows, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
+  switch (waves_of_block(L, nh, rule_rows)) {
     case 1: bwd_w<T, D, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
     case 2: bwd_w<T, D, 2>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
     default: bwd_w<T, D, 4>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
@@ -494,23 +496,24 @@ static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const floa
 }
 
 void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,
-                   int causal, const DropDesc& drop, hipStream_t st, int whole) {
+                   int causal, const DropDesc& drop, hipStream_t st, int64_t rule_rows) {
   if (B * L <= 0) return;
-  if (whole <= 0) whole = B;
+  if (rule_rows <= 0) rule_rows = (int64_t)B * L;
   if (dtype == BF16 && d == 64) attention_fwd_mfma(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
-  else if (dtype == BF16) fwd_t<bf16_t, 32>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
-  else if (d == 32) fwd_t<float, 32>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
-  else fwd_t<float, 64>(qkv, ctx, lse, rows, B, whole, L, nh, causal, drop, st);
+  else if (dtype == BF16) fwd_t<bf16_t, 32>(qkv, ctx, lse, rows, B, rule_rows, L, nh, causal, drop, st);
+  else if (d == 32) fwd_t<float, 32>(qkv, ctx, lse, rows, B, rule_rows, L, nh, causal, drop, st);
+  else fwd_t<float, 64>(qkv, ctx, lse, rows, B, rule_rows, L, nh, causal, drop, st);
 }
 
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta,
                    void* dqkv, const Rows& rows, int B, int L, int nh, int d, int causal, const DropDesc& drop,
-                   hipStream_t st, hipEvent_t done) {
+                   hipStream_t st, hipEvent_t done, int64_t rule_rows) {
   if (B * L <= 0) return;
+  if (rule_rows <= 0) rule_rows = (int64_t)B * L;
   if (dtype == BF16 && d == 64) attention_bwd_mfma(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
-  else if (dtype == BF16) bwd_t<bf16_t, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
-  else if (d == 32) bwd_t<float, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
-  else bwd_t<float, 64>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else if (dtype == BF16) bwd_t<bf16_t, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, rule_rows, L, nh, causal, drop, st, done);
+  else if (d == 32) bwd_t<float, 32>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, rule_rows, L, nh, causal, drop, st, done);
+  else bwd_t<float, 64>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, rule_rows, L, nh, causal, drop, st, done);
 }
 
 }  // namespace mk

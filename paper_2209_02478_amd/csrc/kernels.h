@@ -137,12 +137,12 @@ int layernorm_bwd_static(int dtype, const void* dy, bool dy_f32, const void* x, 
 void gelu_bwd(int dtype, void* d, const void* pre, int64_t n, int tanh_form, hipStream_t st, hipEvent_t done = nullptr);
 // drop: dropout of the probabilities (the
 // softmax normaliser counts all of them; ctx = (mask * scale * P) V).
-// whole: samples of the batch that these B are a part of (0: B), by which the order of fp32 sums is chosen
+// rule_rows: rows the order of fp32 sums is chosen by (0: B * L), as in GemmArgs
 void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,
-                   int causal, const DropDesc& drop, hipStream_t st, int whole = 0);
+                   int causal, const DropDesc& drop, hipStream_t st, int64_t rule_rows = 0);
 void attention_bwd(int dtype, const void* qkv, const void* ctx, const void* dctx, const float* lse,
                    float* delta, void* dqkv, const Rows& rows, int B, int L, int nh, int d, int causal,
-                   const DropDesc& drop, hipStream_t st, hipEvent_t done = nullptr);
+                   const DropDesc& drop, hipStream_t st, hipEvent_t done = nullptr, int64_t rule_rows = 0);
 void softmax_xent(int dtype, void* logits, int64_t ld, const int32_t* labels, float* row_loss,
                   float* loss, int T, int V, int n_valid, hipStream_t st);
 // T: rows (B * L, or the real ones when rows.ends is given)

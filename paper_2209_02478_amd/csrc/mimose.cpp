@@ -651,7 +651,7 @@ void Step::layer_forward_rows(int l, LayerActs& A, int b0, int nb, hipStream_t s
   lin(a, H, p.wqkv, p.bqkv, at(A.qkv, 3 * H), 3 * H, nullptr, nullptr, 0, false);
   mk::attention_fwd(dt_, at(A.qkv, 3 * H), at(A.ctx, H), A.lse + (int64_t)b0 * nh * L_,
                     mk::Rows{lens_ ? lens_ + b0 : nullptr, ends_ ? ends_ + b0 : nullptr, (int32_t)r0}, nb, L_, nh, d, f_.causal,
-                    mk::DropDesc(), s, B_);
+                    mk::DropDesc(), s, rule_rows());
   lin(at(A.ctx, H), H, p.wo, p.bo, at(A.s1, H, wide_), H, x, nullptr, 0, wide_);
   if (f_.pre_ln) {
     ln(at(A.s1, H), p.ln2g, p.ln2b, at(A.u, H), false);
@@ -703,7 +703,8 @@ void Step::layer_forward(int l, LayerActs& A, bool rebuild) {
   {
     Timed t(this, MIMOSE_K_ATTN_FWD, 4.0 * attention_pairs(B_, L_, lens_host) * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
-      mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, rows(), B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_);
+      mk::attention_fwd(dt_, A.qkv, A.ctx, A.lse, rows(), B_, L_, nh, d, f_.causal, drop_desc(4 * (uint32_t)(l + 1), true), st_,
+                        rule_rows());
   }
   // with dropout the product lands in the sum's buffer and the LayerNorm behind it first makes
   // sum = residual + dropout(product) in place; without it the residual rides in the epilogue
@@ -793,7 +794,7 @@ void Step::layer_backward(int l, LayerActs& A) {
     Timed t(this, MIMOSE_K_ATTN_BWD, 8.0 * attention_pairs(B_, L_, lens_host) * H * (f_.causal ? 0.5 : 1.0));
     if (!dry_)
       mk::attention_bwd(dt_, A.qkv, A.ctx, dctx, A.lse, delta, dqkv, rows(), B_, L_, nh, d, f_.causal,
-                        drop_desc(4 * (uint32_t)(l + 1), true), st_, done_event());
+                        drop_desc(4 * (uint32_t)(l + 1), true), st_, done_event(), rule_rows());
   }
   fork_behind_kernel();
   const void* a = f_.pre_ln ? A.n1 : A.x;
