@@ -117,10 +117,11 @@ struct LnBwdMasked {
   Rows rows;
   int B = 0, L = 0;
 };
-// done (optional; of gelu_bwd and attention_bwd too): an event for the end of the last kernel, bound to its launch
+// done (optional; of gelu_bwd and attention_bwd too): an event for the end of the last kernel, bound to its launch.
+// beside: other kernels run at the same time on another stream (as in GemmArgs)
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
                         const void* add, float* partial, int T, int H, float eps, const LnBwdMasked& extra, hipStream_t st,
-                        hipEvent_t done = nullptr);
+                        hipEvent_t done = nullptr, bool beside = false);
 // chunk_at (optional, device): T is the padded row count, and chunk_at[c] says which of the partial
 // rows belongs to its rows c * kRowBlock .. (-1: left out, they would add zeros)
 void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T, int H,

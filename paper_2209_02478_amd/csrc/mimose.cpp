@@ -456,7 +456,8 @@ class Step {
     const double bytes = (dy_f32 ? 4.0 : es_d()) + (x_f32 ? 4.0 : es_d()) + es_d() * (add ? 2.0 : 1.0);
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
     if (!dry_) {
-      mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, mk::LnBwdMasked(), st_);
+      mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, mk::LnBwdMasked(), st_,
+                             nullptr, second_stream());
       mk::layernorm_bwd_reduce(partial, g(gi), g(bi), chunk_at_, chunk_at_ ? Tpad_ : T_, f_.hidden, st_);
     }
     c_->arena.pop_to(m);
@@ -474,7 +475,9 @@ class Step {
     Timed t(this, MIMOSE_K_LN_BWD, bytes * T_ * f_.hidden);
     mk::LnBwdMasked ex;
     if (masked) { ex.masked = masked; ex.d = drop_desc(site); ex.rows = rows(); ex.B = B_; ex.L = L_; }
-    if (!dry_) mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, ex, st_, done);
+    if (!dry_)
+      mk::layernorm_bwd_rows(dt_, dy, dy_f32, x, x_f32, w(gi), dx, add, partial, T_, f_.hidden, f_.ln_eps, ex, st_, done,
+                             second_stream());
     return partial;
   }
   void ln_bwd_reduce(const float* partial, int gi, int bi) {

@@ -337,11 +337,12 @@ __global__ __launch_bounds__(256) void ln_fwd_vec_kernel(TX* __restrict__ x, con
 // works, and 16 waves fall behind 4 (level at 4400-8192 rows, 10000 x 768 25.9 us against 21.3).
 // Of 4 waves' rows two are ahead from the third block to a unit on: three waves then fit a SIMD, where four rows'
 // elements leave two (bf16 16384 x 768 39.7 -> 36.5 us, 131072 x 1024 296 -> 241; fp32 rows 38.3 -> 35.5, 300 -> 296).
-// Four for fewer blocks, which wait for memory and not for each other, and from 14 blocks to a unit on, where in bf16
-// four are behind alone but leave more to the weight gradients beside: iterations with two against four, ms:
-// 16384 rows 19.05 / 19.12, 51200 160.1 / 160.4, 65536 198.5 / 196.6, 131072 388.2 / 386.6.  Wide rows in fp32
-// (three chunks a lane and more), of which no step measured has that many, stay with two: 57360 x 1024 alone 160 -> 153
-// us, with a residual 229 -> 202, 131072 x 1024 351 -> 340, 131072 x 768 267 -> 263.
+// Four for fewer blocks, which wait for memory and not for each other, and from 14 blocks to a unit on beside the weight
+// gradients (layernorm_bwd_rows' `beside`), to which they leave more: iterations with two against four, ms: 16384 rows
+// 19.05 / 19.12, 51200 160.1 / 160.4, 65536 198.5 / 196.6, 131072 388.2 / 386.6.  Alone two are ahead there too (with
+// four -> two, us: bf16 65536 x 768 134 -> 107, x 1024 141 -> 113; fp32 rows 119 -> 110, 153 -> 150; up to 512 columns
+// 1-7 %), and so are wide rows in fp32 (three chunks a lane and more), of which no step measured has that many:
+// 57360 x 1024 160 -> 153, with a residual 229 -> 202, 131072 x 1024 351 -> 340, x 768 267 -> 263.
 // All four rows' sums side by side gained nothing and lost up to half.  Same outputs as ln_bwd_kernel, and the same order
 // of the sums over rows; the sums over a row's columns run over other columns per lane.
 template <typename TD, typename TX, typename T, int NC, int AHEAD, int WAVES>
@@ -944,13 +945,13 @@ void dropout_layernorm_fwd(int dtype, void* x, bool x_f32, const void* resid, co
 
 template <typename TD, typename TX, typename T>
 static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, const void* add, float* partial,
-                     int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st, hipEvent_t done) {
+                     int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st, hipEvent_t done, bool beside) {
   dim3 grid((T_ + kRowsPerChunk - 1) / kRowsPerChunk);
   if (vec_ok<T>(H, {dy, x, g, dx, add, ex.masked})) {
     const int nc = (H / Chunk<T>::N + 63) / 64;
-    const bool few = grid.x <= 256, ahead2 = grid.x > 512 && (grid.x <= 3584 || nc > 2);
-#define A_(NC, AHEAD, WAVES) LAUNCH_MARKED_((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), st, done, (const TD*)dy, \
-                                   (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
+    const bool few = grid.x <= 256, ahead2 = grid.x > 512 && (!beside || grid.x <= 3584 || nc > 2);
+#define A_(NC, AHEAD, WAVES) LAUNCH_MARKED_((ln_bwd_vec_kernel<TD, TX, T, NC, AHEAD, WAVES>), grid, dim3(64 * WAVES), st, \
+                                   done, (const TD*)dy, (const TX*)x, (const T*)g, (T*)dx, (const T*)add, partial, (T*)ex.masked, \
                                    DropRows{ex.d, ex.rows, ex.B, ex.L}, T_, H, eps)
 #define V_(NC) do { if (few) A_(NC, 1, 16); else if (ahead2) A_(NC, 2, 4); else A_(NC, 4, 4); } while (0)
     if (nc <= 1) { V_(1); return; }
@@ -974,13 +975,13 @@ static void ln_bwd_t(const void* dy, const void* x, const void* g, void* dx, con
 }
 void layernorm_bwd_rows(int dtype, const void* dy, bool dy_f32, const void* x, bool x_f32, const void* gamma, void* dx,
                         const void* add, float* partial, int T_, int H, float eps, const LnBwdMasked& ex, hipStream_t st,
-                        hipEvent_t done) {
+                        hipEvent_t done, bool beside) {
   if (T_ <= 0) return;
-  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
-  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
-  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
-  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
-  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done);
+  if (dtype != BF16) ln_bwd_t<float, float, float>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done, beside);
+  else if (dy_f32 && x_f32) ln_bwd_t<float, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done, beside);
+  else if (dy_f32) ln_bwd_t<float, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done, beside);
+  else if (x_f32) ln_bwd_t<bf16_t, float, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done, beside);
+  else ln_bwd_t<bf16_t, bf16_t, bf16_t>(dy, x, gamma, dx, add, partial, T_, H, eps, ex, st, done, beside);
 }
 static_assert(kRowsPerChunk == kRowBlock, "padding is left out in whole chunks");
 void layernorm_bwd_reduce(const float* partial, float* dgamma, float* dbeta, const int32_t* chunk_at, int T_, int H,

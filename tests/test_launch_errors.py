@@ -16,6 +16,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 RUNTIME = r"""
 #include <cstdlib>
 #include <cstring>
+#include <map>
+#include <string>
+#include <vector>
 struct dim3 { unsigned x, y, z; };
 static long next_event = 1, marks = 0, fail_at = -1;
 static void* bad = nullptr;                 // the event whose marking failed
@@ -49,8 +52,14 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { memcpy(d, s, 
 int hipFuncSetAttribute(const void*, int, int) { return 0; }
 int __hipPushCallConfiguration(dim3, dim3, size_t, void*) { return 0; }
 int __hipPopCallConfiguration(dim3* a, dim3* b, size_t* n, void** s) { *a = *b = {1, 1, 1}; *n = 0; *s = nullptr; return 0; }
-int hipLaunchKernel(const void*, dim3, dim3, void**, size_t, void*) { return 0; }
-int hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, void*, void* start, void* stop, int) {
+static std::map<const void*, std::string>& kernels() { static std::map<const void*, std::string> k; return k; }
+static std::vector<const void*> launches;
+void __hipRegisterFunction(void*, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { kernels()[host] = name; }
+long shim_launches() { return (long)launches.size(); }
+const char* shim_kernel(long i) { return kernels()[launches[i]].c_str(); }
+int hipLaunchKernel(const void* k, dim3, dim3, void**, size_t, void*) { launches.push_back(k); return 0; }
+int hipExtLaunchKernel(const void* k, dim3, dim3, void**, size_t, void*, void* start, void* stop, int) {
+  launches.push_back(k);
   mark(start);
   return mark(stop);
 }
