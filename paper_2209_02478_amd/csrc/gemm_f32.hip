@@ -6,10 +6,13 @@
 // (v_mfma_f32_16x16x32_bf16: products exact, sums in fp32); the other three are below 2^-26 of the
 // product, under the 2^-24 that one fp32 rounding costs.  x0 y0 has accumulators of its own; the other five, 2^-8
 // of it, share a second set, added at the end.  (In one set the small products lose their last bits against a large
-// sum, 1.7 times the error of fp32 MFMAs.)  Errors against 64 bits, 2-norm over the result's, fp32 MFMAs -> here, on
-// N(0,1) operands: 768 indices 2.5-5.0e-7 -> 0.9-1.6e-7, 3072 5.0e-7 -> 1.6-3.4e-7, 30522 1.6e-6 -> 0.8e-6.  With both
-// operands of one sign, whose errors are a third of those, there is no bias, and 0.4-0.7 times the error, or 1.4
-// times it where the fp32 MFMAs had four partial sums and this has one (1408 x 768, K = 3072 2.1e-7 -> 3.0e-7).
+// sum, 1.7 times the error of fp32 MFMAs.)  A single way's turn has two slices, each with its own sum of x0 y0: two
+// sums of half the size and half the roundings have half the error, in the same time (the registers of the 128 x 128
+// tiles do not hold them).  Errors against 64 bits, 2-norm over the result's, fp32 MFMAs -> here, on N(0,1) operands:
+// 768 indices 2.5e-7 -> 1.1-1.6e-7, 3072 5.0-9.9e-7 -> 1.6-3.4e-7, 30522 1.6e-6 -> 0.8e-6.  With both operands of one
+// sign, whose errors are a third to two thirds of those, there is no bias, and 0.2-0.75 times the error, or 1.3-1.4
+// times it where the fp32 MFMAs had four partial sums and the 128 x 128 tiles have one (1408 x 2304, K = 768
+// 1.0e-7 -> 1.4e-7; 4096 x 768, K = 3072 7.4e-7 -> 2.6e-7).
 //
 // What is split is the value times 2^16, and sums are times 2^32 until the end: every part is then a bf16 number, denormal
 // ones included, for every fp32 value down to 2^-149.  (Unscaled, the third part loses bits from 2^-109 on and the
@@ -229,11 +232,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
     for (int half = 0; half < 4; ++half) split_half(v, half, buf, kmajor);
     add_rows(v, kmajor);
   };
-  f32x4 acc[TM][TN], low[TM][TN];                   // sums of the large products, of the five others
+  // sums of the large products, of every ND-th slice where a way has the reduction to itself; and of the five others
+  constexpr int SETS = WK == 1 ? ND : 1;
+  f32x4 sums[SETS][TM][TN], low[TM][TN];
+  f32x4 (&acc)[TM][TN] = sums[0];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) {
+      low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < SETS; ++s) sums[s][i][j] = low[i][j];
+    }
 
   const int a_at = slot_at<TM>(wm * 16 * TM + place<TM>(l16), q), b_at = OPERAND + slot_at<TN>(wn * 16 * TN + place<TN>(l16), q);
   bf16x8 fa[3][TM], fb[3][TN];
@@ -247,13 +257,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
       for (int j = 0; j < TN; ++j) fb[pl][j] = *(const bf16x8*)(at + pl * PLANE_B + j * 1024 + b_at);
     }
   };
-  auto multiply = [&](int x) {                      // one of the six products
+  auto multiply = [&](int x, int u) {               // one of the six products of a turn's slice u
     constexpr int PA[6] = {0, 1, 0, 1, 2, 0}, PB[6] = {0, 0, 1, 1, 0, 2};
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        f32x4& sum = x ? low[i][j] : acc[i][j];
+        f32x4& sum = x ? low[i][j] : sums[u % SETS][i][j];
         sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[PA[x]][i], fb[PB[x]][j], sum, 0, 0, 0);
       }
   };
@@ -284,7 +294,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
           for (int x = 0; x < 6; ++x) {
             if (LOADS && x >= 1 && x <= 4) split_half(v, x - 1, buf ^ 1, kmajor);
             if (LOADS && x == 5) { add_rows(v, kmajor); load(v, kmajor); }
-            multiply(x);
+            multiply(x, u);
 #pragma unroll
             for (int f = 0; f < TM * TN; ++f) {
               __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // an MFMA
@@ -307,7 +317,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
           if (t + 1 + ND < n_slices) fetch(t + 1 + ND, v, kmajor);
         }
 #pragma unroll
-        for (int x = 0; x < 6; ++x) multiply(x);
+        for (int x = 0; x < 6; ++x) multiply(x, u);
         __syncthreads();
       }
     }
@@ -320,7 +330,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_split_kernel(GemmDev 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int s = 1; s < SETS; ++s) acc[i][j] += sums[s][i][j];
+      acc[i][j] += low[i][j];
+    }
   if (p.a_rowsum && tile_n == 0) {                    // the shares of a row, in order
     float* red = (float*)smem;                        // [8 WK shares][BM rows]
     if (mine_a) {

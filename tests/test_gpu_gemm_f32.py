@@ -34,6 +34,9 @@ def variant(M, N, K):
     return min(range(len(TILES)), key=estimate)
 
 
+SUMS = [1, 2, 2, 2, 4, 2, 2]          # that share an element's reduction: the ways, or a single way's two slices of a turn
+
+
 # (M, N, K) -> variant it gets; remainders of tiles, of slices and of ways' turns
 SHAPES = {(1, 1, 1): 4, (33, 65, 31): 4, (130, 129, 100): 4, (130, 70, 515): 4,        # 32 x 32, four ways
           (130, 2300, 250): 3, (130, 1867, 99): 3,                                     # 32 x 32, two
@@ -130,6 +133,10 @@ def test_pipelined_loop(M, N, K, a_k, b_k):
             # Independent errors of at most that size have a mean of its 1 / sqrt(M N) (four times that here), and the last rounding
             # of a sum may lean to one side by a quarter; one that went down in each of K / 32 slices would be K / 64 roundings.
             assert abs((err / mag).mean()) <= U / 4 + 4 * (K / 32 + 16) * U / np.sqrt(M * N)
+            # 2-norm: s sums of mag / s each, that grow evenly in K / (8 s) roundings (the matrix core rounds for eight indices), each
+            # off by at most 0.5 of a roundoff (rms; 0.42 on average), and two or three roundings of the whole
+            s = SUMS[LONG[M, N, K]]
+            assert np.linalg.norm(err) <= 0.5 * U * np.sqrt(K / (24 * s * s) + 2) * np.linalg.norm(prod)
 
 
 @pytest.mark.parametrize("a_k,b_k", [(1, 1), (1, 0), (0, 0)])
