@@ -2,8 +2,8 @@
 // (v_mfma_f32_32x32x2_f32), without materialising the L x L matrices.
 //
 // Head sizes 32 and 64; the fp32 configuration, and bf16 with head size 32 (bf16 with head size 64
-// runs on the bf16 kernels of attention_mfma.hip).  A block owns 32 query rows (forward, dQ) or 32
-// key rows (dK/dV) and its W waves (one, two or four, see waves_of_block) take the 32-row tiles of the opposite rows
+// runs on the bf16 kernels of attention_mfma.hip).  A group of W waves (one, two or four; R groups to a block, see
+// block_shape) owns 32 query rows (forward, dQ) or 32 key rows (dK/dV) and takes the 32-row tiles of the opposite rows
 // in turn; their results are added in wave order at the end.  An MFMA of 32 x 32 x 2 takes 64 clocks, a tile 64-128 of
 // them: a wave that walks all tiles of its rows is a chain of 3 us for each, while a short batch has fewer waves than
 // the chip has SIMDs.  Nothing is shared but the own rows: a wave loads a tile's rows from memory straight into
@@ -39,7 +39,7 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
 
 namespace {
 
-constexpr int TR = 32;                 // own rows of a block, and rows of a streamed tile
+constexpr int TR = 32;                 // own rows of a group of waves, and rows of a streamed tile
 
 __device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
 __device__ __forceinline__ float4 load4(const bf16_t* p) {
@@ -146,24 +146,27 @@ __device__ __forceinline__ int pair_of_block() { return blockIdx.z * 8 + blockId
 }  // namespace
 
 // qkv row stride is 3*H; head hh of token t: q at t*3H + hh*D, k at +H, v at +2H.
-template <typename T, int D, int W>
-__global__ __launch_bounds__(64 * W, 3) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
+template <typename T, int D, int W, int R>
+__global__ __launch_bounds__(64 * W * R, 3) void attn_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx,
                                                        float* __restrict__ lse, Rows rows, int L, int nh, int pairs, int causal,
                                                        DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], tiles[W][TR * (D + 4)];
-  __shared__ float ms[W][TR], ls[W][TR];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
-  const int i0 = blockIdx.y * TR, bh = pair_of_block();
+  __shared__ __attribute__((aligned(16))) float own_q_of[R][TR * (D + 4)], tiles_of[R][W][TR * (D + 4)];
+  __shared__ float ms_of[R][W][TR], ls_of[R][W][TR];
+  const int lane = threadIdx.x & 63, wave_of_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_of_block / W, wave = wave_of_block % W, ql = lane & 31, h = lane >> 5;
+  float(&own_q)[TR * (D + 4)] = own_q_of[group], (&tiles)[W][TR * (D + 4)] = tiles_of[group];
+  float(&ms)[W][TR] = ms_of[group], (&ls)[W][TR] = ls_of[group];
+  const int i0 = (blockIdx.y * R + group) * TR, bh = pair_of_block();
   if (bh >= pairs) return;
   const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if (i0 >= sm.n) return;
+  if ((int)(blockIdx.y * R) * TR >= sm.n) return;     // (a group of the block may yet have no rows: no tiles, no stores)
   const T* base = qkv + sm.first * ld3 + hh * D;
   const int qi = i0 + ql, qc = min(qi, sm.n - 1);
   const float scale = rsqrtf((float)D);
-  const int kend = causal ? min(sm.keys, i0 + TR) : sm.keys;
+  const int kend = i0 >= sm.n ? 0 : causal ? min(sm.keys, i0 + TR) : sm.keys;
   float4 k[D / 8], v[D / 8];
   auto fetch = [&](int k0) {
     fetch_rows<T, D>(base + H, ld3, k0, sm.n - 1, ql, h, k);
@@ -246,25 +249,28 @@ __global__ __launch_bounds__(64 * W, 3) void attn_fwd_kernel(const T* __restrict
 }
 
 // also writes delta_i = dO_i O_i for the dK/dV kernel, which runs after this one
-template <typename T, int D, int W>
-__global__ __launch_bounds__(64 * W, 3) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
+template <typename T, int D, int W, int R>
+__global__ __launch_bounds__(64 * W * R, 3) void attn_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
                                                           const T* __restrict__ dctx, const float* __restrict__ lse,
                                                           float* __restrict__ delta, T* __restrict__ dqkv, Rows rows, int L,
                                                           int nh, int pairs, int causal, DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_q[TR * (D + 4)], own_g[TR * (D + 4)], tiles[W][TR * (D + 4)];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ql = lane & 31, h = lane >> 5;
-  const int i0 = blockIdx.y * TR, bh = pair_of_block();
+  __shared__ __attribute__((aligned(16))) float own_q_of[R][TR * (D + 4)], own_g_of[R][TR * (D + 4)], tiles_of[R][W][TR * (D + 4)];
+  const int lane = threadIdx.x & 63, wave_of_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_of_block / W, wave = wave_of_block % W, ql = lane & 31, h = lane >> 5;
+  float(&own_q)[TR * (D + 4)] = own_q_of[group], (&own_g)[TR * (D + 4)] = own_g_of[group];
+  float(&tiles)[W][TR * (D + 4)] = tiles_of[group];
+  const int i0 = (blockIdx.y * R + group) * TR, bh = pair_of_block();
   if (bh >= pairs) return;
   const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if (i0 >= sm.n) return;
+  if ((int)(blockIdx.y * R) * TR >= sm.n) return;     // (a group of the block may yet have no rows: no tiles, no stores)
   const T* base = qkv + sm.first * ld3 + hh * D;
   const int qi = i0 + ql, qc = min(qi, sm.n - 1);
   const float scale = rsqrtf((float)D);
   float4 k[D / 8], v[D / 8];
-  const int kend = causal ? min(sm.keys, i0 + TR) : sm.keys;
+  const int kend = i0 >= sm.n ? 0 : causal ? min(sm.keys, i0 + TR) : sm.keys;
   auto fetch = [&](int k0) {
     fetch_rows<T, D>(base + H, ld3, k0, sm.n - 1, ql, h, k);
     fetch_rows<T, D>(base + 2 * H, ld3, k0, sm.n - 1, ql, h, v);
@@ -334,21 +340,24 @@ __global__ __launch_bounds__(64 * W, 3) void attn_bwd_dq_kernel(const T* __restr
   if (qi < sm.n) store_sum<T, D, W>(out, tiles[0], TR * (D + 4), min(W, (kend + TR - 1) / TR), wave, lane, factor);
 }
 
-template <typename T, int D, int W>
-__global__ __launch_bounds__(64 * W, 2) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
+template <typename T, int D, int W, int R>
+__global__ __launch_bounds__(64 * W * R, 2) void attn_bwd_dkv_kernel(const T* __restrict__ qkv, const T* __restrict__ dctx,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                            T* __restrict__ dqkv, Rows rows, int L, int nh, int pairs, int causal,
                                                            DropDesc drop) {
-  __shared__ __attribute__((aligned(16))) float own_k[TR * (D + 4)], own_v[TR * (D + 4)], tiles[W][TR * (D + 4)];
-  __shared__ __attribute__((aligned(16))) float stats[W][2][TR];      // lse and delta of the tile's queries
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kl = lane & 31, h = lane >> 5;
-  const int j0 = blockIdx.y * TR, bh = pair_of_block();
+  __shared__ __attribute__((aligned(16))) float own_k_of[R][TR * (D + 4)], own_v_of[R][TR * (D + 4)], tiles_of[R][W][TR * (D + 4)];
+  __shared__ __attribute__((aligned(16))) float stats_of[R][W][2][TR];      // lse and delta of the tile's queries
+  const int lane = threadIdx.x & 63, wave_of_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_of_block / W, wave = wave_of_block % W, kl = lane & 31, h = lane >> 5;
+  float(&own_k)[TR * (D + 4)] = own_k_of[group], (&own_v)[TR * (D + 4)] = own_v_of[group];
+  float(&tiles)[W][TR * (D + 4)] = tiles_of[group], (&stats)[W][2][TR] = stats_of[group];
+  const int j0 = (blockIdx.y * R + group) * TR, bh = pair_of_block();
   if (bh >= pairs) return;
   const int b = bh / nh, hh = bh - b * nh;
   const int H = nh * D;
   const int64_t ld3 = 3 * (int64_t)H;
   const Sample sm = sample_rows(rows, b, L);
-  if (j0 >= sm.n) return;
+  if ((int)(blockIdx.y * R) * TR >= sm.n) return;     // (a group of the block may yet have no rows: no tiles, no stores)
   const T* base = qkv + sm.first * ld3 + hh * D;
   const T* gbase = dctx + sm.first * H + hh * D;
   const int ki = j0 + kl;
@@ -437,62 +446,68 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bwd_dkv_kernel(const T* __rest
   if (in) store_sum<T, D, W>(out + 2 * H, tiles[0], TR * (D + 4), n, wave, lane, factor);
 }
 
-// Waves of a block, by the tiles of a sample and the blocks that the rows of the batch make (without padding that was left
-// out of them; of halves on two streams the whole batch's).  Four make the chain of a sample's tiles a quarter as
-// long; a wave without a tile only takes LDS and a place, and every further one's sums have to be added.  So four
-// where the blocks alone do not fill the chip: up to 512 of them for each tile of a sample, and up to 768 where of four
-// waves' last turn two or three would idle; one where a sample has two tiles or three and the blocks do fill it.
+// Shape of a block, by the tiles of a sample and the blocks of 32 rows that the rows of the batch make (without padding
+// that was left out of them; of halves on two streams the whole batch's).  Four waves make the chain of a sample's
+// tiles a quarter as long; a wave without a tile only takes LDS and a place, and every further one's sums have to be added.
+// So four where the blocks alone do not fill the chip: up to 512 of them for each tile of a sample, and up to 768 where of
+// four waves' last turn two or three would idle; one where a sample has two tiles or three and the blocks do fill it.
 // Iterations go by it too (12 layers in fp32, 16 x 141 padded to 88 on average: 9.47 / 9.10 / 8.98 ms with one / two / four).
-// Forward + backward in us with one / two / four waves, 12 heads of 64 in fp32 (heads of 32 alike), against two waves of
-// a block on 64 rows that share tiles in LDS:
-//   512 x 32 tokens 180 / 213 / 279 against 231    128 x 64 127 / 133 / 176 against 133    16 x 64 40 / 40 / 42 against 37
-//   8 x 64 35 / 26.5 / 27 against 36               128 x 96 239 / 262 / 277 against 287    8 x 128 65 / 62 / 48 against 61
-//   32 x 128 115 / 126 / 114 against 121           32 x 141 188 / 171 / 196 against 204
-//   32 x 256 379 / 349 / 333 against 348           16 x 512 causal 575 / 459 / 433 against 606
-// (One tile of 12-192 pairs stays 3-7 % behind that, a microsecond for the three kernels, 257-512 blocks of two tiles of
-// head size 64 10 % and 1536-3072 of head size 32 2-6 %, whatever the waves.)
-static int waves_of_block(int L, int nh, int64_t rule_rows) {
+// Two tiles' two waves twice in a block, 64 rows, where that is at most a block to a unit and 32 rows' blocks were more
+// (a second block on a unit costs 50 %, a second group in its block 20), and with head size 32 from 1536 blocks of 32 rows
+// on.  The same sums either way.
+// Forward + backward in us with one / two / twice two / four waves, 12 heads of 64 in fp32 (heads of 32 alike), against
+// two waves of a block on 64 rows that share tiles in LDS:
+//   512 x 32 tokens 180 / 213 / - / 279 against 231     128 x 64 126 / 136 / 133 / 182 against 135
+//   8 x 64 35 / 26.4 / 31.5 / 27 against 36             12-20 x 64 38-39 / 39-41 / 32-34 / 41-42 against 36-38
+//   32 x 96 90 / 93 / 101 / 96 against 98               8 x 128 63 / 61 / 48 / 47 against 63
+//   32 x 128 113 / 126 / 109 / 114 against 123          32 x 141 188 / 171 / - / 196 against 204
+//   64 x 256 682 / 629 / 615 / 645 against 643          16 x 512 causal 575 / 459 / - / 433 against 606
+//   head size 32: 64 x 64 43.9 / 43.2 / 40.9 / 54 against 42.3, 128 x 64 71.4 / 71.5 / 68.6 / 92 against 72.0
+// (One tile of 12-192 pairs with head size 64 stays 3-4 % behind that, a microsecond for the three kernels.)
+struct BlockShape { int waves, groups; };
+static BlockShape block_shape(int L, int nh, int d, int64_t rule_rows) {
   const int tiles = (L + TR - 1) / TR;
   const int64_t blocks = (rule_rows + L - 1) / L * nh * tiles;
-  if (tiles == 1 || (tiles <= 3 && blocks >= 768 * (tiles - 1))) return 1;
+  if (tiles == 2 && ((blocks > 256 && blocks <= 512) || (d == 32 && blocks >= 1536))) return {2, 2};
+  if (tiles == 1 || (tiles <= 3 && blocks >= 768 * (tiles - 1))) return {1, 1};
   const bool idle = tiles == 3 || tiles == 5 || tiles == 6;   // (behind more turns the last weighs little)
-  return tiles == 2 || blocks >= (idle ? 768 : 512 * (int64_t)tiles) ? 2 : 4;
+  return {tiles == 2 || blocks >= (idle ? 768 : 512 * (int64_t)tiles) ? 2 : 4, 1};
 }
 
-template <typename T, int D, int W>
+template <typename T, int D, int W, int R>
 static void fwd_w(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int causal,
                   const DropDesc& drop, hipStream_t st) {
   const int pairs = B * nh;
-  hipLaunchKernelGGL((attn_fwd_kernel<T, D, W>), dim3(8, (L + TR - 1) / TR, (pairs + 7) / 8), dim3(64 * W), 0, st, (const T*)qkv,
-                     (T*)ctx, lse, rows, L, nh, pairs, causal, drop);
+  hipLaunchKernelGGL((attn_fwd_kernel<T, D, W, R>), dim3(8, (L + TR * R - 1) / (TR * R), (pairs + 7) / 8), dim3(64 * W * R), 0,
+                     st, (const T*)qkv, (T*)ctx, lse, rows, L, nh, pairs, causal, drop);
 }
 template <typename T, int D>
 static void fwd_t(const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int64_t rule_rows, int L, int nh, int causal,
                   const DropDesc& drop, hipStream_t st) {
-  switch (waves_of_block(L, nh, rule_rows)) {
-    case 1: fwd_w<T, D, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
-    case 2: fwd_w<T, D, 2>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
-    default: fwd_w<T, D, 4>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st); break;
-  }
+  const BlockShape shape = block_shape(L, nh, D, rule_rows);
+  if (shape.groups == 2) fwd_w<T, D, 2, 2>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
+  else if (shape.waves == 1) fwd_w<T, D, 1, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
+  else if (shape.waves == 2) fwd_w<T, D, 2, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
+  else fwd_w<T, D, 4, 1>(qkv, ctx, lse, rows, B, L, nh, causal, drop, st);
 }
-template <typename T, int D, int W>
+template <typename T, int D, int W, int R>
 static void bwd_w(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv,
                   const Rows& rows, int B, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
   const int pairs = B * nh;
-  const dim3 grid(8, (L + TR - 1) / TR, (pairs + 7) / 8);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D, W>), grid, dim3(64 * W), 0, st, (const T*)qkv, (const T*)ctx, (const T*)dctx, lse,
-                     delta, (T*)dqkv, rows, L, nh, pairs, causal, drop);
-  LAUNCH_MARKED_((attn_bwd_dkv_kernel<T, D, W>), grid, dim3(64 * W), st, done, (const T*)qkv, (const T*)dctx, lse, delta,
+  const dim3 grid(8, (L + TR * R - 1) / (TR * R), (pairs + 7) / 8);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D, W, R>), grid, dim3(64 * W * R), 0, st, (const T*)qkv, (const T*)ctx,
+                     (const T*)dctx, lse, delta, (T*)dqkv, rows, L, nh, pairs, causal, drop);
+  LAUNCH_MARKED_((attn_bwd_dkv_kernel<T, D, W, R>), grid, dim3(64 * W * R), st, done, (const T*)qkv, (const T*)dctx, lse, delta,
                  (T*)dqkv, rows, L, nh, pairs, causal, drop);
 }
 template <typename T, int D>
 static void bwd_t(const void* qkv, const void* ctx, const void* dctx, const float* lse, float* delta, void* dqkv, const Rows& rows,
                   int B, int64_t rule_rows, int L, int nh, int causal, const DropDesc& drop, hipStream_t st, hipEvent_t done) {
-  switch (waves_of_block(L, nh, rule_rows)) {
-    case 1: bwd_w<T, D, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
-    case 2: bwd_w<T, D, 2>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
-    default: bwd_w<T, D, 4>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done); break;
-  }
+  const BlockShape shape = block_shape(L, nh, D, rule_rows);
+  if (shape.groups == 2) bwd_w<T, D, 2, 2>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else if (shape.waves == 1) bwd_w<T, D, 1, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else if (shape.waves == 2) bwd_w<T, D, 2, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
+  else bwd_w<T, D, 4, 1>(qkv, ctx, dctx, lse, delta, dqkv, rows, B, L, nh, causal, drop, st, done);
 }
 
 void attention_fwd(int dtype, const void* qkv, void* ctx, float* lse, const Rows& rows, int B, int L, int nh, int d,

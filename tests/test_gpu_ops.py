@@ -657,17 +657,41 @@ def test_attention_fp32_waves(dtype, d, causal, L, lengths, p_drop):
     attention_case(dtype, len(lengths) if lengths else 2, L, 3, d, causal, seed=L + 5, lengths=lengths, p_drop=p_drop)
 
 
-# Waves of a block by tiles of 32 rows and by blocks of the batch (samples x heads x tiles): one, two or four
+# Waves of a block by tiles of 32 rows and by blocks of the batch (samples x heads x tiles): one, two, twice two or four
 @pytest.mark.parametrize("dtype,d", [(0, 64), (0, 32), (1, 32)])
 @pytest.mark.parametrize("B,L,nh,causal,p_drop", [(3, 31, 3, 0, 0.2), (5, 32, 2, 1, 0.0),        # one tile: one wave
                                                   (127, 64, 3, 0, 0.0), (128, 64, 3, 1, 0.0),    # 762, 768 blocks of two: two, one
                                                   (129, 33, 3, 0, 0.2),                          # 774, the last of one row
                                                   (170, 96, 3, 0, 0.0), (171, 70, 3, 0, 0.2),    # 1530, 1539 of three: two, one
                                                   (52, 129, 3, 1, 0.2),                          # 780 of five: two
-                                                  (171, 97, 3, 0, 0.0)])                         # 2052 of four: two
+                                                  (171, 97, 3, 0, 0.0),                          # 2052 of four: two
+                                                  (42, 64, 3, 0, 0.2), (43, 64, 3, 0, 0.2),      # 252, 258 of two: two, twice two
+                                                  (85, 33, 3, 1, 0.0), (86, 50, 3, 0, 0.0),      # 510, 516: twice two, two
+                                                  (256, 64, 3, 0, 0.2)])                         # 1536: one, with d = 32 twice two
 def test_attention_waves_of_a_block(dtype, d, B, L, nh, causal, p_drop):
     lengths = [(1, L, max(1, L - 1), min(L, 32), min(L, 33), max(1, L // 2))[b % 6] for b in range(B)]
     attention_case(dtype, B, L, nh, d, causal, seed=L + B, lengths=lengths, p_drop=p_drop)
+
+
+@pytest.mark.parametrize("dtype,d", [(0, 64), (0, 32), (1, 32)])
+def test_attention_groups_of_a_block_bits(dtype, d):
+    """Two groups of waves in a block (258 blocks of 32 rows) give every sample the bits that one gives it (252)."""
+    B, L, nh = 43, 60, 3
+    st = torch.bfloat16 if dtype else torch.float32
+    g = torch.Generator(device=DEV).manual_seed(d + dtype)
+    H = nh * d
+    qkv, dctx = torch.randn(B * L, 3 * H, generator=g, device=DEV).to(st), torch.randn(B * L, H, generator=g, device=DEV).to(st)
+    lengths = torch.tensor([(60, 32, 33, 1, 59)[b % 5] for b in range(B)], dtype=torch.int32, device=DEV)
+    for causal in (0, 1):
+        out = []
+        for n in (B, B - 1):
+            ctx, dq = torch.zeros(n * L, H, dtype=st, device=DEV), torch.zeros(n * L, 3 * H, dtype=st, device=DEV)
+            lse, delta = torch.zeros(n * nh * L, device=DEV), torch.zeros(n * nh * L, device=DEV)
+            mi.mimose_op_attention_fwd(dtype, qkv, ctx, lse, n, L, nh, d, causal, lengths=lengths)
+            mi.mimose_op_attention_bwd(dtype, qkv, ctx, dctx, lse, delta, dq, n, L, nh, d, causal, lengths=lengths)
+            sync()
+            out.append((ctx, lse, delta, dq))
+        assert all(torch.equal(a[:len(b)], b) for a, b in zip(*out))
 
 
 # dropout of the probabilities: the kept set is the oracle's (integer comparisons of generator

@@ -268,6 +268,25 @@ def test_padded_batch_at_the_budget_of_the_whole_one(dtype, H, B, L, cut):
     m.close()
 
 
+@pytest.mark.parametrize("dtype,H,B", [("fp32", 64, 150), ("fp32", 128, 150), ("bf16", 64, 100)])
+@pytest.mark.parametrize("causal", [0, 1])
+def test_padded_batch_with_two_groups_to_an_attention_block(dtype, H, B, causal):
+    """Samples of up to two tiles of 32 rows, of which many have one: half of an attention block then has no rows."""
+    L, nh, own = 60, 2, (60, 5, 32, 33, 20)
+    shape = synthdata.ModelShape(2, H, nh, 4 * H, 300, L, dtype, causal=causal)
+    lengths = [own[b % 5] for b in range(B)]
+    rows = (sum(lengths), sum((n + 15) // 16 * 16 for n in lengths)) if dtype == "fp32" else (B * L,)
+    assert all(256 < nh * 2 * -(-r // L) <= 512 for r in rows)
+    tokens, labels, lens = synthdata.make_padded_batch(shape, lengths, 59)
+    m = mi.Mimose(synthdata.shape_dict(shape), 0, arena_bytes=512 * MiB)
+    params = synthdata.make_params(shape, 58, perturb=True)
+    m.load_params(params)
+    m.force_plan(0b01)
+    fp32 = dtype == "fp32"
+    check_against_oracle(shape, m, params, tokens, labels, 1e-4 if fp32 else 1e-2, 1e-3 if fp32 else 2e-2, lengths=lens)
+    m.close()
+
+
 @pytest.mark.parametrize("name", ["fp32_postln", "bf16_preln_causal", "bf16_stages"])
 def test_padded_step_counts_the_operations_of_its_real_tokens(name):
     """useful and recompute flops of a padded step are those of its samples at their own lengths, and
